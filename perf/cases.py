@@ -308,3 +308,102 @@ def tolerance(case):
     if case.get("formats", "").endswith("_f8"):  # the fp8 pipeline aligns groups of products: 9e-6, largest 1.2e-4
         return {"rel": 4e-5, "max": 5e-4}
     return {"rel": 8e-7, "max": 4e-6}  # exact products, binary32 sums: 1e-7, largest 6e-7
+
+
+# ---- the same in 64 bits, from the definition: nothing below uses the package's arithmetic --------------
+# kind: (fraction bits, smallest exponent, largest value); integer grids have spacing 1
+_GRID = {L.INT8: (None, 0, 127.0), L.INT4: (None, 0, 7.0), L.E4M3: (3, -6, 448.0), L.E5M2: (2, -14, 57344.0)}
+
+
+def _r16(n, seed, offset):
+    """16 random bits of elements 0 .. n-1: Philox4x32-10, block offset + i // 8, slice i % 8."""
+    low = 0xFFFFFFFF
+    block = torch.arange((n + 7) // 8, dtype=torch.int64, device=DEV) + offset
+    c0, c1 = block & low, (block >> 32) & low
+    c2, c3 = torch.zeros_like(c0), torch.zeros_like(c0)
+    k0, k1 = seed & low, (seed >> 32) & low
+    for _ in range(10):
+        p0, p1 = c0 * 0xD2511F53, c2 * 0xCD9E8D57  # modulo 2^64: the high half is exact after the mask
+        c0, c1, c2, c3 = ((p1 >> 32) & low) ^ c1 ^ k0, p1 & low, ((p0 >> 32) & low) ^ c3 ^ k1, p0 & low
+        k0, k1 = (k0 + 0x9E3779B9) & low, (k1 + 0xBB67AE85) & low
+    return torch.stack([w >> s & 0xFFFF for w in (c0, c1, c2, c3) for s in (0, 16)], 1).reshape(-1)[:n]
+
+
+def _scale(x, kind):
+    return float((x.abs().max().float().cpu() / _GRID[kind][2]).item())
+
+
+def _quantized(x, kind, seed, offset):
+    """x on its grid, in binary64 (scale included)."""
+    m, emin, qmax = _GRID[kind]
+    s = _scale(x, kind)
+    inv = float((torch.tensor(1.0) / torch.tensor(s)).item())
+    t = (x.float() * inv).clamp(-qmax, qmax).double()
+    d = 1.0 if m is None else torch.exp2((torch.frexp(t).exponent - 1).clamp(min=emin).double() - m)
+    y = t / d
+    low = y.floor()
+    eps = (_r16(x.numel(), seed, offset).view(x.shape).double() + 0.5) / 65536
+    return (low + (y - low >= eps)) * d * s
+
+
+def _exact_step(M, N, K, formats, w_bf16, seed):
+    fwd, bwd, grad = FORMATS[formats]
+    A = synth.gaussian_torch((M, K), 1.0, seed, DEV)
+    W = synth.gaussian_torch((N, K), 0.02, seed + 1, DEV, torch.bfloat16 if w_bf16 else None)
+    dY = synth.gaussian_torch((M, N), 1e-3, seed + 2, DEV)
+    q, offset = [], 0
+    for t, kind in ((A, fwd), (W, fwd), (A, bwd), (W, bwd), (dY, grad)):
+        q.append(_quantized(t, kind, seed, offset))
+        offset += (t.numel() + 7) // 8
+    return q[0] @ q[1].t(), q[4] @ q[3], q[4].t() @ q[2]
+
+
+def _exact_module(case, seed):
+    M, N, K = case["M"], case["N"], case["K"]
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    W = (torch.randn((N, K), device=DEV, generator=g) * 0.02).to(torch.bfloat16)
+    qat = case["objective"] == "qat"
+    results, dW, position, wb, ab = [], 0.0, 0, (N * K + 7) // 8, (M * K + 7) // 8
+    for i in range(case["micro"]):
+        x = synth.gaussian_torch((M, K), 1.0, seed + 10 + 2 * i, DEV)
+        dy = synth.gaussian_torch((M, N), 1e-3, seed + 11 + 2 * i, DEV)
+        if qat:
+            wq = _quantized(W, L.E5M2, seed, position)
+            y, a = x.double() @ wq.t(), _quantized(x, L.E5M2, seed, position + wb)
+            position += wb + ab
+        else:
+            y = _quantized(x, L.INT8, seed, position + wb) @ _quantized(W, L.INT8, seed, position).t()
+            a = _quantized(x, L.E5M2, seed, position + wb + ab)
+            wq = _quantized(W, L.E5M2, seed, position + wb + 2 * ab)
+            position += 2 * wb + 2 * ab
+        d = _quantized(dy, L.E5M2, seed, position)
+        position += (M * N + 7) // 8
+        results.append((y, d @ wq))
+        dW = dW + d.t() @ a
+    return results, dW, None  # the weight is rounded to bfloat16 with random thresholds
+
+
+def exact(case, seed):
+    op = case["op"]
+    if op == "quantize":
+        n = case["rows"] * case["cols"]
+        x = synth.outlier_tensor_torch(n, seed, DEV)
+        if case["bf16"]:
+            x = x.to(torch.bfloat16)
+        qmax = {"int8": 127.0, "int4": 7.0, "e4m3": 448.0, "e5m2": 57344.0, "e4m1": 384.0}[case["kind"]]
+        return None, (x.abs().max().double() / qmax).view(1)
+    if op in ("step", "step_plain"):
+        return _exact_step(case["M"], case["N"], case["K"], case["formats"], case["w_bf16"], seed)
+    if op == "block":
+        return [_exact_step(case["M"], N, K, case["formats"], case["w_bf16"], seed + 100 * i)
+                for i, (N, K) in enumerate(BLOCKS[case["block"]])]
+    if op == "module":
+        return _exact_module(case, seed)
+    M, N, K, kind = case["M"], case["N"], case["K"], KINDS[case["kind"]]
+    A = synth.gaussian_torch((M, K), 1.0, seed, DEV, torch.bfloat16 if case.get("a_bf16") else None)
+    W = synth.gaussian_torch((N, K), 0.02, seed + 1, DEV, torch.bfloat16 if case["w_bf16"] else None)
+    wq = _quantized(W, kind, seed, (M * K + 7) // 8)
+    if op == "fwd":
+        return _quantized(A, kind, seed, 0) @ wq.t()
+    dY = synth.gaussian_torch((M, N), 1e-3, seed + 2, DEV, torch.bfloat16 if case["a_bf16"] else None)
+    return A.double() @ wq.t(), dY.double() @ wq
