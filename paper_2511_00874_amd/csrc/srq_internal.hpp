@@ -23,7 +23,7 @@ struct QuantArgs {
   const uint64_t* counter_dev;  // if not null: its value is added to counter_offset on the device
 };
 
-// codes: rows x cols (transpose_out = 0) or cols x rows (1).  Shapes already validated.
+// codes: rows x cols (transpose_out = 0) or cols x rows (1), one byte each, INT4 two per byte.  Shapes already validated.
 hipError_t launch_quantize(void* codes, const void* x, size_t rows, size_t cols, int transpose_out,
                            const QuantArgs& a, hipStream_t stream);
 

@@ -1,8 +1,6 @@
 // Tensor-level SR quantizer kernels (Def. 3: element-wise, independent thresholds) and the
 // per-tensor absmax scale.  HBM-bound streaming kernels for gfx950: 128-bit loads, one
 // Philox block per 8 consecutive elements, 64-bit (or 32-bit for nibbles) stores.
-#include <type_traits>
-
 #include "srq_device.hpp"
 #include "srq_internal.hpp"
 
@@ -38,7 +36,7 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_kernel(uint8_t* __restri
     float v[8];
     uint32_t c[8];
     load_group<SRC>(v, x, g, n);
-    quantize_group<KIND, ROUND, STORE == STORE_BF16>(c, v, inv, counter_offset + g, k0, k1);
+    quantize_group<KIND, ROUND, false>(c, v, inv, counter_offset + g, k0, k1);
     const size_t base = g * 8;
     if constexpr (STORE == STORE_NIBBLE) {
       const uint32_t word = pack_nibbles(c);
@@ -46,16 +44,6 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_kernel(uint8_t* __restri
         __builtin_nontemporal_store(word, reinterpret_cast<uint32_t*>(out + base / 2));
       } else {
         for (size_t j = 0; base + 2 * j < n; ++j) out[base / 2 + j] = (uint8_t)(word >> (8 * j));
-      }
-    } else if constexpr (STORE == STORE_BF16) {
-      uint16_t* o16 = reinterpret_cast<uint16_t*>(out);
-      if (base + 8 <= n) {
-        u32x4 word = {c[0] | (c[1] << 16), c[2] | (c[3] << 16), c[4] | (c[5] << 16), c[6] | (c[7] << 16)};
-        __builtin_nontemporal_store(word, reinterpret_cast<u32x4*>(o16 + base));
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (base + j < n) o16[base + j] = (uint16_t)c[j];
       }
     } else {
       if (base + 8 <= n) {
@@ -88,78 +76,163 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_f32_kernel(uint8_t* __re
 }
 
 // ---- transposed output --------------------------------------------------------------------
-// A block quantizes a TR x TC tile (thresholds keyed by the row-major SOURCE index, so the
-// codes equal those of the same-layout kernel), turns it through LDS, and writes it as
-// TC rows of TR contiguous codes.
-constexpr int TR = 128, TC = 64;
+// A workgroup quantizes a tile of TR source rows x TC source columns (thresholds keyed by the
+// row-major SOURCE index, so the codes equal those of the same-layout kernel), turns it through
+// LDS, and writes TC runs of TR consecutive codes.  HBM-bound: what it is built around is whole
+// lines on the store side.
+//   - A thread takes a piece that is several rows deep, so the codes of neighbouring rows, which are
+//     neighbours in the output, are packed in registers and go to LDS a word (or two) at a time.
+//     binary32: 4 columns x 8 rows (a 16-byte load per row; the lanes of a pair hold the two halves of
+//     each Philox group, the even lane draws the blocks of the first four rows, the odd lane those
+//     of the last four, and they trade two words per block).  bfloat16: 8 columns x 4 rows.  All loads of
+//     a piece are issued before its first code is made.
+//   - A run whose length or place is not a multiple of 16 bytes (a row count that is not one) leaves
+//     16 bytes at a time from the first multiple of four on, put together from LDS words by a byte
+//     shift; only the up to 3 + 3 bytes at its ends go one by one.
+//   - Tile order: XCD x takes a contiguous range of an order that walks groups of TBAND row bands,
+//     band index fastest: workgroups that run together on one XCD write neighbouring runs of the
+//     same output rows and read neighbouring columns of the same source rows, and the lines that two
+//     tiles share are joined in that L2.  (Groups of 8 / 16 / 32 bands, binary32 -> int8: 12288 x 3080
+//     40 / 41 / 42 us, 65536 x 4096 241 / 227 / 229.)
+// Against the form before (a group of 8 codes per thread, byte-wise LDS writes, 128-row tiles, a ragged
+// run byte by byte): 12289 x 3080 bfloat16 -> int8 82 -> 35 us, binary32 99 -> 47; 12288 x 3080 binary32
+// 52 -> 41 (189 MB: 4.6 TB/s); 65536 x 4096 binary32 311 -> 227 (5.9 TB/s), bfloat16 162 -> 130.
+constexpr int TC = 64;
+typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at a multiple of four
+constexpr uint32_t TBAND = 16;
+constexpr uint32_t TRANSPOSE_GRID = 1u << 20;  // workgroups per launch at most; the rest of the tiles by a loop
 
-template <int KIND, int SRC, int ROUND, int STORE>
+template <int KIND, int SRC, int ROUND, int STORE, int TR>
 __global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
     uint8_t* __restrict__ out, const void* __restrict__ x, uint32_t rows, uint32_t cols, float scale,
     const float* scale_dev, int kind, uint64_t seed, uint64_t counter_host, const uint64_t* counter_dev) {
-  const uint64_t counter_offset = first_block(counter_host, counter_dev);
-  // one tile element per code: a byte, or 16 bits when the grid values are stored as bfloat16
-  using elem_t = typename std::conditional<STORE == STORE_BF16, uint16_t, uint8_t>::type;
-  constexpr int ES = sizeof(elem_t);
-  constexpr int PITCH = TR + 4 / ES;            // elements; keeps rows 4-byte aligned
-  __shared__ __attribute__((aligned(16))) elem_t tile[TC * PITCH];
+  static_assert(STORE == STORE_BYTE || STORE == STORE_NIBBLE, "codes");
+  constexpr bool F32 = SRC == SRQ_F32;
+  constexpr int DIV = STORE == STORE_NIBBLE ? 2 : 1;  // codes per byte
+  constexpr int SEG = TR / DIV;                       // bytes of a run
+  // pitch: the pieces a wave instruction writes fall on all 64 banks (16 column quads x 4 row octets of
+  // 8 bytes, or 8 column groups x 8 row quads of 4)
+  constexpr int PITCH = SEG + (F32 ? 8 : 4);
+  __shared__ __attribute__((aligned(16))) uint8_t tile[TC * PITCH + 8];
   const InvScale inv = inv_scale(scale, scale_dev, kind);
+  const uint64_t ctr = first_block(counter_host, counter_dev);
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-  const uint32_t r0 = blockIdx.y * TR, c0 = blockIdx.x * TC;
-  const size_t n = (size_t)rows * cols;
+  const uint32_t tiles_x = (cols + TC - 1) / TC, tiles_y = (rows + TR - 1) / TR;
+  const uint32_t ntiles = tiles_x * tiles_y, chunk = (ntiles + 7u) >> 3;
+  const uint32_t begin = (blockIdx.x & 7u) * chunk, end = min(ntiles, begin + chunk);
+  const uint32_t orow = rows / DIV;  // bytes of an output row (rows is even where two codes share a byte)
+
+  for (uint32_t work = begin + (blockIdx.x >> 3); work < end; work += gridDim.x >> 3) {
+    const uint32_t band = work / (TBAND * tiles_x), band0 = band * TBAND;
+    const uint32_t bands = min(TBAND, tiles_y - band0), within = work - band0 * tiles_x;
+    const uint32_t r0 = (band0 + within % bands) * TR, c0 = (within / bands) * TC;
+
+    constexpr int PR = F32 ? 8 : 4, PC = F32 ? 4 : 8;  // rows x columns of a thread's piece
+    constexpr int PIECES = TR * TC / (PR * PC) / QBLOCK;
+    static_assert(PIECES >= 1, "a piece per thread");
 #pragma unroll
-  for (int it = 0; it < (TR * TC / 8) / QBLOCK; ++it) {
-    const uint32_t id = it * QBLOCK + threadIdx.x;
-    const uint32_t gc = id % (TC / 8), r = id / (TC / 8);
-    const uint32_t row = r0 + r, col = c0 + gc * 8;
-    uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (row < rows && col < cols) {  // cols % 8 == 0: a group never straddles the edge
-      const size_t g = ((size_t)row * cols + col) / 8;
-      float v[8];
-      load_group<SRC>(v, x, g, n);
-      quantize_group<KIND, ROUND, STORE == STORE_BF16>(c, v, inv, counter_offset + g, k0, k1);
-    }
+    for (int it = 0; it < PIECES; ++it) {
+      const uint32_t id = it * QBLOCK + threadIdx.x;
+      const uint32_t cl = (id % (TC / PC)) * PC, rl = (id / (TC / PC)) * PR;
+      const uint32_t col = c0 + cl, row = r0 + rl;
+      const bool col_ok = col < cols;  // cols % 8 == 0: a piece never straddles the edge
+      const size_t e0 = (size_t)row * cols + col;
+      u32x4 raw[PR];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) tile[(gc * 8 + j) * PITCH + r] = (elem_t)c[j];
-  }
-  __syncthreads();
-  // TC columns x (TR / 16) chunks of 16 source rows
+      for (int i = 0; i < PR; ++i) {
+        const bool ok = col_ok && row + i < rows;
+        const size_t e = ok ? e0 + (size_t)i * cols : 0;  // outside: element 0, and its code is dropped
+        if constexpr (F32) raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(static_cast<const float*>(x) + e));
+        else raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(x) + e));
+      }
+      uint32_t c[PR][PC];
+      if constexpr (F32) {
+        const bool odd = threadIdx.x & 1u;
 #pragma unroll
-  for (int it = 0; it < (TC * TR / 16) / QBLOCK; ++it) {
-    const uint32_t id = it * QBLOCK + threadIdx.x;
-    const uint32_t ch = id % (TR / 16), c = id / (TR / 16);
-    const uint32_t col = c0 + c, row = r0 + ch * 16;
-    if (col >= cols || row >= rows) continue;
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(&tile[c * PITCH + ch * 16]);
-    uint32_t w[4 * ES];
+        for (int i = 0; i < 4; ++i) {
+          uint32_t addA[4], addB[4];  // rows i and i + 4
+          if constexpr (ROUND == SRQ_SR) {
+            uint32_t w[4];
+            philox_block(ctr + (e0 + (size_t)(odd ? i + 4 : i) * cols) / 8, k0, k1, w);
+            const uint32_t s0 = odd ? w[0] : w[2], s1 = odd ? w[1] : w[3];  // what the other lane needs
+            const uint32_t t0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s0, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+            const uint32_t t1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s1, 0xB1, 0xF, 0xF, true);
+            sr_addends(odd ? t0 : w[0], odd ? t1 : w[1], addA);
+            sr_addends(odd ? w[2] : t0, odd ? w[3] : t1, addB);
+          } else {
 #pragma unroll
-    for (int i = 0; i < 4 * ES; ++i) w[i] = src[i];
-    const bool whole = row + 16 <= rows && (rows % 16) == 0;  // 16 rows, aligned destination
-    if constexpr (STORE == STORE_NIBBLE) {
-      // pairs along the output's contiguous dimension (source rows); rows is even
-      auto squeeze = [](uint32_t v) {  // 4 code bytes -> 4 nibbles (16 bits)
-        return (v & 0xFu) | ((v >> 4) & 0xF0u) | ((v >> 8) & 0xF00u) | ((v >> 12) & 0xF000u);
-      };
-      const uint32_t lo = squeeze(w[0]) | (squeeze(w[1]) << 16), hi = squeeze(w[2]) | (squeeze(w[3]) << 16);
-      uint8_t* dst = out + ((size_t)col * rows + row) / 2;
-      if (whole) {
-        *reinterpret_cast<u32x2*>(dst) = u32x2{lo, hi};
+            for (int e = 0; e < 4; ++e) addA[e] = addB[e] = RTN_ADDEND;
+          }
+          quantize_quad<KIND, ROUND, false>(c[i], __uint_as_float(raw[i].x), __uint_as_float(raw[i].y),
+                                            __uint_as_float(raw[i].z), __uint_as_float(raw[i].w), inv, addA);
+          quantize_quad<KIND, ROUND, false>(c[i + 4], __uint_as_float(raw[i + 4].x), __uint_as_float(raw[i + 4].y),
+                                            __uint_as_float(raw[i + 4].z), __uint_as_float(raw[i + 4].w), inv, addB);
+        }
       } else {
-        const uint64_t both = (uint64_t)lo | ((uint64_t)hi << 32);
-        for (uint32_t j = 0; row + 2 * j < rows && j < 8; ++j) dst[j] = (uint8_t)(both >> (8 * j));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float v[8];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[2 * e] = bf16_to_f32(raw[i][e] & 0xFFFFu);
+            v[2 * e + 1] = bf16_to_f32(raw[i][e] >> 16);
+          }
+          quantize_group<KIND, ROUND, false>(c[i], v, inv, ctr + (e0 + (size_t)i * cols) / 8, k0, k1);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < PC; ++e) {
+        uint8_t* const dst = tile + (cl + e) * PITCH + rl / DIV;
+#pragma unroll
+        for (int h = 0; h < PR; h += 4) {
+          const uint32_t q[4] = {c[h][e], c[h + 1][e], c[h + 2][e], c[h + 3][e]};
+          if constexpr (STORE == STORE_NIBBLE) *reinterpret_cast<uint16_t*>(dst + h / 2) = (uint16_t)pack4_nibbles(q);
+          else *reinterpret_cast<uint32_t*>(dst + h) = pack4_bytes(q);
+        }
+      }
+    }
+    __syncthreads();
+    const uint32_t rb = r0 / DIV, nb = min((uint32_t)SEG, orow - rb);  // the runs of this tile, in bytes
+    if ((orow & 15u) == 0) {
+      // every run starts at a multiple of 16 bytes and is a multiple of 16 long
+#pragma unroll
+      for (int it = 0; it < TC * SEG / 16 / QBLOCK; ++it) {
+        const uint32_t id = it * QBLOCK + threadIdx.x;
+        const uint32_t ch = id % (SEG / 16), cl = id / (SEG / 16);
+        if (c0 + cl >= cols || ch * 16 >= nb) continue;
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(tile + cl * PITCH + ch * 16);
+        *reinterpret_cast<u32x4*>(out + (size_t)(c0 + cl) * orow + rb + ch * 16) = u32x4{src[0], src[1], src[2], src[3]};
       }
     } else {
-      elem_t* dst = reinterpret_cast<elem_t*>(out) + (size_t)col * rows + row;
-      if (whole) {
+      // one lane per four words of a run: h bytes up to the first aligned address, then whole words; the
+      // last lane, whose words are never all there when a run has ends, takes the ends
+      constexpr int LANES = SEG / 16;
 #pragma unroll
-        for (int i = 0; i < ES; ++i)
-          reinterpret_cast<u32x4*>(dst)[i] = u32x4{w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]};
-      } else {
-        constexpr int PER = 4 / ES;  // elements per 32-bit word
-        for (uint32_t j = 0; j < 16 && row + j < rows; ++j)
-          dst[j] = (elem_t)(w[j / PER] >> (8 * ES * (j % PER)));
+      for (int it = 0; it < TC * LANES / QBLOCK; ++it) {
+        const uint32_t id = it * QBLOCK + threadIdx.x;
+        const uint32_t w = (id % LANES) * 4, cl = id / LANES;
+        if (c0 + cl >= cols) continue;
+        const uint8_t* const run = tile + cl * PITCH;
+        uint8_t* const dst = out + (size_t)(c0 + cl) * orow + rb;
+        const uint32_t h = min((0u - (uint32_t)(uintptr_t)dst) & 3u, nb), words = (nb - h) >> 2;
+        const uint32_t* const src = reinterpret_cast<const uint32_t*>(run) + w;  // bytes h + 4 w ... of the run
+        u32x4a4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_alignbyte(src[e + 1], src[e], h);
+        if (w + 4 <= words) {
+          *reinterpret_cast<u32x4a4*>(dst + h + 4 * w) = v;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (w + e < words) *reinterpret_cast<uint32_t*>(dst + h + 4 * (w + e)) = v[e];
+          if (id % LANES == LANES - 1) {
+            for (uint32_t j = 0; j < h; ++j) dst[j] = run[j];
+            for (uint32_t j = h + 4 * words; j < nb; ++j) dst[j] = run[j];
+          }
+        }
       }
     }
+    __syncthreads();  // the tile is free for the next one
   }
 }
 
@@ -335,10 +408,16 @@ template <int KIND, int SRC, int ROUND, int STORE>
 hipError_t launch_one(void* codes, const void* x, size_t rows, size_t cols, int transpose_out,
                       const QuantArgs& a, hipStream_t stream) {
   if (transpose_out) {
-    dim3 grid((unsigned)((cols + TC - 1) / TC), (unsigned)((rows + TR - 1) / TR));
-    quantize_transpose_kernel<KIND, SRC, ROUND, STORE><<<grid, QBLOCK, 0, stream>>>(
-        static_cast<uint8_t*>(codes), x, (uint32_t)rows, (uint32_t)cols, a.scale, a.scale_dev, a.kind, a.seed,
-        a.counter_offset, a.counter_dev);
+    // 256 rows where they still give every CU several tiles (runs of 256 bytes), else 128
+    const size_t tiles_x = (cols + TC - 1) / TC, big = tiles_x * ((rows + 255) / 256), small = tiles_x * ((rows + 127) / 128);
+    auto launch = [&](auto kern, size_t ntiles) {
+      const size_t per_xcd = (ntiles + 7) / 8;
+      const unsigned grid = 8u * (unsigned)(per_xcd < TRANSPOSE_GRID / 8 ? per_xcd : TRANSPOSE_GRID / 8);
+      kern<<<grid, QBLOCK, 0, stream>>>(static_cast<uint8_t*>(codes), x, (uint32_t)rows, (uint32_t)cols, a.scale,
+                                        a.scale_dev, a.kind, a.seed, a.counter_offset, a.counter_dev);
+    };
+    if (big >= 2048) launch(&quantize_transpose_kernel<KIND, SRC, ROUND, STORE, 256>, big);
+    else launch(&quantize_transpose_kernel<KIND, SRC, ROUND, STORE, 128>, small);
   } else {
     const size_t n = rows * cols;
     size_t done = 0;  // elements handled by the coalesced chunk kernel
@@ -355,7 +434,7 @@ hipError_t launch_one(void* codes, const void* x, size_t rows, size_t cols, int 
     if (done < n) {
       // remainder (or a bfloat16 source, whose groups are one 16-byte load each already)
       const size_t es = SRC == SRQ_F32 ? 4 : 2;
-      const size_t out_bytes = STORE == STORE_NIBBLE ? done / 2 : STORE == STORE_BF16 ? done * 2 : done;
+      const size_t out_bytes = STORE == STORE_NIBBLE ? done / 2 : done;
       const int grid = grid_for((n - done + 7) / 8, QBLOCK * 4, 1 << 20);
       quantize_flat_kernel<KIND, SRC, ROUND, STORE><<<grid, QBLOCK, 0, stream>>>(
           static_cast<uint8_t*>(codes) + out_bytes, static_cast<const uint8_t*>(x) + done * es, n - done, a.scale,
@@ -383,22 +462,11 @@ hipError_t launch_quantize(void* codes, const void* x, size_t rows, size_t cols,
   if (rows * cols == 0) return hipSuccess;
   switch (a.kind) {
     case SRQ_INT8: return dispatch_src_round<SRQ_INT8, STORE_BYTE>(codes, x, rows, cols, transpose_out, a, stream);
-    case SRQ_INT4:
-      return a.store == STORE_NIBBLE
-                 ? dispatch_src_round<SRQ_INT4, STORE_NIBBLE>(codes, x, rows, cols, transpose_out, a, stream)
-                 : dispatch_src_round<SRQ_INT4, STORE_BYTE>(codes, x, rows, cols, transpose_out, a, stream);
-    case SRQ_E4M3:
-      return a.store == STORE_BF16
-                 ? dispatch_src_round<SRQ_E4M3, STORE_BF16>(codes, x, rows, cols, transpose_out, a, stream)
-                 : dispatch_src_round<SRQ_E4M3, STORE_BYTE>(codes, x, rows, cols, transpose_out, a, stream);
-    case SRQ_E5M2:
-      return a.store == STORE_BF16
-                 ? dispatch_src_round<SRQ_E5M2, STORE_BF16>(codes, x, rows, cols, transpose_out, a, stream)
-                 : dispatch_src_round<SRQ_E5M2, STORE_BYTE>(codes, x, rows, cols, transpose_out, a, stream);
+    case SRQ_INT4: return dispatch_src_round<SRQ_INT4, STORE_NIBBLE>(codes, x, rows, cols, transpose_out, a, stream);
+    case SRQ_E4M3: return dispatch_src_round<SRQ_E4M3, STORE_BYTE>(codes, x, rows, cols, transpose_out, a, stream);
+    case SRQ_E5M2: return dispatch_src_round<SRQ_E5M2, STORE_BYTE>(codes, x, rows, cols, transpose_out, a, stream);
     case SRQ_E4M2: case SRQ_E4M1: case SRQ_E4M0:
-      return a.store == STORE_BF16
-                 ? dispatch_src_round<SRQ_E4MX, STORE_BF16>(codes, x, rows, cols, transpose_out, a, stream)
-                 : dispatch_src_round<SRQ_E4MX, STORE_BYTE>(codes, x, rows, cols, transpose_out, a, stream);
+      return dispatch_src_round<SRQ_E4MX, STORE_BYTE>(codes, x, rows, cols, transpose_out, a, stream);
     default: return hipErrorInvalidValue;
   }
 }

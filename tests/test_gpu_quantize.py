@@ -80,6 +80,30 @@ def test_thresholds_scanned_on_hard_constants(kind):
     assert np.array_equal(got, oracle_codes(xd, kind, 1.0, 0, 0, oracle.RTN))
 
 
+# runs that start and end off every alignment, one tile and several, both tile heights (256 rows from 2048
+# such tiles up), full and partial groups of 16 row bands, fewer rows than a word holds
+@pytest.mark.parametrize("shape", [(1, 8), (3, 16), (5, 72), (129, 64), (257, 136), (2051, 200), (4098, 72),
+                                   (524290, 8), (524288, 8), (525301, 8), (260, 16392)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_transposed_codes_at_odd_row_counts(shape, bf16):
+    x = synth.gaussian(shape, 2.0, 3)
+    flat = x.reshape(-1)
+    flat[-min(flat.size, _specials().size):] = _specials()[:flat.size]
+    xd = to_dev(x, bf16)
+    for kind in (L.INT8, L.INT4, L.E4M3, L.E5M2, L.E4M1):
+        if kind == L.INT4 and shape[0] % 2:
+            continue  # two codes of a byte are neighbours in the output
+        mode = L.RTN if shape[0] == 2051 else L.SR
+        say("transpose", L.KIND_NAMES[kind], "bf16" if bf16 else "f32", shape)
+        q = L.Quant(kind, 0.037, seed=0xDEADBEEFCAFE1234, counter_offset=2**64 - 5, round_mode=mode)
+        guard = torch.full((x.size + 64,), 0xA5, dtype=torch.uint8, device=xd.device)
+        n = x.size // 2 if kind == L.INT4 else x.size
+        L.sr_quantize(xd, q, transpose_out=True, out=guard[:n])
+        want = oracle_codes(xd, kind, 0.037, 0xDEADBEEFCAFE1234, 2**64 - 5, mode, transpose=True)
+        assert np.array_equal(guard[:n].cpu().numpy(), want)
+        assert bool((guard[n:] == 0xA5).all())
+
+
 def test_bf16_transposed():
     x = synth.gaussian((256, 136), 0.02, 5)
     xd = to_dev(x, bf16=True)
