@@ -129,6 +129,21 @@ def test_absmax_scale_and_device_scale_path(kind, bf16):
     assert np.array_equal(got, got2)
 
 
+# the one-launch form up to 256 KiB, the three-launch form beyond it (one element more), a share per workgroup
+# that ends in a partial piece, the change from many to few workgroups; the maximum at either end or nowhere
+@pytest.mark.parametrize("n", [1, 7, 4095, 65536, 65537, 131072, 131073, 1048583, 4194311])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_absmax_scale_finds_the_maximum_wherever_it_is(n, bf16):
+    x = synth.gaussian((n,), 1e-3, 5)
+    for where, v in ((0, 2.0), (n - 1, -3.0), (n // 2, 5.0), (None, 0.0)):
+        y = np.zeros_like(x) if where is None else x.copy()
+        if where is not None:
+            y[where] = v
+        say("absmax", n, "bf16" if bf16 else "f32", where)
+        s = float(L.sr_absmax_scale(to_dev(y, bf16), L.INT8).item())
+        assert s == (1.0 if where is None else float(np.float32(abs(v)) / np.float32(127)))
+
+
 @pytest.mark.parametrize("kind", [L.INT8, L.E5M2, L.E4M3])
 def test_vanishing_tensor_gets_the_floored_scale_not_saturation(kind):
     # max|x| / Qmax below 2^-100: both absmax entry points floor the step there, and the codes
