@@ -252,9 +252,10 @@ int run_linear(float* out, const void* x, int dtx, size_t xr, size_t xc, int x_t
 // Products of the weight-only objective (Sec. 3.2): out (P x Q) = x . Q(w)^T with the row operand
 // x (P x R, R contiguous, binary32 or bfloat16) taken as it is.  The bf16 matrix pipeline multiplies
 // exactly: w is written as the bfloat16 numbers of its grid values (R contiguous); a bfloat16 x is
-// used in place; a binary32 x becomes three bfloat16 planes that sum to it, side by side in each
-// row, multiplied in one launch over the contraction 3 R against [w | w | w], so the planes are
-// added inside the binary32 accumulators.
+// used in place by the product of two bfloat16 matrices, a binary32 x by the one that cuts it into
+// three bfloat16 numbers in registers.
+// The plan says how much workspace a call asks for, which callers have by query: for a binary32 x
+// more than it uses (three planes of x, w three times over; what w does not take is room for slices).
 struct WeightOnlyPlan {
   int planes;  // 1: x is bfloat16 already; 3: binary32
   size_t x_bytes, zcodes_bytes, z_bytes, z3_bytes, gemm_bytes;
@@ -289,35 +290,24 @@ int run_weight_only(float* out, const void* x, int dtx, const void* w, int dtw, 
   if (st != SRQ_OK) return st;
   if (!aligned16(out) || !aligned16(x)) return SRQ_ERR_ALIGN;
   const WeightOnlyPlan wp = plan_weight_only(dtx, qw->kind, P, Q, R);
-  const size_t R3 = (size_t)wp.planes * R;  // contraction length of the launch
+  const size_t R3 = (size_t)wp.planes * R, total = weight_only_total(wp);
   if (!fits_u32(R3) || !gemm_operands_addressable(P, Q, R3, PIPE_BF16)) return SRQ_ERR_UNSUPPORTED;
-  if (!workspace_ok(workspace, workspace_bytes, weight_only_total(wp))) return SRQ_ERR_WORKSPACE;
+  if (!workspace_ok(workspace, workspace_bytes, total)) return SRQ_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  uint8_t* xplanes = static_cast<uint8_t*>(workspace);
-  uint8_t* zcodes = xplanes + wp.x_bytes;
-  uint8_t* zvals = zcodes + wp.zcodes_bytes;
-  uint8_t* z3 = zvals + wp.z_bytes;
-  void* gws = z3 + wp.z3_bytes;
-  const bool w_int = kind_is_int(qw->kind);
+  uint8_t* zvals = static_cast<uint8_t*>(workspace);
+  uint8_t* gws = zvals + wp.z_bytes;
   QuantJobs jobs;
   jobs.njobs = 1;
-  jobs.job[0] = make_job(qw, w, dtw, wr, wc, w_tr, w_int ? STORE_BYTE : STORE_BF16, w_int ? zcodes : zvals, nullptr);
+  jobs.job[0] = make_job(qw, w, dtw, wr, wc, w_tr, STORE_BF16, zvals, nullptr);
   if (launch_quantize_jobs(jobs, s) != hipSuccess) return SRQ_ERR_HIP;
-  if (w_int && launch_int_codes_to_bf16(reinterpret_cast<uint16_t*>(zvals), zcodes, Q * R, s) != hipSuccess)
-    return SRQ_ERR_HIP;
-  const uint8_t* xop = static_cast<const uint8_t*>(x);
-  const uint8_t* zop = zvals;
-  if (wp.planes == 3) {
-    if (launch_split3(reinterpret_cast<uint16_t*>(xplanes), static_cast<const float*>(x), P, R, s) != hipSuccess ||
-        launch_repeat3(reinterpret_cast<uint16_t*>(z3), reinterpret_cast<const uint16_t*>(zvals), Q, R, s) != hipSuccess)
-      return SRQ_ERR_HIP;
-    xop = xplanes;
-    zop = z3;
-  }
   const GemmScale sc{1.0f, 1.0f, qw->scale, nullptr, qw->scale_dev};
-  return launch_gemm_codes(out, xop, SRQ_E5M2, zop, SRQ_E5M2, P, Q, R3, 2 * R3, PIPE_BF16, sc, false, gws, s) == hipSuccess
-             ? SRQ_OK
-             : SRQ_ERR_HIP;
+  const hipError_t e =
+      wp.planes == 3
+          ? launch_gemm_f32_bf16(out, static_cast<const float*>(x), reinterpret_cast<const uint16_t*>(zvals), P, Q, R, sc,
+                                 gws, total - wp.z_bytes, s)
+          : launch_gemm_codes(out, static_cast<const uint8_t*>(x), SRQ_E5M2, zvals, SRQ_E5M2, P, Q, R, 2 * R, PIPE_BF16,
+                              sc, false, gws, s);
+  return e == hipSuccess ? SRQ_OK : SRQ_ERR_HIP;
 }
 
 bool is_none(const srq_quant* q) { return q && q->kind == SRQ_NONE; }

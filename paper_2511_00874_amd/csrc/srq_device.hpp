@@ -98,9 +98,9 @@ struct InvScale {
 
 // One element through Eq. 1 on grid KIND.  Returns the code in the low 8 bits (integers:
 // two's complement byte; INT4 values are in [-7,7], sign-extended to the byte).  With
-// AS_BF16 (8-bit float grids only) it returns instead the bfloat16 bit pattern of the grid
-// point q * D itself -- every E4M3 / E5M2 value is a normal bfloat16 number -- which is what
-// the exact (bf16 matrix pipeline) product consumes.
+// AS_BF16 it returns instead the bfloat16 bit pattern of the grid point q * D itself -- every
+// grid value is a normal bfloat16 number -- which is what the exact (bf16 matrix pipeline)
+// product consumes.
 // FIX_NAN = false leaves the NaN rule to the caller (quantize_quad applies it per quad).
 // Integer codes come back sign-extended to 32 bits: take the low byte (or nibble).
 template <int KIND, int ROUND, bool AS_BF16 = false, bool FIX_NAN = true>
@@ -108,13 +108,12 @@ __device__ __forceinline__ uint32_t quantize_elem(float x, const InvScale& s, ui
   using G = Grid<KIND>;
   uint32_t code;
   if constexpr (!G::is_float) {
-    static_assert(!AS_BF16, "integer grids are stored as bytes");
     const int QI = KIND == SRQ_INTX ? s.sub_qi : (G::qmax << 16);
     const float y16 = __fmul_rn(x, s.inv16);                            // t * 2^16, D = 1
     int u = ROUND == SRQ_SR ? cvt_rpi(y16) : cvt_flr(y16);              // saturating
     u = min(max(u, -QI), QI);                                           // clamp t to +-Qmax
     const int q = (u + (int)addend) >> 16;
-    code = (uint32_t)q;
+    code = AS_BF16 ? __float_as_uint((float)q) >> 16 : (uint32_t)q;     // (at most 7 significant bits)
     if (FIX_NAN && x != x) code = 0u;
   } else {
     const int m = KIND == SRQ_E4MX ? s.sub_m : G::mbits;

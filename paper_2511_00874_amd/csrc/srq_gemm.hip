@@ -118,6 +118,75 @@ __device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rsrc, uint32_t 
                : "memory");
 }
 
+// Epilogue of a wave: its TM x TN block of 32 x 32 MFMA results, first row p0 and column q0 of the output.
+// MFMA result register r of lane l: MFMA row 8*(r/4) + 4*(l/32) + r%4 (a q), MFMA column l%32 (a p).
+// The wave turns its block through its own piece of LDS (`stage`), a band of 32 p-rows at a time (of
+// at most 96 columns), so that every global store instruction writes whole rows of the band.
+constexpr int epilogue_columns(int TN) { return 32 * (TN <= 3 ? TN : TN % 3 == 0 ? 3 : 2); }
+constexpr int epilogue_wave_bytes(int TN) { return 32 * (epilogue_columns(TN) + 4) * 4; }
+
+template <class MMA, int TM, int TN>
+__device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typename MMA::acc_t (&acc)[TM][TN], uint8_t* stage,
+                                                uint32_t lane, uint32_t p0, uint32_t q0, uint32_t slice) {
+  constexpr int COLS = epilogue_columns(TN), JB = COLS / 32;
+  static_assert(TN % JB == 0, "whole bands");
+  constexpr int EP_PITCH = COLS + 4;                  // floats; +4 staggers the banks
+  constexpr int CPR = COLS / 4;                       // 16-byte chunks per band row
+  constexpr int EP_ITERS = 32 * CPR / 64;
+  uint32_t* ep = reinterpret_cast<uint32_t*>(stage);
+  const float s = total_scale(g);
+  const bool q_vec = (g.Q & 3u) == 0;
+  uint32_t* const pbase = g.nsplit > 1 ? g.partial + (size_t)slice * g.P * g.Q : nullptr;
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+#pragma unroll
+    for (int j0 = 0; j0 < TN; j0 += JB) {
+#pragma unroll
+      for (int j = 0; j < JB; ++j)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq)
+          *reinterpret_cast<v4u*>(ep + (lane & 31u) * EP_PITCH + j * 32 + 8 * gq + 4 * (lane >> 5)) =
+              v4u{MMA::bits(acc[i][j0 + j][4 * gq]), MMA::bits(acc[i][j0 + j][4 * gq + 1]),
+                  MMA::bits(acc[i][j0 + j][4 * gq + 2]), MMA::bits(acc[i][j0 + j][4 * gq + 3])};
+      const uint32_t pb = p0 + i * 32, qb = q0 + j0 * 32;
+#pragma unroll
+      for (int it = 0; it < EP_ITERS; ++it) {
+        const uint32_t id = it * 64 + lane, row = id / CPR, c = id % CPR;
+        const uint32_t p = pb + row, q = qb + c * 4;
+        const v4u raw = *reinterpret_cast<const v4u*>(ep + row * EP_PITCH + c * 4);
+        if (p >= g.P || q >= g.Q) continue;
+        const size_t idx = (size_t)p * g.Q + q;
+        if (pbase) {
+          if (q_vec) {
+            // write-through: nothing of the partial tile stays dirty in the L2 when the kernel
+            // ends, and the reduction launched next still finds it in the last-level cache
+            asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" : : "v"(pbase + idx), "v"(raw) : "memory");
+          } else {
+            for (int e = 0; e < 4 && q + e < g.Q; ++e) pbase[idx + e] = raw[e];
+          }
+        } else {
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = __fmul_rn(MMA::to_f32(MMA::from_bits(raw[e])), s);
+          float* dst = g.out + idx;
+          if (q_vec) {
+            if (g.accumulate) {
+              const v4f o = *reinterpret_cast<const v4f*>(dst);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = __fadd_rn(v[e], o[e]);
+            }
+            // the result is not read again by this kernel: a streaming store keeps it from pushing
+            // operand panels out of the L2
+            __builtin_nontemporal_store(v4f{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4f*>(dst));
+          } else {
+            for (int e = 0; e < 4 && q + e < g.Q; ++e) dst[e] = g.accumulate ? __fadd_rn(v[e], dst[e]) : v[e];
+          }
+        }
+      }
+    }
+  }
+}
+
 // Besides its tiles a launch can carry the slice sum of an EARLIER product (`rider`, complete when
 // this launch starts): memory-bound work that runs beside the matrix work, in the resident slots
 // the tiles leave free and in the tail of the launch, instead of in a launch of its own.
@@ -325,67 +394,10 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, Sl
     }
   }
 
-  // epilogue.  MFMA result register r of lane l: MFMA row 8*(r/4) + 4*(l/32) + r%4 (a q),
-  // MFMA column l%32 (a p).  Each wave turns its tile through its own piece of LDS, one band
-  // of 32 p-rows at a time, so that every global store instruction writes whole rows of the
-  // band: WTN * 4 contiguous bytes per row.
-  constexpr int EP_PITCH = WTN + 4;                   // floats; +4 staggers the banks
-  constexpr int EP_WAVE = 32 * EP_PITCH * 4;          // bytes per wave
-  static_assert(NW * EP_WAVE <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
-  constexpr int CPR = WTN / 4;                        // 16-byte chunks per band row
-  constexpr int EP_ITERS = 32 * CPR / 64;
   wait_vmcnt<0>();   // the zero-filled stages issued past the end must have landed too
   __syncthreads();
-  uint32_t* ep = reinterpret_cast<uint32_t*>(lds + wave * EP_WAVE);
-  const float s = total_scale(g);
-  const bool q_vec = (g.Q & 3u) == 0;
-  const uint32_t qw0 = q0 + wq * WTN;
-  uint32_t* const pbase = g.nsplit > 1 ? g.partial + (size_t)slice * g.P * g.Q : nullptr;
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq)
-        *reinterpret_cast<v4u*>(ep + (lane & 31u) * EP_PITCH + j * 32 + 8 * gq + 4 * (lane >> 5)) =
-            v4u{MMA::bits(acc[i][j][4 * gq]), MMA::bits(acc[i][j][4 * gq + 1]), MMA::bits(acc[i][j][4 * gq + 2]),
-                MMA::bits(acc[i][j][4 * gq + 3])};
-    const uint32_t pb = p0 + wp * WTM + i * 32;
-#pragma unroll
-    for (int it = 0; it < EP_ITERS; ++it) {
-      const uint32_t id = it * 64 + lane, row = id / CPR, c = id % CPR;
-      const uint32_t p = pb + row, q = qw0 + c * 4;
-      const v4u raw = *reinterpret_cast<const v4u*>(ep + row * EP_PITCH + c * 4);
-      if (p >= g.P || q >= g.Q) continue;
-      const size_t idx = (size_t)p * g.Q + q;
-      if (pbase) {
-        if (q_vec) {
-          // write-through: nothing of the partial tile stays dirty in the L2 when the kernel
-          // ends, and the reduction launched next still finds it in the last-level cache
-          asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" : : "v"(pbase + idx), "v"(raw) : "memory");
-        } else {
-          for (int e = 0; e < 4 && q + e < g.Q; ++e) pbase[idx + e] = raw[e];
-        }
-      } else {
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = __fmul_rn(MMA::to_f32(MMA::from_bits(raw[e])), s);
-        float* dst = g.out + idx;
-        if (q_vec) {
-          if (g.accumulate) {
-            const v4f o = *reinterpret_cast<const v4f*>(dst);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = __fadd_rn(v[e], o[e]);
-          }
-          // the result is not read again by this kernel: a streaming store keeps it from pushing
-          // operand panels out of the L2
-          __builtin_nontemporal_store(v4f{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4f*>(dst));
-        } else {
-          for (int e = 0; e < 4 && q + e < g.Q; ++e) dst[e] = g.accumulate ? __fadd_rn(v[e], dst[e]) : v[e];
-        }
-      }
-    }
-  }
+  static_assert(NW * epilogue_wave_bytes(TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
+  write_wave_tile<MMA, TM, TN>(g, acc, lds + wave * epilogue_wave_bytes(TN), lane, p0 + wp * WTM, q0 + wq * WTN, slice);
 }
 
 // ---- 256 x 256 tiles, workgroups that stay -------------------------------------------------------
@@ -724,6 +736,141 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
   }
 }
 
+// ---- binary32 rows times bfloat16 columns (the weight-only objective) ---------------------------
+// X is binary32 as the caller has it; the bf16 pipeline multiplies it exactly once it is cut into three
+// bfloat16 numbers that sum to it: p0 its top 8 significand bits, p1 the top 8 of the remainder, p2 what
+// is left (binary32 has 24 bits; both subtractions are exact; a non-finite x gives a NaN part).  The
+// cut is made in registers, between the LDS read and the MFMAs: 32 x 16 values cost a wave 44 vector
+// operations and feed 3 TN MFMAs, so a wave owns 32 rows and ALL columns of the workgroup's tile (no
+// other wave cuts the same values), and the vector work hides behind the matrix work of the other
+// waves of the SIMD.  The matrix pipe bounds it: three products per value are what exactness costs.
+// Compared with planes written to memory by a kernel of their own and one product over the tripled
+// contraction (the earlier form) there is no 6-byte copy of X, no threefold copy of Z, and a Z
+// fragment read from LDS serves three MFMAs.  Whole calls, int8 weights, us before and now: 8192 x 3072 x 768
+// forward 136 -> 110, its input gradient 165 -> 121; 16384 x 4096 x 1024 374 -> 348 (1.2 PFLOP/s of MFMAs)
+// and 457 -> 350; 272 x 4096 x 4096 93 -> 59; 256 x 256 x 256 19 -> 13.  Three stages in the ring (two
+// workgroups per CU instead of three): 110 -> 113, 348 -> 365.
+// A stage is 32 elements of the contraction: rows of 128 bytes of X (chunk c of row r at
+// c ^ ((r >> 1) & 7), as above) and of 64 bytes of Z (chunk c of row r at c ^ ((r >> 2) & 3): sixteen
+// consecutive rows reading one chunk fall on sixteen different 16-byte slots of the 64 banks).
+// g.R, g.pitch, g.k_per_split: bytes of Z; a byte of Z stands for two of X.
+__device__ __forceinline__ void cut3(const v4f (&x)[2], v4i (&plane)[3]) {
+  uint32_t b0[8], b1[8], b2[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float v = x[e >> 2][e & 3];
+    b0[e] = __float_as_uint(v);
+    const float r1 = __fsub_rn(v, __uint_as_float(b0[e] & 0xFFFF0000u));
+    b1[e] = __float_as_uint(r1);
+    b2[e] = __float_as_uint(__fsub_rn(r1, __uint_as_float(b1[e] & 0xFFFF0000u)));
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {  // the high halves of two neighbours
+    plane[0][e] = (int)__builtin_amdgcn_perm(b0[2 * e + 1], b0[2 * e], 0x07060302u);
+    plane[1][e] = (int)__builtin_amdgcn_perm(b1[2 * e + 1], b1[2 * e], 0x07060302u);
+    plane[2][e] = (int)__builtin_amdgcn_perm(b2[2 * e + 1], b2[2 * e], 0x07060302u);
+  }
+}
+
+template <int NW, int TN, int STAGES>
+__global__ __launch_bounds__(NW * 64) void gemm_cut3_kernel(GemmParams g) {
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  constexpr int BM = 32 * NW, BN = 32 * TN;
+  constexpr int XROW = 128, ZROW = 64;  // bytes of a stage per row
+  constexpr int STAGE = BM * XROW + BN * ZROW;
+  constexpr int XL = BM / 8 / NW, ZL = BN / 16 / NW, LPW = XL + ZL;  // wave-level DMA instructions per stage
+  static_assert(XL == 4 && ZL * 16 * NW == BN && (STAGES - 2) * LPW <= 63, "DMA split over the waves");
+  const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lds_base = (uint32_t)(size_t)(lds_void*)lds;
+  // workgroup -> tile as in gemm_nt_kernel
+  constexpr uint32_t GROUP = 8;
+  const uint32_t ntiles = g.tiles_p * g.tiles_q, nwork = ntiles * g.nsplit, chunk = (nwork + 7u) >> 3;
+  const uint32_t work = (blockIdx.x & 7u) * chunk + (blockIdx.x >> 3);
+  if ((blockIdx.x >> 3) >= chunk || work >= nwork) return;
+  const uint32_t slice = work / ntiles, tile = work - slice * ntiles;
+  const uint32_t band = tile / (GROUP * g.tiles_q), band_p = band * GROUP;
+  const uint32_t band_rows = min(GROUP, g.tiles_p - band_p), in_band = tile - band * GROUP * g.tiles_q;
+  const uint32_t p0 = (band_p + in_band % band_rows) * BM, q0 = (in_band / band_rows) * BN;
+  const uint32_t kbeg = slice * g.k_per_split, kend = min(g.R, kbeg + g.k_per_split);
+  const int ktiles = (int)((kend - kbeg + ZROW - 1) / ZROW);
+
+  const __amdgpu_buffer_rsrc_t xrsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(g.X), 0, (int)(g.P * g.pitch_x), 0x00020000);
+  const __amdgpu_buffer_rsrc_t zrsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(g.Z), 0, (int)(g.Q * g.pitch), 0x00020000);
+
+  // DMA: an instruction fills 8 rows of X (lane L: row L / 8, the chunk whose slot is L % 8; the swizzle
+  // depends on the parity of the 8-row block) or 16 rows of Z (row L / 4, the chunk whose slot is L % 4)
+  const uint32_t xc0 = ((lane & 7u) ^ (lane >> 4)) * 16, xc1 = xc0 ^ 64u;
+  const uint32_t zc = ((lane & 3u) ^ ((lane >> 4) & 3u)) * 16;
+  const uint32_t xvoff = (p0 + wave * 32 + (lane >> 3)) * g.pitch_x;
+  const uint32_t zvoff = (q0 + wave * ZL * 16 + (lane >> 2)) * g.pitch;
+  auto issue = [&](int kt, int buf) {
+    const uint32_t zk = kbeg + (uint32_t)kt * ZROW, xk = 2 * zk;
+    const uint32_t xs = lds_base + buf * STAGE + wave * 32 * XROW;
+    const uint32_t zs = lds_base + buf * STAGE + BM * XROW + wave * ZL * 1024;
+#pragma unroll
+    for (int i = 0; i < XL; ++i) {
+      const uint32_t k = xk + ((i & 1) ? xc1 : xc0);
+      lds_dma16(xrsrc, xs + i * 1024, k < 2 * kend ? xvoff + i * 8 * g.pitch_x + k : OOB);
+    }
+    const uint32_t k = zk + zc;
+#pragma unroll
+    for (int i = 0; i < ZL; ++i) lds_dma16(zrsrc, zs + i * 1024, k < kend ? zvoff + i * 16 * g.pitch + k : OOB);
+  };
+
+  // operand reads: lane (row = lane % 32, kgroup = lane / 32) takes 8 elements of the contraction
+  uint32_t xoff[4], zoff[2];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    xoff[t] = (wave * 32 + (lane & 31u)) * XROW + ((((t >> 1) * 4 + (t & 1) + (lane >> 5) * 2) ^ ((lane >> 1) & 7u)) << 4);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) zoff[t] = BM * XROW + (lane & 31u) * ZROW + (((2 * t + (lane >> 5)) ^ ((lane >> 2) & 3u)) << 4);
+
+  v16f acc[1][TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][j][r] = 0.0f;
+
+#pragma unroll
+  for (int s = 0; s < STAGES - 1; ++s) issue(s, s);  // stages past the end load zeros
+  for (int kt0 = 0; kt0 < ktiles; kt0 += STAGES) {
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s) {
+      const int kt = kt0 + s;
+      if (kt < ktiles) {
+        wait_vmcnt<(STAGES - 2) * LPW>();
+        __syncthreads();
+        issue(kt + STAGES - 1, (s + STAGES - 1) % STAGES);
+        const uint8_t* const stage = lds + s * STAGE;
+        v4f x[2][2];
+        v4i z[2][TN];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          x[ks][0] = *reinterpret_cast<const v4f*>(stage + xoff[2 * ks]);
+          x[ks][1] = *reinterpret_cast<const v4f*>(stage + xoff[2 * ks + 1]);
+#pragma unroll
+          for (int j = 0; j < TN; ++j) z[ks][j] = *reinterpret_cast<const v4i*>(stage + zoff[ks] + j * 32 * ZROW);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          v4i plane[3];
+          cut3(x[ks], plane);
+#pragma unroll
+          for (int b = 2; b >= 0; --b)  // small parts first
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[0][j] = BF16Mma::mma(z[ks][j], plane[b], acc[0][j]);
+        }
+      }
+    }
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+  static_assert(NW * epilogue_wave_bytes(TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
+  write_wave_tile<BF16Mma, 1, TN>(g, acc, lds + wave * epilogue_wave_bytes(TN), lane, p0 + wave * 32, q0, slice);
+}
+
 // The slice sum in a launch of its own.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(SliceSum r) {
   if (r.is_int) slice_sum<true>(r, blockIdx.x, gridDim.x);
@@ -888,6 +1035,68 @@ hipError_t launch_mma(const GemmParams& g, const Plan& pl, const SliceSumPlan& s
   return launch_tile<MMA, 64, 64, 2, 2, 3>(g, ss, stream);
 }
 
+// Tiles and contraction slices of gemm_cut3_kernel, by the same model: 128 x 128 tiles of four waves,
+// 64 x 64 of two for outputs too small to give every CU one; a stage is 32 elements.
+struct Cut3Kind {
+  int waves, tn, per_cu;
+  double rate_chip, fixed;
+};
+constexpr Cut3Kind CUT3_KINDS[] = {{4, 4, 3, 1.2e15, 8.0}, {2, 2, 6, 0.5e15, 8.0}};
+
+struct Cut3Plan {
+  int kind;
+  uint32_t nsplit, k_per_split;  // bytes of Z
+};
+Cut3Plan make_cut3_plan(size_t P, size_t Q, size_t R, size_t partial_bytes) {
+  const size_t ksteps = (2 * R + 63) / 64;
+  Cut3Plan best{};
+  double best_time = -1.0;
+  size_t best_n = 1;
+  for (int kind = 0; kind < 2; ++kind) {
+    const Cut3Kind& k = CUT3_KINDS[kind];
+    const size_t bm = 32 * k.waves, bn = 32 * k.tn, t = ((P + bm - 1) / bm) * ((Q + bn - 1) / bn);
+    size_t max_split = ksteps >= 32 ? ksteps / 16 : 1;
+    if (max_split > 64) max_split = 64;
+    for (size_t n = 1; n <= max_split; ++n) {
+      if (n > 1 && n * P * Q * sizeof(uint32_t) > partial_bytes) break;
+      const size_t per_cu = (t * n + NUM_CU - 1) / NUM_CU;  // items of the busiest CU
+      const size_t stages = (ksteps + n - 1) / n;
+      // a CU's rate with fewer workgroups than it holds
+      const double share = per_cu >= (size_t)k.per_cu ? 1.0 : per_cu >= 2 ? 0.95 : 0.7;
+      double time = (double)per_cu * ((double)stages + k.fixed) * 3.0 * 2.0 * bm * bn * 32 / (k.rate_chip / NUM_CU * share);
+      if (n > 1) time += 2.0 * (double)n * (double)P * (double)Q * 4.0 / PARTIAL_BYTES_PER_SECOND + 3e-6;
+      if (best_time < 0.0 || time < best_time) {
+        best_time = time;
+        best.kind = kind;
+        best_n = n;
+      }
+    }
+  }
+  const size_t steps_per = (ksteps + best_n - 1) / best_n;
+  best.k_per_split = (uint32_t)(steps_per * 64);
+  best.nsplit = (uint32_t)((ksteps + steps_per - 1) / steps_per);
+  return best;
+}
+
+template <int NW, int TN, int STAGES>
+hipError_t launch_cut3(GemmParams g, hipStream_t stream) {
+  constexpr int LDS_BYTES = STAGES * (32 * NW * 128 + 32 * TN * 64);
+  auto kern = &gemm_cut3_kernel<NW, TN, STAGES>;
+  static const hipError_t configured = hipFuncSetAttribute(
+      reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+  if (configured != hipSuccess) return configured;
+  g.tiles_p = (g.P + 32 * NW - 1) / (32 * NW);
+  g.tiles_q = (g.Q + 32 * TN - 1) / (32 * TN);
+  const uint32_t blocks = ((g.tiles_p * g.tiles_q * g.nsplit + 7) / 8) * 8;
+  kern<<<blocks, NW * 64, LDS_BYTES, stream>>>(g);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || g.nsplit == 1) return e;
+  SliceSum own{};
+  own.partial = g.partial; own.out = g.out; own.nsplit = g.nsplit; own.total = (size_t)g.P * g.Q;
+  own.s = GemmScale{g.alpha, g.sx, g.sz, g.sx_dev, g.sz_dev};
+  return launch_slice_sum(own, stream);
+}
+
 }  // namespace
 
 size_t gemm_workspace_bytes(size_t P, size_t Q, size_t R, int pipe) {
@@ -940,6 +1149,22 @@ hipError_t launch_slice_sum(const SliceSum& r, hipStream_t stream) {
   if (r.total == 0) return hipSuccess;
   splitk_reduce_kernel<<<slice_sum_blocks(r, 256, 4), 256, 0, stream>>>(r);
   return hipGetLastError();
+}
+
+hipError_t launch_gemm_f32_bf16(float* out, const float* X, const uint16_t* Z, size_t P, size_t Q, size_t R,
+                                const GemmScale& s, void* partial, size_t partial_bytes, hipStream_t stream) {
+  const Cut3Plan pl = make_cut3_plan(P, Q, R, partial_bytes);
+  GemmParams g{};
+  g.out = out;
+  g.partial = static_cast<uint32_t*>(partial);
+  g.X = reinterpret_cast<const uint8_t*>(X);
+  g.Z = reinterpret_cast<const uint8_t*>(Z);
+  g.P = (uint32_t)P; g.Q = (uint32_t)Q; g.R = g.pitch = (uint32_t)(2 * R);
+  g.pitch_x = (uint32_t)(4 * R);
+  g.k_per_split = pl.k_per_split;
+  g.nsplit = pl.nsplit;
+  g.alpha = s.alpha; g.sx = s.sx; g.sz = s.sz; g.sx_dev = s.sx_dev; g.sz_dev = s.sz_dev;
+  return pl.kind == 0 ? launch_cut3<4, 4, 2>(g, stream) : launch_cut3<2, 2, 3>(g, stream);
 }
 
 }  // namespace srq

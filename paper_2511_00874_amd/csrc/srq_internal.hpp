@@ -12,7 +12,7 @@ namespace srq {
 enum StoreMode {
   STORE_BYTE = 0,   // one byte per element (INT4 values sign-extended to the byte)
   STORE_NIBBLE = 1, // INT4 only: two elements per byte along the output's contiguous dim
-  STORE_BF16 = 2    // E4M3 / E5M2 only: the grid value itself as bfloat16 (two bytes per element)
+  STORE_BF16 = 2    // the grid value itself as bfloat16 (two bytes per element)
 };
 
 struct QuantArgs {
@@ -82,13 +82,6 @@ hipError_t launch_absmax_batch(AbsmaxBatch& b, hipStream_t stream);
 hipError_t launch_update_bf16(uint16_t* w, const float* g, float eta, size_t n, int round, uint64_t seed,
                               uint64_t counter_offset, hipStream_t stream);
 
-// Weight-only objective (Sec. 3.2).  split3: x (rows x cols binary32, cols % 8 == 0) as rows x 3 cols
-// bfloat16, row m = [p0 | p1 | p2] with p0 + p1 + p2 = x row m exactly.  repeat3: rows x cols bfloat16
-// -> rows x 3 cols, each row three times over.  Integer codes (n bytes, n % 8 == 0) -> bfloat16 values.
-hipError_t launch_split3(uint16_t* out, const float* x, size_t rows, size_t cols, hipStream_t stream);
-hipError_t launch_repeat3(uint16_t* out, const uint16_t* in, size_t rows, size_t cols, hipStream_t stream);
-hipError_t launch_int_codes_to_bf16(uint16_t* out, const uint8_t* codes, size_t n, hipStream_t stream);
-
 hipError_t launch_absmax_scale(float* scale_out_dev, const void* x, int dtype, size_t n, int kind,
                                hipStream_t stream);
 
@@ -135,6 +128,11 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
 // s.alpha carries a factor 1/16 (the kernel multiplies 16 * value).  Only where
 // gemm_takes_packed_x says so: the int8 pipeline on the 256 x 256 tiles.
 bool gemm_takes_packed_x(size_t P, size_t Q, size_t R, int pipe);
+// Weight-only objective (Sec. 3.2): out (P x Q) = X . Z^T, X binary32 as it is (P x R), Z bfloat16 (Q x R),
+// R % 16 == 0; exact products, binary32 sums.  `partial`: room for slices of the contraction (as many as
+// fit; none if partial_bytes is 0).  Operands below 2 GiB each (gemm_operands_addressable).
+hipError_t launch_gemm_f32_bf16(float* out, const float* X, const uint16_t* Z, size_t P, size_t Q, size_t R,
+                                const GemmScale& s, void* partial, size_t partial_bytes, hipStream_t stream);
 // a deferred slice sum that found no later launch to ride on
 hipError_t launch_slice_sum(const SliceSum& r, hipStream_t stream);
 

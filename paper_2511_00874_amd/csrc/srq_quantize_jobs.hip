@@ -305,8 +305,11 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
   const uint32_t local = blockIdx.x - j.first_block;
   const bool bf = j.store == STORE_BF16;
   switch (j.kind) {
-    case SRQ_INT8: run_job<SRQ_INT8, false>(j, local, smem); break;
-    case SRQ_INT4: run_job<SRQ_INT4, false>(j, local, smem); break;
+    case SRQ_INT8: case SRQ_INT4:
+      if (bf) run_job<SRQ_INTX, true>(j, local, smem);
+      else if (j.kind == SRQ_INT8) run_job<SRQ_INT8, false>(j, local, smem);
+      else run_job<SRQ_INT4, false>(j, local, smem);
+      break;
     case SRQ_E4M3:
       if (bf) run_job<SRQ_E4M3, true>(j, local, smem);
       else run_job<SRQ_E4M3, false>(j, local, smem);
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
 }  // namespace
 
 // Requirements (checked by the callers): rows % 16 == 0 and cols % 16 == 0 for every job,
-// store is STORE_BYTE or STORE_BF16 (STORE_BF16 only with E4M3 / E5M2).
+// store is STORE_BYTE or STORE_BF16.
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
   uint32_t first = 0;
   for (int i = 0; i < jobs.njobs; ++i) {

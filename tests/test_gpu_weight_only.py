@@ -84,6 +84,29 @@ def test_gpt2_mlp_shape_int8_weights():
     check_product(dA, ref, ab, "dA")
 
 
+# binary32 rows: less than a tile, edges of the 64- and 128-wide tiles, contractions that end inside a
+# stage of 32 elements, one stage, a sliced contraction whose last slice is short, many tiles
+@pytest.mark.parametrize("M,N,K", [(16, 16, 16), (64, 64, 48), (80, 112, 32), (144, 272, 80), (128, 128, 4112),
+                                   (48, 2064, 1040), (2064, 2064, 144)])
+def test_binary32_rows_at_the_edges_of_tiles_stages_and_slices(M, N, K):
+    A, dY, W, sW = _case(M, N, K, L.E4M3, False, True, seed=90)
+    qW, oq = L.Quant(L.E4M3, sW, seed=6, counter_offset=3), oracle.Quant(L.E4M3, sW, seed=6, counter_offset=3)
+    say("binary32 rows", M, N, K)
+    Y = L.sr_linear_fwd(A, W, NOQ, qW).cpu().numpy()
+    ref, ab = oracle.linear_fwd_weight_only(host_src(A), host_src(W), oq, want_abs=True)
+    check_product(Y, ref, ab, "Y")
+    dA = L.sr_linear_bwd_data(dY, W, NOQ, qW).cpu().numpy()
+    ref, ab = oracle.linear_bwd_data_weight_only(host_src(dY), host_src(W), oq, want_abs=True)
+    check_product(dA, ref, ab, "dA")
+    # a non-finite value reaches its own row of the result and no other
+    clean = torch.from_numpy(Y).to(DEV)
+    A[M // 2, K - 1] = float("inf")
+    Y = L.sr_linear_fwd(A, W, NOQ, qW)
+    assert bool(torch.isnan(Y[M // 2]).all())
+    keep = torch.arange(M, device=DEV) != M // 2
+    assert torch.equal(Y[keep], clean[keep])
+
+
 def test_where_the_identity_quantizer_is_not_accepted():
     A = torch.zeros((16, 16), device=DEV)
     q8 = L.Quant(L.INT8, 1.0)
