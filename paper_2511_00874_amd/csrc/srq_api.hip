@@ -62,15 +62,24 @@ int check_pair(int kx, int kz) {
   return SRQ_ERR_UNSUPPORTED;
 }
 
+// From this many multiplications per product on (M N K: the same for the three products of a layer),
+// any two 8-bit float operands are multiplied from their one-byte codes: half the bytes written by the
+// quantizer and read by the product for two instructions per four codes.  E4M3 calls, bfloat16 form
+// against codes: backward 4096 x 2048 x 2048 117 -> 94 us, 16384 x 5632 x 2048 911 -> 732, 1008 x 768 x 768
+// 26 -> 19, 512 x 768 x 768 19.1 -> 18.0.  At 256 x 512 x 512 and below both take the time of their
+// launches (18 us) and the bfloat16 form stays.
+constexpr size_t CODES_MIN_WORK = 1ull << 27;
+bool codes_pay(size_t M, size_t N, size_t K) { return M * N >= CODES_MIN_WORK / K; }
+
 // Matrix pipeline for a product of two quantized operands; -1 if the two disagree.
-int pick_pipe(const srq_quant* qx, const srq_quant* qz) {
+int pick_pipe(const srq_quant* qx, const srq_quant* qz, bool e5m2_call, bool big) {
   if (kind_is_int(qx->kind)) return PIPE_I8;
   const bool fx = qx->flags & SRQ_FLAG_F8_PIPELINE, fz = qz->flags & SRQ_FLAG_F8_PIPELINE;
   if (fx != fz) return -1;
   if (fx) return PIPE_F8;
-  // exact pipelines: E5M2 x E5M2 multiplies straight from the one-byte codes; anything with an
-  // E4M3-family operand goes through the bfloat16 form
-  return qx->kind == SRQ_E5M2 && qz->kind == SRQ_E5M2 ? PIPE_F16C : PIPE_BF16;
+  // exact pipelines: calls whose operands are all E5M2, and large products of any 8-bit floats, multiply
+  // straight from the one-byte codes; small ones with an E4M3-family operand go through the bfloat16 form
+  return (e5m2_call && qx->kind == SRQ_E5M2 && qz->kind == SRQ_E5M2) || big ? PIPE_F16C : PIPE_BF16;
 }
 
 // int32 accumulation is exact while R * 127^2 < 2^31
@@ -127,17 +136,18 @@ struct ProductPlan {
   size_t es, x_bytes, z_bytes, gemm_bytes;
 };
 
-// from_codes = false: an operand shared with another product is stored as bfloat16 there, so
-// this product may not use the pipeline that reads one-byte E5M2 codes.
+// e5m2_call = false: an operand of the product is shared with another one that has an E4M3-family
+// operand, so E5M2 x E5M2 is treated like any other pair of 8-bit floats here.
 int plan_product(ProductPlan& pp, const srq_quant* qx, const srq_quant* qz, size_t P, size_t Q, size_t R,
-                 bool from_codes = true) {
+                 bool e5m2_call = true) {
   int st = check_pair(qx->kind, qz->kind);
   if (st != SRQ_OK) return st;
   if (!int_contraction_ok(qx->kind, R)) return SRQ_ERR_UNSUPPORTED;
-  pp.pipe = pick_pipe(qx, qz);
+  pp.pipe = pick_pipe(qx, qz, e5m2_call, codes_pay(P, Q, R));
   if (pp.pipe < 0) return SRQ_ERR_UNSUPPORTED;
-  if (pp.pipe == PIPE_F16C && !from_codes) pp.pipe = PIPE_BF16;
-  if (!gemm_operands_addressable(P, Q, R, pp.pipe)) return SRQ_ERR_UNSUPPORTED;
+  // (the size limit of the pairs that have a bfloat16 form is that form's, whichever they take)
+  const bool e5m2 = e5m2_call && qx->kind == SRQ_E5M2 && qz->kind == SRQ_E5M2;
+  if (!gemm_operands_addressable(P, Q, R, pp.pipe == PIPE_F16C && !e5m2 ? PIPE_BF16 : pp.pipe)) return SRQ_ERR_UNSUPPORTED;
   pp.es = pp.pipe == PIPE_BF16 ? 2 : 1;
   pp.x_bytes = align_up(P * R * pp.es, WS_ALIGN);
   pp.z_bytes = align_up(Q * R * pp.es, WS_ALIGN);
@@ -601,11 +611,12 @@ int sr_linear_bwd_phase(float* dA, float* dW, const void* dY, int dtypedY, const
   if (!aligned16(dA) || !aligned16(dW)) return SRQ_ERR_ALIGN;
   if (beta != 0.0f && beta != 1.0f) return SRQ_ERR_UNSUPPORTED;
   ProductPlan pd, pw;  // dA = dY (M x N) . Wt (K x N)^T ;  dW = dYt (N x M) . At (K x M)^T
-  // Q(dY) is stored once for both products: one-byte codes only if all three formats are E5M2
-  const bool codes = qW_bwd->kind == SRQ_E5M2 && qA_bwd->kind == SRQ_E5M2;
-  st = plan_product(pd, qdY_bwd, qW_bwd, M, K, N, codes);
+  // Q(dY) is stored once for both products: one-byte codes only if all three formats are E5M2, or
+  // the products are large
+  const bool e5m2 = qW_bwd->kind == SRQ_E5M2 && qA_bwd->kind == SRQ_E5M2;
+  st = plan_product(pd, qdY_bwd, qW_bwd, M, K, N, e5m2);
   if (st != SRQ_OK) return st;
-  st = plan_product(pw, qdY_bwd, qA_bwd, N, K, M, codes);
+  st = plan_product(pw, qdY_bwd, qA_bwd, N, K, M, e5m2);
   if (st != SRQ_OK) return st;
   if (pd.pipe != pw.pipe) return SRQ_ERR_UNSUPPORTED;  // one stored form of Q(dY) serves both products
   const size_t need = pd.x_bytes + pd.z_bytes + pd.gemm_bytes + pw.x_bytes + pw.z_bytes + pw.gemm_bytes;
@@ -682,7 +693,7 @@ int sr_linear_fwd_stash_phase(float* Y, const void* A, int dtypeA, const void* W
   if (st != SRQ_OK) return st;
   // the stored form of the backward operands: the pipeline their products with dY will use
   if (check_pair(qA_bwd->kind, qW_bwd->kind) != SRQ_OK) return SRQ_ERR_UNSUPPORTED;
-  const int stash_pipe = pick_pipe(qA_bwd, qW_bwd);
+  const int stash_pipe = pick_pipe(qA_bwd, qW_bwd, true, codes_pay(M, N, K));
   if (stash_pipe < 0) return SRQ_ERR_UNSUPPORTED;
   if (!workspace_ok(workspace, workspace_bytes, pf.x_bytes + pf.z_bytes + pf.gemm_bytes)) return SRQ_ERR_WORKSPACE;
   if (!workspace_ok(stash, stash_bytes, sr_linear_stash_bytes(M, N, K))) return SRQ_ERR_WORKSPACE;
@@ -725,13 +736,15 @@ int sr_linear_bwd_stashed_phase(float* dA, float* dW, const void* dY, int dtyped
   if (!aligned16(dA) || !aligned16(dW)) return SRQ_ERR_ALIGN;
   if (beta != 0.0f && beta != 1.0f) return SRQ_ERR_UNSUPPORTED;
   ProductPlan pd, pw;
-  // all three operands in one stored form, the one the stash was written in (one-byte codes
-  // when A and W are both E5M2, which then needs an E5M2 dY as well)
+  // all three operands in one stored form, the one the stash was written in; A and W both E5M2
+  // need an E5M2 dY as well, whatever the size
   if (check_pair(qA_bwd->kind, qW_bwd->kind) != SRQ_OK) return SRQ_ERR_UNSUPPORTED;
-  const int stash_pipe = pick_pipe(qA_bwd, qW_bwd);
-  st = plan_product(pd, qdY_bwd, qW_bwd, M, K, N, stash_pipe == PIPE_F16C);
+  const int stash_pipe = pick_pipe(qA_bwd, qW_bwd, true, codes_pay(M, N, K));
+  const bool e5m2 = qA_bwd->kind == SRQ_E5M2 && qW_bwd->kind == SRQ_E5M2;
+  if (stash_pipe == PIPE_F16C && e5m2 && qdY_bwd->kind != SRQ_E5M2) return SRQ_ERR_UNSUPPORTED;
+  st = plan_product(pd, qdY_bwd, qW_bwd, M, K, N, e5m2);
   if (st != SRQ_OK) return st;
-  st = plan_product(pw, qdY_bwd, qA_bwd, N, K, M, stash_pipe == PIPE_F16C);
+  st = plan_product(pw, qdY_bwd, qA_bwd, N, K, M, e5m2);
   if (st != SRQ_OK) return st;
   if (pd.pipe != pw.pipe || pd.pipe != stash_pipe) return SRQ_ERR_UNSUPPORTED;
   const size_t need = pd.x_bytes + pd.gemm_bytes + pw.x_bytes + pw.gemm_bytes;

@@ -107,10 +107,10 @@ __global__ __launch_bounds__(256) void fused_fwd_kernel(FusedParams f) {
       const uint32_t chunk = (swz ^ (uint32_t)(2 * ks)) << 4;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
-        xe[i] = MMA::expand(*reinterpret_cast<const raw_t*>(lds + (wp * WTM + i * 32 + (lane & 31u)) * BK + chunk));
+        xe[i] = MMA::expand_x(*reinterpret_cast<const raw_t*>(lds + (wp * WTM + i * 32 + (lane & 31u)) * BK + chunk));
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        ze[j] = MMA::expand(*reinterpret_cast<const raw_t*>(lds + BM * BK + (wq * WTN + j * 32 + (lane & 31u)) * BK + chunk));
+        ze[j] = MMA::expand_z(*reinterpret_cast<const raw_t*>(lds + BM * BK + (wq * WTN + j * 32 + (lane & 31u)) * BK + chunk));
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -176,7 +176,7 @@ hipError_t launch_fused_fwd(float* out, const void* x, const QuantArgs& qx, cons
   // 64 x 64 tiles while they still give every CU a workgroup; 128 x 128 beyond (half the re-rounding)
   const bool large = ((P + 63) / 64) * ((Q + 63) / 64) > 1024;
   if (kind_is_int(qx.kind)) return launch_fused<I8Mma, SRQ_INTX>(f, large, stream);
-  return launch_fused<E5M2F16Mma, SRQ_E5M2>(f, large, stream);
+  return launch_fused<F8F16Mma<1, 1>, SRQ_E5M2>(f, large, stream);
 }
 
 }  // namespace srq

@@ -7,9 +7,9 @@
 // operands with the contraction index contiguous.  Four matrix pipelines:
 //   int8 codes          v_mfma_i32_32x32x32_i8        int32 accumulators, exact
 //   E4M3/E5M2 as bf16   v_mfma_f32_32x32x16_bf16      exact products, binary32 sums
-//   E5M2 codes as f16   v_mfma_f32_32x32x16_f16       the same, from one-byte codes: an E5M2 code is the
-//                                                     high byte of the binary16 number of the same value,
-//                                                     so the operands are widened in registers
+//   E4M3/E5M2 as f16    v_mfma_f32_32x32x16_f16       the same, from one-byte codes: every value is a
+//                                                     binary16 number, the operands are widened in
+//                                                     registers
 //   E4M3/E5M2 codes     v_mfma_f32_32x32x64_f8f6f4    fp8 pipeline (aligns groups of 8 products)
 //
 // Kernel shape.  A workgroup owns a BM x BN output tile, its waves a WGM x WGN grid of
@@ -332,9 +332,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, Sl
         __builtin_amdgcn_sched_barrier(0);
         frag_t xe[TM], ze[TN];  // (a plain copy unless the pipeline widens its operands)
 #pragma unroll
-        for (int i = 0; i < TM; ++i) xe[i] = MMA::expand(xf[ks % (PF + 1)][i]);
+        for (int i = 0; i < TM; ++i) xe[i] = MMA::expand_x(xf[ks % (PF + 1)][i]);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) ze[j] = MMA::expand(zf[ks % (PF + 1)][j]);
+        for (int j = 0; j < TN; ++j) ze[j] = MMA::expand_z(zf[ks % (PF + 1)][j]);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -349,18 +349,18 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, Sl
       // groups below pin that interleaving).
       frag_t xe[2][TM], ze[2][TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) xe[0][i] = MMA::expand(xf[0][i]);
+      for (int i = 0; i < TM; ++i) xe[0][i] = MMA::expand_x(xf[0][i]);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) ze[0][j] = MMA::expand(zf[0][j]);
+      for (int j = 0; j < TN; ++j) ze[0][j] = MMA::expand_z(zf[0][j]);
 #pragma unroll
       for (int ks = 0; ks < KSUB; ++ks) {
         if (ks + PF < KSUB) fetch(ks + PF);
         __builtin_amdgcn_sched_barrier(0);
         if (ks + 1 < KSUB) {
 #pragma unroll
-          for (int i = 0; i < TM; ++i) xe[(ks + 1) & 1][i] = MMA::expand(xf[(ks + 1) % (PF + 1)][i]);
+          for (int i = 0; i < TM; ++i) xe[(ks + 1) & 1][i] = MMA::expand_x(xf[(ks + 1) % (PF + 1)][i]);
 #pragma unroll
-          for (int j = 0; j < TN; ++j) ze[(ks + 1) & 1][j] = MMA::expand(zf[(ks + 1) % (PF + 1)][j]);
+          for (int j = 0; j < TN; ++j) ze[(ks + 1) & 1][j] = MMA::expand_z(zf[(ks + 1) % (PF + 1)][j]);
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -582,11 +582,11 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
           const int hi = (int)0xF0F0F0F0u;
           xe[i] = frag_t{(x[0] << 4) & hi, (x[1] << 4) & hi, x[0] & hi, x[1] & hi};
         } else {
-          xe[i] = MMA::expand(xf[ks % (PF + 1)][i]);
+          xe[i] = MMA::expand_x(xf[ks % (PF + 1)][i]);
         }
       }
 #pragma unroll
-      for (int j = 0; j < TN; ++j) ze[j] = MMA::expand(zf[ks % (PF + 1)][j]);
+      for (int j = 0; j < TN; ++j) ze[j] = MMA::expand_z(zf[ks % (PF + 1)][j]);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -1136,9 +1136,14 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
   if (x_packed) return launch_persist<I8Mma, true>(g, ss, stream);
   if (pipe == PIPE_I8) return launch_mma<I8Mma>(g, pl, ss, stream);
   if (pipe == PIPE_BF16) return launch_mma<BF16Mma>(g, pl, ss, stream);
-  if (pipe == PIPE_F16C) return launch_mma<E5M2F16Mma>(g, pl, ss, stream);
   // the Z operand is the first MFMA operand, X the second
   const int fx = kindX == SRQ_E5M2, fz = kindZ == SRQ_E5M2;
+  if (pipe == PIPE_F16C) {
+    if (!fz && !fx) return launch_mma<F8F16Mma<0, 0>>(g, pl, ss, stream);
+    if (!fz && fx) return launch_mma<F8F16Mma<0, 1>>(g, pl, ss, stream);
+    if (fz && !fx) return launch_mma<F8F16Mma<1, 0>>(g, pl, ss, stream);
+    return launch_mma<F8F16Mma<1, 1>>(g, pl, ss, stream);
+  }
   if (!fz && !fx) return launch_mma<F8Mma<0, 0>>(g, pl, ss, stream);
   if (!fz && fx) return launch_mma<F8Mma<0, 1>>(g, pl, ss, stream);
   if (fz && !fx) return launch_mma<F8Mma<1, 0>>(g, pl, ss, stream);

@@ -20,13 +20,14 @@ typedef __attribute__((address_space(3))) void lds_void;
 constexpr int BK = 128;  // bytes of contraction per LDS stage
 
 // raw_t: what a lane reads from LDS for one contraction sub-step (a multiple of 16 bytes);
-// frag_t: what the MFMA(s) of that sub-step consume; expand() turns one into the other.
+// frag_t: what the MFMA(s) of that sub-step consume; expand_x() / expand_z() turn one into the other.
 struct I8Mma {
   using acc_t = v16i;
   using raw_t = v4i;
   using frag_t = v4i;
   static constexpr bool WIDENS = false;
-  static __device__ __forceinline__ frag_t expand(raw_t r) { return r; }
+  static __device__ __forceinline__ frag_t expand_x(raw_t r) { return r; }
+  static __device__ __forceinline__ frag_t expand_z(raw_t r) { return r; }
   static constexpr int KSTEP = 32;  // contraction bytes per MFMA
   static __device__ __forceinline__ acc_t mma(frag_t a, frag_t b, acc_t c) {
     return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
@@ -44,7 +45,8 @@ struct BF16Mma {
   using raw_t = v4i;
   using frag_t = v4i;  // 8 bfloat16
   static constexpr bool WIDENS = false;
-  static __device__ __forceinline__ frag_t expand(raw_t r) { return r; }
+  static __device__ __forceinline__ frag_t expand_x(raw_t r) { return r; }
+  static __device__ __forceinline__ frag_t expand_z(raw_t r) { return r; }
   static constexpr int KSTEP = 32;  // bytes: 16 elements per MFMA
   static __device__ __forceinline__ acc_t mma(frag_t a, frag_t b, acc_t c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c,
@@ -62,7 +64,8 @@ struct F8Mma {
   using raw_t = v8i;
   using frag_t = v8i;
   static constexpr bool WIDENS = false;
-  static __device__ __forceinline__ frag_t expand(raw_t r) { return r; }
+  static __device__ __forceinline__ frag_t expand_x(raw_t r) { return r; }
+  static __device__ __forceinline__ frag_t expand_z(raw_t r) { return r; }
   static constexpr int KSTEP = 64;
   static __device__ __forceinline__ acc_t mma(frag_t a, frag_t b, acc_t c) {
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, FA, FB, 0, 0, 0, 0);
@@ -72,28 +75,39 @@ struct F8Mma {
   static __device__ __forceinline__ uint32_t bits(float v) { return __float_as_uint(v); }
 };
 
-// E5M2 codes on the f16 pipeline.  E5M2 is binary16 cut to its high byte, so (code << 8) is the
-// binary16 number of the same value (subnormals included; the MFMA honours binary16 subnormals).
-// A lane reads 16 codes per sub-step and widens them with four byte permutes into two operands
-// of 8 halves: one sub-step is two MFMAs of depth 16.  Products are exact (6-bit significands),
-// sums binary32, as on the bf16 pipeline, with half the operand bytes through LDS.
-struct E5M2F16Mma {
+// 8-bit float codes on the f16 pipeline: every E4M3 and E5M2 value is a binary16 number (subnormals
+// included; the MFMA honours them).  A lane reads 16 codes per sub-step and widens them, two per
+// instruction, into two operands of 8 halves: one sub-step is two MFMAs of depth 16.  E5M2 is
+// binary16 cut to its high byte, so (code << 8) is the number: a byte permute.  E4M3 goes through the
+// conversion of the fp8 unit, NaN included.  Products are exact (at most 8 significand bits), sums
+// binary32, as on the bf16 pipeline, with half the operand bytes through LDS.
+// ZE5 / XE5: the format of the first (Z) / second (X) MFMA operand, 0 = E4M3, 1 = E5M2
+template <int ZE5, int XE5>
+struct F8F16Mma {
   using acc_t = v16f;
   using raw_t = v4i;   // 16 codes
   using frag_t = v8i;  // 16 halves: codes 0..7, then 8..15
   static constexpr bool WIDENS = true;
   static constexpr int MFMA_PER_MMA = 2, VALU_PER_EXPAND = 8;
   static constexpr int KSTEP = 32;  // 32 codes (two lane groups of 16) per sub-step
-  static __device__ __forceinline__ frag_t expand(raw_t r) {
+  template <int E5>
+  static __device__ __forceinline__ frag_t widen(raw_t r) {
     frag_t f;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const uint32_t d = (uint32_t)r[c];
-      f[(c >> 1) * 4 + (c & 1) * 2 + 0] = (int)__builtin_amdgcn_perm(d, d, 0x010c000cu);  // codes 0,1 -> high bytes
-      f[(c >> 1) * 4 + (c & 1) * 2 + 1] = (int)__builtin_amdgcn_perm(d, d, 0x030c020cu);  // codes 2,3
+      if constexpr (E5) {
+        f[2 * c] = (int)__builtin_amdgcn_perm(d, d, 0x010c000cu);  // codes 0,1 -> high bytes
+        f[2 * c + 1] = (int)__builtin_amdgcn_perm(d, d, 0x030c020cu);  // codes 2,3
+      } else {
+        f[2 * c] = __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d, 1.0f, false));
+        f[2 * c + 1] = __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(d, 1.0f, true));
+      }
     }
     return f;
   }
+  static __device__ __forceinline__ frag_t expand_x(raw_t r) { return widen<XE5>(r); }
+  static __device__ __forceinline__ frag_t expand_z(raw_t r) { return widen<ZE5>(r); }
   static __device__ __forceinline__ acc_t mma(frag_t a, frag_t b, acc_t c) {
     const v4i a0 = {a[0], a[1], a[2], a[3]}, a1 = {a[4], a[5], a[6], a[7]};
     const v4i b0 = {b[0], b[1], b[2], b[3]}, b1 = {b[4], b[5], b[6], b[7]};

@@ -249,6 +249,49 @@ def test_llama_shapes_int4_gradient_bf16_weights():
         _run_layer(t, _quants(kinds, t, seed=2), sample=65536)
 
 
+# 1008 x 256 x 512 multiplications lie below the line from which 8-bit float operands are multiplied from
+# their codes, 1024 x 256 x 512 on it; the ragged shapes end inside tiles and stages; 4096 x 2064 x 2064
+# takes the 256 x 256 tiles and 256 x 272 x 8208 a sliced contraction
+@pytest.mark.parametrize("M,N,K", [(1008, 256, 512), (1024, 256, 512), (2064, 272, 304), (256, 272, 8208), (4096, 2064, 2064)])
+def test_eight_bit_float_formats_around_the_code_product_line(M, N, K):
+    for dy, w, a in ((L.E4M3, L.E4M3, L.E4M3), (L.E5M2, L.E4M3, L.E5M2), (L.E4M3, L.E5M2, L.E5M2),
+                     (L.E4M1, L.E5M2, L.E4M3)):
+        say("8-bit floats", M, N, K, [L.KIND_NAMES[k] for k in (dy, w, a)])
+        kinds = {"A_fwd": a, "W_fwd": L.E4M3, "A_bwd": a, "W_bwd": w, "dY_bwd": dy}
+        t = _layer(M, N, K, 31, std_dy=1e-3, w_bf16=True)
+        q = _quants(kinds, t, seed=5)
+        _run_layer(t, q, sample=2048)
+        # from the stash of an integer forward pass: the same codes, the same products
+        qi = L.Quant(L.INT8, 0.05, seed=8)
+        _, stash = L.sr_linear_fwd_stash(t["A"], t["W"], qi, qi, q["A_bwd"][0], q["W_bwd"][0])
+        args = (t["dY"], stash, K, q["dY_bwd"][0], q["W_bwd"][0], q["A_bwd"][0])
+        if a == w == L.E5M2 and dy != L.E5M2:
+            with pytest.raises(L.SrqError):
+                L.sr_linear_bwd_stashed(*args)
+        else:
+            want = L.sr_linear_bwd(t["dY"], t["W"], t["A"], *(q[n][0] for n in ("dY_bwd", "W_bwd", "A_bwd")))
+            for got, ref in zip(L.sr_linear_bwd_stashed(*args), want):
+                assert torch.equal(got, ref)
+
+
+def test_every_e4m3_value_is_widened_exactly():
+    # scale 1 and values on the grid: the quantizer passes them through, and against an identity the
+    # product returns each of them, subnormals and the largest included; a NaN reaches its row only
+    M, K = 1024, 512
+    vals = oracle.decode_array(L.E4M3, np.arange(256, dtype=np.uint8))
+    A = np.resize(np.where(np.isfinite(vals), vals, 0.0), (M, K)).astype(np.float32)
+    A = np.stack([np.roll(A[i], i) for i in range(M)])
+    W = np.eye(K, dtype=np.float32)
+    for ka, kw in ((L.E4M3, L.E4M3), (L.E4M3, L.E5M2)):
+        Y = L.sr_linear_fwd(to_dev(A), to_dev(W), L.Quant(ka, 1.0, seed=1), L.Quant(kw, 1.0, seed=2)).cpu().numpy()
+        assert np.array_equal(Y, A)
+    A[700, 3] = np.nan
+    Y = L.sr_linear_fwd(to_dev(A), to_dev(W), L.Quant(L.E4M3, 1.0, seed=1), L.Quant(L.E4M3, 1.0, seed=2)).cpu().numpy()
+    assert np.isnan(Y[700]).all()
+    keep = np.arange(M) != 700
+    assert np.array_equal(Y[keep], A[keep])
+
+
 def _two_stream_stash_step(t, q):
     """The benchmark's launch configuration: the stash pair in halves, the quantizing halves on one stream and
     the products on another, events between them; returns Y, dA, dW."""
