@@ -198,20 +198,27 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+// A 16-byte load of a source tensor: streaming, or cached for one that is small enough to be met again in
+// the last-level cache (cached_source).
+template <bool CACHED, class T>
+__device__ __forceinline__ T load_source(const T* p) {
+  if constexpr (CACHED) return *p;
+  else return __builtin_nontemporal_load(p);
+}
+
 // Load the 8 elements of group g (element index 8g..8g+7) as binary32; lanes beyond n read 0.
-template <int SRC>
+template <int SRC, bool CACHED = false>
 __device__ __forceinline__ void load_group(float (&v)[8], const void* x, size_t g, size_t n) {
   const size_t base = g * 8;
   if (base + 8 <= n) {
     if constexpr (SRC == SRQ_F32) {
       const f32x4* p = reinterpret_cast<const f32x4*>(static_cast<const float*>(x) + base);
-      const f32x4 a = __builtin_nontemporal_load(p);
-      const f32x4 b = __builtin_nontemporal_load(p + 1);
+      const f32x4 a = load_source<CACHED>(p);
+      const f32x4 b = load_source<CACHED>(p + 1);
       v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
       v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
     } else {
-      const u32x4 a = __builtin_nontemporal_load(
-          reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(x) + base));
+      const u32x4 a = load_source<CACHED>(reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(x) + base));
       v[0] = bf16_to_f32(a.x & 0xFFFFu); v[1] = bf16_to_f32(a.x >> 16);
       v[2] = bf16_to_f32(a.y & 0xFFFFu); v[3] = bf16_to_f32(a.y >> 16);
       v[4] = bf16_to_f32(a.z & 0xFFFFu); v[5] = bf16_to_f32(a.z >> 16);
@@ -277,14 +284,14 @@ __device__ __forceinline__ void store_through4(void* p, uint32_t v) {
   asm volatile("global_store_dword %0, %1, off sc0 sc1" : : "v"(p), "v"(v) : "memory");
 }
 
-template <int KIND, int ROUND, int STORE>
+template <int KIND, int ROUND, int STORE, bool CACHED = false>
 __device__ __forceinline__ void quantize_chunk_f32(uint8_t* __restrict__ out, const float* __restrict__ x,
                                                    size_t chunk, uint32_t lane, const InvScale& s, uint32_t k0,
                                                    uint32_t k1, uint64_t counter_offset) {
   constexpr bool AS_BF16 = STORE == 2;
   const size_t e0 = chunk * CHUNK + 4 * lane;  // first element of this lane's first quad
-  const f32x4 a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(x + e0));
-  const f32x4 b = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(x + e0 + 256));
+  const f32x4 a = load_source<CACHED>(reinterpret_cast<const f32x4*>(x + e0));
+  const f32x4 b = load_source<CACHED>(reinterpret_cast<const f32x4*>(x + e0 + 256));
   uint32_t addA[4], addB[4];
   if constexpr (ROUND == SRQ_SR) {
     const bool odd = lane & 1u;

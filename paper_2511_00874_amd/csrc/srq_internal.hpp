@@ -15,6 +15,15 @@ enum StoreMode {
   STORE_BF16 = 2    // the grid value itself as bfloat16 (two bytes per element)
 };
 
+// The scale of a tensor is found in one pass over it and its codes are made in another.  A tensor of at
+// most this many bytes is read with cached loads by both, so that the second pass finds what the first
+// left in the last-level cache (256 MiB, shared with everything else in flight); a larger one is
+// streamed by both.  Training steps of a 2048 x 2048 linear, everything streamed against this line: 1024
+// tokens 68 -> 65 us, 2048 82 -> 77, 4096 (32 MiB an activation) 123 -> 121; 6144 tokens (48 MiB) with
+// a line of 64 MiB 168 -> 172.  One pass cached and the other streamed is slower than either.
+constexpr size_t CACHED_SOURCE_BYTES = (size_t)40 << 20;
+inline bool cached_source(size_t n, int dtype) { return n * (dtype == SRQ_F32 ? 4 : 2) <= CACHED_SOURCE_BYTES; }
+
 struct QuantArgs {
   int kind, round, dtype, store;
   float scale;
@@ -68,6 +77,7 @@ struct AbsmaxBatch {
   const void* x[ABSMAX_MAX];
   size_t n[ABSMAX_MAX];
   int dtype[ABSMAX_MAX];
+  int cached[ABSMAX_MAX];  // cached_source() of the tensor, filled by the launcher
   uint32_t first_block[ABSMAX_MAX], nblocks[ABSMAX_MAX];
   int out_tensor[ABSMAX_MAX], out_kind[ABSMAX_MAX];
   float out_qmax[ABSMAX_MAX];

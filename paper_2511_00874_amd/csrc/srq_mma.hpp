@@ -79,7 +79,8 @@ struct F8Mma {
 // included; the MFMA honours them).  A lane reads 16 codes per sub-step and widens them, two per
 // instruction, into two operands of 8 halves: one sub-step is two MFMAs of depth 16.  E5M2 is
 // binary16 cut to its high byte, so (code << 8) is the number: a byte permute.  E4M3 goes through the
-// conversion of the fp8 unit, NaN included.  Products are exact (at most 8 significand bits), sums
+// conversion of the fp8 unit, NaN included (for E5M2 the conversion is 1 % faster than the permute on
+// 128 x 128 tiles and 5 to 10 % slower on 128 x 192).  Products are exact (at most 8 significand bits), sums
 // binary32, as on the bf16 pipeline, with half the operand bytes through LDS.
 // ZE5 / XE5: the format of the first (Z) / second (X) MFMA operand, 0 = E4M3, 1 = E5M2
 template <int ZE5, int XE5>

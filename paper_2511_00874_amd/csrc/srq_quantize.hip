@@ -258,7 +258,7 @@ __device__ __forceinline__ uint32_t abs_bits_finite(float f) {
 // max of the finite |x_i| bit patterns over the 16-byte pieces [g0, g1) of x (4 binary32 or 8
 // bfloat16 elements each; the last piece of the tensor may be partial): thread t of nt, eight loads in
 // flight per lane, the pieces of a workgroup contiguous in memory
-template <int SRC>
+template <int SRC, bool CACHED>
 __device__ __forceinline__ uint32_t absmax_pieces(const void* __restrict__ x, size_t n, size_t g0, size_t g1, uint32_t t,
                                                   uint32_t nt) {
   constexpr int PER = SRC == SRQ_F32 ? 4 : 8;
@@ -280,16 +280,16 @@ __device__ __forceinline__ uint32_t absmax_pieces(const void* __restrict__ x, si
   for (; i + 7 * (size_t)nt < gf; i += 8 * (size_t)nt) {
     u32x4 a[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) a[j] = __builtin_nontemporal_load(p + i + j * (size_t)nt);
+    for (int j = 0; j < 8; ++j) a[j] = load_source<CACHED>(p + i + j * (size_t)nt);
 #pragma unroll
     for (int j = 0; j < 8; ++j) fold(a[j]);
   }
   for (; i + 3 * (size_t)nt < gf; i += 4 * (size_t)nt) {
-    const u32x4 a = __builtin_nontemporal_load(p + i), b = __builtin_nontemporal_load(p + i + nt);
-    const u32x4 c = __builtin_nontemporal_load(p + i + 2 * (size_t)nt), d = __builtin_nontemporal_load(p + i + 3 * (size_t)nt);
+    const u32x4 a = load_source<CACHED>(p + i), b = load_source<CACHED>(p + i + nt);
+    const u32x4 c = load_source<CACHED>(p + i + 2 * (size_t)nt), d = load_source<CACHED>(p + i + 3 * (size_t)nt);
     fold(a); fold(b); fold(c); fold(d);
   }
-  for (; i < gf; i += nt) fold(__builtin_nontemporal_load(p + i));
+  for (; i < gf; i += nt) fold(load_source<CACHED>(p + i));
   if (g1 > full && t < n - full * PER) {  // the partial last piece, element by element
     const size_t e = full * PER + t;
     m = max(m, abs_bits_finite(SRC == SRQ_F32 ? static_cast<const float*>(x)[e]
@@ -332,7 +332,7 @@ template <int SRC>
 __global__ __launch_bounds__(ABSMAX_BLOCK) void absmax_small_kernel(float* __restrict__ scale, const void* __restrict__ x,
                                                                     size_t n, float qmax) {
   constexpr size_t PER = SRC == SRQ_F32 ? 4 : 8;
-  const uint32_t m = block_umax(absmax_pieces<SRC>(x, n, 0, (n + PER - 1) / PER, threadIdx.x, ABSMAX_BLOCK));
+  const uint32_t m = block_umax(absmax_pieces<SRC, true>(x, n, 0, (n + PER - 1) / PER, threadIdx.x, ABSMAX_BLOCK));
   if (threadIdx.x == 0) *scale = scale_of(m, qmax);
 }
 
@@ -342,14 +342,14 @@ __global__ __launch_bounds__(ABSMAX_BLOCK) void absmax_small_kernel(float* __res
 // whose maximum is not above what the word holds already does not ask.  (A stale word costs an
 // atomic that changes nothing; the maximum is the same.)  Against 2048 workgroups of 256 with an atomic
 // each: 2^28 binary32 values 179 -> 160 us (6.7 TB/s), 2^25 36 -> 29, 2^25 bfloat16 32 -> 20.
-template <int SRC>
+template <int SRC, bool CACHED>
 __global__ __launch_bounds__(ABSMAX_BLOCK) void absmax_kernel(uint32_t* __restrict__ acc,
                                                               const void* __restrict__ x, size_t n) {
   // every workgroup one contiguous share of the tensor
   constexpr size_t PER = SRC == SRQ_F32 ? 4 : 8;
   const size_t pieces = (n + PER - 1) / PER, share = (pieces + gridDim.x - 1) / gridDim.x;
   const size_t g0 = (size_t)blockIdx.x * share, g1 = g0 + share < pieces ? g0 + share : pieces;
-  const uint32_t m = block_umax(g0 < pieces ? absmax_pieces<SRC>(x, n, g0, g1, threadIdx.x, ABSMAX_BLOCK) : 0u);
+  const uint32_t m = block_umax(g0 < pieces ? absmax_pieces<SRC, CACHED>(x, n, g0, g1, threadIdx.x, ABSMAX_BLOCK) : 0u);
   // bit patterns of non-negative floats order like the floats
   if (threadIdx.x == 0 && m > __hip_atomic_load(acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(acc, m);
 }
@@ -375,9 +375,14 @@ __global__ __launch_bounds__(QBLOCK) void absmax_multi_kernel(AbsmaxBatch b) {
   const size_t pieces = (n + per - 1) / per, share = (pieces + nblk - 1) / nblk;
   const size_t g0 = (size_t)local * share, g1 = g0 + share < pieces ? g0 + share : pieces;
   uint32_t m = 0u;
-  if (g0 < pieces)
-    m = b.dtype[t] == SRQ_F32 ? absmax_pieces<SRQ_F32>(x, n, g0, g1, threadIdx.x, QBLOCK)
-                              : absmax_pieces<SRQ_BF16>(x, n, g0, g1, threadIdx.x, QBLOCK);
+  if (g0 < pieces) {
+    if (b.dtype[t] == SRQ_F32)
+      m = b.cached[t] ? absmax_pieces<SRQ_F32, true>(x, n, g0, g1, threadIdx.x, QBLOCK)
+                      : absmax_pieces<SRQ_F32, false>(x, n, g0, g1, threadIdx.x, QBLOCK);
+    else
+      m = b.cached[t] ? absmax_pieces<SRQ_BF16, true>(x, n, g0, g1, threadIdx.x, QBLOCK)
+                      : absmax_pieces<SRQ_BF16, false>(x, n, g0, g1, threadIdx.x, QBLOCK);
+  }
   m = wave_umax(m);
   __shared__ uint32_t part[QBLOCK / 64];
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
@@ -521,6 +526,7 @@ size_t absmax_batch_plan(AbsmaxBatch& b) {
 hipError_t launch_absmax_batch(AbsmaxBatch& b, hipStream_t stream) {
   const size_t blocks = absmax_batch_plan(b);
   for (int i = 0; i < b.nouts; ++i) b.out_qmax[i] = qmax_of(b.out_kind[i]);
+  for (int t = 0; t < b.ntensors; ++t) b.cached[t] = cached_source(b.n[t], b.dtype[t]);
   absmax_multi_kernel<<<(unsigned)blocks, QBLOCK, 0, stream>>>(b);
   absmax_multi_finish_kernel<<<b.ntensors, FINISH_BLOCK, 0, stream>>>(b);
   return hipGetLastError();
@@ -541,8 +547,10 @@ hipError_t launch_absmax_scale(float* scale_out_dev, const void* x, int dtype, s
   const size_t groups = (n + 7) / 8;
   const int wide = grid_for(groups, ABSMAX_BLOCK, 128), deep = grid_for(groups, ABSMAX_BLOCK * 4, 512);
   const int grid = wide > deep ? wide : deep;
-  if (f32) absmax_kernel<SRQ_F32><<<grid, ABSMAX_BLOCK, 0, stream>>>(acc, x, n);
-  else absmax_kernel<SRQ_BF16><<<grid, ABSMAX_BLOCK, 0, stream>>>(acc, x, n);
+  const bool cached = cached_source(n, dtype);
+  const auto kern = f32 ? (cached ? &absmax_kernel<SRQ_F32, true> : &absmax_kernel<SRQ_F32, false>)
+                        : (cached ? &absmax_kernel<SRQ_BF16, true> : &absmax_kernel<SRQ_BF16, false>);
+  kern<<<grid, ABSMAX_BLOCK, 0, stream>>>(acc, x, n);
   absmax_finish_kernel<<<1, 1, 0, stream>>>(scale_out_dev, qmax);
   return hipGetLastError();
 }

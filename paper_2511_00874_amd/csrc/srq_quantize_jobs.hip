@@ -35,11 +35,6 @@ __device__ __forceinline__ void job_quantize_group(uint32_t (&c)[8], const float
   else quantize_group<KIND, SRQ_RTN, AS_BF16>(c, v, inv, 0, 0, 0);
 }
 
-__device__ __forceinline__ void job_load_group(float (&v)[8], const QuantJob& j, size_t g, size_t n) {
-  if (j.dtype == SRQ_F32) load_group<SRQ_F32>(v, j.x, g, n);
-  else load_group<SRQ_BF16>(v, j.x, g, n);
-}
-
 // 8 codes of one group to a row-major destination (elements base .. base+7, all in range)
 template <bool AS_BF16>
 __device__ __forceinline__ void store_group(uint8_t* out, size_t base, const uint32_t (&c)[8]) {
@@ -58,7 +53,7 @@ __device__ __forceinline__ void store_group(uint8_t* out, size_t base, const uin
 // left over group-wise.  A group of a bfloat16 source is one 16-byte load: a thread issues four of
 // them, a block's width apart, before it rounds the first (11.5 M weights -> int8: 14.0 us, one after
 // another 15.6).
-template <int KIND, bool AS_BF16>
+template <int KIND, bool AS_BF16, bool CACHED>
 __device__ __forceinline__ void flat_path(const QuantJob& j, uint32_t local, uint32_t nblocks) {
   const InvScale inv = inv_scale(j.scale, j.scale_dev, j.kind);
   const uint64_t ctr = first_block(j.counter_offset, j.counter_dev);
@@ -69,14 +64,14 @@ __device__ __forceinline__ void flat_path(const QuantJob& j, uint32_t local, uin
     const float* x = static_cast<const float*>(j.x);
     for (size_t c = (size_t)local * (QBLOCK / 64) + (threadIdx.x >> 6); c < nchunks; c += waves) {
       if (j.round == SRQ_SR)
-        quantize_chunk_f32<KIND, SRQ_SR, AS_BF16 ? 2 : 0>(j.out, x, c, threadIdx.x & 63u, inv, k0, k1, ctr);
+        quantize_chunk_f32<KIND, SRQ_SR, AS_BF16 ? 2 : 0, CACHED>(j.out, x, c, threadIdx.x & 63u, inv, k0, k1, ctr);
       else
-        quantize_chunk_f32<KIND, SRQ_RTN, AS_BF16 ? 2 : 0>(j.out, x, c, threadIdx.x & 63u, inv, k0, k1, ctr);
+        quantize_chunk_f32<KIND, SRQ_RTN, AS_BF16 ? 2 : 0, CACHED>(j.out, x, c, threadIdx.x & 63u, inv, k0, k1, ctr);
     }
     for (size_t g = nchunks * (CHUNK / 8) + (size_t)local * QBLOCK + threadIdx.x; g < ngroups; g += (size_t)nblocks * QBLOCK) {
       float v[8];
       uint32_t c[8];
-      load_group<SRQ_F32>(v, j.x, g, n);
+      load_group<SRQ_F32, CACHED>(v, j.x, g, n);
       job_quantize_group<KIND, AS_BF16>(c, v, inv, j, ctr, g, k0, k1);
       store_group<AS_BF16>(j.out, g * 8, c);
     }
@@ -88,7 +83,7 @@ __device__ __forceinline__ void flat_path(const QuantJob& j, uint32_t local, uin
 #pragma unroll
       for (int i = 0; i < FLAT_GROUPS_PER_BLOCK / QBLOCK; ++i) {
         const size_t g = g0 + i * QBLOCK;
-        raw[i] = __builtin_nontemporal_load(x + (g < ngroups ? g : g0));
+        raw[i] = load_source<CACHED>(x + (g < ngroups ? g : g0));
       }
 #pragma unroll
       for (int i = 0; i < FLAT_GROUPS_PER_BLOCK / QBLOCK; ++i) {
@@ -110,7 +105,7 @@ __device__ __forceinline__ void flat_path(const QuantJob& j, uint32_t local, uin
 
 // transposed output (cols x rows), optionally a same-layout output as well (out2): the same
 // codes, or those of a second (integer) quantizer of the same values
-template <int KIND, bool AS_BF16, int TR>
+template <int KIND, bool AS_BF16, int TR, bool CACHED>
 __device__ __forceinline__ void transpose_path(const QuantJob& j, uint32_t local, uint8_t* smem) {
   using elem_t = typename std::conditional<AS_BF16, uint16_t, uint8_t>::type;
   constexpr int ES = sizeof(elem_t);
@@ -162,8 +157,8 @@ __device__ __forceinline__ void transpose_path(const QuantJob& j, uint32_t local
       const bool okA = r0 + rA < rows && col < cols, okB = r0 + rB < rows && col < cols;
       const size_t eA = (size_t)(r0 + rA) * cols + col, eB = (size_t)(r0 + rB) * cols + col;
       f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-      if (okA) a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(x + eA));
-      if (okB) b = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(x + eB));
+      if (okA) a = load_source<CACHED>(reinterpret_cast<const f32x4*>(x + eA));
+      if (okB) b = load_source<CACHED>(reinterpret_cast<const f32x4*>(x + eB));
       uint32_t addA[4], addB[4];
       if (j.round == SRQ_SR) {
         uint32_t w[4];
@@ -245,7 +240,7 @@ __device__ __forceinline__ void transpose_path(const QuantJob& j, uint32_t local
       if (row < rows && col < cols) {
         const size_t g = ((size_t)row * cols + col) / 8;
         float v[8];
-        job_load_group(v, j, g, n);
+        load_group<SRQ_BF16, CACHED>(v, j.x, g, n);
         job_quantize_group<KIND, AS_BF16>(c, v, inv, j, ctr, g, k0, k1);
         if (j.out2 && j.kind2 == 0) {
           store_group<AS_BF16>(j.out2, g * 8, c);
@@ -295,19 +290,20 @@ __device__ __forceinline__ void transpose_path(const QuantJob& j, uint32_t local
   }
 }
 
-template <int KIND, bool AS_BF16>
+template <int KIND, bool AS_BF16, bool CACHED>
 __device__ __forceinline__ void run_job(const QuantJob& j, uint32_t local, uint8_t* smem) {
   if (j.transpose) {
     if constexpr (AS_BF16) {
-      transpose_path<KIND, true, 128>(j, local, smem);
+      transpose_path<KIND, true, 128, CACHED>(j, local, smem);
     } else {
-      if (tile_rows(false, j.rows, j.cols) == 256) transpose_path<KIND, false, 256>(j, local, smem);
-      else transpose_path<KIND, false, 128>(j, local, smem);
+      if (tile_rows(false, j.rows, j.cols) == 256) transpose_path<KIND, false, 256, CACHED>(j, local, smem);
+      else transpose_path<KIND, false, 128, CACHED>(j, local, smem);
     }
   }
-  else flat_path<KIND, AS_BF16>(j, local, j.nblocks);
+  else flat_path<KIND, AS_BF16, CACHED>(j, local, j.nblocks);
 }
 
+template <bool CACHED>
 __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[TC * (128 + 2) * 2];
   static_assert(TC * (256 + 4) <= (int)sizeof(smem), "the tile of 256 rows of bytes fits as well");
@@ -331,21 +327,21 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
   const bool bf = j.store == STORE_BF16;
   switch (j.kind) {
     case SRQ_INT8: case SRQ_INT4:
-      if (bf) run_job<SRQ_INTX, true>(j, local, smem);
-      else if (j.kind == SRQ_INT8) run_job<SRQ_INT8, false>(j, local, smem);
-      else run_job<SRQ_INT4, false>(j, local, smem);
+      if (bf) run_job<SRQ_INTX, true, CACHED>(j, local, smem);
+      else if (j.kind == SRQ_INT8) run_job<SRQ_INT8, false, CACHED>(j, local, smem);
+      else run_job<SRQ_INT4, false, CACHED>(j, local, smem);
       break;
     case SRQ_E4M3:
-      if (bf) run_job<SRQ_E4M3, true>(j, local, smem);
-      else run_job<SRQ_E4M3, false>(j, local, smem);
+      if (bf) run_job<SRQ_E4M3, true, CACHED>(j, local, smem);
+      else run_job<SRQ_E4M3, false, CACHED>(j, local, smem);
       break;
     case SRQ_E5M2:
-      if (bf) run_job<SRQ_E5M2, true>(j, local, smem);
-      else run_job<SRQ_E5M2, false>(j, local, smem);
+      if (bf) run_job<SRQ_E5M2, true, CACHED>(j, local, smem);
+      else run_job<SRQ_E5M2, false, CACHED>(j, local, smem);
       break;
     default:  // E4M2 / E4M1 / E4M0
-      if (bf) run_job<SRQ_E4MX, true>(j, local, smem);
-      else run_job<SRQ_E4MX, false>(j, local, smem);
+      if (bf) run_job<SRQ_E4MX, true, CACHED>(j, local, smem);
+      else run_job<SRQ_E4MX, false, CACHED>(j, local, smem);
       break;
   }
 }
@@ -356,8 +352,10 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
 // store is STORE_BYTE or STORE_BF16.
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
   uint32_t first = 0;
+  bool cached = true;  // decided for the launch (two forms inside one kernel cost more than they gave)
   for (int i = 0; i < jobs.njobs; ++i) {
     QuantJob& j = jobs.job[i];
+    cached = cached && cached_source((size_t)j.rows * j.cols, j.dtype);
     size_t nb;
     if (j.transpose) {
       const size_t tr = tile_rows(j.store == STORE_BF16, j.rows, j.cols);
@@ -372,7 +370,8 @@ hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
     first += (uint32_t)nb;
   }
   if (first == 0) return hipSuccess;
-  quantize_jobs_kernel<<<first, QBLOCK, 0, stream>>>(jobs);
+  if (cached) quantize_jobs_kernel<true><<<first, QBLOCK, 0, stream>>>(jobs);
+  else quantize_jobs_kernel<false><<<first, QBLOCK, 0, stream>>>(jobs);
   return hipGetLastError();
 }
 
