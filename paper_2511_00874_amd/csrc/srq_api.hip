@@ -69,7 +69,9 @@ int check_pair(int kx, int kz) {
 // 26 -> 19, 512 x 768 x 768 19.1 -> 18.0.  At 256 x 512 x 512 and below both take the time of their
 // launches (18 us) and the bfloat16 form stays.
 constexpr size_t CODES_MIN_WORK = 1ull << 27;
-bool codes_pay(size_t M, size_t N, size_t K) { return M * N >= CODES_MIN_WORK / K; }
+// M N K >= CODES_MIN_WORK without the triple product, which may not fit 64 bits.  Rounded up, so that it is the
+// same in every order of the three: the products of a call share stored operands and must agree.
+bool codes_pay(size_t M, size_t N, size_t K) { return M * N >= (CODES_MIN_WORK + K - 1) / K; }
 
 // Matrix pipeline for a product of two quantized operands; -1 if the two disagree.
 int pick_pipe(const srq_quant* qx, const srq_quant* qz, bool e5m2_call, bool big) {

@@ -3,6 +3,7 @@
 No GPU here: every call below is rejected by validation before anything is launched.
 """
 import ctypes as C
+import itertools
 import os
 import re
 
@@ -140,6 +141,26 @@ def test_linear_argument_checks(lib):
     assert r.sr_linear_fwd(*args, 64, 128, 128, C.byref(_q(lib, 1, flags=4)), C.byref(q8), None, 0, None) == -5
     assert r.sr_gemm_codes(buf, buf, 1, buf, 3, 16, 16, 16, 1.0, 0.0, None, 0, None) == -6
     assert r.sr_gemm_codes(buf, buf, 1, buf, 1, 16, 16, 24, 1.0, 0.0, None, 0, None) == -4
+
+
+# M N K a little below 2^27 multiplications, from which 8-bit float products are multiplied from their
+# codes: however the three sizes are ordered, every product of a call (and the stash) is on the same side of the
+# line, so the call gets as far as the check of its workspace
+@pytest.mark.parametrize("dims", [(34944, 48, 80), (43680, 48, 64), (58240, 48, 48), (174752, 16, 48), (1008, 256, 512),
+                                  (1024, 256, 512), (34960, 48, 80), (524288, 16, 16)])
+def test_eight_bit_float_calls_of_every_size_agree_on_a_pipeline(lib, dims):
+    r = lib.raw
+    buf = 0x1000
+    q8 = _q(lib, lib.INT8)
+    for M, N, K in itertools.permutations(dims):
+        for dy, w, a in ((lib.E4M3, lib.E4M3, lib.E4M3), (lib.E5M2, lib.E4M3, lib.E5M2), (lib.E4M3, lib.E5M2, lib.E4M1)):
+            qdY, qW, qA = (C.byref(_q(lib, k)) for k in (dy, w, a))
+            assert r.sr_linear_bwd(buf, buf, buf, 0, buf, 0, buf, 0, M, N, K, qdY, qW, qA, 0.0, buf, 256, None) == -5
+            assert r.sr_linear_bwd_stashed(buf, buf, buf, 0, M, N, K, qdY, qW, qA, buf, 1 << 40, 0.0, buf, 256,
+                                           None) == -5
+            if K * 127**2 < 2**31:  # (the int32 sums of the integer forward product)
+                assert r.sr_linear_fwd_stash(buf, buf, 0, buf, 0, M, N, K, C.byref(q8), C.byref(q8), qA, qW, buf, 1 << 40,
+                                             buf, 256, None) == -5
 
 
 def test_workspace_sizes(lib):

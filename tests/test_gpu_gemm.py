@@ -250,9 +250,11 @@ def test_llama_shapes_int4_gradient_bf16_weights():
 
 
 # 1008 x 256 x 512 multiplications lie below the line from which 8-bit float operands are multiplied from
-# their codes, 1024 x 256 x 512 on it; the ragged shapes end inside tiles and stages; 4096 x 2064 x 2064
+# their codes, 1024 x 256 x 512 on it, 43680 x 64 x 48 and its turn so close below that M N and 2^27 / K agree when
+# cut to whole numbers; the ragged shapes end inside tiles and stages; 4096 x 2064 x 2064
 # takes the 256 x 256 tiles and 256 x 272 x 8208 a sliced contraction
-@pytest.mark.parametrize("M,N,K", [(1008, 256, 512), (1024, 256, 512), (2064, 272, 304), (256, 272, 8208), (4096, 2064, 2064)])
+@pytest.mark.parametrize("M,N,K", [(1008, 256, 512), (1024, 256, 512), (43680, 64, 48), (64, 48, 43680), (2064, 272, 304),
+                                   (256, 272, 8208), (4096, 2064, 2064)])
 def test_eight_bit_float_formats_around_the_code_product_line(M, N, K):
     for dy, w, a in ((L.E4M3, L.E4M3, L.E4M3), (L.E5M2, L.E4M3, L.E5M2), (L.E4M3, L.E5M2, L.E5M2),
                      (L.E4M1, L.E5M2, L.E4M3)):
