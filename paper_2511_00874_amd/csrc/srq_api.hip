@@ -81,7 +81,8 @@ int pick_pipe(const srq_quant* qx, const srq_quant* qz, bool e5m2_call, bool big
   if (fx) return PIPE_F8;
   // exact pipelines: calls whose operands are all E5M2, and large products of any 8-bit floats, multiply
   // straight from the one-byte codes; small ones with an E4M3-family operand go through the bfloat16 form
-  return (e5m2_call && qx->kind == SRQ_E5M2 && qz->kind == SRQ_E5M2) || big ? PIPE_F16C : PIPE_BF16;
+  if (e5m2_call && qx->kind == SRQ_E5M2 && qz->kind == SRQ_E5M2) return PIPE_F16C;
+  return big ? PIPE_F16W : PIPE_BF16;
 }
 
 // int32 accumulation is exact while R * 127^2 < 2^31
@@ -147,9 +148,7 @@ int plan_product(ProductPlan& pp, const srq_quant* qx, const srq_quant* qz, size
   if (!int_contraction_ok(qx->kind, R)) return SRQ_ERR_UNSUPPORTED;
   pp.pipe = pick_pipe(qx, qz, e5m2_call, codes_pay(P, Q, R));
   if (pp.pipe < 0) return SRQ_ERR_UNSUPPORTED;
-  // (the size limit of the pairs that have a bfloat16 form is that form's, whichever they take)
-  const bool e5m2 = e5m2_call && qx->kind == SRQ_E5M2 && qz->kind == SRQ_E5M2;
-  if (!gemm_operands_addressable(P, Q, R, pp.pipe == PIPE_F16C && !e5m2 ? PIPE_BF16 : pp.pipe)) return SRQ_ERR_UNSUPPORTED;
+  if (!gemm_operands_addressable(P, Q, R, pp.pipe)) return SRQ_ERR_UNSUPPORTED;
   pp.es = pp.pipe == PIPE_BF16 ? 2 : 1;
   pp.x_bytes = align_up(P * R * pp.es, WS_ALIGN);
   pp.z_bytes = align_up(Q * R * pp.es, WS_ALIGN);
@@ -743,7 +742,6 @@ int sr_linear_bwd_stashed_phase(float* dA, float* dW, const void* dY, int dtyped
   if (check_pair(qA_bwd->kind, qW_bwd->kind) != SRQ_OK) return SRQ_ERR_UNSUPPORTED;
   const int stash_pipe = pick_pipe(qA_bwd, qW_bwd, true, codes_pay(M, N, K));
   const bool e5m2 = qA_bwd->kind == SRQ_E5M2 && qW_bwd->kind == SRQ_E5M2;
-  if (stash_pipe == PIPE_F16C && e5m2 && qdY_bwd->kind != SRQ_E5M2) return SRQ_ERR_UNSUPPORTED;
   st = plan_product(pd, qdY_bwd, qW_bwd, M, K, N, e5m2);
   if (st != SRQ_OK) return st;
   st = plan_product(pw, qdY_bwd, qA_bwd, N, K, M, e5m2);

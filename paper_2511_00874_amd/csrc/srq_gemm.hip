@@ -41,7 +41,7 @@ struct GemmParams {
   uint32_t P, Q, R;      // R: bytes per operand row (contraction length x element size)
   uint32_t pitch;        // bytes between operand rows (>= R, multiple of 16)
   uint32_t pitch_x;      // the same for X when its rows hold two 4-bit values per byte (else = pitch)
-  uint32_t k_per_split;  // bytes of R per z-slice, multiple of BK
+  uint32_t k_per_split;  // bytes of R per z-slice, multiple of BK / 2
   uint32_t nsplit;
   uint32_t tiles_p, tiles_q;
   float alpha, sx, sz;
@@ -939,6 +939,23 @@ Plan make_plan(size_t P, size_t Q, size_t row_bytes) {
   return best;
 }
 
+// The plan of a product on one of the pipelines.  PIPE_F16W has half the row bytes of PIPE_BF16, and by its own
+// count would cut long contractions into half as many slices: every accumulator would then sum twice as many
+// products one after another, and round about 1.4 times as far from the exact result.  Where its slices would be longer
+// than those of PIPE_BF16 it takes that plan, the same slices in half the bytes.  E4M3 steps, us and error of the
+// results against 64 bits with its own slices and with those: 1472 x 1440 x 4448 129 (9.4e-8), 130 (7.0e-8), on PIPE_BF16
+// 143; 224 x 1248 x 1792, where a slice sum is a launch more, 43 (5.9e-8), 47 (5.0e-8), on PIPE_BF16 51.  (The error
+// equals that of PIPE_BF16.)
+Plan plan_for(size_t P, size_t Q, size_t R, int pipe) {
+  if (pipe == PIPE_BF16) return make_plan(P, Q, 2 * R);
+  const Plan pl = make_plan(P, Q, R);
+  if (pipe != PIPE_F16W) return pl;
+  Plan wide = make_plan(P, Q, 2 * R);
+  if (wide.nsplit == 1 || 2 * (size_t)pl.k_per_split <= wide.k_per_split) return pl;
+  wide.k_per_split /= 2;
+  return wide;
+}
+
 // What a launch is asked to do about slice sums: carry the one of an earlier product (`carry`,
 // may be null or empty), and either run its own afterwards or hand it to the caller (`defer`).
 struct SliceSumPlan {
@@ -1100,7 +1117,7 @@ hipError_t launch_cut3(GemmParams g, hipStream_t stream) {
 }  // namespace
 
 size_t gemm_workspace_bytes(size_t P, size_t Q, size_t R, int pipe) {
-  const Plan pl = make_plan(P, Q, pipe == PIPE_BF16 ? 2 * R : R);
+  const Plan pl = plan_for(P, Q, R, pipe);
   return pl.nsplit > 1 ? (size_t)pl.nsplit * P * Q * sizeof(uint32_t) : 0;
 }
 
@@ -1109,7 +1126,7 @@ bool gemm_takes_packed_x(size_t P, size_t Q, size_t R, int pipe) {
 }
 
 bool gemm_operands_addressable(size_t P, size_t Q, size_t R, int pipe) {
-  const size_t rb = pipe == PIPE_BF16 ? 2 * R : R;
+  const size_t rb = pipe == PIPE_BF16 || pipe == PIPE_F16W ? 2 * R : R;
   return (P + 256) * rb < (1ull << 31) && (Q + 256) * rb < (1ull << 31);
 }
 
@@ -1119,7 +1136,7 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
                              SliceSum* defer, bool x_packed) {
   const SliceSumPlan ss{carry, defer};
   const size_t row_bytes = pipe == PIPE_BF16 ? 2 * R : R;
-  const Plan pl = make_plan(P, Q, row_bytes);
+  const Plan pl = plan_for(P, Q, R, pipe);
   if (x_packed && !(pipe == PIPE_I8 && pl.tile == 0)) return hipErrorInvalidValue;  // see gemm_takes_packed_x
   GemmParams g;
   g.out = out;
@@ -1138,7 +1155,7 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
   if (pipe == PIPE_BF16) return launch_mma<BF16Mma>(g, pl, ss, stream);
   // the Z operand is the first MFMA operand, X the second
   const int fx = kindX == SRQ_E5M2, fz = kindZ == SRQ_E5M2;
-  if (pipe == PIPE_F16C) {
+  if (pipe == PIPE_F16C || pipe == PIPE_F16W) {
     if (!fz && !fx) return launch_mma<F8F16Mma<0, 0>>(g, pl, ss, stream);
     if (!fz && fx) return launch_mma<F8F16Mma<0, 1>>(g, pl, ss, stream);
     if (fz && !fx) return launch_mma<F8F16Mma<1, 0>>(g, pl, ss, stream);

@@ -294,6 +294,25 @@ def test_every_e4m3_value_is_widened_exactly():
     assert np.array_equal(Y[keep], A[keep])
 
 
+# weight gradients whose bfloat16 form cuts the contraction into more slices than the code form would by its own
+# count, on each tile shape, and one whose slices end inside a stage of 128 codes
+@pytest.mark.parametrize("M,N,K", [(2064, 1296, 560), (2064, 1488, 1296), (1600, 1152, 176), (1600, 1296, 560)])
+@pytest.mark.parametrize("pair", [(L.E4M3, L.E4M3), (L.E5M2, L.E4M3)])
+def test_code_products_are_no_less_precise_than_the_bfloat16_form(M, N, K, pair):
+    # grid values and scale 1: the quantizers pass them through.  Both products are exact and both sum in
+    # binary32; over no more terms per accumulator the 2-norm of the error over the outputs (at least 2 x 10^5
+    # of them) is no larger but for chance, which is below 1 %
+    rng = torch.Generator().manual_seed(M + N)
+    on_grid = {L.E4M3: torch.float8_e4m3fn, L.E5M2: torch.float8_e5m2}
+    dY, A = ((torch.randn((M, c), generator=rng)).to(on_grid[k]).float() for c, k in zip((N, K), pair))
+    say("error of", M, N, K, [L.KIND_NAMES[k] for k in pair])
+    got = L.sr_linear_bwd_weight(dY.to(DEV), A.to(DEV), *(L.Quant(k, 1.0, seed=i) for i, k in enumerate(pair)))
+    wide = L.sr_gemm_bf16(*(t.T.contiguous().to(DEV, torch.bfloat16) for t in (dY, A)))
+    ref = (dY.double().T @ A.double()).to(DEV)
+    err, err_wide = ((p.double() - ref).norm().item() for p in (got, wide))
+    assert err <= 1.05 * err_wide, (err / ref.norm().item(), err_wide / ref.norm().item())
+
+
 def _two_stream_stash_step(t, q):
     """The benchmark's launch configuration: the stash pair in halves, the quantizing halves on one stream and
     the products on another, events between them; returns Y, dA, dW."""
