@@ -747,7 +747,7 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
 // Compared with planes written to memory by a kernel of their own and one product over the tripled
 // contraction (the earlier form) there is no 6-byte copy of X, no threefold copy of Z, and a Z
 // fragment read from LDS serves three MFMAs.  Whole calls, int8 weights, us before and now: 8192 x 3072 x 768
-// forward 136 -> 110, its input gradient 165 -> 121; 16384 x 4096 x 1024 374 -> 348 (1.2 PFLOP/s of MFMAs)
+// forward 136 -> 110, its input gradient 165 -> 128; 16384 x 4096 x 1024 374 -> 348 (1.2 PFLOP/s of MFMAs)
 // and 457 -> 350; 272 x 4096 x 4096 93 -> 59; 256 x 256 x 256 19 -> 13.  Three stages in the ring (two
 // workgroups per CU instead of three): 110 -> 113, 348 -> 365.
 // A stage is 32 elements of the contraction: rows of 128 bytes of X (chunk c of row r at
@@ -772,8 +772,14 @@ __device__ __forceinline__ void cut3(const v4f (&x)[2], v4i (&plane)[3]) {
   }
 }
 
-template <int NW, int TN, int STAGES>
-__global__ __launch_bounds__(NW * 64) void gemm_cut3_kernel(GemmParams g) {
+// TWO: the large parts gather in one set of accumulators, the middle and small ones in another, and the two are added
+// at the end.  A binary32 sum rounds at its own size whatever it is given, so one set over all three parts rounds
+// three times for every 16 products instead of once: error over the 2-norm, 736 x 688 x 1744 2.5e-7 with one set,
+// 7.1e-8 with two, 10976 x 1760 x 3312 5.4e-7 and 1.4e-7.  Twice the accumulators are 189 registers instead of 125,
+// two workgroups per CU instead of three: 8192 x 3072 x 768 forward and input gradient 233 us against 253, 16384 x 4096
+// x 1024 737 against 774.  Three stages in that ring (147 KiB of LDS): 251 and 767.  make_cut3_plan says which.
+template <int NW, int TN, int STAGES, bool TWO>
+__global__ __launch_bounds__(NW * 64, TWO ? 2 : 1) void gemm_cut3_kernel(GemmParams g) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   constexpr int BM = 32 * NW, BN = 32 * TN;
   constexpr int XROW = 128, ZROW = 64;  // bytes of a stage per row
@@ -827,11 +833,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_cut3_kernel(GemmParams g) {
 #pragma unroll
   for (int t = 0; t < 2; ++t) zoff[t] = BM * XROW + (lane & 31u) * ZROW + (((2 * t + (lane >> 5)) ^ ((lane >> 2) & 3u)) << 4);
 
-  v16f acc[1][TN];
+  v16f acc[1][TN], low[TWO ? TN : 1];
 #pragma unroll
   for (int j = 0; j < TN; ++j)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[0][j][r] = 0.0f;
+    for (int r = 0; r < 16; ++r) acc[0][j][r] = low[TWO ? j : 0][r] = 0.0f;
 
 #pragma unroll
   for (int s = 0; s < STAGES - 1; ++s) issue(s, s);  // stages past the end load zeros
@@ -860,13 +866,22 @@ __global__ __launch_bounds__(NW * 64) void gemm_cut3_kernel(GemmParams g) {
 #pragma unroll
           for (int b = 2; b >= 0; --b)  // small parts first
 #pragma unroll
-            for (int j = 0; j < TN; ++j) acc[0][j] = BF16Mma::mma(z[ks][j], plane[b], acc[0][j]);
+            for (int j = 0; j < TN; ++j) {
+              v16f& sum = TWO && b > 0 ? low[TWO ? j : 0] : acc[0][j];
+              sum = BF16Mma::mma(z[ks][j], plane[b], sum);
+            }
         }
       }
     }
   }
   wait_vmcnt<0>();
   __syncthreads();
+  if constexpr (TWO) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[0][j][r] = __fadd_rn(acc[0][j][r], low[j][r]);
+  }
   static_assert(NW * epilogue_wave_bytes(TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
   write_wave_tile<BF16Mma, 1, TN>(g, acc, lds + wave * epilogue_wave_bytes(TN), lane, p0 + wave * 32, q0, slice);
 }
@@ -1058,24 +1073,35 @@ struct Cut3Kind {
   int waves, tn, per_cu;
   double rate_chip, fixed;
 };
-constexpr Cut3Kind CUT3_KINDS[] = {{4, 4, 3, 1.2e15, 8.0}, {2, 2, 6, 0.5e15, 8.0}};
+constexpr Cut3Kind CUT3_KINDS[2][2] = {{{4, 4, 3, 1.2e15, 8.0}, {2, 2, 6, 0.5e15, 8.0}},   // one set of accumulators
+                                       {{4, 4, 2, 1.2e15, 8.0}, {2, 2, 6, 0.5e15, 8.0}}};  // two
 
 struct Cut3Plan {
   int kind;
+  bool two;
   uint32_t nsplit, k_per_split;  // bytes of Z
 };
+// Precision: no less than that of one bfloat16 product over the three parts side by side (a contraction of 3 R), for
+// which a caller's workspace is sized.  Uncut, that product rounds its accumulators 3 R / 16 times, most of them at
+// full size: one set of accumulators does no worse.  Cut, it sums the large parts in slices of their own, as
+// long as its plan makes them, and two sets of accumulators over slices no longer than those do no worse.  (Error of that
+// product and of this one: 736 x 688 x 1744, seven slices there, 1.1e-7 and 7.1e-8; 16384 x 4096 x 1024, uncut, 8.3e-7 and 6.0e-7.)
 Cut3Plan make_cut3_plan(size_t P, size_t Q, size_t R, size_t partial_bytes) {
   const size_t ksteps = (2 * R + 63) / 64;
+  const Plan whole = make_plan(P, Q, 6 * R);
   Cut3Plan best{};
+  best.two = whole.nsplit > 1;
+  const size_t min_split = best.two ? (2 * R + whole.k_per_split - 1) / whole.k_per_split : 1;
   double best_time = -1.0;
   size_t best_n = 1;
   for (int kind = 0; kind < 2; ++kind) {
-    const Cut3Kind& k = CUT3_KINDS[kind];
+    const Cut3Kind& k = CUT3_KINDS[best.two][kind];
     const size_t bm = 32 * k.waves, bn = 32 * k.tn, t = ((P + bm - 1) / bm) * ((Q + bn - 1) / bn);
     size_t max_split = ksteps >= 32 ? ksteps / 16 : 1;
     if (max_split > 64) max_split = 64;
-    for (size_t n = 1; n <= max_split; ++n) {
-      if (n > 1 && n * P * Q * sizeof(uint32_t) > partial_bytes) break;
+    if (max_split < min_split) max_split = min_split;
+    for (size_t n = min_split; n <= max_split; ++n) {
+      if (n > min_split && n * P * Q * sizeof(uint32_t) > partial_bytes) break;
       const size_t per_cu = (t * n + NUM_CU - 1) / NUM_CU;  // items of the busiest CU
       const size_t stages = (ksteps + n - 1) / n;
       // a CU's rate with fewer workgroups than it holds
@@ -1095,10 +1121,10 @@ Cut3Plan make_cut3_plan(size_t P, size_t Q, size_t R, size_t partial_bytes) {
   return best;
 }
 
-template <int NW, int TN, int STAGES>
+template <int NW, int TN, int STAGES, bool TWO>
 hipError_t launch_cut3(GemmParams g, hipStream_t stream) {
   constexpr int LDS_BYTES = STAGES * (32 * NW * 128 + 32 * TN * 64);
-  auto kern = &gemm_cut3_kernel<NW, TN, STAGES>;
+  auto kern = &gemm_cut3_kernel<NW, TN, STAGES, TWO>;
   static const hipError_t configured = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
   if (configured != hipSuccess) return configured;
@@ -1186,7 +1212,8 @@ hipError_t launch_gemm_f32_bf16(float* out, const float* X, const uint16_t* Z, s
   g.k_per_split = pl.k_per_split;
   g.nsplit = pl.nsplit;
   g.alpha = s.alpha; g.sx = s.sx; g.sz = s.sz; g.sx_dev = s.sx_dev; g.sz_dev = s.sz_dev;
-  return pl.kind == 0 ? launch_cut3<4, 4, 2>(g, stream) : launch_cut3<2, 2, 3>(g, stream);
+  if (pl.two) return pl.kind == 0 ? launch_cut3<4, 4, 2, true>(g, stream) : launch_cut3<2, 2, 3, true>(g, stream);
+  return pl.kind == 0 ? launch_cut3<4, 4, 2, false>(g, stream) : launch_cut3<2, 2, 3, false>(g, stream);
 }
 
 }  // namespace srq

@@ -107,6 +107,31 @@ def test_binary32_rows_at_the_edges_of_tiles_stages_and_slices(M, N, K):
     assert torch.equal(Y[keep], clean[keep])
 
 
+# contractions that one bfloat16 product over the three parts side by side would leave whole (the first two) and
+# would cut into 3, 6, 7 and 11 slices
+@pytest.mark.parametrize("M,N,K", [(256, 256, 256), (2064, 1040, 272), (1888, 416, 544), (688, 720, 1152), (736, 688, 1744),
+                                   (432, 576, 2320)])
+def test_binary32_rows_are_no_less_precise_than_their_parts_side_by_side(M, N, K):
+    # grid values and scale 1: the quantizer passes W through.  Both forms multiply the same exact parts and sum in
+    # binary32, this one with no more roundings at the size of the sum; over 6 x 10^4 outputs and more the 2-norm of the
+    # error is no larger but for chance, which is below 1 %
+    rng = torch.Generator().manual_seed(K)
+    W = torch.randn((N, K), generator=rng).to(torch.float8_e4m3fn).float()
+    A, part, parts = torch.randn((M, K), generator=rng), None, []
+    rest = A.clone()
+    for _ in range(3):
+        part = (rest.view(torch.int32) & -65536).view(torch.float32)
+        parts.append(part)
+        rest = rest - part
+    assert not rest.any()
+    say("error of", M, N, K)
+    got = L.sr_linear_fwd(A.to(DEV), W.to(DEV), NOQ, L.Quant(L.E4M3, 1.0, seed=1))
+    side = L.sr_gemm_bf16(torch.cat(parts, 1).to(DEV, torch.bfloat16), torch.cat([W] * 3, 1).to(DEV, torch.bfloat16))
+    ref = (A.double() @ W.double().T).to(DEV)
+    err, err_side = ((p.double() - ref).norm().item() for p in (got, side))
+    assert err <= 1.05 * err_side, (err / ref.norm().item(), err_side / ref.norm().item())
+
+
 def test_where_the_identity_quantizer_is_not_accepted():
     A = torch.zeros((16, 16), device=DEV)
     q8 = L.Quant(L.INT8, 1.0)
