@@ -253,6 +253,7 @@ int run_linear(float* out, const void* x, int dtx, size_t xr, size_t xc, int x_t
   const int store = pp.pipe == PIPE_BF16 ? STORE_BF16 : STORE_BYTE;
   QuantJobs jobs;
   jobs.njobs = 2;
+  jobs.other_bytes = 4 * P * Q;  // the result, of the shape of the layer's third tensor
   jobs.job[0] = make_job(qx, x, dtx, xr, xc, x_tr, store, xcodes, nullptr);
   jobs.job[1] = make_job(qz, z, dtz, zr, zc, z_tr, store, zcodes, nullptr);
   if ((phase & SRQ_PHASE_QUANTIZE) && launch_quantize_jobs(jobs, s) != hipSuccess) return SRQ_ERR_HIP;
@@ -707,6 +708,7 @@ int sr_linear_fwd_stash_phase(float* Y, const void* A, int dtypeA, const void* W
   const int store = stash_pipe == PIPE_BF16 ? STORE_BF16 : STORE_BYTE;
   QuantJobs jobs;
   jobs.njobs = 2;
+  jobs.other_bytes = 4 * M * N;  // Y
   jobs.job[0] = make_dual_job(qA_bwd, qA_fwd, A, dtypeA, M, K, store, a_t, a_codes);
   jobs.job[1] = make_dual_job(qW_bwd, qW_fwd, W, dtypeW, N, K, store, w_t, w_codes);
   if ((phase & SRQ_PHASE_QUANTIZE) && launch_quantize_jobs(jobs, s) != hipSuccess) return SRQ_ERR_HIP;
@@ -760,6 +762,7 @@ int sr_linear_bwd_stashed_phase(float* dA, float* dW, const void* dY, int dtyped
   const int store = pd.pipe == PIPE_BF16 ? STORE_BF16 : STORE_BYTE;
   QuantJobs jobs;
   jobs.njobs = 1;
+  jobs.other_bytes = 4 * (M + N) * K;  // A and W
   jobs.job[0] = make_job(qdY_bwd, dY, dtypedY, M, N, 1, store, dy_t, dy_rm);
   const PackedDy pk = packed_dy(qdY_bwd, dtypedY, pd, pw, M, N, K);
   jobs.job[0].pack_2 = pk.rm;

@@ -199,7 +199,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // A 16-byte load of a source tensor: streaming, or cached for one that is small enough to be met again in
-// the last-level cache (cached_source).
+// the last-level cache (the load policy in srq_internal.hpp).
 template <bool CACHED, class T>
 __device__ __forceinline__ T load_source(const T* p) {
   if constexpr (CACHED) return *p;

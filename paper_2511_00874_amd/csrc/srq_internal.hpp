@@ -15,14 +15,22 @@ enum StoreMode {
   STORE_BF16 = 2    // the grid value itself as bfloat16 (two bytes per element)
 };
 
-// The scale of a tensor is found in one pass over it and its codes are made in another.  A tensor of at
-// most this many bytes is read with cached loads by both, so that the second pass finds what the first
-// left in the last-level cache (256 MiB, shared with everything else in flight); a larger one is
-// streamed by both.  Training steps of a 2048 x 2048 linear, everything streamed against this line: 1024
-// tokens 68 -> 65 us, 2048 82 -> 77, 4096 (32 MiB an activation) 123 -> 121; 6144 tokens (48 MiB) with
-// a line of 64 MiB 168 -> 172.  One pass cached and the other streamed is slower than either.
-constexpr size_t CACHED_SOURCE_BYTES = (size_t)40 << 20;
-inline bool cached_source(size_t n, int dtype) { return n * (dtype == SRQ_F32 ? 4 : 2) <= CACHED_SOURCE_BYTES; }
+// Cached or streaming loads of a source.  The scale of a tensor is found in one pass over it and its codes are made
+// in another; whether the second pass finds the tensor in the last-level cache (256 MiB) depends on all that is touched in
+// between, so both rules count a whole layer, not a tensor.
+//   - An absmax call whose tensors take up to ABSMAX_CACHED_BYTES together reads them with cached loads: what it leaves is
+//     found by cached and streaming loads alike.  Beyond, what it reads first is gone by the end and cached loads
+//     only push out what the next kernels want.
+//   - A quantizer launch reads with cached loads if A, W and Y or dY of its layer take up to JOBS_CACHED_BYTES together
+//     (those it does not read counted as binary32): then the tensor is there again for the next pass, and the operands
+//     fit beside it.  Beyond, streaming loads find what is there and leave the room to the codes and results.
+// Training steps (scales of A and W, forward, scale of dY, backward), us with everything streamed, with both rules, and
+// with cached absmax loads alone: 1024 x 2048 x 2048 (20 MiB a layer) 74.5, 71.3, 72.3; 2048 x 2048 x 2048 (40) 87.5, 82.6, 84.3;
+// 4096 x 2048 x 2048 (72; absmax calls 40 and 32) 128.6, 124.7, 124.7, and 128 with cached quantizer loads; 16384 x 512 x
+// 2048 (162) 185.9, 185.5, and 196 where the 32 MiB dY alone is read with cached loads by both passes; 6144 x 2048 x 2048 170.9, 168.5.
+constexpr size_t ABSMAX_CACHED_BYTES = (size_t)88 << 20;
+constexpr size_t JOBS_CACHED_BYTES = (size_t)56 << 20;
+inline size_t source_bytes(size_t n, int dtype) { return n * (dtype == SRQ_F32 ? 4 : 2); }
 
 struct QuantArgs {
   int kind, round, dtype, store;
@@ -65,6 +73,7 @@ struct QuantJob {
 };
 struct QuantJobs {
   int njobs;
+  size_t other_bytes = 0;  // of the layer's tensors that this launch does not read, in binary32 (for the load policy)
   QuantJob job[QUANT_JOBS_MAX];
 };
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream);
@@ -77,7 +86,7 @@ struct AbsmaxBatch {
   const void* x[ABSMAX_MAX];
   size_t n[ABSMAX_MAX];
   int dtype[ABSMAX_MAX];
-  int cached[ABSMAX_MAX];  // cached_source() of the tensor, filled by the launcher
+  int cached;  // the load policy, filled by the launcher
   uint32_t first_block[ABSMAX_MAX], nblocks[ABSMAX_MAX];
   int out_tensor[ABSMAX_MAX], out_kind[ABSMAX_MAX];
   float out_qmax[ABSMAX_MAX];

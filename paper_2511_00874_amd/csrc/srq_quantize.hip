@@ -377,10 +377,10 @@ __global__ __launch_bounds__(QBLOCK) void absmax_multi_kernel(AbsmaxBatch b) {
   uint32_t m = 0u;
   if (g0 < pieces) {
     if (b.dtype[t] == SRQ_F32)
-      m = b.cached[t] ? absmax_pieces<SRQ_F32, true>(x, n, g0, g1, threadIdx.x, QBLOCK)
+      m = b.cached ? absmax_pieces<SRQ_F32, true>(x, n, g0, g1, threadIdx.x, QBLOCK)
                       : absmax_pieces<SRQ_F32, false>(x, n, g0, g1, threadIdx.x, QBLOCK);
     else
-      m = b.cached[t] ? absmax_pieces<SRQ_BF16, true>(x, n, g0, g1, threadIdx.x, QBLOCK)
+      m = b.cached ? absmax_pieces<SRQ_BF16, true>(x, n, g0, g1, threadIdx.x, QBLOCK)
                       : absmax_pieces<SRQ_BF16, false>(x, n, g0, g1, threadIdx.x, QBLOCK);
   }
   m = wave_umax(m);
@@ -526,7 +526,9 @@ size_t absmax_batch_plan(AbsmaxBatch& b) {
 hipError_t launch_absmax_batch(AbsmaxBatch& b, hipStream_t stream) {
   const size_t blocks = absmax_batch_plan(b);
   for (int i = 0; i < b.nouts; ++i) b.out_qmax[i] = qmax_of(b.out_kind[i]);
-  for (int t = 0; t < b.ntensors; ++t) b.cached[t] = cached_source(b.n[t], b.dtype[t]);
+  size_t bytes = 0;
+  for (int t = 0; t < b.ntensors; ++t) bytes += source_bytes(b.n[t], b.dtype[t]);
+  b.cached = bytes <= ABSMAX_CACHED_BYTES;
   absmax_multi_kernel<<<(unsigned)blocks, QBLOCK, 0, stream>>>(b);
   absmax_multi_finish_kernel<<<b.ntensors, FINISH_BLOCK, 0, stream>>>(b);
   return hipGetLastError();
@@ -536,7 +538,7 @@ hipError_t launch_absmax_scale(float* scale_out_dev, const void* x, int dtype, s
                                hipStream_t stream) {
   const bool f32 = dtype == SRQ_F32;
   const float qmax = qmax_of(kind);
-  if (n * (f32 ? 4 : 2) <= ABSMAX_SMALL_BYTES) {
+  if (source_bytes(n, dtype) <= ABSMAX_SMALL_BYTES) {
     if (f32) absmax_small_kernel<SRQ_F32><<<1, ABSMAX_BLOCK, 0, stream>>>(scale_out_dev, x, n, qmax);
     else absmax_small_kernel<SRQ_BF16><<<1, ABSMAX_BLOCK, 0, stream>>>(scale_out_dev, x, n, qmax);
     return hipGetLastError();
@@ -547,7 +549,7 @@ hipError_t launch_absmax_scale(float* scale_out_dev, const void* x, int dtype, s
   const size_t groups = (n + 7) / 8;
   const int wide = grid_for(groups, ABSMAX_BLOCK, 128), deep = grid_for(groups, ABSMAX_BLOCK * 4, 512);
   const int grid = wide > deep ? wide : deep;
-  const bool cached = cached_source(n, dtype);
+  const bool cached = source_bytes(n, dtype) <= ABSMAX_CACHED_BYTES;
   const auto kern = f32 ? (cached ? &absmax_kernel<SRQ_F32, true> : &absmax_kernel<SRQ_F32, false>)
                         : (cached ? &absmax_kernel<SRQ_BF16, true> : &absmax_kernel<SRQ_BF16, false>);
   kern<<<grid, ABSMAX_BLOCK, 0, stream>>>(acc, x, n);

@@ -352,10 +352,10 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
 // store is STORE_BYTE or STORE_BF16.
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
   uint32_t first = 0;
-  bool cached = true;  // decided for the launch (two forms inside one kernel cost more than they gave)
+  size_t bytes = jobs.other_bytes;
   for (int i = 0; i < jobs.njobs; ++i) {
     QuantJob& j = jobs.job[i];
-    cached = cached && cached_source((size_t)j.rows * j.cols, j.dtype);
+    bytes += source_bytes((size_t)j.rows * j.cols, j.dtype);
     size_t nb;
     if (j.transpose) {
       const size_t tr = tile_rows(j.store == STORE_BF16, j.rows, j.cols);
@@ -370,7 +370,8 @@ hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
     first += (uint32_t)nb;
   }
   if (first == 0) return hipSuccess;
-  if (cached) quantize_jobs_kernel<true><<<first, QBLOCK, 0, stream>>>(jobs);
+  // decided for the launch (two forms inside one kernel cost more than they gave)
+  if (bytes <= JOBS_CACHED_BYTES) quantize_jobs_kernel<true><<<first, QBLOCK, 0, stream>>>(jobs);
   else quantize_jobs_kernel<false><<<first, QBLOCK, 0, stream>>>(jobs);
   return hipGetLastError();
 }
