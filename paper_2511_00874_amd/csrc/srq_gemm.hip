@@ -747,7 +747,7 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
 // Compared with planes written to memory by a kernel of their own and one product over the tripled
 // contraction (the earlier form) there is no 6-byte copy of X, no threefold copy of Z, and a Z
 // fragment read from LDS serves three MFMAs.  Whole calls, int8 weights, us before and now: 8192 x 3072 x 768
-// forward 136 -> 110, its input gradient 165 -> 128; 16384 x 4096 x 1024 374 -> 348 (1.2 PFLOP/s of MFMAs)
+// forward 136 -> 110, its input gradient 165 -> 121; 16384 x 4096 x 1024 374 -> 348 (1.2 PFLOP/s of MFMAs)
 // and 457 -> 350; 272 x 4096 x 4096 93 -> 59; 256 x 256 x 256 19 -> 13.  Three stages in the ring (two
 // workgroups per CU instead of three): 110 -> 113, 348 -> 365.
 // A stage is 32 elements of the contraction: rows of 128 bytes of X (chunk c of row r at
@@ -1074,7 +1074,7 @@ struct Cut3Kind {
   double rate_chip, fixed;
 };
 constexpr Cut3Kind CUT3_KINDS[2][2] = {{{4, 4, 3, 1.2e15, 8.0}, {2, 2, 6, 0.5e15, 8.0}},   // one set of accumulators
-                                       {{4, 4, 2, 1.2e15, 8.0}, {2, 2, 6, 0.5e15, 8.0}}};  // two
+                                       {{4, 4, 2, 1.1e15, 8.0}, {2, 2, 6, 0.5e15, 8.0}}};  // two
 
 struct Cut3Plan {
   int kind;
@@ -1083,35 +1083,42 @@ struct Cut3Plan {
 };
 // Precision: no less than that of one bfloat16 product over the three parts side by side (a contraction of 3 R), for
 // which a caller's workspace is sized.  Uncut, that product rounds its accumulators 3 R / 16 times, most of them at
-// full size: one set of accumulators does no worse.  Cut, it sums the large parts in slices of their own, as
-// long as its plan makes them, and two sets of accumulators over slices no longer than those do no worse.  (Error of that
-// product and of this one: 736 x 688 x 1744, seven slices there, 1.1e-7 and 7.1e-8; 16384 x 4096 x 1024, uncut, 8.3e-7 and 6.0e-7.)
+// full size: one set of accumulators does no worse.  Cut, it sums the large parts in slices of their own, as long as
+// its plan makes them: two sets of accumulators over slices no longer than those do no worse.  Cut in two, it has every large
+// part and half of the next in one accumulator, and one set over two slices does no worse either; in more, one set does
+// (six slices of 192 at 688 x 720 x 1152: 1.4e-7 against 8.3e-8, two sets over two slices 6.7e-8).  Error of that product and
+// of this one: 736 x 688 x 1744, seven slices there, 1.1e-7 and 7.1e-8; 8192 x 3072 x 768, the input gradient in two, 3.8e-7
+// and 3.7e-7; 16384 x 4096 x 1024, uncut, 8.3e-7 and 6.0e-7.
 Cut3Plan make_cut3_plan(size_t P, size_t Q, size_t R, size_t partial_bytes) {
   const size_t ksteps = (2 * R + 63) / 64;
   const Plan whole = make_plan(P, Q, 6 * R);
   Cut3Plan best{};
-  best.two = whole.nsplit > 1;
-  const size_t min_split = best.two ? (2 * R + whole.k_per_split - 1) / whole.k_per_split : 1;
   double best_time = -1.0;
   size_t best_n = 1;
-  for (int kind = 0; kind < 2; ++kind) {
-    const Cut3Kind& k = CUT3_KINDS[best.two][kind];
-    const size_t bm = 32 * k.waves, bn = 32 * k.tn, t = ((P + bm - 1) / bm) * ((Q + bn - 1) / bn);
-    size_t max_split = ksteps >= 32 ? ksteps / 16 : 1;
-    if (max_split > 64) max_split = 64;
-    if (max_split < min_split) max_split = min_split;
-    for (size_t n = min_split; n <= max_split; ++n) {
-      if (n > min_split && n * P * Q * sizeof(uint32_t) > partial_bytes) break;
-      const size_t per_cu = (t * n + NUM_CU - 1) / NUM_CU;  // items of the busiest CU
-      const size_t stages = (ksteps + n - 1) / n;
-      // a CU's rate with fewer workgroups than it holds
-      const double share = per_cu >= (size_t)k.per_cu ? 1.0 : per_cu >= 2 ? 0.95 : 0.7;
-      double time = (double)per_cu * ((double)stages + k.fixed) * 3.0 * 2.0 * bm * bn * 32 / (k.rate_chip / NUM_CU * share);
-      if (n > 1) time += 2.0 * (double)n * (double)P * (double)Q * 4.0 / PARTIAL_BYTES_PER_SECOND + 3e-6;
-      if (best_time < 0.0 || time < best_time) {
-        best_time = time;
-        best.kind = kind;
-        best_n = n;
+  for (int two = whole.nsplit > 2; two < (whole.nsplit > 1 ? 2 : 1); ++two) {
+    const size_t longest = whole.nsplit > 1 ? whole.k_per_split / (two ? 64 : 192) : ksteps;  // stages of a slice
+    const size_t min_split = (ksteps + longest - 1) / longest;
+    for (int kind = 0; kind < 2; ++kind) {
+      const Cut3Kind& k = CUT3_KINDS[two][kind];
+      const size_t bm = 32 * k.waves, bn = 32 * k.tn, t = ((P + bm - 1) / bm) * ((Q + bn - 1) / bn);
+      size_t max_split = ksteps >= 32 ? ksteps / 16 : 1;
+      if (max_split > 64) max_split = 64;
+      if (max_split < min_split) max_split = min_split;
+      for (size_t n = min_split; n <= max_split; ++n) {
+        // (two sets over the fewest slices always fit: there are no more of them than that product has)
+        if (n > 1 && n * P * Q * sizeof(uint32_t) > partial_bytes) break;
+        const size_t per_cu = (t * n + NUM_CU - 1) / NUM_CU;  // items of the busiest CU
+        const size_t stages = (ksteps + n - 1) / n;
+        // a CU's rate with fewer workgroups than it holds
+        const double share = per_cu >= (size_t)k.per_cu ? 1.0 : per_cu >= 2 ? 0.95 : 0.7;
+        double time = (double)per_cu * ((double)stages + k.fixed) * 3.0 * 2.0 * bm * bn * 32 / (k.rate_chip / NUM_CU * share);
+        if (n > 1) time += 2.0 * (double)n * (double)P * (double)Q * 4.0 / PARTIAL_BYTES_PER_SECOND + 3e-6;
+        if (best_time < 0.0 || time < best_time) {
+          best_time = time;
+          best.kind = kind;
+          best.two = two != 0;
+          best_n = n;
+        }
       }
     }
   }

@@ -108,9 +108,9 @@ def test_binary32_rows_at_the_edges_of_tiles_stages_and_slices(M, N, K):
 
 
 # contractions that one bfloat16 product over the three parts side by side would leave whole (the first two) and
-# would cut into 3, 6, 7 and 11 slices
-@pytest.mark.parametrize("M,N,K", [(256, 256, 256), (2064, 1040, 272), (1888, 416, 544), (688, 720, 1152), (736, 688, 1744),
-                                   (432, 576, 2320)])
+# would cut into 2, 2, 3, 6, 7 and 11 slices
+@pytest.mark.parametrize("M,N,K", [(256, 256, 256), (2064, 1040, 272), (1200, 608, 400), (8192, 768, 3072),
+                                   (1888, 416, 544), (688, 720, 1152), (736, 688, 1744), (432, 576, 2320)])
 def test_binary32_rows_are_no_less_precise_than_their_parts_side_by_side(M, N, K):
     # grid values and scale 1: the quantizer passes W through.  Both forms multiply the same exact parts and sum in
     # binary32, this one with no more roundings at the size of the sum; over 6 x 10^4 outputs and more the 2-norm of the
