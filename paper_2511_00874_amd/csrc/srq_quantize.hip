@@ -102,13 +102,8 @@ typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16
 constexpr uint32_t TBAND = 16;
 constexpr uint32_t TRANSPOSE_GRID = 1u << 20;  // workgroups per launch at most; the rest of the tiles by a loop
 
-__device__ __forceinline__ uint32_t opaque(uint32_t v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 template <int KIND, int SRC, int ROUND, int STORE, int TR>
-__global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
+__global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
     uint8_t* __restrict__ out, const void* __restrict__ x, uint32_t rows, uint32_t cols, float scale,
     const float* scale_dev, int kind, uint64_t seed, uint64_t counter_host, const uint64_t* counter_dev) {
   static_assert(STORE == STORE_BYTE || STORE == STORE_NIBBLE, "codes");
@@ -117,7 +112,7 @@ __global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
   constexpr int SEG = TR / DIV;                       // bytes of a run
   // pitch: the pieces a wave instruction writes fall on all 64 banks (16 column quads x 4 row octets of
   // 8 bytes, or 8 column groups x 8 row quads of 4)
-  constexpr int PITCH = SEG + 4;
+  constexpr int PITCH = SEG + (F32 ? 8 : 4);
   __shared__ __attribute__((aligned(16))) uint8_t tile[TC * PITCH + 8];
   const InvScale inv = inv_scale(scale, scale_dev, kind);
   const uint64_t ctr = first_block(counter_host, counter_dev);
@@ -132,10 +127,10 @@ __global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
     const uint32_t bands = min(TBAND, tiles_y - band0), within = work - band0 * tiles_x;
     const uint32_t r0 = (band0 + within % bands) * TR, c0 = (within / bands) * TC;
 
-    constexpr int PR = 4, PC = F32 ? 4 : 8;  // rows x columns of a thread's piece
+    constexpr int PR = F32 ? 8 : 4, PC = F32 ? 4 : 8;  // rows x columns of a thread's piece
     constexpr int PIECES = TR * TC / (PR * PC) / QBLOCK;
     static_assert(PIECES >= 1, "a piece per thread");
-#pragma unroll 1
+#pragma unroll
     for (int it = 0; it < PIECES; ++it) {
       const uint32_t id = it * QBLOCK + threadIdx.x;
       const uint32_t cl = (id % (TC / PC)) * PC, rl = (id / (TC / PC)) * PR;
@@ -154,11 +149,11 @@ __global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
       if constexpr (F32) {
         const bool odd = threadIdx.x & 1u;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          uint32_t addA[4], addB[4];  // rows i and i + 2
+        for (int i = 0; i < 4; ++i) {
+          uint32_t addA[4], addB[4];  // rows i and i + 4
           if constexpr (ROUND == SRQ_SR) {
             uint32_t w[4];
-            philox_block(ctr + (e0 + (size_t)(odd ? i + 2 : i) * cols) / 8, k0, k1, w);
+            philox_block(ctr + (e0 + (size_t)(odd ? i + 4 : i) * cols) / 8, k0, k1, w);
             const uint32_t s0 = odd ? w[0] : w[2], s1 = odd ? w[1] : w[3];  // what the other lane needs
             const uint32_t t0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s0, 0xB1, 0xF, 0xF, true);  // lane ^ 1
             const uint32_t t1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s1, 0xB1, 0xF, 0xF, true);
@@ -170,8 +165,8 @@ __global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
           }
           quantize_quad<KIND, ROUND, false>(c[i], __uint_as_float(raw[i].x), __uint_as_float(raw[i].y),
                                             __uint_as_float(raw[i].z), __uint_as_float(raw[i].w), inv, addA);
-          quantize_quad<KIND, ROUND, false>(c[i + 2], __uint_as_float(raw[i + 2].x), __uint_as_float(raw[i + 2].y),
-                                            __uint_as_float(raw[i + 2].z), __uint_as_float(raw[i + 2].w), inv, addB);
+          quantize_quad<KIND, ROUND, false>(c[i + 4], __uint_as_float(raw[i + 4].x), __uint_as_float(raw[i + 4].y),
+                                            __uint_as_float(raw[i + 4].z), __uint_as_float(raw[i + 4].w), inv, addB);
         }
       } else {
 #pragma unroll
@@ -198,12 +193,11 @@ __global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
     }
     __syncthreads();
     const uint32_t rb = r0 / DIV, nb = min((uint32_t)SEG, orow - rb);  // the runs of this tile, in bytes
-    const uint32_t t = opaque(threadIdx.x);  // (addresses from here on are not kept over the loop)
     if ((orow & 15u) == 0) {
       // every run starts at a multiple of 16 bytes and is a multiple of 16 long
 #pragma unroll
       for (int it = 0; it < TC * SEG / 16 / QBLOCK; ++it) {
-        const uint32_t id = it * QBLOCK + t;
+        const uint32_t id = it * QBLOCK + threadIdx.x;
         const uint32_t ch = id % (SEG / 16), cl = id / (SEG / 16);
         if (c0 + cl >= cols || ch * 16 >= nb) continue;
         const uint32_t* src = reinterpret_cast<const uint32_t*>(tile + cl * PITCH + ch * 16);
@@ -215,7 +209,7 @@ __global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
       constexpr int LANES = SEG / 16;
 #pragma unroll
       for (int it = 0; it < TC * LANES / QBLOCK; ++it) {
-        const uint32_t id = it * QBLOCK + t;
+        const uint32_t id = it * QBLOCK + threadIdx.x;
         const uint32_t w = (id % LANES) * 4, cl = id / LANES;
         if (c0 + cl >= cols) continue;
         const uint8_t* const run = tile + cl * PITCH;
