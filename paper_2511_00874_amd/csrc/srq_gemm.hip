@@ -420,15 +420,6 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, Sl
 // the buffer of its last stage is the staging area of the epilogue (the other one is receiving the
 // next tile's first stage); it is handed back to the ring by the barrier of the next stage.
 // Every loop bound below is uniform over the workgroup, so all waves meet at every barrier.
-// The lane index again, as a value the optimiser cannot see through.  Address arithmetic that is
-// derived from it inside a loop is recomputed there (a few VALU operations) instead of being
-// hoisted out of the loop and held in registers across it: in the kernel below the accumulators and
-// operand fragments leave no room for that.
-__device__ __forceinline__ uint32_t opaque(uint32_t v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
 struct TileItem {
   uint32_t valid, p0, q0, slice, kbeg, kend;
 };

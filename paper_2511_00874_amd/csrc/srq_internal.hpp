@@ -32,6 +32,14 @@ constexpr size_t ABSMAX_CACHED_BYTES = (size_t)88 << 20;
 constexpr size_t JOBS_CACHED_BYTES = (size_t)56 << 20;
 inline size_t source_bytes(size_t n, int dtype) { return n * (dtype == SRQ_F32 ? 4 : 2); }
 
+// A value (a lane or thread index) as one the optimiser cannot see through.  Address arithmetic that is derived from it
+// inside a loop is recomputed there (a few VALU operations) instead of being hoisted out of the loop and held in
+// registers across it.
+__device__ __forceinline__ uint32_t opaque(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 struct QuantArgs {
   int kind, round, dtype, store;
   float scale;

@@ -97,13 +97,17 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_f32_kernel(uint8_t* __re
 // Against the form before (a group of 8 codes per thread, byte-wise LDS writes, 128-row tiles, a ragged
 // run byte by byte): 12289 x 3080 bfloat16 -> int8 82 -> 35 us, binary32 99 -> 47; 12288 x 3080 binary32
 // 52 -> 41 (189 MB: 4.6 TB/s); 65536 x 4096 binary32 311 -> 227 (5.9 TB/s), bfloat16 162 -> 130.
+//   - At most 64 registers (the launch bounds): a wave of it then fits on a SIMD beside two of the persistent product
+//     kernel, so that on a second stream it runs beside a product and not behind it.  That takes no more than to
+//     recompute the addresses of the store side (opaque); alone it is as fast.  Six calls on 16384 x 4096 beside int8 products
+//     of 8192 cubed, us a call at 94 registers and at 64: binary32 490 and 177, bfloat16 478 and 145.
 constexpr int TC = 64;
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at a multiple of four
 constexpr uint32_t TBAND = 16;
 constexpr uint32_t TRANSPOSE_GRID = 1u << 20;  // workgroups per launch at most; the rest of the tiles by a loop
 
 template <int KIND, int SRC, int ROUND, int STORE, int TR>
-__global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
+__global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
     uint8_t* __restrict__ out, const void* __restrict__ x, uint32_t rows, uint32_t cols, float scale,
     const float* scale_dev, int kind, uint64_t seed, uint64_t counter_host, const uint64_t* counter_dev) {
   static_assert(STORE == STORE_BYTE || STORE == STORE_NIBBLE, "codes");
@@ -130,7 +134,7 @@ __global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
     constexpr int PR = F32 ? 8 : 4, PC = F32 ? 4 : 8;  // rows x columns of a thread's piece
     constexpr int PIECES = TR * TC / (PR * PC) / QBLOCK;
     static_assert(PIECES >= 1, "a piece per thread");
-#pragma unroll
+#pragma unroll 1
     for (int it = 0; it < PIECES; ++it) {
       const uint32_t id = it * QBLOCK + threadIdx.x;
       const uint32_t cl = (id % (TC / PC)) * PC, rl = (id / (TC / PC)) * PR;
@@ -193,11 +197,12 @@ __global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
     }
     __syncthreads();
     const uint32_t rb = r0 / DIV, nb = min((uint32_t)SEG, orow - rb);  // the runs of this tile, in bytes
+    const uint32_t t = opaque(threadIdx.x);  // (addresses from here on are not kept over the loop)
     if ((orow & 15u) == 0) {
       // every run starts at a multiple of 16 bytes and is a multiple of 16 long
 #pragma unroll
       for (int it = 0; it < TC * SEG / 16 / QBLOCK; ++it) {
-        const uint32_t id = it * QBLOCK + threadIdx.x;
+        const uint32_t id = it * QBLOCK + t;
         const uint32_t ch = id % (SEG / 16), cl = id / (SEG / 16);
         if (c0 + cl >= cols || ch * 16 >= nb) continue;
         const uint32_t* src = reinterpret_cast<const uint32_t*>(tile + cl * PITCH + ch * 16);
@@ -209,7 +214,7 @@ __global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
       constexpr int LANES = SEG / 16;
 #pragma unroll
       for (int it = 0; it < TC * LANES / QBLOCK; ++it) {
-        const uint32_t id = it * QBLOCK + threadIdx.x;
+        const uint32_t id = it * QBLOCK + t;
         const uint32_t w = (id % LANES) * 4, cl = id / LANES;
         if (c0 + cl >= cols) continue;
         const uint8_t* const run = tile + cl * PITCH;
