@@ -315,46 +315,51 @@ __device__ __forceinline__ float scale_of(uint32_t amax_bits, float qmax) {
   return amax == 0.0f ? 1.0f : fmaxf(__fdiv_rn(amax, qmax), MIN_SCALE);
 }
 
-constexpr int ABSMAX_BLOCK = 1024;
-
-// max over the workgroup, valid in thread 0
+// max over a workgroup of THREADS, valid in thread 0
+template <int THREADS>
 __device__ __forceinline__ uint32_t block_umax(uint32_t m) {
-  __shared__ uint32_t part[ABSMAX_BLOCK / 64];
+  __shared__ uint32_t part[THREADS / 64];
   m = wave_umax(m);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int i = 1; i < ABSMAX_BLOCK / 64; ++i) m = max(m, part[i]);
+    for (int i = 1; i < THREADS / 64; ++i) m = max(m, part[i]);
   }
   return m;
 }
 
-// A tensor of up to 256 KiB: one workgroup reads it and writes the scale in one launch (a call by itself
-// 23 -> 19 us; at 512 KiB 25 us, at 1 MiB 33 against 23 for the three launches).
+// A tensor of up to 256 KiB: one workgroup reads it and writes the scale in one launch.  GPU us a call, against the three
+// launches of larger ones: binary32 128 KiB 2.9 and 5.5, 256 KiB 4.0 and 5.5; bfloat16 3.9 and 5.4, 6.2 and 5.7.
+// Latency bounds it, so it is as wide as a workgroup can be.  Beside a product on another stream it then waits for the
+// end of the product kernel (256 KiB, beside int8 products of 8192 cubed, 150 us; of 256 threads 20 us, but alone 5.1 instead of
+// 4.0): what follows such a call, the product of a small layer, waits for the same CUs anyway.
+constexpr int ABSMAX_SMALL_BLOCK = 1024;
 constexpr size_t ABSMAX_SMALL_BYTES = 256u << 10;
 template <int SRC>
-__global__ __launch_bounds__(ABSMAX_BLOCK) void absmax_small_kernel(float* __restrict__ scale, const void* __restrict__ x,
-                                                                    size_t n, float qmax) {
+__global__ __launch_bounds__(ABSMAX_SMALL_BLOCK) void absmax_small_kernel(float* __restrict__ scale, const void* __restrict__ x,
+                                                                          size_t n, float qmax) {
   constexpr size_t PER = SRC == SRQ_F32 ? 4 : 8;
-  const uint32_t m = block_umax(absmax_pieces<SRC, true>(x, n, 0, (n + PER - 1) / PER, threadIdx.x, ABSMAX_BLOCK));
+  const uint32_t m = block_umax<ABSMAX_SMALL_BLOCK>(
+      absmax_pieces<SRC, true>(x, n, 0, (n + PER - 1) / PER, threadIdx.x, ABSMAX_SMALL_BLOCK));
   if (threadIdx.x == 0) *scale = scale_of(m, qmax);
 }
 
 // A larger one: the maximum gathers in the scale's own word, between a launch that clears it and one
 // that turns it into the scale.  Atomics on one address from eight XCDs are served one after
-// another, about 30 ns each, so there are few of them: workgroups of 1024 threads, and a workgroup
+// another, about 30 ns each, so there are few of them: at most two workgroups per CU, and a workgroup
 // whose maximum is not above what the word holds already does not ask.  (A stale word costs an
-// atomic that changes nothing; the maximum is the same.)  Against 2048 workgroups of 256 with an atomic
-// each: 2^28 binary32 values 179 -> 160 us (6.7 TB/s), 2^25 36 -> 29, 2^25 bfloat16 32 -> 20.
+// atomic that changes nothing; the maximum is the same.)  Workgroups of 256 threads with 64 registers at most (the launch
+// bounds) start on a CU that a persistent product kernel holds; of 1024 they waited for its end.
+constexpr int ABSMAX_BLOCK = 256;
 template <int SRC, bool CACHED>
-__global__ __launch_bounds__(ABSMAX_BLOCK) void absmax_kernel(uint32_t* __restrict__ acc,
+__global__ __launch_bounds__(ABSMAX_BLOCK, 8) void absmax_kernel(uint32_t* __restrict__ acc,
                                                               const void* __restrict__ x, size_t n) {
   // every workgroup one contiguous share of the tensor
   constexpr size_t PER = SRC == SRQ_F32 ? 4 : 8;
   const size_t pieces = (n + PER - 1) / PER, share = (pieces + gridDim.x - 1) / gridDim.x;
   const size_t g0 = (size_t)blockIdx.x * share, g1 = g0 + share < pieces ? g0 + share : pieces;
-  const uint32_t m = block_umax(g0 < pieces ? absmax_pieces<SRC, CACHED>(x, n, g0, g1, threadIdx.x, ABSMAX_BLOCK) : 0u);
+  const uint32_t m = block_umax<ABSMAX_BLOCK>(g0 < pieces ? absmax_pieces<SRC, CACHED>(x, n, g0, g1, threadIdx.x, ABSMAX_BLOCK) : 0u);
   // bit patterns of non-negative floats order like the floats
   if (threadIdx.x == 0 && m > __hip_atomic_load(acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(acc, m);
 }
@@ -543,16 +548,19 @@ hipError_t launch_absmax_scale(float* scale_out_dev, const void* x, int dtype, s
                                hipStream_t stream) {
   const bool f32 = dtype == SRQ_F32;
   const float qmax = qmax_of(kind);
+  const size_t pieces = (source_bytes(n, dtype) + 15) / 16;
   if (source_bytes(n, dtype) <= ABSMAX_SMALL_BYTES) {
-    if (f32) absmax_small_kernel<SRQ_F32><<<1, ABSMAX_BLOCK, 0, stream>>>(scale_out_dev, x, n, qmax);
-    else absmax_small_kernel<SRQ_BF16><<<1, ABSMAX_BLOCK, 0, stream>>>(scale_out_dev, x, n, qmax);
+    if (f32) absmax_small_kernel<SRQ_F32><<<1, ABSMAX_SMALL_BLOCK, 0, stream>>>(scale_out_dev, x, n, qmax);
+    else absmax_small_kernel<SRQ_BF16><<<1, ABSMAX_SMALL_BLOCK, 0, stream>>>(scale_out_dev, x, n, qmax);
     return hipGetLastError();
   }
   uint32_t* acc = reinterpret_cast<uint32_t*>(scale_out_dev);
   absmax_init_kernel<<<1, 1, 0, stream>>>(acc);
-  // 32768 elements per workgroup, fewer while that makes less than 128 of them; two per CU at most
-  const size_t groups = (n + 7) / 8;
-  const int wide = grid_for(groups, ABSMAX_BLOCK, 128), deep = grid_for(groups, ABSMAX_BLOCK * 4, 512);
+  // 16 loads per thread, 64 to 512 workgroups.  GPU us a call, binary32 / bfloat16: 4 MiB 7.4 / 7.9, 16 MiB 9.7 / 11.3 (eight
+  // loads and 512 workgroups 12.3 / 12.7), 64 MiB 20.6 / 20.3 (768 workgroups 24.8 / 23.1, 2048 36 / 36), 1 GiB 163 / 164 (178 / 175);
+  // workgroups of 1024 threads 7.5 / 7.9, 9.4 / 11.6, 18.3 / 22.1, 167 / 165.  Six calls on 256 MiB beside int8 products of 8192
+  // cubed on another stream 97 / 61 us each, with those 487 / 467.
+  const int wide = grid_for(pieces, ABSMAX_BLOCK, 64), deep = grid_for(pieces, ABSMAX_BLOCK * 16, 512);
   const int grid = wide > deep ? wide : deep;
   const bool cached = source_bytes(n, dtype) <= ABSMAX_CACHED_BYTES;
   const auto kern = f32 ? (cached ? &absmax_kernel<SRQ_F32, true> : &absmax_kernel<SRQ_F32, false>)
