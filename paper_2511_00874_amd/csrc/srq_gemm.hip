@@ -1059,13 +1059,14 @@ hipError_t launch_mma(const GemmParams& g, const Plan& pl, const SliceSumPlan& s
 }
 
 // Tiles and contraction slices of gemm_cut3_kernel, by the same model: 128 x 128 tiles of four waves,
-// 64 x 64 of two for outputs too small to give every CU one; a stage is 32 elements.
+// 64 x 64 of two for outputs too small to give every CU one; a stage is 32 elements.  per_cu: workgroups a CU holds
+// (rings of 48 KiB, or registers with two sets of accumulators; rings of 36 KiB).
 struct Cut3Kind {
   int waves, tn, per_cu;
   double rate_chip, fixed;
 };
-constexpr Cut3Kind CUT3_KINDS[2][2] = {{{4, 4, 3, 1.2e15, 8.0}, {2, 2, 6, 0.5e15, 8.0}},   // one set of accumulators
-                                       {{4, 4, 2, 1.1e15, 8.0}, {2, 2, 6, 0.5e15, 8.0}}};  // two
+constexpr Cut3Kind CUT3_KINDS[2][2] = {{{4, 4, 3, 1.2e15, 8.0}, {2, 2, 4, 0.5e15, 8.0}},   // one set of accumulators
+                                       {{4, 4, 2, 1.1e15, 8.0}, {2, 2, 4, 0.5e15, 8.0}}};  // two
 
 struct Cut3Plan {
   int kind;
