@@ -451,7 +451,10 @@ template <int KIND, int SRC, int ROUND, int STORE>
 hipError_t launch_one(void* codes, const void* x, size_t rows, size_t cols, int transpose_out,
                       const QuantArgs& a, hipStream_t stream) {
   if (transpose_out) {
-    // 256 rows where they still give every CU several tiles (runs of 256 bytes), else 128
+    // 256 rows (runs of 256 bytes) from 2^28 elements or so up, where the store side is the limit, else 128: twice the
+    // workgroups.  us with 128 and 256, int8: 4096 x 4096 binary32 17.3 and 18.2, 8192 x 4096 34 and 37 (bfloat16 23.8 and 24.1), 16384 x
+    // 4096 64 and 70 (38 and 42), 65536 x 2048 119 and 120 (74 and 75), 65536 x 4096 237 and 229 (136 and 138), 65537 x 4096 278 and 245
+    // (186 and 154), 4096 x 65536 235 and 231 (157 and 146)
     const size_t tiles_x = (cols + TC - 1) / TC, big = tiles_x * ((rows + 255) / 256), small = tiles_x * ((rows + 127) / 128);
     auto launch = [&](auto kern, size_t ntiles) {
       const size_t per_xcd = (ntiles + 7) / 8;
@@ -459,7 +462,7 @@ hipError_t launch_one(void* codes, const void* x, size_t rows, size_t cols, int 
       kern<<<grid, QBLOCK, 0, stream>>>(static_cast<uint8_t*>(codes), x, (uint32_t)rows, (uint32_t)cols, a.scale,
                                         a.scale_dev, a.kind, a.seed, a.counter_offset, a.counter_dev);
     };
-    if (big >= 2048) launch(&quantize_transpose_kernel<KIND, SRC, ROUND, STORE, 256>, big);
+    if (big >= 16384) launch(&quantize_transpose_kernel<KIND, SRC, ROUND, STORE, 256>, big);
     else launch(&quantize_transpose_kernel<KIND, SRC, ROUND, STORE, 128>, small);
   } else {
     const size_t n = rows * cols;

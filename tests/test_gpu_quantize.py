@@ -80,10 +80,11 @@ def test_thresholds_scanned_on_hard_constants(kind):
     assert np.array_equal(got, oracle_codes(xd, kind, 1.0, 0, 0, oracle.RTN))
 
 
-# runs that start and end off every alignment, one tile and several, both tile heights (256 rows from 2048
+# runs that start and end off every alignment, one tile and several, both tile heights (256 rows from 16384
 # such tiles up), full and partial groups of 16 row bands, fewer rows than a word holds
 @pytest.mark.parametrize("shape", [(1, 8), (3, 16), (5, 72), (129, 64), (257, 136), (2051, 200), (4098, 72),
-                                   (524290, 8), (524288, 8), (525301, 8), (260, 16392)])
+                                   (524290, 8), (524288, 8), (525301, 8), (260, 16392),
+                                   (4194306, 8)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_transposed_codes_at_odd_row_counts(shape, bf16):
     x = synth.gaussian(shape, 2.0, 3)
