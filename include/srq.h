@@ -105,12 +105,12 @@ typedef struct {
  * sub-grids of E4M3).
  * Default (flag clear): products are exact and sums are accumulated in binary32, so the result
  * equals the exact product of the quantized matrices (Sec. 2.2.2) to binary32 rounding.  Two
- * E5M2 operands are multiplied from their one-byte codes, widened to binary16 inside the kernel
- * (an E5M2 code is the high byte of the binary16 number of the same value), on the f16 matrix
- * pipeline.  For any other pair the quantizer writes each grid value as a bfloat16 number
- * (every E4M3 / E5M2 value is one) and the product runs on the bf16 matrix pipeline.  The two
- * pipelines group the contraction differently, so their binary32 sums can differ in the last
- * bits.
+ * E5M2 operands, and any pair where the product takes M N K >= 2^27 multiplications, are
+ * multiplied from their one-byte codes, widened to binary16 inside the kernel (every E4M3 / E5M2
+ * value is a binary16 number), on the f16 matrix pipeline.  For a smaller product of any other
+ * pair the quantizer writes each grid value as a bfloat16 number and the product runs on the bf16
+ * matrix pipeline.  The two pipelines group the contraction differently, so their binary32 sums
+ * can differ in the last bits; neither is less precise.
  * With SRQ_FLAG_F8_PIPELINE set on BOTH operands' quantizers the one-byte codes go to the fp8
  * matrix pipeline at twice the rate.  That hardware adds the products of each run of 8
  * consecutive contraction indices after aligning them to the largest one and truncating to 14
@@ -180,7 +180,7 @@ int sr_gemm_codes(float* out, const void* X, int kindX, const void* Z, int kindZ
 size_t sr_gemm_workspace_bytes(size_t P, size_t Q, size_t R);
 
 /* The same product for operands held as bfloat16 values (the form in which the linear entry
- * points store E4M3 / E5M2 operands by default): X is P x R, Z is Q x R bfloat16, R % 8 == 0.
+ * points store the operands of small products with an E4M3-family operand): X is P x R, Z is Q x R bfloat16, R % 8 == 0.
  * Products are exact and sums binary32, on the bf16 matrix pipeline. */
 int sr_gemm_bf16(float* out, const void* X, const void* Z, size_t P, size_t Q, size_t R, float alpha,
                  float beta, void* workspace, size_t workspace_bytes, void* stream);
@@ -284,7 +284,7 @@ int sr_linear_bwd_weight(float* dW, const void* dY, int dtypedY, const void* A, 
  * and all three operands are quantized in one launch.  The results are equal bit for bit
  * whenever the two products use the same pipeline in both forms of the call (always, except
  * when exactly one of W, A shares the E5M2 format with dY: the stored Q(dY) then has to serve
- * both products as bfloat16, and the E5M2 x E5M2 product differs from the separate call in the
+ * both products in one form, and the E5M2 x E5M2 product differs from the separate call in the
  * order of its binary32 sums).  The form in which the workspace holds the quantized operands is
  * the library's own (a 4-bit Q(dY) of a binary32 dY, for one, is kept two values per byte for the
  * products that run on 256 x 256 tiles; the results are those of one byte per value bit for bit).
