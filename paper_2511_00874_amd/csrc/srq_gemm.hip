@@ -118,6 +118,40 @@ __device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rsrc, uint32_t 
                : "memory");
 }
 
+// Four results of row p, columns q .. q + 3 (p and q inside the output), given as accumulator bits: a slice's partial
+// sums as they are, final results scaled.
+template <class MMA>
+__device__ __forceinline__ void store_quad(const GemmParams& g, uint32_t* pbase, uint32_t p, uint32_t q, const v4u& raw,
+                                           float s, bool q_vec) {
+  const size_t idx = (size_t)p * g.Q + q;
+  if (pbase) {
+    if (q_vec) {
+      // write-through: nothing of the partial tile stays dirty in the L2 when the kernel
+      // ends, and the reduction launched next still finds it in the last-level cache
+      asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" : : "v"(pbase + idx), "v"(raw) : "memory");
+    } else {
+      for (int e = 0; e < 4 && q + e < g.Q; ++e) pbase[idx + e] = raw[e];
+    }
+  } else {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = __fmul_rn(MMA::to_f32(MMA::from_bits(raw[e])), s);
+    float* dst = g.out + idx;
+    if (q_vec) {
+      if (g.accumulate) {
+        const v4f o = *reinterpret_cast<const v4f*>(dst);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __fadd_rn(v[e], o[e]);
+      }
+      // the result is not read again by this kernel: a streaming store keeps it from pushing
+      // operand panels out of the L2
+      __builtin_nontemporal_store(v4f{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4f*>(dst));
+    } else {
+      for (int e = 0; e < 4 && q + e < g.Q; ++e) dst[e] = g.accumulate ? __fadd_rn(v[e], dst[e]) : v[e];
+    }
+  }
+}
+
 // Epilogue of a wave: its TM x TN block of 32 x 32 MFMA results, first row p0 and column q0 of the output.
 // MFMA result register r of lane l: MFMA row 8*(r/4) + 4*(l/32) + r%4 (a q), MFMA column l%32 (a p).
 // The wave turns its block through its own piece of LDS (`stage`), a band of 32 p-rows at a time (of
@@ -155,33 +189,7 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
         const uint32_t p = pb + row, q = qb + c * 4;
         const v4u raw = *reinterpret_cast<const v4u*>(ep + row * EP_PITCH + c * 4);
         if (p >= g.P || q >= g.Q) continue;
-        const size_t idx = (size_t)p * g.Q + q;
-        if (pbase) {
-          if (q_vec) {
-            // write-through: nothing of the partial tile stays dirty in the L2 when the kernel
-            // ends, and the reduction launched next still finds it in the last-level cache
-            asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" : : "v"(pbase + idx), "v"(raw) : "memory");
-          } else {
-            for (int e = 0; e < 4 && q + e < g.Q; ++e) pbase[idx + e] = raw[e];
-          }
-        } else {
-          float v[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = __fmul_rn(MMA::to_f32(MMA::from_bits(raw[e])), s);
-          float* dst = g.out + idx;
-          if (q_vec) {
-            if (g.accumulate) {
-              const v4f o = *reinterpret_cast<const v4f*>(dst);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = __fadd_rn(v[e], o[e]);
-            }
-            // the result is not read again by this kernel: a streaming store keeps it from pushing
-            // operand panels out of the L2
-            __builtin_nontemporal_store(v4f{v[0], v[1], v[2], v[3]}, reinterpret_cast<v4f*>(dst));
-          } else {
-            for (int e = 0; e < 4 && q + e < g.Q; ++e) dst[e] = g.accumulate ? __fadd_rn(v[e], dst[e]) : v[e];
-          }
-        }
+        store_quad<MMA>(g, pbase, p, q, raw, s, q_vec);
       }
     }
   }
@@ -192,15 +200,20 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
 // the tiles leave free and in the tail of the launch, instead of in a launch of its own.
 // Workgroups [0, gemm_blocks) multiply, the rest sum.  (Measured against this: the rider groups
 // spread through the launch, every fourth group of 8 -- slower.)
-template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, SliceSum rider, uint32_t gemm_blocks) {
+// KG > 1: KG groups of WGM x WGN waves share the tile.  Each group multiplies its own sub-steps of every stage, and the
+// groups' sums are added through LDS at the end.  For workgroups that are few: a CU with a single workgroup of four waves
+// has one wave per SIMD, which nothing covers while it waits for LDS or at the barrier (2048 x 2048 x 4096 int8, with the
+// loads of the stages left out 17.8 us, with the matrix work left out 24.0, together 25.4); the groups put two there and a
+// deeper ring of stages keeps more loads in flight (17.4 with the matrix work left out, 23.8 in all).
+template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1>
+__global__ __launch_bounds__(WGM* WGN* KG * 64) void gemm_nt_kernel(GemmParams g, SliceSum rider, uint32_t gemm_blocks) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   if (blockIdx.x >= gemm_blocks) {
     if (rider.is_int) slice_sum<true>(rider, blockIdx.x - gemm_blocks, gridDim.x - gemm_blocks);
     else slice_sum<false>(rider, blockIdx.x - gemm_blocks, gridDim.x - gemm_blocks);
     return;
   }
-  constexpr int NW = WGM * WGN;
+  constexpr int NG = WGM * WGN, NW = NG * KG;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile (p x q)
   constexpr int TM = WTM / 32, TN = WTN / 32;
   constexpr int STAGE = (BM + BN) * BK;
@@ -212,11 +225,13 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, Sl
   using frag_t = typename MMA::frag_t;
   using raw_t = typename MMA::raw_t;
   constexpr int FC = sizeof(raw_t) / 16;  // 16-byte chunks a lane reads per sub-step
-  constexpr int KSUB = BK / MMA::KSTEP;
+  constexpr int KSUB = BK / MMA::KSTEP / KG;  // sub-steps of a stage that a wave multiplies
+  static_assert(KSUB >= 1, "every group has a sub-step");
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);  // the same, known to be uniform
-  const uint32_t wp = wave / WGN, wq = wave % WGN;
+  const uint32_t kg = KG > 1 ? wave_u / NG : 0u;  // group
+  const uint32_t wp = wave % NG / WGN, wq = wave % WGN;
   const uint32_t lds_base = (uint32_t)(size_t)(lds_void*)lds;
   // Workgroup -> tile.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each
   // with its own L2.  XCD x takes the contiguous range [x * chunk, (x+1) * chunk) of a tile
@@ -253,27 +268,30 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, Sl
   // DMA addressing: a wave instruction fills 8 tile rows (1 KiB of LDS, lane L at L*16); lane L
   // fetches row L/8 and the logical chunk whose physical slot is L%8.  (r >> 1) & 7 depends on
   // the parity of the 8-row block, hence two per-lane offsets.
-  static_assert(XL % 2 == 0 && ZL % 2 == 0, "row blocks of a wave must start at an even block");
   const uint32_t lrow = lane >> 3;
-  const uint32_t lchunk0 = (lane & 7u) ^ (lane >> 4), lchunk1 = lchunk0 ^ 4u;  // even / odd row block
+  const uint32_t lchunk = (lane & 7u) ^ (lane >> 4);  // of an even row block; ^ 4: of an odd one
+  const uint32_t xchunk0 = lchunk ^ (XL % 2 ? (wave_u & 1u) * 4u : 0u), xchunk1 = xchunk0 ^ 4u;
+  const uint32_t zchunk0 = lchunk ^ (ZL % 2 ? (wave_u & 1u) * 4u : 0u), zchunk1 = zchunk0 ^ 4u;
   const uint32_t xvoff = (p0 + wave * XL * 8 + lrow) * g.pitch + kbeg;
   const uint32_t zvoff = (q0 + wave * ZL * 8 + lrow) * g.pitch + kbeg;
 
   auto issue = [&](int kt, int buf) {
     const uint32_t koff = (uint32_t)kt * BK;
     // beyond the contraction the lane loads zeros (offset past the buffer)
-    const uint32_t kc0 = koff + lchunk0 * 16, kc1 = koff + lchunk1 * 16;
-    const bool live0 = kbeg + kc0 < kend, live1 = kbeg + kc1 < kend;
+    const uint32_t xc0 = koff + xchunk0 * 16, xc1 = koff + xchunk1 * 16;
+    const uint32_t zc0 = koff + zchunk0 * 16, zc1 = koff + zchunk1 * 16;
+    const bool xlive0 = kbeg + xc0 < kend, xlive1 = kbeg + xc1 < kend;
+    const bool zlive0 = kbeg + zc0 < kend, zlive1 = kbeg + zc1 < kend;
     const uint32_t xs = lds_base + buf * STAGE + wave_u * XL * 1024;
     const uint32_t zs = lds_base + buf * STAGE + BM * BK + wave_u * ZL * 1024;
 #pragma unroll
     for (int i = 0; i < XL; ++i)
       lds_dma16(xrsrc, xs + i * 1024,
-                (i & 1) ? (live1 ? xvoff + kc1 + i * 8 * g.pitch : OOB) : (live0 ? xvoff + kc0 + i * 8 * g.pitch : OOB));
+                (i & 1) ? (xlive1 ? xvoff + xc1 + i * 8 * g.pitch : OOB) : (xlive0 ? xvoff + xc0 + i * 8 * g.pitch : OOB));
 #pragma unroll
     for (int i = 0; i < ZL; ++i)
       lds_dma16(zrsrc, zs + i * 1024,
-                (i & 1) ? (live1 ? zvoff + kc1 + i * 8 * g.pitch : OOB) : (live0 ? zvoff + kc0 + i * 8 * g.pitch : OOB));
+                (i & 1) ? (zlive1 ? zvoff + zc1 + i * 8 * g.pitch : OOB) : (zlive0 ? zvoff + zc0 + i * 8 * g.pitch : OOB));
   };
 
   // operand reads: lane (row = lane % 32, kgroup = lane / 32) takes FC chunks per MFMA;
@@ -282,7 +300,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, Sl
   uint32_t xoff[KSUB * FC], zoff[KSUB * FC];
 #pragma unroll
   for (int t = 0; t < KSUB * FC; ++t) {
-    const uint32_t tt = (t / FC) * 2 * FC + (t % FC);
+    const uint32_t tt = (t / FC + kg * KSUB) * 2 * FC + (t % FC);
     xoff[t] = (wp * WTM + (lane & 31u)) * BK + ((swz ^ tt) << 4);
     zoff[t] = BM * BK + (wq * WTN + (lane & 31u)) * BK + ((swz ^ tt) << 4);
   }
@@ -322,9 +340,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, Sl
     };
 #pragma unroll
     for (int ks = 0; ks < PF && ks < KSUB; ++ks) fetch(ks);
-    // the interleaved widening below keeps two widened operand sets live: it fits the register
-    // file of the 4-wave workgroups (two of them per CU), not of the 8-wave 256 x 256 one
-    constexpr bool INTERLEAVE = MMA::WIDENS && NW <= 4;
+    // the interleaved widening below keeps two widened operand sets live: it fits the register file beside wave
+    // tiles of up to 64 x 96
+    constexpr bool INTERLEAVE = MMA::WIDENS && TM * TN <= 6;
     if constexpr (!INTERLEAVE) {
 #pragma unroll
       for (int ks = 0; ks < KSUB; ++ks) {
@@ -396,8 +414,48 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_nt_kernel(GemmParams g, Sl
 
   wait_vmcnt<0>();   // the zero-filled stages issued past the end must have landed too
   __syncthreads();
-  static_assert(NW * epilogue_wave_bytes(TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
-  write_wave_tile<MMA, TM, TN>(g, acc, lds + wave * epilogue_wave_bytes(TN), lane, p0 + wp * WTM, q0 + wq * WTN, slice);
+  if constexpr (KG == 1) {
+    static_assert(NW * epilogue_wave_bytes(TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
+    write_wave_tile<MMA, TM, TN>(g, acc, lds + wave * epilogue_wave_bytes(TN), lane, p0 + wp * WTM, q0 + wq * WTN, slice);
+  } else {
+    // The groups' sums meet in LDS, IP row blocks of every wave at a time, and are added in a fixed order by the threads
+    // that write them out, whole rows of the tile per instruction.
+    constexpr int EP_PITCH = BN + 4, CPR = BN / 4, RING = STAGES * STAGE;
+    constexpr int IP = TM % 2 == 0 && KG * WGM * 64 * EP_PITCH * 4 <= RING ? 2 : 1, ROWS = WGM * IP * 32;
+    static_assert(KG * ROWS * EP_PITCH * 4 <= RING && ROWS * CPR % (NW * 64) == 0, "the sums must fit in the ring");
+    uint32_t* const ep = reinterpret_cast<uint32_t*>(lds);
+    const float s = total_scale(g);
+    const bool q_vec = (g.Q & 3u) == 0;
+    uint32_t* const pbase = g.nsplit > 1 ? g.partial + (size_t)slice * g.P * g.Q : nullptr;
+#pragma unroll
+    for (int i0 = 0; i0 < TM; i0 += IP) {
+      uint32_t* const mine = ep + (kg * ROWS + wp * IP * 32 + (lane & 31u)) * EP_PITCH + wq * WTN + 4 * (lane >> 5);
+#pragma unroll
+      for (int i = 0; i < IP; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int gq = 0; gq < 4; ++gq)
+            *reinterpret_cast<v4u*>(mine + i * 32 * EP_PITCH + j * 32 + 8 * gq) =
+                v4u{MMA::bits(acc[i0 + i][j][4 * gq]), MMA::bits(acc[i0 + i][j][4 * gq + 1]),
+                    MMA::bits(acc[i0 + i][j][4 * gq + 2]), MMA::bits(acc[i0 + i][j][4 * gq + 3])};
+      __syncthreads();
+#pragma unroll
+      for (int it = 0; it < ROWS * CPR / (NW * 64); ++it) {
+        const uint32_t id = it * NW * 64 + tid, row = id / CPR, c = id % CPR;
+        const uint32_t p = p0 + row / (IP * 32) * WTM + i0 * 32 + row % (IP * 32), q = q0 + c * 4;
+        v4u raw = *reinterpret_cast<const v4u*>(ep + row * EP_PITCH + c * 4);
+#pragma unroll
+        for (int k = 1; k < KG; ++k) {
+          const v4u more = *reinterpret_cast<const v4u*>(ep + (k * ROWS + row) * EP_PITCH + c * 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) raw[e] = MMA::bits(MMA::from_bits(raw[e]) + MMA::from_bits(more[e]));
+        }
+        if (p < g.P && q < g.Q) store_quad<MMA>(g, pbase, p, q, raw, s, q_vec);
+      }
+      if (i0 + IP < TM) __syncthreads();
+    }
+  }
 }
 
 // ---- 256 x 256 tiles, workgroups that stay -------------------------------------------------------
@@ -978,11 +1036,11 @@ uint32_t slice_sum_blocks(const SliceSum& r, uint32_t threads, uint32_t per_thre
   return (uint32_t)(blocks < 1 ? 1 : blocks);
 }
 
-template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES>
+template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1>
 hipError_t launch_tile(GemmParams g, const SliceSumPlan& ss, hipStream_t stream) {
   constexpr int LDS_BYTES = STAGES * (BM + BN) * BK;
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
-  auto kern = &gemm_nt_kernel<MMA, BM, BN, WGM, WGN, STAGES>;
+  auto kern = &gemm_nt_kernel<MMA, BM, BN, WGM, WGN, STAGES, KG>;
   // once per kernel (a function-local static: its initialisation is safe against concurrent
   // first calls from several host threads)
   static const hipError_t configured = hipFuncSetAttribute(
@@ -995,9 +1053,9 @@ hipError_t launch_tile(GemmParams g, const SliceSumPlan& ss, hipStream_t stream)
   uint32_t carry_blocks = 0;
   if (ss.carry && ss.carry->total > 0) {
     carry = *ss.carry;
-    carry_blocks = slice_sum_blocks(carry, WGM * WGN * 64, 16);
+    carry_blocks = slice_sum_blocks(carry, WGM * WGN * KG * 64, 16);
   }
-  kern<<<dim3(gemm_blocks + carry_blocks), WGM * WGN * 64, LDS_BYTES, stream>>>(g, carry, gemm_blocks);
+  kern<<<dim3(gemm_blocks + carry_blocks), WGM * WGN * KG * 64, LDS_BYTES, stream>>>(g, carry, gemm_blocks);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   SliceSum own{};
@@ -1050,10 +1108,51 @@ hipError_t launch_persist(GemmParams g, const SliceSumPlan& ss, hipStream_t stre
   return e;
 }
 
+// One launch of 64 x 64 tiles over the whole contraction in place of the plan's slices (or of its 128-row tiles), where
+// the output is so small that the chip holds all of those tiles at once, two a CU: nothing is written out twice, no sum is
+// left to a second launch, and there are four times as many workgroups.  Times of both in microseconds from straight
+// lines through measurements (st: stages; `widens`: 8-bit floats on the f16 pipeline, which does twice the matrix work a
+// stage).  Products, us, as planned and this way, int8 and E5M2: 1008 x 768 x 3072 (three slices) 14.2 -> 7.6, 16.4 -> 10.4;
+// 512 x 1024 x 4096 13.6 -> 8.1, 16.1 -> 12.5; 1024 x 2048 x 2048 (128 x 128 tiles) 12.5 -> 8.9, 17.3 -> 12.2; 256 x 256 x
+// 2048 6.8 -> 5.3, 7.7 -> 7.6.  The other side of the lines: 768 x 768 x 12288 (seven slices) 18.2 -> 20.0, 21.8 -> 29.4; 16 x 5632 x 5632
+// 11.5 -> 9.4, 13.6 -> 14.9; beyond 512 tiles 3072 x 768 x 1008 9.0 -> 9.9.
+bool small_in_one_pass(const GemmParams& g, const Plan& pl, bool widens) {
+  const size_t t64 = (size_t)((g.P + 63) / 64) * ((g.Q + 63) / 64);
+  const size_t items = (size_t)((g.P + pl.bm - 1) / pl.bm) * ((g.Q + pl.bn - 1) / pl.bn) * pl.nsplit;
+  if (pl.tile == 0 || t64 > 2 * NUM_CU) return false;
+  if (pl.tile == 2 && pl.nsplit == 1) return true;
+  if (items > NUM_CU) return false;
+  const double st = (double)((g.R + BK - 1) / BK), slice = (double)(pl.k_per_split / BK);
+  const double once = t64 <= NUM_CU ? (widens ? 3.0 + 0.29 * st : 2.6 + 0.18 * st)
+                                    : (widens ? 4.7 + 0.465 * st : 4.6 + 0.27 * st);
+  const double planned = pl.tile == 2 ? (widens ? 7.0 + 0.28 * slice : 6.4 + 0.25 * slice)
+                                      : (widens ? 5.3 + 0.74 * slice : 5.2 + 0.5 * slice) + (pl.nsplit > 1 ? 4.5 : 0.0);
+  return once < planned;
+}
+
 template <class MMA>
 hipError_t launch_mma(const GemmParams& g, const Plan& pl, const SliceSumPlan& ss, hipStream_t stream) {
-  if (pl.tile == 0) return launch_persist<MMA>(g, ss, stream);                  // 8 waves of 128 x 64, persistent
-  if (pl.tile == 1) return launch_tile<MMA, 128, 128, 2, 2, 2>(g, ss, stream);  // 4 waves of 64 x 64
+  if (pl.tile == 0) return launch_persist<MMA>(g, ss, stream);  // 8 waves of 128 x 64, persistent
+  // In binary32 the parts of a sum are to be no longer than the plan's slices: two groups of waves stand for two of
+  // them, four for four.
+  constexpr bool INT = std::is_same<typename MMA::acc_t, v16i>::value;
+  if (small_in_one_pass(g, pl, MMA::WIDENS)) {
+    GemmParams once = g;
+    once.nsplit = 1;
+    once.k_per_split = (g.R + BK - 1) / BK * BK;
+    if (INT || pl.nsplit <= 2) return launch_tile<MMA, 64, 64, 2, 2, 4, 2>(once, ss, stream);  // 8 waves of 32 x 32
+    if constexpr (BK / MMA::KSTEP >= 4) {
+      if (pl.nsplit <= 4) return launch_tile<MMA, 64, 64, 1, 2, 5, 4>(once, ss, stream);  // 8 waves of 64 x 32
+    }
+  }
+  if (pl.tile == 1) {  // waves of 64 x 64
+    // A workgroup that has a CU to itself and a long contraction: eight waves in two groups instead of four, and a ring
+    // of four stages.  2048 x 2048 x 4096 int8 25.5 -> 23.2 us, E5M2 34.3 -> 33.3; 512 x 5632 x 5632 30.5 -> 24.3, 40.5 ->
+    // 37.5; with 8 stages a slice (512 x 1024 x 4096) 13.6 -> 14.4.
+    const size_t items = (size_t)((g.P + 127) / 128) * ((g.Q + 127) / 128) * g.nsplit;
+    if (items <= NUM_CU && g.k_per_split >= 16 * BK) return launch_tile<MMA, 128, 128, 2, 2, 4, 2>(g, ss, stream);
+    return launch_tile<MMA, 128, 128, 2, 2, 2>(g, ss, stream);
+  }
   if (pl.tile == 3) return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);  // 4 waves of 64 x 96
   return launch_tile<MMA, 64, 64, 2, 2, 3>(g, ss, stream);
 }

@@ -96,6 +96,30 @@ def test_gemm_e5m2_from_codes_is_exact_like_the_bf16_form(P, Q, R):
     assert np.all(np.abs(got - same) <= 2e-6 * ab)
 
 
+# groups of waves that share a tile: 64 x 64 tiles in one pass (edges of tiles, a contraction that ends inside a
+# sub-step, Q not a multiple of 4, exactly 512 tiles), in place of two to four slices, and 128 x 128 tiles with a CU each
+@pytest.mark.parametrize("P,Q,R", [(16, 16, 16), (65, 63, 144), (130, 67, 1040), (257, 250, 2064), (1008, 768, 3072),
+                                   (500, 1020, 4080), (2048, 1024, 528), (1040, 1936, 2064)])
+def test_gemm_with_groups_of_waves(P, Q, R):
+    rng = np.random.default_rng(P)
+    idx = np.concatenate([rng.integers(0, P * Q, size=4000), [0, Q - 1, (P - 1) * Q, P * Q - 1]]).astype(np.uint64)
+    at = torch.from_numpy(idx.astype(np.int64)).to(DEV)
+    C = torch.from_numpy(rng.standard_normal((P, Q)).astype(np.float32)).to(DEV)
+    for kind in (L.INT8, L.E5M2):
+        say("gemm groups", L.KIND_NAMES[kind], P, Q, R)
+        X, Z = _rand_codes((P, R), kind, 31), _rand_codes((Q, R), kind, 32)
+        ref, ab = oracle.gemm_fwd(X, kind, 0.5, Z, kind, 0.5, want_abs=True, at=idx)
+        f = (lambda **k: L.sr_gemm_codes(to_dev(X), kind, to_dev(Z), kind, alpha=0.25, **k)) if kind == L.INT8 else \
+            (lambda **k: L.sr_gemm_e5m2(to_dev(X), to_dev(Z), alpha=0.25, **k))
+        got = f()
+        if kind == L.INT8:
+            assert np.array_equal(got.view(-1)[at].cpu().numpy(), ref)
+        else:
+            check_product(got.view(-1)[at].cpu().numpy(), ref, ab)
+        assert torch.equal(f(out=C.clone(), beta=1.0), got + C)     # the sum is rounded once, then added
+        assert torch.equal(f(), got)
+
+
 def test_fp8_pipeline_aligns_groups_of_eight_products_to_14_bits():
     # What the hardware does, pinned: in E4M3, 256 * 256 = 2^16 next to 1 * 1 inside one run of 8
     # contraction indices loses the 1 (bits below 2^(16-13) are dropped); in the next run of 8 it
