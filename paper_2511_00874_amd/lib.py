@@ -128,8 +128,13 @@ def _dev(t):
     return t.data_ptr()
 
 
+# The handle of the current device's current stream, as torch.cuda.current_stream().cuda_stream gives it, without the stream
+# object and the device lookups that call makes (4 us a call, as much as a kernel launch)
+_current_device, _current_raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(_current_device())
 
 
 class Quant:
@@ -141,21 +146,19 @@ class Quant:
         self.counter_offset, self.round_mode, self.flags = counter_offset, round_mode, flags
 
     def c(self):
-        q = srq_quant()
-        q.kind, q.round, q.flags = self.kind, self.round_mode, self.flags
-        if isinstance(self.scale, torch.Tensor):
-            q.scale, q.scale_dev = 0.0, _dev(self.scale)
+        scale, offset, flags = self.scale, self.counter_offset, self.flags
+        if isinstance(scale, torch.Tensor):
+            value, scale_dev = 0.0, _dev(scale)
         else:
-            q.scale, q.scale_dev = float(self.scale), None
-        q.seed = self.seed & (2**64 - 1)
-        if isinstance(self.counter_offset, torch.Tensor):
+            value, scale_dev = float(scale), None
+        if isinstance(offset, torch.Tensor):
             # a 1-element int64 device tensor: the kernels read the offset when they run
-            assert self.counter_offset.dtype == torch.int64 and self.counter_offset.numel() == 1
-            q.flags |= FLAG_COUNTER_DEV
-            q.counter_offset = _dev(self.counter_offset)
+            assert offset.dtype == torch.int64 and offset.numel() == 1
+            flags |= FLAG_COUNTER_DEV
+            offset = _dev(offset)
         else:
-            q.counter_offset = self.counter_offset & (2**64 - 1)
-        return q
+            offset &= 2**64 - 1
+        return srq_quant(self.kind, self.round_mode, value, flags, scale_dev, self.seed & (2**64 - 1), offset)
 
 
 def sr_absmax_scale(x, kind, out=None):
@@ -296,9 +299,8 @@ def sr_linear_workspace_bytes(op, M, N, K):
 
 
 def _ws(op, M, N, K, workspace, device):
-    need = sr_linear_workspace_bytes(op, M, N, K)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
+        workspace = torch.empty(sr_linear_workspace_bytes(op, M, N, K), dtype=torch.uint8, device=device)
     return workspace
 
 

@@ -17,6 +17,11 @@ MAX_ROWS = 16384
 NOQ = L.Quant(L.NONE, 1.0)  # the identity quantizer of the weight-only objective
 
 
+def _rows(t, r0, r1):
+    """Rows r0 .. r1 - 1 of t; t itself where that is all of them (a view costs as much as a kernel launch)."""
+    return t if r0 == 0 and r1 == t.shape[0] else t[r0:r1]
+
+
 class SRLinearFn(torch.autograd.Function):
     """Everything the backward pass of ONE forward call needs travels on the autograd context:
     the saved activation -- as the codes of its backward quantizer when the forward pass can write
@@ -117,7 +122,7 @@ class SRLinear(torch.nn.Module):
         y = torch.empty((M, N), dtype=torch.float32, device=a.device)
         for r0 in range(0, M, MAX_ROWS):
             r1 = min(M, r0 + MAX_ROWS)
-            L.sr_linear_fwd(a[r0:r1], w, NOQ, saved["qw"], out=y[r0:r1],
+            L.sr_linear_fwd(_rows(a, r0, r1), w, NOQ, saved["qw"], out=_rows(y, r0, r1),
                             workspace=self._workspace(L.OP_FWD_WEIGHT_ONLY, r1 - r0))
         return y, saved
 
@@ -126,7 +131,7 @@ class SRLinear(torch.nn.Module):
         da = torch.empty((M, self.in_features), dtype=torch.float32, device=dy.device)
         for r0 in range(0, M, MAX_ROWS):
             r1 = min(M, r0 + MAX_ROWS)
-            L.sr_linear_bwd_data(dy[r0:r1], self.weight, NOQ, saved["qw"], out=da[r0:r1],
+            L.sr_linear_bwd_data(_rows(dy, r0, r1), self.weight, NOQ, saved["qw"], out=_rows(da, r0, r1),
                                  workspace=self._workspace(L.OP_BWD_DATA_WEIGHT_ONLY, r1 - r0))
         if self.have_grad:
             self.dW.addmm_(dy.t(), a)
@@ -164,11 +169,12 @@ class SRLinear(torch.nn.Module):
             qa = self._q("A_fwd", sc[0:1], pos_a + (r0 * K) // 8)
             if stash:
                 qa_bwd = self._q("A_bwd", saved["sA"], saved["pos_a"] + (r0 * K) // 8)
-                _, st = L.sr_linear_fwd_stash(a[r0:r1], w, qa, qw, qa_bwd, saved["qw"], out=y[r0:r1],
+                _, st = L.sr_linear_fwd_stash(_rows(a, r0, r1), w, qa, qw, qa_bwd, saved["qw"], out=_rows(y, r0, r1),
                                               workspace=self._workspace(L.OP_FWD_STASH, r1 - r0))
                 saved["stash"].append(st)
             else:
-                L.sr_linear_fwd(a[r0:r1], w, qa, qw, out=y[r0:r1], workspace=self._workspace(L.OP_FWD, r1 - r0))
+                L.sr_linear_fwd(_rows(a, r0, r1), w, qa, qw, out=_rows(y, r0, r1),
+                                workspace=self._workspace(L.OP_FWD, r1 - r0))
         return y, saved
 
     def _backward(self, dy, a, saved):
@@ -190,11 +196,11 @@ class SRLinear(torch.nn.Module):
             qa = self._q("A_bwd", saved["sA"], saved["pos_a"] + (r0 * K) // 8)
             beta = 1.0 if self.have_grad else 0.0
             if "stash" in saved:
-                L.sr_linear_bwd_stashed(dy[r0:r1], saved["stash"][i], K, qdy, saved["qw"], qa, out_dA=da[r0:r1],
-                                        out_dW=self.dW, beta=beta, workspace=self._workspace(L.OP_BWD_STASHED, r1 - r0))
+                L.sr_linear_bwd_stashed(_rows(dy, r0, r1), saved["stash"][i], K, qdy, saved["qw"], qa,
+                                        out_dA=_rows(da, r0, r1), out_dW=self.dW, beta=beta, workspace=self._workspace(L.OP_BWD_STASHED, r1 - r0))
             else:
-                L.sr_linear_bwd(dy[r0:r1], w, a[r0:r1], qdy, saved["qw"], qa, out_dA=da[r0:r1], out_dW=self.dW,
-                                beta=beta, workspace=self._workspace(L.OP_BWD, r1 - r0))
+                L.sr_linear_bwd(_rows(dy, r0, r1), w, _rows(a, r0, r1), qdy, saved["qw"], qa,
+                                out_dA=_rows(da, r0, r1), out_dW=self.dW, beta=beta, workspace=self._workspace(L.OP_BWD, r1 - r0))
             self.have_grad = True
         return da
 
