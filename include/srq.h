@@ -198,8 +198,8 @@ size_t sr_gemm_e5m2_workspace_bytes(size_t P, size_t Q, size_t R);
 /* Forward pass, Alg. 1:  Y = Q(A; qA_fwd) Q(W; qW_fwd)^T.
  * M, N, K multiples of 16.  workspace: sr_linear_workspace_bytes(SRQ_OP_FWD, M, N, K).
  * The operands are quantized once into the workspace and multiplied from there -- except for an
- * integer pair with an output of at most four 64 x 64 tiles and K <= 256, which is rounded inside
- * the product kernel (as sr_linear_fwd_fused; same result bit for bit, workspace untouched).
+ * integer pair with an output of at most 256 64 x 64 tiles and K <= 128, or at most four and K <= 256, which is
+ * rounded inside the product kernel (as sr_linear_fwd_fused; same result bit for bit, workspace untouched).
  * Weight-only objective (Sec. 3.2): with qA_fwd->kind == SRQ_NONE, Y = A Q(W; qW_fwd)^T with A
  * as it is: every product a * w_hat is exact and the sums are accumulated in binary32 (a
  * bfloat16 A is multiplied in place on the bf16 matrix pipeline, a binary32 A as three bfloat16

@@ -237,13 +237,15 @@ int run_linear(float* out, const void* x, int dtx, size_t xr, size_t xc, int x_t
   if (st != SRQ_OK) return st;
   if (!workspace_ok(workspace, workspace_bytes, pp.x_bytes + pp.z_bytes + pp.gemm_bytes)) return SRQ_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // An output of at most four 64 x 64 tiles over a short contraction: every element is used by one
-  // or two tiles, and rounding it inside the product (no codes in memory, one launch instead of
-  // two) is the faster form -- measured 9.6 against 14.2 us on the 64 x 128 x 128 layer, but 27
-  // against 14 us already at 128 x 128 x 768.  Integer pairs only: their results are the same bit
-  // for bit in both forms.
+  // A short contraction and few 64 x 64 tiles: rounding inside the product (no codes in memory, one launch instead of
+  // two) although an element is rounded once for every tile that uses it.  One stage (R <= 128): up to a tile a CU --
+  // 64 x 128 x 128 5.0 against 6.4 us with two launches, 512 x 512 x 128 5.3 against 6.8, 1024 x 1024 x 128 6.2 against
+  // 7.4, 4096 x 256 x 128 6.6 against 7.5.  Two stages: only where the call is as long as its launches -- 128 x 128 x 256
+  // 7.2 against 6.8 us on the GPU, and a launch less to wait for; 128 x 128 x 384 9.5 against 7.3.  Integer pairs
+  // only: their results are the same bit for bit in both forms.
+  const size_t tiles = ((P + 63) / 64) * ((Q + 63) / 64);
   if (phase == SRQ_PHASE_BOTH && !x_tr && !z_tr && beta == 0.0f && pp.pipe == PIPE_I8 &&
-      ((P + 63) / 64) * ((Q + 63) / 64) <= 4 && R <= 256 && !((qx->flags | qz->flags) & SRQ_FLAG_QUANTIZE_ONCE))
+      ((tiles <= 4 && R <= 256) || (tiles <= 256 && R <= 128)) && !((qx->flags | qz->flags) & SRQ_FLAG_QUANTIZE_ONCE))
     return launch_fused_fwd(out, x, make_args(qx, dtx, STORE_BYTE), z, make_args(qz, dtz, STORE_BYTE), P, Q, R, s) == hipSuccess
                ? SRQ_OK
                : SRQ_ERR_HIP;

@@ -64,10 +64,48 @@ __device__ __forceinline__ void stage_codes(uint8_t* tile, const FusedOperand& o
   }
 }
 
+// The same by NT threads, thread t, with two groups loaded before the first is rounded: for few tiles, where nothing
+// else covers a load.  (With several workgroups on a CU the form above is faster, 8192 x 3072 x 768 228 against 234 us.)
+template <int KIND, int ROWS, int NT>
+__device__ __forceinline__ void stage_codes_ahead(uint8_t* tile, const FusedOperand& op, const InvScale& s, uint64_t block0,
+                                                  uint32_t row0, uint32_t k0, uint32_t R, uint32_t t) {
+  const uint32_t key0 = (uint32_t)op.seed, key1 = (uint32_t)(op.seed >> 32);
+  const size_t n = (size_t)op.rows * R;
+  static_assert(ROWS * 16 % (2 * NT) == 0, "whole steps");
+  for (uint32_t g0 = t; g0 < ROWS * 16u; g0 += 2u * NT) {
+    float v[2][8];
+#pragma unroll
+    for (uint32_t a = 0; a < 2; ++a) {
+      const uint32_t row = row0 + ((g0 + a * NT) >> 4), k = k0 + ((g0 + a * NT) & 15u) * 8u;
+      if (row < op.rows && k < R) {
+        const size_t group = ((size_t)row * R + k) >> 3;
+        if (op.dtype == SRQ_F32) load_group<SRQ_F32>(v[a], op.x, group, n);
+        else load_group<SRQ_BF16>(v[a], op.x, group, n);
+      }
+    }
+#pragma unroll
+    for (uint32_t a = 0; a < 2; ++a) {
+      const uint32_t r = (g0 + a * NT) >> 4, kg = (g0 + a * NT) & 15u;
+      const uint32_t row = row0 + r, k = k0 + kg * 8u;
+      uint32_t c[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+      if (row < op.rows && k < R) {
+        const size_t group = ((size_t)row * R + k) >> 3;
+        if (op.round == SRQ_SR) quantize_group<KIND, SRQ_SR, false>(c, v[a], s, block0 + group, key0, key1);
+        else quantize_group<KIND, SRQ_RTN, false>(c, v[a], s, block0 + group, key0, key1);
+      }
+      const uint32_t lo[4] = {c[0], c[1], c[2], c[3]}, hi[4] = {c[4], c[5], c[6], c[7]};
+      const u32x2 w = {pack4_bytes(lo), pack4_bytes(hi)};
+      *reinterpret_cast<u32x2*>(tile + r * BK + (swizzled_chunk(r, kg >> 1) << 4) + (kg & 1u) * 8u) = w;
+    }
+  }
+}
+
 // KIND: SRQ_INTX (int8 / int4 values as bytes, int8 pipeline) or SRQ_E5M2 (codes, f16 pipeline).
-// 256 threads: 2 x 2 waves, wave tile BM/2 x BN/2.
-template <class MMA, int KIND, int BM, int BN>
-__global__ __launch_bounds__(256) void fused_fwd_kernel(FusedParams f) {
+// The first four waves multiply: 2 x 2, wave tile BM/2 x BN/2.  NT = 256: they also do the rounding, X and then Z.
+// NT = 1024, for calls of few tiles, where a workgroup's time is a chain of loads and Philox blocks per thread (four groups of
+// X, then four of Z): half of sixteen waves round X and half Z, two groups a thread.
+template <class MMA, int KIND, int BM, int BN, int NT>
+__global__ __launch_bounds__(NT) void fused_fwd_kernel(FusedParams f) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[(BM + BN) * BK];
   constexpr int WTM = BM / 2, WTN = BN / 2, TM = WTM / 32, TN = WTN / 32;
   using acc_t = typename MMA::acc_t;
@@ -98,9 +136,16 @@ __global__ __launch_bounds__(256) void fused_fwd_kernel(FusedParams f) {
 
   for (uint32_t k0 = 0; k0 < f.R; k0 += BK) {
     if (k0) __syncthreads();  // every wave has multiplied the stage before
-    stage_codes<KIND, BM>(lds, f.X, sx, bx, p0, k0, f.R);
-    stage_codes<KIND, BN>(lds + BM * BK, f.Z, sz, bz, q0, k0, f.R);
+    if constexpr (NT == 256) {
+      stage_codes<KIND, BM>(lds, f.X, sx, bx, p0, k0, f.R);
+      stage_codes<KIND, BN>(lds + BM * BK, f.Z, sz, bz, q0, k0, f.R);
+    } else if (__builtin_amdgcn_readfirstlane(wave) < NT / 128) {
+      stage_codes_ahead<KIND, BM, NT / 2>(lds, f.X, sx, bx, p0, k0, f.R, threadIdx.x);
+    } else {
+      stage_codes_ahead<KIND, BN, NT / 2>(lds + BM * BK, f.Z, sz, bz, q0, k0, f.R, threadIdx.x - NT / 2);
+    }
     __syncthreads();
+    if (NT > 256 && wave >= 4) continue;
 #pragma unroll
     for (int ks = 0; ks < KSUB; ++ks) {
       frag_t xe[TM], ze[TN];
@@ -118,6 +163,7 @@ __global__ __launch_bounds__(256) void fused_fwd_kernel(FusedParams f) {
     }
   }
 
+  if (NT > 256 && wave >= 4) return;
   // MFMA result register r of lane l: q = 8 (r / 4) + 4 (l / 32) + r % 4, p = l % 32
   const float sxv = f.X.scale_dev ? *f.X.scale_dev : f.X.scale, szv = f.Z.scale_dev ? *f.Z.scale_dev : f.Z.scale;
   const float s = __fmul_rn(1.0f, __fmul_rn(sxv, szv));
@@ -148,14 +194,21 @@ FusedOperand make_operand(const void* x, size_t rows, const QuantArgs& a) {
   return o;
 }
 
+// Up to two tiles a CU: sixteen waves a tile.  Scales given, us with four waves and with sixteen, int8 and E5M2: 64 x 128 x 128
+// 6.7 -> 4.9, 7.6 -> 5.8; 128 x 128 x 768 27.3 -> 16.3, 33.9 -> 22.6; 512 x 512 x 512 19.4 -> 12.1, 23.7 -> 16.7; 2048 x 1024 x
+// 512 (512 tiles) 32.3 -> 29.5, 39.3 -> 37.8.  With four tiles a CU the workgroups of four waves cover each other and
+// sixteen are slower: 2048 x 2048 x 256 24.4 -> 29.1, 31.2 -> 37.0.
+constexpr uint32_t FEW_TILES = 512;
+
 template <class MMA, int KIND>
 hipError_t launch_fused(const FusedParams& f, bool large_tiles, hipStream_t stream) {
   if (large_tiles) {
     const uint32_t blocks = ((f.P + 127) / 128) * ((f.Q + 127) / 128);
-    fused_fwd_kernel<MMA, KIND, 128, 128><<<blocks, 256, 0, stream>>>(f);
+    fused_fwd_kernel<MMA, KIND, 128, 128, 256><<<blocks, 256, 0, stream>>>(f);
   } else {
     const uint32_t blocks = ((f.P + 63) / 64) * ((f.Q + 63) / 64);
-    fused_fwd_kernel<MMA, KIND, 64, 64><<<blocks, 256, 0, stream>>>(f);
+    if (blocks <= FEW_TILES) fused_fwd_kernel<MMA, KIND, 64, 64, 1024><<<blocks, 1024, 0, stream>>>(f);
+    else fused_fwd_kernel<MMA, KIND, 64, 64, 256><<<blocks, 256, 0, stream>>>(f);
   }
   return hipGetLastError();
 }

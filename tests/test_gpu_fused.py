@@ -98,6 +98,19 @@ def test_many_tiles_large_tile_kernel_sampled():
     _check(A, W, qA, qW, sample=20000)
 
 
+# 64 x 64 tiles, ragged: the most that sr_linear_fwd rounds inside the product (256, one stage) and more; the most that
+# sixteen waves take each (512) and more
+@pytest.mark.parametrize("M,N,K", [(16, 16, 16), (1024, 1008, 128), (1040, 1024, 112), (2032, 1024, 144),
+                                   (2048, 1040, 272)])
+@pytest.mark.parametrize("kind", [L.INT8, L.E5M2])
+def test_few_and_many_tiles_sampled(M, N, K, kind):
+    say("fused tiles", M, N, K, L.KIND_NAMES[kind])
+    A, W, _ = synth.single_layer(M, N, K, 17)
+    A, W = to_dev(A), to_dev(W, True)
+    qA, qW = _pair(A, W, kind, kind, seed=3)
+    _check(A, W, qA, qW, exact=kind == L.INT8, sample=4000)
+
+
 def test_device_resident_scale_and_counter():
     # scales and stream positions read on the device, as a captured step passes them
     M, N, K = 64, 128, 128
