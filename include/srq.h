@@ -200,6 +200,8 @@ size_t sr_gemm_e5m2_workspace_bytes(size_t P, size_t Q, size_t R);
  * The operands are quantized once into the workspace and multiplied from there -- except for an
  * integer pair with an output of at most 256 64 x 64 tiles and K <= 128, or at most four and K <= 256, which is
  * rounded inside the product kernel (as sr_linear_fwd_fused; same result bit for bit, workspace untouched).
+ * Y may share memory with A and W (the sources are then always quantized first and written over afterwards), but not
+ * with A in the weight-only objective, whose product reads A.
  * Weight-only objective (Sec. 3.2): with qA_fwd->kind == SRQ_NONE, Y = A Q(W; qW_fwd)^T with A
  * as it is: every product a * w_hat is exact and the sums are accumulated in binary32 (a
  * bfloat16 A is multiplied in place on the bf16 matrix pipeline, a binary32 A as three bfloat16
@@ -237,7 +239,8 @@ int sr_linear_bwd_phase(float* dA, float* dW, const void* dY, int dtypedY, const
  * on large shapes it is many times slower than sr_linear_fwd and exists there to be measured.
  * Formats: qA_fwd and qW_fwd both integer (results equal to sr_linear_fwd bit for bit: the int32
  * sums are exact), or both SRQ_E5M2 (exact products, binary32 sums; SRQ_FLAG_F8_PIPELINE is
- * ignored); any other pair, and SRQ_NONE, is SRQ_ERR_UNSUPPORTED.  M, N, K multiples of 16. */
+ * ignored); any other pair, and SRQ_NONE, is SRQ_ERR_UNSUPPORTED.  M, N, K multiples of 16.  Y must not share
+ * memory with A or W. */
 int sr_linear_fwd_fused(float* Y, const void* A, int dtypeA, const void* W, int dtypeW, size_t M,
                         size_t N, size_t K, const srq_quant* qA_fwd, const srq_quant* qW_fwd,
                         void* stream);

@@ -215,6 +215,12 @@ PackedDy packed_dy(const srq_quant* qdY, int dtypedY, const ProductPlan& pd, con
   return PackedDy{nib && gemm_takes_packed_x(M, K, N, PIPE_I8), nib && gemm_takes_packed_x(N, K, M, PIPE_I8)};
 }
 
+// Whether a result of `n` floats at `out` shares memory with a source of `elems` elements at `x`.
+bool overlaps(const float* out, size_t n, const void* x, size_t elems, int dtype) {
+  const uintptr_t o = reinterpret_cast<uintptr_t>(out), a = reinterpret_cast<uintptr_t>(x);
+  return o < a + source_bytes(elems, dtype) && a < o + n * sizeof(float);
+}
+
 // One product of Alg. 1 / Alg. 2: quantize both operands into the workspace (one launch) with
 // the contraction index contiguous, then multiply.
 //   out (P x Q) = Q(x)[P x R] . Q(z)[Q x R]^T,  x given as xr x xc (transposed if x_tr), same for z
@@ -242,10 +248,12 @@ int run_linear(float* out, const void* x, int dtx, size_t xr, size_t xc, int x_t
   // 64 x 128 x 128 5.0 against 6.4 us with two launches, 512 x 512 x 128 5.3 against 6.8, 1024 x 1024 x 128 6.2 against
   // 7.4, 4096 x 256 x 128 6.6 against 7.5.  Two stages: only where the call is as long as its launches -- 128 x 128 x 256
   // 7.2 against 6.8 us on the GPU, and a launch less to wait for; 128 x 128 x 384 9.5 against 7.3.  Integer pairs
-  // only: their results are the same bit for bit in both forms.
+  // only: their results are the same bit for bit in both forms.  Not where the result lies over a source: a workgroup
+  // would write elements that another has yet to read, while the two launches read all of the sources first.
   const size_t tiles = ((P + 63) / 64) * ((Q + 63) / 64);
   if (phase == SRQ_PHASE_BOTH && !x_tr && !z_tr && beta == 0.0f && pp.pipe == PIPE_I8 &&
-      ((tiles <= 4 && R <= 256) || (tiles <= 256 && R <= 128)) && !((qx->flags | qz->flags) & SRQ_FLAG_QUANTIZE_ONCE))
+      ((tiles <= 4 && R <= 256) || (tiles <= 256 && R <= 128)) && !((qx->flags | qz->flags) & SRQ_FLAG_QUANTIZE_ONCE) &&
+      !overlaps(out, P * Q, x, P * R, dtx) && !overlaps(out, P * Q, z, Q * R, dtz))
     return launch_fused_fwd(out, x, make_args(qx, dtx, STORE_BYTE), z, make_args(qz, dtz, STORE_BYTE), P, Q, R, s) == hipSuccess
                ? SRQ_OK
                : SRQ_ERR_HIP;

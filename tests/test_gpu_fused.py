@@ -111,6 +111,27 @@ def test_few_and_many_tiles_sampled(M, N, K, kind):
     _check(A, W, qA, qW, exact=kind == L.INT8, sample=4000)
 
 
+# M, N, K that sr_linear_fwd rounds inside the product where the result lies apart; shift: where the result begins, in elements from
+# the start of the source that it lies over
+@pytest.mark.parametrize("M,N,K,over,shift", [(1024, 128, 128, "A", 0), (128, 128, 128, "W", 0), (64, 128, 256, "A", 256),
+                                              (512, 512, 128, "A", -4096), (512, 96, 112, "W", 1024)])
+@pytest.mark.parametrize("static", [False, True])
+def test_a_result_over_a_source_is_written_after_it_is_read(M, N, K, over, shift, static):
+    say("result over", over, M, N, K, shift, static)
+    A, W, _ = synth.single_layer(M, N, K, 19)
+    A, W = to_dev(A), to_dev(W)
+    qA, qW = _pair(A, W, L.INT8, L.INT8, seed=6)
+    ref = L.sr_linear_fwd(A, W, qA[0], qW[0])
+    src = A if over == "A" else W
+    lead = max(-shift, 0)
+    buf = torch.zeros(lead + max(src.numel(), shift + M * N) + 64, dtype=torch.float32, device=A.device)
+    moved = buf[lead:lead + src.numel()].view(src.shape).copy_(src)
+    Y = buf[lead + shift:lead + shift + M * N].view(M, N)
+    f = L.sr_linear_fwd_static if static else L.sr_linear_fwd
+    f(moved if over == "A" else A, moved if over == "W" else W, qA[0], qW[0], out=Y)
+    assert torch.equal(Y, ref)
+
+
 def test_device_resident_scale_and_counter():
     # scales and stream positions read on the device, as a captured step passes them
     M, N, K = 64, 128, 128
