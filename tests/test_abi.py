@@ -6,6 +6,8 @@ import ctypes as C
 import itertools
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -183,3 +185,15 @@ def test_compute_calls_need_device_tensors(lib):
     x = torch.zeros(16)
     with pytest.raises(RuntimeError):
         lib.sr_quantize(x, lib.Quant(lib.INT8, 1.0))
+
+
+def test_import_without_the_raw_stream_calls(lib):
+    # a torch without a GPU build has neither: the module loads and refuses host tensors with its own error
+    code = ("import torch\n"
+            "for n in ('_cuda_getDevice', '_cuda_getCurrentRawStream'):\n"
+            "    if hasattr(torch._C, n): delattr(torch._C, n)\n"
+            "from paper_2511_00874_amd import lib as L\n"
+            "try: L.sr_quantize(torch.zeros(8, 8), L.Quant(L.INT8, 1.0))\n"
+            "except RuntimeError as e: assert 'device tensors' in str(e), e\n"
+            "else: raise AssertionError('a host tensor was accepted')\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
