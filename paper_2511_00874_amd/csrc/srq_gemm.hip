@@ -26,11 +26,13 @@
 
 #include "srq_internal.hpp"
 #include "srq_mma.hpp"
+#include "srq_plan.hpp"
 
 namespace srq {
 namespace {
 
 using namespace mma;
+static_assert(BK == STAGE_BYTES, "the plan counts the kernels' stages");
 typedef int v2i __attribute__((ext_vector_type(2)));
 
 struct GemmParams {
@@ -941,85 +943,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(SliceSum r) {
   else slice_sum<false>(r, blockIdx.x, gridDim.x);
 }
 
-struct Plan {
-  int tile;  // 0: 256x256, 1: 128x128, 2: 64x64, 3: 128x192
-  int bm, bn;
-  uint32_t nsplit, k_per_split;
-};
-
-constexpr int NUM_CU = 256;
-
-// Tile shape and number of contraction slices by a cost model (seconds, for ranking only):
-//   time = rounds x (stages per item + fixed per-item stages) x operations per stage / rate
-//          + the pass over the partial results that every extra slice adds.
-// `rate` is what a CU sustains with that tile shape once its slots are full (measured, int8: the
-// other pipelines scale alike): 256 x 256 tiles on workgroups that stay run one per CU and hide
-// most of a tile's start and end; the 128-row tiles run two workgroups per CU (one alone gets
-// about 0.85 of the CU's rate); 64 x 64 is for problems too small for anything else.
-struct TileKind {
-  int tile, bm, bn, per_cu;
-  double rate_chip;   // operations per second over the whole chip, slots full
-  double fixed;       // start + end of an item, in stages
-};
-constexpr TileKind TILE_KINDS[] = {
-    {0, 256, 256, 1, 2.1e15, 6.0},
-    {1, 128, 128, 2, 1.45e15, 3.0},
-    {3, 128, 192, 2, 1.5e15, 3.0},
-    {2, 64, 64, 4, 0.5e15, 4.0},
-};
-constexpr double PARTIAL_BYTES_PER_SECOND = 4.0e12;  // partial tiles out and back in
-
-Plan make_plan(size_t P, size_t Q, size_t row_bytes) {
-  const size_t ksteps = (row_bytes + BK - 1) / BK;
-  Plan best{};
-  double best_time = 0.0;
-  bool have = false;
-  for (const TileKind& k : TILE_KINDS) {
-    const size_t t = ((P + k.bm - 1) / k.bm) * ((Q + k.bn - 1) / k.bn);
-    // slices only for long contractions (at least 8 stages each), at most 64
-    size_t max_split = ksteps >= 16 ? ksteps / 8 : 1;
-    if (max_split > 64) max_split = 64;
-    const double ops_stage = 2.0 * k.bm * k.bn * BK;
-    const double rate_cu = k.rate_chip / NUM_CU;
-    for (size_t n = 1; n <= max_split; ++n) {
-      const size_t items = t * n, slots = (size_t)NUM_CU * k.per_cu;
-      const size_t rounds = (items + slots - 1) / slots;
-      const size_t stages = (ksteps + n - 1) / n;
-      // a workgroup's share of its CU: alone, or one of per_cu
-      const double share = items <= (size_t)NUM_CU ? (k.per_cu > 1 ? 0.85 : 1.0) : 1.0 / k.per_cu;
-      double time = (double)rounds * ((double)stages + k.fixed) * ops_stage / (rate_cu * share);
-      if (n > 1) time += 2.0 * (double)n * (double)P * (double)Q * 4.0 / PARTIAL_BYTES_PER_SECOND;
-      if (!have || time < best_time) {
-        have = true;
-        best_time = time;
-        best.tile = k.tile; best.bm = k.bm; best.bn = k.bn;
-        best.nsplit = (uint32_t)n;
-      }
-    }
-  }
-  const size_t steps_per = (ksteps + best.nsplit - 1) / best.nsplit;
-  best.k_per_split = (uint32_t)(steps_per * BK);
-  best.nsplit = (uint32_t)((ksteps + steps_per - 1) / steps_per);
-  return best;
-}
-
-// The plan of a product on one of the pipelines.  PIPE_F16W has half the row bytes of PIPE_BF16, and by its own
-// count would cut long contractions into half as many slices: every accumulator would then sum twice as many
-// products one after another, and round about 1.4 times as far from the exact result.  Where its slices would be longer
-// than those of PIPE_BF16 it takes that plan, the same slices in half the bytes.  E4M3 steps, us and error of the
-// results against 64 bits with its own slices and with those: 1472 x 1440 x 4448 129 (9.4e-8), 130 (7.0e-8), on PIPE_BF16
-// 143; 224 x 1248 x 1792, where a slice sum is a launch more, 43 (5.9e-8), 47 (5.0e-8), on PIPE_BF16 51.  (The error
-// equals that of PIPE_BF16.)
-Plan plan_for(size_t P, size_t Q, size_t R, int pipe) {
-  if (pipe == PIPE_BF16) return make_plan(P, Q, 2 * R);
-  const Plan pl = make_plan(P, Q, R);
-  if (pipe != PIPE_F16W) return pl;
-  Plan wide = make_plan(P, Q, 2 * R);
-  if (wide.nsplit == 1 || 2 * (size_t)pl.k_per_split <= wide.k_per_split) return pl;
-  wide.k_per_split /= 2;
-  return wide;
-}
-
 // What a launch is asked to do about slice sums: carry the one of an earlier product (`carry`,
 // may be null or empty), and either run its own afterwards or hand it to the caller (`defer`).
 struct SliceSumPlan {
@@ -1108,53 +1031,22 @@ hipError_t launch_persist(GemmParams g, const SliceSumPlan& ss, hipStream_t stre
   return e;
 }
 
-// One launch of 64 x 64 tiles over the whole contraction in place of the plan's slices (or of its 128-row tiles), where
-// the output is so small that the chip holds all of those tiles at once, two a CU: nothing is written out twice, no sum is
-// left to a second launch, and there are four times as many workgroups.  Times of both in microseconds from straight
-// lines through measurements (st: stages; `widens`: 8-bit floats on the f16 pipeline, which does twice the matrix work a
-// stage).  Products, us, as planned and this way, int8 and E5M2: 1008 x 768 x 3072 (three slices) 14.2 -> 7.6, 16.4 -> 10.4;
-// 512 x 1024 x 4096 13.6 -> 8.1, 16.1 -> 12.5; 1024 x 2048 x 2048 (128 x 128 tiles) 12.5 -> 8.9, 17.3 -> 12.2; 256 x 256 x
-// 2048 6.8 -> 5.3, 7.7 -> 7.6.  The other side of the lines: 768 x 768 x 12288 (seven slices) 18.2 -> 20.0, 21.8 -> 29.4; 16 x 5632 x 5632
-// 11.5 -> 9.4, 13.6 -> 14.9; beyond 512 tiles 3072 x 768 x 1008 9.0 -> 9.9.
-bool small_in_one_pass(const GemmParams& g, const Plan& pl, bool widens) {
-  const size_t t64 = (size_t)((g.P + 63) / 64) * ((g.Q + 63) / 64);
-  const size_t items = (size_t)((g.P + pl.bm - 1) / pl.bm) * ((g.Q + pl.bn - 1) / pl.bn) * pl.nsplit;
-  if (pl.tile == 0 || t64 > 2 * NUM_CU) return false;
-  if (pl.tile == 2 && pl.nsplit == 1) return true;
-  if (items > NUM_CU) return false;
-  const double st = (double)((g.R + BK - 1) / BK), slice = (double)(pl.k_per_split / BK);
-  const double once = t64 <= NUM_CU ? (widens ? 3.0 + 0.29 * st : 2.6 + 0.18 * st)
-                                    : (widens ? 4.7 + 0.465 * st : 4.6 + 0.27 * st);
-  const double planned = pl.tile == 2 ? (widens ? 7.0 + 0.28 * slice : 6.4 + 0.25 * slice)
-                                      : (widens ? 5.3 + 0.74 * slice : 5.2 + 0.5 * slice) + (pl.nsplit > 1 ? 4.5 : 0.0);
-  return once < planned;
-}
-
 template <class MMA>
-hipError_t launch_mma(const GemmParams& g, const Plan& pl, const SliceSumPlan& ss, hipStream_t stream) {
-  if (pl.tile == 0) return launch_persist<MMA>(g, ss, stream);  // 8 waves of 128 x 64, persistent
-  // In binary32 the parts of a sum are to be no longer than the plan's slices: two groups of waves stand for two of
-  // them, four for four.
-  constexpr bool INT = std::is_same<typename MMA::acc_t, v16i>::value;
-  if (small_in_one_pass(g, pl, MMA::WIDENS)) {
-    GemmParams once = g;
-    once.nsplit = 1;
-    once.k_per_split = (g.R + BK - 1) / BK * BK;
-    if (INT || pl.nsplit <= 2) return launch_tile<MMA, 64, 64, 2, 2, 4, 2>(once, ss, stream);  // 8 waves of 32 x 32
-    if constexpr (BK / MMA::KSTEP >= 4) {
-      if (pl.nsplit <= 4) return launch_tile<MMA, 64, 64, 1, 2, 5, 4>(once, ss, stream);  // 8 waves of 64 x 32
-    }
+hipError_t launch_mma(GemmParams g, const Launch& l, const SliceSumPlan& ss, hipStream_t stream) {
+  g.nsplit = l.nsplit;
+  g.k_per_split = l.k_per_split;
+  switch (l.form) {
+    case FORM_256x256: return launch_persist<MMA>(g, ss, stream);                        // 8 waves of 128 x 64, persistent
+    case FORM_128x128: return launch_tile<MMA, 128, 128, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 64
+    case FORM_128x128_G2: return launch_tile<MMA, 128, 128, 2, 2, 4, 2>(g, ss, stream);  // 8 waves of 64 x 64
+    case FORM_128x192: return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 96
+    case FORM_64x64: return launch_tile<MMA, 64, 64, 2, 2, 3>(g, ss, stream);            // 4 waves of 32 x 32
+    case FORM_64x64_G2: return launch_tile<MMA, 64, 64, 2, 2, 4, 2>(g, ss, stream);      // 8 waves of 32 x 32
+    case FORM_64x64_G4:                                                                  // 8 waves of 64 x 32
+      if constexpr (BK / MMA::KSTEP >= 4) return launch_tile<MMA, 64, 64, 1, 2, 5, 4>(g, ss, stream);
+      break;
   }
-  if (pl.tile == 1) {  // waves of 64 x 64
-    // A workgroup that has a CU to itself and a long contraction: eight waves in two groups instead of four, and a ring
-    // of four stages.  2048 x 2048 x 4096 int8 25.5 -> 23.2 us, E5M2 34.3 -> 33.3; 512 x 5632 x 5632 30.5 -> 24.3, 40.5 ->
-    // 37.5; with 8 stages a slice (512 x 1024 x 4096) 13.6 -> 14.4.
-    const size_t items = (size_t)((g.P + 127) / 128) * ((g.Q + 127) / 128) * g.nsplit;
-    if (items <= NUM_CU && g.k_per_split >= 16 * BK) return launch_tile<MMA, 128, 128, 2, 2, 4, 2>(g, ss, stream);
-    return launch_tile<MMA, 128, 128, 2, 2, 2>(g, ss, stream);
-  }
-  if (pl.tile == 3) return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);  // 4 waves of 64 x 96
-  return launch_tile<MMA, 64, 64, 2, 2, 3>(g, ss, stream);
+  return hipErrorInvalidValue;
 }
 
 // Tiles and contraction slices of gemm_cut3_kernel, by the same model: 128 x 128 tiles of four waves,
@@ -1275,20 +1167,21 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
   g.alpha = s.alpha; g.sx = s.sx; g.sz = s.sz; g.sx_dev = s.sx_dev; g.sz_dev = s.sz_dev;
   g.accumulate = accumulate ? 1 : 0;
   if (x_packed) return launch_persist<I8Mma, true>(g, ss, stream);
-  if (pipe == PIPE_I8) return launch_mma<I8Mma>(g, pl, ss, stream);
-  if (pipe == PIPE_BF16) return launch_mma<BF16Mma>(g, pl, ss, stream);
+  const Launch l = choose_launch(pl, P, Q, row_bytes, pipe);
+  if (pipe == PIPE_I8) return launch_mma<I8Mma>(g, l, ss, stream);
+  if (pipe == PIPE_BF16) return launch_mma<BF16Mma>(g, l, ss, stream);
   // the Z operand is the first MFMA operand, X the second
   const int fx = kindX == SRQ_E5M2, fz = kindZ == SRQ_E5M2;
   if (pipe == PIPE_F16C || pipe == PIPE_F16W) {
-    if (!fz && !fx) return launch_mma<F8F16Mma<0, 0>>(g, pl, ss, stream);
-    if (!fz && fx) return launch_mma<F8F16Mma<0, 1>>(g, pl, ss, stream);
-    if (fz && !fx) return launch_mma<F8F16Mma<1, 0>>(g, pl, ss, stream);
-    return launch_mma<F8F16Mma<1, 1>>(g, pl, ss, stream);
+    if (!fz && !fx) return launch_mma<F8F16Mma<0, 0>>(g, l, ss, stream);
+    if (!fz && fx) return launch_mma<F8F16Mma<0, 1>>(g, l, ss, stream);
+    if (fz && !fx) return launch_mma<F8F16Mma<1, 0>>(g, l, ss, stream);
+    return launch_mma<F8F16Mma<1, 1>>(g, l, ss, stream);
   }
-  if (!fz && !fx) return launch_mma<F8Mma<0, 0>>(g, pl, ss, stream);
-  if (!fz && fx) return launch_mma<F8Mma<0, 1>>(g, pl, ss, stream);
-  if (fz && !fx) return launch_mma<F8Mma<1, 0>>(g, pl, ss, stream);
-  return launch_mma<F8Mma<1, 1>>(g, pl, ss, stream);
+  if (!fz && !fx) return launch_mma<F8Mma<0, 0>>(g, l, ss, stream);
+  if (!fz && fx) return launch_mma<F8Mma<0, 1>>(g, l, ss, stream);
+  if (fz && !fx) return launch_mma<F8Mma<1, 0>>(g, l, ss, stream);
+  return launch_mma<F8Mma<1, 1>>(g, l, ss, stream);
 }
 
 hipError_t launch_slice_sum(const SliceSum& r, hipStream_t stream) {

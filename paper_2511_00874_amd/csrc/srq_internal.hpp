@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/srq.h"
+#include "srq_plan.hpp"
 
 namespace srq {
 
@@ -119,16 +120,6 @@ struct GemmScale {
   float sx, sz;
   const float* sx_dev;
   const float* sz_dev;
-};
-// Which matrix pipeline multiplies the operands.
-enum Pipe {
-  PIPE_I8 = 0,   // int8 codes, int32 accumulators (exact)
-  PIPE_F8 = 1,   // E4M3 / E5M2 codes on the fp8 pipeline (hardware aligns groups of 8 products)
-  PIPE_BF16 = 2, // E4M3 / E5M2 grid values widened to bfloat16: exact products, binary32 sums
-  PIPE_F16C = 3, // E4M3 / E5M2 codes widened to binary16 inside the kernel: the same arithmetic as PIPE_BF16
-                 // from one byte per element
-  PIPE_F16W = 4  // PIPE_F16C where small products take PIPE_BF16: slices of the contraction at most as long as
-                 // PIPE_BF16 makes them (a sum's rounding errors grow with the slice), and its size limit
 };
 // R is the contraction length in elements; operand rows hold R bytes, or 2 R bytes (PIPE_BF16).
 size_t gemm_workspace_bytes(size_t P, size_t Q, size_t R, int pipe);

@@ -1,0 +1,150 @@
+// How a product is cut into tiles and slices of the contraction, and which kernel form multiplies it.  Host arithmetic only
+// (no GPU headers: a test compiles it by itself).
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+namespace srq {
+
+// Which matrix pipeline multiplies the operands.
+enum Pipe {
+  PIPE_I8 = 0,   // int8 codes, int32 accumulators (exact)
+  PIPE_F8 = 1,   // E4M3 / E5M2 codes on the fp8 pipeline (hardware aligns groups of 8 products)
+  PIPE_BF16 = 2, // E4M3 / E5M2 grid values widened to bfloat16: exact products, binary32 sums
+  PIPE_F16C = 3, // E4M3 / E5M2 codes widened to binary16 inside the kernel: the same arithmetic as PIPE_BF16
+                 // from one byte per element
+  PIPE_F16W = 4  // PIPE_F16C where small products take PIPE_BF16: slices of the contraction at most as long as
+                 // PIPE_BF16 makes them (a sum's rounding errors grow with the slice), and its size limit
+};
+
+constexpr int STAGE_BYTES = 128;  // bytes of the contraction that a kernel takes per stage
+
+struct Plan {
+  int tile;  // 0: 256x256, 1: 128x128, 2: 64x64, 3: 128x192
+  int bm, bn;
+  uint32_t nsplit, k_per_split;
+};
+
+constexpr int NUM_CU = 256;
+
+// Tile shape and number of contraction slices by a cost model (seconds, for ranking only):
+//   time = rounds x (stages per item + fixed per-item stages) x operations per stage / rate
+//          + the pass over the partial results that every extra slice adds.
+// `rate` is what a CU sustains with that tile shape once its slots are full (measured, int8: the
+// other pipelines scale alike): 256 x 256 tiles on workgroups that stay run one per CU and hide
+// most of a tile's start and end; the 128-row tiles run two workgroups per CU (one alone gets
+// about 0.85 of the CU's rate); 64 x 64 is for problems too small for anything else.
+struct TileKind {
+  int tile, bm, bn, per_cu;
+  double rate_chip;   // operations per second over the whole chip, slots full
+  double fixed;       // start + end of an item, in stages
+};
+constexpr TileKind TILE_KINDS[] = {
+    {0, 256, 256, 1, 2.1e15, 6.0},
+    {1, 128, 128, 2, 1.45e15, 3.0},
+    {3, 128, 192, 2, 1.5e15, 3.0},
+    {2, 64, 64, 4, 0.5e15, 4.0},
+};
+constexpr double PARTIAL_BYTES_PER_SECOND = 4.0e12;  // partial tiles out and back in
+
+inline Plan make_plan(size_t P, size_t Q, size_t row_bytes) {
+  const size_t ksteps = (row_bytes + STAGE_BYTES - 1) / STAGE_BYTES;
+  Plan best{};
+  double best_time = 0.0;
+  bool have = false;
+  for (const TileKind& k : TILE_KINDS) {
+    const size_t t = ((P + k.bm - 1) / k.bm) * ((Q + k.bn - 1) / k.bn);
+    // slices only for long contractions (at least 8 stages each), at most 64
+    size_t max_split = ksteps >= 16 ? ksteps / 8 : 1;
+    if (max_split > 64) max_split = 64;
+    const double ops_stage = 2.0 * k.bm * k.bn * STAGE_BYTES;
+    const double rate_cu = k.rate_chip / NUM_CU;
+    for (size_t n = 1; n <= max_split; ++n) {
+      const size_t items = t * n, slots = (size_t)NUM_CU * k.per_cu;
+      const size_t rounds = (items + slots - 1) / slots;
+      const size_t stages = (ksteps + n - 1) / n;
+      // a workgroup's share of its CU: alone, or one of per_cu
+      const double share = items <= (size_t)NUM_CU ? (k.per_cu > 1 ? 0.85 : 1.0) : 1.0 / k.per_cu;
+      double time = (double)rounds * ((double)stages + k.fixed) * ops_stage / (rate_cu * share);
+      if (n > 1) time += 2.0 * (double)n * (double)P * (double)Q * 4.0 / PARTIAL_BYTES_PER_SECOND;
+      if (!have || time < best_time) {
+        have = true;
+        best_time = time;
+        best.tile = k.tile; best.bm = k.bm; best.bn = k.bn;
+        best.nsplit = (uint32_t)n;
+      }
+    }
+  }
+  const size_t steps_per = (ksteps + best.nsplit - 1) / best.nsplit;
+  best.k_per_split = (uint32_t)(steps_per * STAGE_BYTES);
+  best.nsplit = (uint32_t)((ksteps + steps_per - 1) / steps_per);
+  return best;
+}
+
+// The plan of a product on one of the pipelines.  PIPE_F16W has half the row bytes of PIPE_BF16, and by its own
+// count would cut long contractions into half as many slices: every accumulator would then sum twice as many
+// products one after another, and round about 1.4 times as far from the exact result.  Where its slices would be longer
+// than those of PIPE_BF16 it takes that plan, the same slices in half the bytes.  E4M3 steps, us and error of the
+// results against 64 bits with its own slices and with those: 1472 x 1440 x 4448 129 (9.4e-8), 130 (7.0e-8), on PIPE_BF16
+// 143; 224 x 1248 x 1792, where a slice sum is a launch more, 43 (5.9e-8), 47 (5.0e-8), on PIPE_BF16 51.  (The error
+// equals that of PIPE_BF16.)
+inline Plan plan_for(size_t P, size_t Q, size_t R, int pipe) {
+  if (pipe == PIPE_BF16) return make_plan(P, Q, 2 * R);
+  const Plan pl = make_plan(P, Q, R);
+  if (pipe != PIPE_F16W) return pl;
+  Plan wide = make_plan(P, Q, 2 * R);
+  if (wide.nsplit == 1 || 2 * (size_t)pl.k_per_split <= wide.k_per_split) return pl;
+  wide.k_per_split /= 2;
+  return wide;
+}
+
+// One launch of 64 x 64 tiles over the whole contraction in place of the plan's slices (or of its 128-row tiles), where
+// the output is so small that the chip holds all of those tiles at once, two a CU: nothing is written out twice, no sum is
+// left to a second launch, and there are four times as many workgroups.  Times of both in microseconds from straight
+// lines through measurements (st: stages; `widens`: 8-bit floats on the f16 pipeline, which does twice the matrix work a
+// stage).  Products, us, as planned and this way, int8 and E5M2: 1008 x 768 x 3072 (three slices) 14.2 -> 7.6, 16.4 -> 10.4;
+// 512 x 1024 x 4096 13.6 -> 8.1, 16.1 -> 12.5; 1024 x 2048 x 2048 (128 x 128 tiles) 12.5 -> 8.9, 17.3 -> 12.2; 256 x 256 x
+// 2048 6.8 -> 5.3, 7.7 -> 7.6.  The other side of the lines: 768 x 768 x 12288 (seven slices) 18.2 -> 20.0, 21.8 -> 29.4; 16 x 5632 x 5632
+// 11.5 -> 9.4, 13.6 -> 14.9; beyond 512 tiles 3072 x 768 x 1008 9.0 -> 9.9.
+inline bool small_in_one_pass(const Plan& pl, size_t P, size_t Q, size_t row_bytes, bool widens) {
+  const size_t t64 = ((P + 63) / 64) * ((Q + 63) / 64);
+  const size_t items = ((P + pl.bm - 1) / pl.bm) * ((Q + pl.bn - 1) / pl.bn) * pl.nsplit;
+  if (pl.tile == 0 || t64 > 2 * NUM_CU) return false;
+  if (pl.tile == 2 && pl.nsplit == 1) return true;
+  if (items > NUM_CU) return false;
+  const double st = (double)((row_bytes + STAGE_BYTES - 1) / STAGE_BYTES), slice = (double)(pl.k_per_split / STAGE_BYTES);
+  const double once = t64 <= NUM_CU ? (widens ? 3.0 + 0.29 * st : 2.6 + 0.18 * st)
+                                    : (widens ? 4.7 + 0.465 * st : 4.6 + 0.27 * st);
+  const double planned = pl.tile == 2 ? (widens ? 7.0 + 0.28 * slice : 6.4 + 0.25 * slice)
+                                      : (widens ? 5.3 + 0.74 * slice : 5.2 + 0.5 * slice) + (pl.nsplit > 1 ? 4.5 : 0.0);
+  return once < planned;
+}
+
+// The kernel form of a planned product, and its slices.  _G2, _G4: groups of waves share a tile.
+enum Form { FORM_256x256, FORM_128x128, FORM_128x128_G2, FORM_128x192, FORM_64x64, FORM_64x64_G2, FORM_64x64_G4 };
+struct Launch {
+  Form form;
+  uint32_t nsplit, k_per_split;
+};
+inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes, int pipe) {
+  const bool widens = pipe == PIPE_F16C || pipe == PIPE_F16W;
+  if (pl.tile == 0) return Launch{FORM_256x256, pl.nsplit, pl.k_per_split};
+  // In binary32 the parts of a sum are to be no longer than the plan's slices: two groups of waves stand for two of
+  // them, four for four.  (PIPE_F8 has two sub-steps a stage, no work for four groups.)
+  if (small_in_one_pass(pl, P, Q, row_bytes, widens)) {
+    const uint32_t whole = (uint32_t)((row_bytes + STAGE_BYTES - 1) / STAGE_BYTES * STAGE_BYTES);
+    if (pipe == PIPE_I8 || pl.nsplit <= 2) return Launch{FORM_64x64_G2, 1, whole};
+    if (pipe != PIPE_F8 && pl.nsplit <= 4) return Launch{FORM_64x64_G4, 1, whole};
+  }
+  if (pl.tile == 1) {
+    // A workgroup that has a CU to itself and a long contraction: eight waves in two groups instead of four, and a ring
+    // of four stages.  2048 x 2048 x 4096 int8 25.5 -> 23.2 us, E5M2 34.3 -> 33.3; 512 x 5632 x 5632 30.5 -> 24.3, 40.5 ->
+    // 37.5; with 8 stages a slice (512 x 1024 x 4096) 13.6 -> 14.4.
+    const size_t items = ((P + 127) / 128) * ((Q + 127) / 128) * pl.nsplit;
+    const bool alone = items <= NUM_CU && pl.k_per_split >= 16 * STAGE_BYTES;
+    return Launch{alone ? FORM_128x128_G2 : FORM_128x128, pl.nsplit, pl.k_per_split};
+  }
+  return Launch{pl.tile == 3 ? FORM_128x192 : FORM_64x64, pl.nsplit, pl.k_per_split};
+}
+
+}  // namespace srq
