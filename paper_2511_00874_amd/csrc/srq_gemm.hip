@@ -1042,8 +1042,9 @@ hipError_t launch_mma(GemmParams g, const Launch& l, const SliceSumPlan& ss, hip
     case FORM_128x192: return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 96
     case FORM_64x64: return launch_tile<MMA, 64, 64, 2, 2, 3>(g, ss, stream);            // 4 waves of 32 x 32
     case FORM_64x64_G2: return launch_tile<MMA, 64, 64, 2, 2, 4, 2>(g, ss, stream);      // 8 waves of 32 x 32
-    case FORM_64x64_G4:                                                                  // 8 waves of 64 x 32
-      if constexpr (BK / MMA::KSTEP >= 4) return launch_tile<MMA, 64, 64, 1, 2, 5, 4>(g, ss, stream);
+    case FORM_64x64_G4:  // 8 waves of 64 x 32; binary32 sums only (choose_launch)
+      if constexpr (BK / MMA::KSTEP >= 4 && !std::is_same<MMA, I8Mma>::value)
+        return launch_tile<MMA, 64, 64, 1, 2, 5, 4>(g, ss, stream);
       break;
   }
   return hipErrorInvalidValue;
