@@ -98,25 +98,31 @@ inline Plan plan_for(size_t P, size_t Q, size_t R, int pipe) {
   return wide;
 }
 
-// One launch of 64 x 64 tiles over the whole contraction in place of the plan's slices (or of its 128-row tiles), where
-// the output is so small that the chip holds all of those tiles at once, two a CU: nothing is written out twice, no sum is
-// left to a second launch, and there are four times as many workgroups.  Times of both in microseconds from straight
-// lines through measurements (st: stages; `widens`: 8-bit floats on the f16 pipeline, which does twice the matrix work a
-// stage).  Products, us, as planned and this way, int8 and E5M2: 1008 x 768 x 3072 (three slices) 14.2 -> 7.6, 16.4 -> 10.4;
-// 512 x 1024 x 4096 13.6 -> 8.1, 16.1 -> 12.5; 1024 x 2048 x 2048 (128 x 128 tiles) 12.5 -> 8.9, 17.3 -> 12.2; 256 x 256 x
-// 2048 6.8 -> 5.3, 7.7 -> 7.6.  The other side of the lines: 768 x 768 x 12288 (seven slices) 18.2 -> 20.0, 21.8 -> 29.4; 16 x 5632 x 5632
-// 11.5 -> 9.4, 13.6 -> 14.9; beyond 512 tiles 3072 x 768 x 1008 9.0 -> 9.9.
+// One launch of 64 x 64 tiles over the whole contraction, with groups of waves, in place of the plan's slices or of its
+// 128-row tiles, where the output is so small that the chip holds all of those tiles at once, two a CU: nothing is written
+// out twice and no sum is left to a second launch.  Times of both in microseconds from straight lines through some 900
+// products of random sizes, each repeated in a graph (st: stages; mb: megabytes of partial sums; `widens`: 8-bit floats on the
+// f16 pipeline, twice the matrix work a stage).  As planned and this way, int8 and E5M2: 1008 x 768 x 3072 (three slices)
+// 13.7 -> 7.1, 15.8 -> 10.2; 512 x 1024 x 4096 (four) 13.3 -> 8.1, 15.6 -> 12.2; 32 x 4240 x 2448 (64 x 64 tiles, two) 6.9 -> 6.0,
+// 8.2 -> 8.7 (stays as planned); 1024 x 2048 x 2048 (128 x 128 tiles, uncut) 12.9 -> 9.3, 17.4 -> 12.4.
+// The other side of the lines: few tiles, whose slices fill more CUs (272 x 80 x 3792 int8 6.8 -> 7.5, 192 x 160 x 2240
+// E5M2 7.6 -> 8.2, 256 x 256 x 2048 bfloat16 6.9 -> 8.0); more than a tile a CU (576 x 2048 x 6000 int8 22.2 -> 29.9).
+// Beyond 48 stages the lines no longer hold (3536 x 128 x 9696 int8 17.6 -> 24.3) and the slices stay.
+// Uncut 64 x 64 tiles: the groups from 7 stages on, 2 to 9 % faster; up to 3 the longer ring and the sum of the groups cost 2 to
+// 7 % (864 x 736 x 48 3.5 -> 3.7 us), in between both take the same time.
 inline bool small_in_one_pass(const Plan& pl, size_t P, size_t Q, size_t row_bytes, bool widens) {
   const size_t t64 = ((P + 63) / 64) * ((Q + 63) / 64);
   const size_t items = ((P + pl.bm - 1) / pl.bm) * ((Q + pl.bn - 1) / pl.bn) * pl.nsplit;
+  const size_t stages = (row_bytes + STAGE_BYTES - 1) / STAGE_BYTES;
   if (pl.tile == 0 || t64 > 2 * NUM_CU) return false;
-  if (pl.tile == 2 && pl.nsplit == 1) return true;
-  if (items > NUM_CU) return false;
-  const double st = (double)((row_bytes + STAGE_BYTES - 1) / STAGE_BYTES), slice = (double)(pl.k_per_split / STAGE_BYTES);
-  const double once = t64 <= NUM_CU ? (widens ? 3.0 + 0.29 * st : 2.6 + 0.18 * st)
-                                    : (widens ? 4.7 + 0.465 * st : 4.6 + 0.27 * st);
-  const double planned = pl.tile == 2 ? (widens ? 7.0 + 0.28 * slice : 6.4 + 0.25 * slice)
-                                      : (widens ? 5.3 + 0.74 * slice : 5.2 + 0.5 * slice) + (pl.nsplit > 1 ? 4.5 : 0.0);
+  if (pl.tile == 2 && pl.nsplit == 1) return stages >= 7;
+  if (items > NUM_CU || (pl.nsplit > 1 && stages > 48)) return false;
+  const double st = (double)stages, slice = (double)(pl.k_per_split / STAGE_BYTES);
+  const double mb = pl.nsplit > 1 ? 4e-6 * pl.nsplit * (double)P * (double)Q : 0.0;
+  const double once = t64 <= NUM_CU ? (widens ? 3.2 + 0.285 * st : 2.75 + 0.18 * st)
+                                    : (widens ? 4.0 + 0.49 * st : 2.5 + 0.44 * st);
+  const double planned = pl.tile == 2 ? 5.6 + (widens ? 0.22 : 0.085) * slice + 0.59 * mb
+                                      : (widens ? 5.8 : 4.0) + 0.73 * slice + 0.44 * mb;
   return once < planned;
 }
 

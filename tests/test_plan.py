@@ -43,3 +43,17 @@ def test_four_groups_are_for_binary32_sums(plan):
                     for R in range(16, 12000, 592)} for pipe in range(5)}
     assert P64_G4 not in forms[I8] and P64_G4 not in forms[F8]
     assert all(P64_G4 in forms[pipe] for pipe in (BF16, F16C, F16W))
+
+
+# products that one pass of 64 x 64 tiles makes slower (us as planned, in one pass), and others that it makes faster
+@pytest.mark.parametrize("P,Q,R,pipe,planned,once", [
+    (864, 736, 48, I8, 3.5, 3.7), (1872, 400, 64, F16C, 3.7, 3.9), (96, 6432, 64, BF16, 3.5, 3.7), (16, 5168, 112, F8, 3.0, 3.3),
+    (272, 80, 3792, I8, 6.8, 7.5), (576, 48, 3856, I8, 6.9, 7.6), (4496, 96, 7456, I8, 16.8, 19.8), (576, 2048, 6000, I8, 22.2, 29.9),
+    (64, 6000, 10192, I8, 21.7, 26.6), (192, 160, 2240, F16C, 7.6, 8.2), (3776, 32, 2768, F16C, 8.4, 9.5),
+    (256, 256, 2048, F16C, 7.3, 7.7), (256, 256, 2048, BF16, 6.9, 8.0), (4432, 208, 2720, BF16, 18.6, 21.7),
+    (1152, 1616, 11408, F8, 46.4, 55.4),
+    (1008, 768, 3072, I8, 13.7, 7.1), (1008, 768, 3072, F16C, 15.8, 10.2), (512, 1024, 4096, F16C, 15.6, 12.2),
+    (16, 5632, 5632, I8, 11.4, 9.8), (32, 5632, 2048, I8, 6.5, 5.4), (1024, 2048, 2048, F16C, 17.4, 12.4),
+    (1024, 2048, 2048, BF16, 21.8, 15.3), (256, 6528, 96, F8, 5.5, 4.6)])
+def test_one_pass_only_where_it_is_faster(plan, P, Q, R, pipe, planned, once):
+    assert (plan(P, Q, R, pipe)["form"] in (P64_G2, P64_G4)) == (once < planned)
