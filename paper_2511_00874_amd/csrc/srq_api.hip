@@ -174,11 +174,11 @@ bool workspace_ok(const void* ws, size_t have, size_t need) {
 
 int launch_product(float* out, const uint8_t* xc, const srq_quant* qx, const uint8_t* zc, const srq_quant* qz,
                    size_t P, size_t Q, size_t R, const ProductPlan& pp, float beta, void* gws, hipStream_t s,
-                   const SliceSum* carry = nullptr, SliceSum* defer = nullptr, bool x_packed = false) {
+                   ProductRole role = ROLE_ANY, const SliceSum* carry = nullptr, SliceSum* defer = nullptr, bool x_packed = false) {
   // packed 4-bit X: the kernel multiplies 16 * value, the factor goes into alpha (a power of two: exact)
   GemmScale sc{x_packed ? 0.0625f : 1.0f, qx->scale, qz->scale, qx->scale_dev, qz->scale_dev};
   return launch_gemm_codes(out, xc, qx->kind, zc, qz->kind, P, Q, R, R * pp.es, pp.pipe, sc, beta == 1.0f, gws,
-                           s, carry, defer, x_packed) == hipSuccess
+                           s, role, carry, defer, x_packed) == hipSuccess
              ? SRQ_OK
              : SRQ_ERR_HIP;
 }
@@ -193,9 +193,10 @@ int launch_backward_products(float* dA, float* dW, const uint8_t* dy_rm, const u
                              void* gws_d, void* gws_w, hipStream_t s, bool packed_rm = false,
                              bool packed_t = false) {
   SliceSum sum_w{};
-  int st = launch_product(dW, dy_t, qdY, a_t, qA, N, K, M, pw, beta, gws_w, s, nullptr, &sum_w, packed_t);
+  int st = launch_product(dW, dy_t, qdY, a_t, qA, N, K, M, pw, beta, gws_w, s, ROLE_WEIGHT_GRADIENT, nullptr,
+                          &sum_w, packed_t);
   if (st != SRQ_OK) return st;
-  st = launch_product(dA, dy_rm, qdY, w_t, qW, M, K, N, pd, 0.0f, gws_d, s, &sum_w, nullptr, packed_rm);
+  st = launch_product(dA, dy_rm, qdY, w_t, qW, M, K, N, pd, 0.0f, gws_d, s, ROLE_ANY, &sum_w, nullptr, packed_rm);
   // the weight gradient is already enqueued: if the launch that was to carry its slice sum
   // failed, finish it in a launch of its own so that dW is whole whatever happens to dA
   if (st != SRQ_OK) (void)launch_slice_sum(sum_w, s);
@@ -227,7 +228,7 @@ bool overlaps(const float* out, size_t n, const void* x, size_t elems, int dtype
 int run_linear(float* out, const void* x, int dtx, size_t xr, size_t xc, int x_tr, const srq_quant* qx,
                const void* z, int dtz, size_t zr, size_t zc, int z_tr, const srq_quant* qz, size_t P,
                size_t Q, size_t R, float beta, void* workspace, size_t workspace_bytes, void* stream,
-               int phase = SRQ_PHASE_BOTH) {
+               int phase = SRQ_PHASE_BOTH, ProductRole role = ROLE_ANY) {
   if (!out) return SRQ_ERR_NULL;
   if (phase < SRQ_PHASE_QUANTIZE || phase > SRQ_PHASE_BOTH) return SRQ_ERR_FORMAT;
   int st = check_operand(x, dtx, qx);
@@ -268,7 +269,7 @@ int run_linear(float* out, const void* x, int dtx, size_t xr, size_t xc, int x_t
   jobs.job[1] = make_job(qz, z, dtz, zr, zc, z_tr, store, zcodes, nullptr);
   if ((phase & SRQ_PHASE_QUANTIZE) && launch_quantize_jobs(jobs, s) != hipSuccess) return SRQ_ERR_HIP;
   if (!(phase & SRQ_PHASE_PRODUCT)) return SRQ_OK;
-  return launch_product(out, xcodes, qx, zcodes, qz, P, Q, R, pp, beta, gws, s);
+  return launch_product(out, xcodes, qx, zcodes, qz, P, Q, R, pp, beta, gws, s, role);
 }
 
 // Products of the weight-only objective (Sec. 3.2): out (P x Q) = x . Q(w)^T with the row operand
@@ -594,7 +595,7 @@ int sr_linear_bwd_weight(float* dW, const void* dY, int dtypedY, const void* A, 
                          size_t N, size_t K, const srq_quant* qdY_bwd, const srq_quant* qA_bwd, float beta,
                          void* workspace, size_t workspace_bytes, void* stream) {
   return run_linear(dW, dY, dtypedY, M, N, 1, qdY_bwd, A, dtypeA, M, K, 1, qA_bwd, N, K, M, beta,
-                    workspace, workspace_bytes, stream);
+                    workspace, workspace_bytes, stream, SRQ_PHASE_BOTH, ROLE_WEIGHT_GRADIENT);
 }
 
 // Alg. 2 in one call: the output gradient is read and quantized once (one Q(dY), as the

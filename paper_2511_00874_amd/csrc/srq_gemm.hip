@@ -1149,8 +1149,8 @@ bool gemm_operands_addressable(size_t P, size_t Q, size_t R, int pipe) {
 
 hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint8_t* Z, int kindZ,
                              size_t P, size_t Q, size_t R, size_t pitch, int pipe, const GemmScale& s,
-                             bool accumulate, void* workspace, hipStream_t stream, const SliceSum* carry,
-                             SliceSum* defer, bool x_packed) {
+                             bool accumulate, void* workspace, hipStream_t stream, ProductRole role,
+                             const SliceSum* carry, SliceSum* defer, bool x_packed) {
   const SliceSumPlan ss{carry, defer};
   const size_t row_bytes = pipe == PIPE_BF16 ? 2 * R : R;
   const Plan pl = plan_for(P, Q, R, pipe);
@@ -1168,7 +1168,9 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
   g.alpha = s.alpha; g.sx = s.sx; g.sz = s.sz; g.sx_dev = s.sx_dev; g.sz_dev = s.sz_dev;
   g.accumulate = accumulate ? 1 : 0;
   if (x_packed) return launch_persist<I8Mma, true>(g, ss, stream);
-  const Launch l = choose_launch(pl, P, Q, row_bytes, pipe);
+  // integer sums are the same in every form: there the launch counts, not the role
+  const bool leaves = pipe == PIPE_I8 ? defer != nullptr : role == ROLE_WEIGHT_GRADIENT;
+  const Launch l = choose_launch(pl, P, Q, row_bytes, pipe, leaves);
   if (pipe == PIPE_I8) return launch_mma<I8Mma>(g, l, ss, stream);
   if (pipe == PIPE_BF16) return launch_mma<BF16Mma>(g, l, ss, stream);
   // the Z operand is the first MFMA operand, X the second

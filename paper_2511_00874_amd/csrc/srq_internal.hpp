@@ -138,9 +138,16 @@ struct SliceSum {
   GemmScale s;
   int accumulate, is_int;
 };
+// Which product of a layer a launch is.  It has a say in the kernel form, and in binary32 the form decides the order of a sum: a
+// product must have the same role in every entry point that promises its result bit for bit (sr_linear_bwd and
+// sr_linear_bwd_weight, the stash and phase calls), whether or not its sum is in fact deferred there.
+enum ProductRole {
+  ROLE_ANY = 0,
+  ROLE_WEIGHT_GRADIENT = 1  // sr_linear_bwd leaves its slice sum to the launch of the input gradient
+};
 hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint8_t* Z, int kindZ,
                              size_t P, size_t Q, size_t R, size_t pitch, int pipe, const GemmScale& s,
-                             bool accumulate, void* workspace, hipStream_t stream,
+                             bool accumulate, void* workspace, hipStream_t stream, ProductRole role = ROLE_ANY,
                              const SliceSum* carry = nullptr, SliceSum* defer = nullptr, bool x_packed = false);
 // x_packed: X holds 4-bit integers two per byte -- byte j of every 8 holds elements j (low nibble)
 // and j + 8 (high nibble) of a run of 16 along the contraction -- in rows of pitch / 2 bytes, and

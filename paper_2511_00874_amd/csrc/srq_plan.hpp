@@ -110,19 +110,23 @@ inline Plan plan_for(size_t P, size_t Q, size_t R, int pipe) {
 // Beyond 48 stages the lines no longer hold (3536 x 128 x 9696 int8 17.6 -> 24.3) and the slices stay.
 // Uncut 64 x 64 tiles: the groups from 7 stages on, 2 to 9 % faster; up to 3 the longer ring and the sum of the groups cost 2 to
 // 7 % (864 x 736 x 48 3.5 -> 3.7 us), in between both take the same time.
-inline bool small_in_one_pass(const Plan& pl, size_t P, size_t Q, size_t row_bytes, bool widens) {
+// `leaves`: the sum of the slices is left to a later launch and runs beside its matrix work.  Slices of 64 x 64 tiles then
+// always stay: the two products of E4M3 backward calls of up to 2^27 multiplications took 10 to 30 % longer otherwise (73 of 80
+// random ones by more than 8 %), E5M2 2048 x 192 x 352 9.4 -> 11.8.  With 128-row tiles there is less to save: M, N, K 5824 x 960
+// x 1216 int8 34.0 -> 39.3 and 4240 x 7360 x 224 E5M2 45.3 -> 50.0 stay in slices, 2736 x 432 x 1312 22.1 -> 17.8 does not.
+inline bool small_in_one_pass(const Plan& pl, size_t P, size_t Q, size_t row_bytes, bool widens, bool leaves) {
   const size_t t64 = ((P + 63) / 64) * ((Q + 63) / 64);
   const size_t items = ((P + pl.bm - 1) / pl.bm) * ((Q + pl.bn - 1) / pl.bn) * pl.nsplit;
   const size_t stages = (row_bytes + STAGE_BYTES - 1) / STAGE_BYTES;
   if (pl.tile == 0 || t64 > 2 * NUM_CU) return false;
   if (pl.tile == 2 && pl.nsplit == 1) return stages >= 7;
-  if (items > NUM_CU || (pl.nsplit > 1 && stages > 48)) return false;
+  if (items > NUM_CU || (pl.nsplit > 1 && stages > 48) || (leaves && pl.tile == 2)) return false;
   const double st = (double)stages, slice = (double)(pl.k_per_split / STAGE_BYTES);
   const double mb = pl.nsplit > 1 ? 4e-6 * pl.nsplit * (double)P * (double)Q : 0.0;
   const double once = t64 <= NUM_CU ? (widens ? 3.2 + 0.285 * st : 2.75 + 0.18 * st)
                                     : (widens ? 4.0 + 0.49 * st : 2.5 + 0.44 * st);
   const double planned = pl.tile == 2 ? 5.6 + (widens ? 0.22 : 0.085) * slice + 0.59 * mb
-                                      : (widens ? 5.8 : 4.0) + 0.73 * slice + 0.44 * mb;
+                                      : (widens ? 5.8 : 4.0) + 0.73 * slice + 0.44 * mb - (leaves && pl.nsplit > 1 ? 1.5 + 0.2 * mb : 0.0);
   return once < planned;
 }
 
@@ -132,12 +136,12 @@ struct Launch {
   Form form;
   uint32_t nsplit, k_per_split;
 };
-inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes, int pipe) {
+inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes, int pipe, bool leaves) {
   const bool widens = pipe == PIPE_F16C || pipe == PIPE_F16W;
   if (pl.tile == 0) return Launch{FORM_256x256, pl.nsplit, pl.k_per_split};
   // In binary32 the parts of a sum are to be no longer than the plan's slices: two groups of waves stand for two of
   // them, four for four.  (PIPE_F8 has two sub-steps a stage, no work for four groups.)
-  if (small_in_one_pass(pl, P, Q, row_bytes, widens)) {
+  if (small_in_one_pass(pl, P, Q, row_bytes, widens, leaves)) {
     const uint32_t whole = (uint32_t)((row_bytes + STAGE_BYTES - 1) / STAGE_BYTES * STAGE_BYTES);
     if (pipe == PIPE_I8 || pl.nsplit <= 2) return Launch{FORM_64x64_G2, 1, whole};
     if (pipe != PIPE_F8 && pl.nsplit <= 4) return Launch{FORM_64x64_G4, 1, whole};

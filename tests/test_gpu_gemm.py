@@ -318,6 +318,27 @@ def test_every_e4m3_value_is_widened_exactly():
     assert np.array_equal(Y[keep], A[keep])
 
 
+# backward calls that leave the slice sum of dW to the launch of dA, in slices of 64 x 64 and of 128 x 128 tiles, and calls that have
+# none: the form of a product, and with it the order of a binary32 sum, is that of the separate calls
+@pytest.mark.parametrize("M,N,K", [(2048, 192, 352), (976, 208, 560), (4240, 1360, 224), (2736, 432, 1312), (4992, 1056, 672)])
+@pytest.mark.parametrize("kind", [L.INT8, L.E5M2, L.E4M3])
+def test_backward_in_one_call_equals_the_separate_calls_where_a_slice_sum_rides(M, N, K, kind):
+    say("sum rides", M, N, K, L.KIND_NAMES[kind])
+    A, W, dY = synth.single_layer(M, N, K, 23, std_dy=1e-3)
+    A, W, dY = to_dev(A), to_dev(W, True), to_dev(dY)
+    q = [L.Quant(kind, oracle.absmax_scale(host_src(t), kind), 4, i << 24) for i, t in enumerate((dY, W, A))]
+    dA, dW = L.sr_linear_bwd(dY, W, A, *q)
+    assert torch.equal(dA, L.sr_linear_bwd_data(dY, W, q[0], q[1]))
+    assert torch.equal(dW, L.sr_linear_bwd_weight(dY, A, q[0], q[2]))
+    dW2 = dW.clone()
+    dA2, _ = L.sr_linear_bwd(dY, W, A, *q, out_dW=dW2, beta=1.0)
+    assert torch.equal(dA2, dA) and torch.equal(dW2, dW + dW)
+    idx = np.random.default_rng(5).integers(0, N * K, size=2000).astype(np.uint64)
+    oq = [oracle.Quant(kind, qq.scale, 4, i << 24) for i, qq in enumerate(q)]
+    ref, ab = oracle.linear_bwd_weight(host_src(dY), host_src(A), oq[0], oq[2], want_abs=True, at=idx)
+    check_product(dW.view(-1).cpu().numpy()[idx.astype(np.int64)], ref, ab)
+
+
 # weight gradients whose bfloat16 form cuts the contraction into more slices than the code form would by its own
 # count, on each tile shape, and one whose slices end inside a stage of 128 codes
 @pytest.mark.parametrize("M,N,K", [(2064, 1296, 560), (2064, 1488, 1296), (1600, 1152, 176), (1600, 1296, 560)])

@@ -13,9 +13,9 @@ P256, P128, P128_G2, P128x192, P64, P64_G2, P64_G4 = range(7)
 WRAP = """
 #include "srq_plan.hpp"
 using namespace srq;
-extern "C" void plan(size_t P, size_t Q, size_t R, int pipe, unsigned* o) {
+extern "C" void plan(size_t P, size_t Q, size_t R, int pipe, int leaves, unsigned* o) {
   const Plan pl = plan_for(P, Q, R, pipe);
-  const Launch l = choose_launch(pl, P, Q, pipe == PIPE_BF16 ? 2 * R : R, pipe);
+  const Launch l = choose_launch(pl, P, Q, pipe == PIPE_BF16 ? 2 * R : R, pipe, leaves);
   o[0] = pl.nsplit; o[1] = l.form; o[2] = l.nsplit; o[3] = l.k_per_split;
 }
 """
@@ -28,11 +28,11 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(d / "plan.cpp"), "-o", str(d / "plan.so")],
                    check=True)
     lib = C.CDLL(str(d / "plan.so"))
-    lib.plan.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_void_p]
+    lib.plan.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_int, C.c_void_p]
 
-    def f(P, Q, R, pipe):
+    def f(P, Q, R, pipe, leaves=False):
         o = (C.c_uint * 4)()
-        lib.plan(P, Q, R, pipe, o)
+        lib.plan(P, Q, R, pipe, leaves, o)
         return dict(planned_slices=o[0], form=o[1], slices=o[2], k_per_split=o[3])
     return f
 
@@ -57,3 +57,16 @@ def test_four_groups_are_for_binary32_sums(plan):
     (1024, 2048, 2048, BF16, 21.8, 15.3), (256, 6528, 96, F8, 5.5, 4.6)])
 def test_one_pass_only_where_it_is_faster(plan, P, Q, R, pipe, planned, once):
     assert (plan(P, Q, R, pipe)["form"] in (P64_G2, P64_G4)) == (once < planned)
+
+
+# weight gradients whose slice sum runs beside the next launch: N x K, contraction M (us of both products of the backward call with
+# the weight gradient in slices, in one pass)
+@pytest.mark.parametrize("M,N,K,pipe,sliced,once", [
+    (1088, 208, 336, BF16, 7.9, 8.9), (976, 208, 560, BF16, 8.0, 8.9), (1808, 528, 256, F16W, 9.9, 12.2),
+    (1376, 624, 256, F16W, 9.3, 10.4), (2048, 192, 352, F16C, 9.7, 11.8), (2432, 304, 288, F16C, 10.5, 13.0),
+    (3968, 128, 960, I8, 11.2, 13.5), (5824, 960, 1216, I8, 34.0, 39.3), (4240, 7360, 224, F16C, 45.3, 50.0),
+    (5776, 2544, 736, F16W, 57.4, 63.7),
+    (1744, 1872, 384, F16W, 18.3, 15.9), (2432, 1440, 384, F16W, 19.0, 16.4), (2736, 432, 1312, F16C, 22.1, 17.8),
+    (3888, 160, 2768, I8, 25.9, 21.6), (1520, 1216, 1104, F16W, 22.6, 19.0)])
+def test_one_pass_where_the_slice_sum_is_left_to_a_later_launch(plan, M, N, K, pipe, sliced, once):
+    assert (plan(N, K, M, pipe, True)["form"] in (P64_G2, P64_G4)) == (once < sliced)
