@@ -206,7 +206,7 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
 // groups' sums are added through LDS at the end.  For workgroups that are few: a CU with a single workgroup of four waves
 // has one wave per SIMD, which nothing covers while it waits for LDS or at the barrier (2048 x 2048 x 4096 int8, with the
 // loads of the stages left out 17.8 us, with the matrix work left out 24.0, together 25.4); the groups put two there and a
-// deeper ring of stages keeps more loads in flight (17.4 with the matrix work left out, 23.8 in all).
+// longer ring of stages keeps more loads in flight (with four, 17.4 with the matrix work left out, 23.8 in all; with three 23.1).
 template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1>
 __global__ __launch_bounds__(WGM* WGN* KG * 64) void gemm_nt_kernel(GemmParams g, SliceSum rider, uint32_t gemm_blocks) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
@@ -1038,13 +1038,14 @@ hipError_t launch_mma(GemmParams g, const Launch& l, const SliceSumPlan& ss, hip
   switch (l.form) {
     case FORM_256x256: return launch_persist<MMA>(g, ss, stream);                        // 8 waves of 128 x 64, persistent
     case FORM_128x128: return launch_tile<MMA, 128, 128, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 64
-    case FORM_128x128_G2: return launch_tile<MMA, 128, 128, 2, 2, 4, 2>(g, ss, stream);  // 8 waves of 64 x 64
+    case FORM_128x128_G2: return launch_tile<MMA, 128, 128, 2, 2, 3, 2>(g, ss, stream);  // 8 waves of 64 x 64
     case FORM_128x192: return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 96
     case FORM_64x64: return launch_tile<MMA, 64, 64, 2, 2, 3>(g, ss, stream);            // 4 waves of 32 x 32
-    case FORM_64x64_G2: return launch_tile<MMA, 64, 64, 2, 2, 4, 2>(g, ss, stream);      // 8 waves of 32 x 32
+    case FORM_64x64_G2:                                                                  // 8 waves of 32 x 32
+      return l.ring == 3 ? launch_tile<MMA, 64, 64, 2, 2, 3, 2>(g, ss, stream) : launch_tile<MMA, 64, 64, 2, 2, 4, 2>(g, ss, stream);
     case FORM_64x64_G4:  // 8 waves of 64 x 32; binary32 sums only (choose_launch)
       if constexpr (BK / MMA::KSTEP >= 4 && !std::is_same<MMA, I8Mma>::value)
-        return launch_tile<MMA, 64, 64, 1, 2, 5, 4>(g, ss, stream);
+        return l.ring == 3 ? launch_tile<MMA, 64, 64, 1, 2, 3, 4>(g, ss, stream) : launch_tile<MMA, 64, 64, 1, 2, 5, 4>(g, ss, stream);
       break;
   }
   return hipErrorInvalidValue;

@@ -130,31 +130,39 @@ inline bool small_in_one_pass(const Plan& pl, size_t P, size_t Q, size_t row_byt
   return once < planned;
 }
 
-// The kernel form of a planned product, and its slices.  _G2, _G4: groups of waves share a tile.
+// The kernel form of a planned product, its slices and the stages of its LDS ring.  _G2, _G4: groups of waves share a tile.
 enum Form { FORM_256x256, FORM_128x128, FORM_128x128_G2, FORM_128x192, FORM_64x64, FORM_64x64_G2, FORM_64x64_G4 };
 struct Launch {
   Form form;
   uint32_t nsplit, k_per_split;
+  int ring;
 };
+// The rings leave room on a CU for quantizer workgroups of another stream, and fewer stages are not slower alone: with eight
+// waves on 128 x 128 tiles three take 0.97 to 1.0 of the time of four (2048 x 2048 x 4096 int8 23.3 and 23.1 us, E5M2
+// 33.2 and 33.2), and beside the quantizer of another layer, M, N, K 2672 x 704 x 6128 E5M2, a step of 66.4 us with four takes 52.5
+// (51.7 with four waves and two stages), 5792 x 592 x 5120 E5M2 77.5 and 66.9 (65.9), 2624 x 896 x 4288 int8 41.8 and 41.6
+// (48.0).  64 x 64 tiles two a CU: three stages as well, 0.94 to 1.0 of the time of four or five alone; one a CU: four and five, as
+// three are up to 1.2 times slower where the operands come from beyond the L2 (16 x 5632 x 5632 int8 9.8 and 12.0).
 inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes, int pipe, bool leaves) {
   const bool widens = pipe == PIPE_F16C || pipe == PIPE_F16W;
-  if (pl.tile == 0) return Launch{FORM_256x256, pl.nsplit, pl.k_per_split};
+  if (pl.tile == 0) return Launch{FORM_256x256, pl.nsplit, pl.k_per_split, 2};
   // In binary32 the parts of a sum are to be no longer than the plan's slices: two groups of waves stand for two of
   // them, four for four.  (PIPE_F8 has two sub-steps a stage, no work for four groups.)
   if (small_in_one_pass(pl, P, Q, row_bytes, widens, leaves)) {
     const uint32_t whole = (uint32_t)((row_bytes + STAGE_BYTES - 1) / STAGE_BYTES * STAGE_BYTES);
-    if (pipe == PIPE_I8 || pl.nsplit <= 2) return Launch{FORM_64x64_G2, 1, whole};
-    if (pipe != PIPE_F8 && pl.nsplit <= 4) return Launch{FORM_64x64_G4, 1, whole};
+    const bool one_a_cu = ((P + 63) / 64) * ((Q + 63) / 64) <= NUM_CU;
+    if (pipe == PIPE_I8 || pl.nsplit <= 2) return Launch{FORM_64x64_G2, 1, whole, one_a_cu ? 4 : 3};
+    if (pipe != PIPE_F8 && pl.nsplit <= 4) return Launch{FORM_64x64_G4, 1, whole, one_a_cu ? 5 : 3};
   }
   if (pl.tile == 1) {
-    // A workgroup that has a CU to itself and a long contraction: eight waves in two groups instead of four, and a ring
-    // of four stages.  2048 x 2048 x 4096 int8 25.5 -> 23.2 us, E5M2 34.3 -> 33.3; 512 x 5632 x 5632 30.5 -> 24.3, 40.5 ->
-    // 37.5; with 8 stages a slice (512 x 1024 x 4096) 13.6 -> 14.4.
+    // A workgroup that has a CU to itself and a long contraction: eight waves in two groups instead of four, and a longer
+    // ring.  2048 x 2048 x 4096 int8 25.9 -> 23.1 us, E5M2 34.0 -> 33.2; 512 x 5632 x 5632 30.4 -> 24.0, 39.1 -> 35.9.
     const size_t items = ((P + 127) / 128) * ((Q + 127) / 128) * pl.nsplit;
-    const bool alone = items <= NUM_CU && pl.k_per_split >= 16 * STAGE_BYTES;
-    return Launch{alone ? FORM_128x128_G2 : FORM_128x128, pl.nsplit, pl.k_per_split};
+    if (items <= NUM_CU && pl.k_per_split >= 16 * STAGE_BYTES) return Launch{FORM_128x128_G2, pl.nsplit, pl.k_per_split, 3};
+    return Launch{FORM_128x128, pl.nsplit, pl.k_per_split, 2};
   }
-  return Launch{pl.tile == 3 ? FORM_128x192 : FORM_64x64, pl.nsplit, pl.k_per_split};
+  if (pl.tile == 3) return Launch{FORM_128x192, pl.nsplit, pl.k_per_split, 2};
+  return Launch{FORM_64x64, pl.nsplit, pl.k_per_split, 3};
 }
 
 }  // namespace srq

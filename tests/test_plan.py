@@ -16,7 +16,7 @@ using namespace srq;
 extern "C" void plan(size_t P, size_t Q, size_t R, int pipe, int leaves, unsigned* o) {
   const Plan pl = plan_for(P, Q, R, pipe);
   const Launch l = choose_launch(pl, P, Q, pipe == PIPE_BF16 ? 2 * R : R, pipe, leaves);
-  o[0] = pl.nsplit; o[1] = l.form; o[2] = l.nsplit; o[3] = l.k_per_split;
+  o[0] = pl.nsplit; o[1] = l.form; o[2] = l.nsplit; o[3] = l.k_per_split; o[4] = l.ring;
 }
 """
 
@@ -31,9 +31,9 @@ def plan(tmp_path_factory):
     lib.plan.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_int, C.c_void_p]
 
     def f(P, Q, R, pipe, leaves=False):
-        o = (C.c_uint * 4)()
+        o = (C.c_uint * 5)()
         lib.plan(P, Q, R, pipe, leaves, o)
-        return dict(planned_slices=o[0], form=o[1], slices=o[2], k_per_split=o[3])
+        return dict(planned_slices=o[0], form=o[1], slices=o[2], k_per_split=o[3], ring=o[4])
     return f
 
 
@@ -70,3 +70,26 @@ def test_one_pass_only_where_it_is_faster(plan, P, Q, R, pipe, planned, once):
     (3888, 160, 2768, I8, 25.9, 21.6), (1520, 1216, 1104, F16W, 22.6, 19.0)])
 def test_one_pass_where_the_slice_sum_is_left_to_a_later_launch(plan, M, N, K, pipe, sliced, once):
     assert (plan(N, K, M, pipe, True)["form"] in (P64_G2, P64_G4)) == (once < sliced)
+
+
+LDS_OF_A_CU = 160 << 10
+QUANTIZER_LDS = 64 * (128 + 2) * 2   # a workgroup of the kernel that writes transposed operands
+
+
+@pytest.mark.parametrize("pipe", range(5))
+def test_groups_of_waves_leave_lds_for_quantizers_of_another_stream(plan, pipe):
+    # what srq.h tells callers of the phase entry points; the forms without groups that they stand in for left as much
+    edge = {P128_G2: 128, P64_G2: 64, P64_G4: 64}
+    seen = set()
+    for P in (16, 80, 656, 1264, 2048, 2672, 5104, 9200):
+        for Q in (64, 304, 704, 1536, 2080, 3232):
+            for R in (16, 144, 1040, 2672, 5424, 6128, 11408):
+                for leaves in (False, True):
+                    p = plan(P, Q, R, pipe, leaves)
+                    if p["form"] in edge:
+                        e = edge[p["form"]]
+                        lds, tiles = p["ring"] * 2 * e * 128, -(-P // e) * -(-Q // e) * p["slices"]
+                        room = LDS_OF_A_CU - min(-(-tiles // 256), LDS_OF_A_CU // lds) * lds
+                        assert room >= 3 * QUANTIZER_LDS, (P, Q, R, leaves, p)
+                        seen.add((p["form"], p["ring"]))
+    assert {(P128_G2, 3), (P64_G2, 3), (P64_G2, 4)} <= seen
