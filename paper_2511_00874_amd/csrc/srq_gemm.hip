@@ -199,7 +199,8 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
 
 // Besides its tiles a launch can carry the slice sum of an EARLIER product (`rider`, complete when
 // this launch starts): memory-bound work that runs beside the matrix work, in the resident slots
-// the tiles leave free and in the tail of the launch, instead of in a launch of its own.
+// the tiles leave free and in the tail of the launch, instead of in a launch of its own.  (Its workgroups are given the LDS of a
+// tile's: the launch chooses a form that leaves such slots, see choose_launch.)
 // Workgroups [0, gemm_blocks) multiply, the rest sum.  (Measured against this: the rider groups
 // spread through the launch, every fourth group of 8 -- slower.)
 // KG > 1: KG groups of WGM x WGN waves share the tile.  Each group multiplies its own sub-steps of every stage, and the
@@ -1170,8 +1171,16 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
   g.accumulate = accumulate ? 1 : 0;
   if (x_packed) return launch_persist<I8Mma, true>(g, ss, stream);
   // integer sums are the same in every form: there the launch counts, not the role
-  const bool leaves = pipe == PIPE_I8 ? defer != nullptr : role == ROLE_WEIGHT_GRADIENT;
-  const Launch l = choose_launch(pl, P, Q, row_bytes, pipe, leaves);
+  bool leaves = role == ROLE_WEIGHT_GRADIENT;
+  uint32_t rides = 0;
+  if (pipe == PIPE_I8) {
+    leaves = defer != nullptr;
+    if (carry && carry->total > 0) rides = carry->nsplit;
+  } else if (role == ROLE_INPUT_GRADIENT) {  // M x K over N here: the weight gradient is N x K over M
+    const Launch w = choose_launch(plan_for(R, Q, P, pipe), R, Q, pipe == PIPE_BF16 ? 2 * P : P, pipe, true, 0);
+    if (w.nsplit > 1) rides = w.nsplit;
+  }
+  const Launch l = choose_launch(pl, P, Q, row_bytes, pipe, leaves, rides);
   if (pipe == PIPE_I8) return launch_mma<I8Mma>(g, l, ss, stream);
   if (pipe == PIPE_BF16) return launch_mma<BF16Mma>(g, l, ss, stream);
   // the Z operand is the first MFMA operand, X the second

@@ -143,14 +143,26 @@ struct Launch {
 // (51.7 with four waves and two stages), 5792 x 592 x 5120 E5M2 77.5 and 66.9 (65.9), 2624 x 896 x 4288 int8 41.8 and 41.6
 // (48.0).  64 x 64 tiles two a CU: three stages as well, 0.94 to 1.0 of the time of four or five alone; one a CU: four and five, as
 // three are up to 1.2 times slower where the operands come from beyond the L2 (16 x 5632 x 5632 int8 9.8 and 12.0).
-inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes, int pipe, bool leaves) {
+// `rides`: slices of an earlier product whose sum the launch carries (0: none).  Its workgroups take as much LDS as a tile's, and
+// where the tiles hold nearly all CUs they wait for them to finish instead of running beside them.
+//   - Eight waves on 128 x 128 tiles with such a sum: up to 224 of them (both products of a backward call, us without groups and
+//     with: E5M2 5328 x 3104 x 736, 252 tiles, 58.1 -> 64.1, 7296 x 1968 x 448, 228 tiles, 37.6 -> 41.5; 6784 x 4016 x 432,
+//     212 tiles, 60.7 -> 56.9), or for integers a contraction of 24 stages, beside which it ends in time (10304 x 5440 x 288,
+//     243 tiles, 65.0 -> 61.9; at 16 and 19 stages 31.5 -> 33.8, 39.5 -> 41.9).
+//   - More than a 64 x 64 tile a CU, uncut: not over 12 stages or fewer beside a sum of more than three slices, a chain of as many
+//     loads (int8 6064 x 1488 x 320, six, 25.1 -> 27.7; E4M3 8240 x 1152 x 160, 13, 27.7 -> 29.7; with two, 2816 x 272 x 368 int8
+//     11.6 -> 10.0).  8-bit floats and sums of four to six slices: not over 6 stages (E5M2 6432 x 208 x 304 14.5 -> 15.8; at twelve,
+//     4832 x 1488 x 320, 27.5 -> 23.6).
+inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes, int pipe, bool leaves, uint32_t rides) {
   const bool widens = pipe == PIPE_F16C || pipe == PIPE_F16W;
   if (pl.tile == 0) return Launch{FORM_256x256, pl.nsplit, pl.k_per_split, 2};
   // In binary32 the parts of a sum are to be no longer than the plan's slices: two groups of waves stand for two of
   // them, four for four.  (PIPE_F8 has two sub-steps a stage, no work for four groups.)
-  if (small_in_one_pass(pl, P, Q, row_bytes, widens, leaves)) {
+  const bool one_a_cu = ((P + 63) / 64) * ((Q + 63) / 64) <= NUM_CU;
+  const bool behind_tiles = rides > 3 && pl.nsplit == 1 && !one_a_cu &&
+                            row_bytes <= (size_t)(pipe == PIPE_I8 || rides > 6 ? 12 : 6) * STAGE_BYTES;
+  if (!behind_tiles && small_in_one_pass(pl, P, Q, row_bytes, widens, leaves)) {
     const uint32_t whole = (uint32_t)((row_bytes + STAGE_BYTES - 1) / STAGE_BYTES * STAGE_BYTES);
-    const bool one_a_cu = ((P + 63) / 64) * ((Q + 63) / 64) <= NUM_CU;
     if (pipe == PIPE_I8 || pl.nsplit <= 2) return Launch{FORM_64x64_G2, 1, whole, one_a_cu ? 4 : 3};
     if (pipe != PIPE_F8 && pl.nsplit <= 4) return Launch{FORM_64x64_G4, 1, whole, one_a_cu ? 5 : 3};
   }
@@ -158,7 +170,9 @@ inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes
     // A workgroup that has a CU to itself and a long contraction: eight waves in two groups instead of four, and a longer
     // ring.  2048 x 2048 x 4096 int8 25.9 -> 23.1 us, E5M2 34.0 -> 33.2; 512 x 5632 x 5632 30.4 -> 24.0, 39.1 -> 35.9.
     const size_t items = ((P + 127) / 128) * ((Q + 127) / 128) * pl.nsplit;
-    if (items <= NUM_CU && pl.k_per_split >= 16 * STAGE_BYTES) return Launch{FORM_128x128_G2, pl.nsplit, pl.k_per_split, 3};
+    const bool room = rides == 0 || items <= 224 || (pipe == PIPE_I8 && pl.k_per_split >= 24 * STAGE_BYTES);
+    if (items <= NUM_CU && pl.k_per_split >= 16 * STAGE_BYTES && room)
+      return Launch{FORM_128x128_G2, pl.nsplit, pl.k_per_split, 3};
     return Launch{FORM_128x128, pl.nsplit, pl.k_per_split, 2};
   }
   if (pl.tile == 3) return Launch{FORM_128x192, pl.nsplit, pl.k_per_split, 2};

@@ -318,9 +318,11 @@ def test_every_e4m3_value_is_widened_exactly():
     assert np.array_equal(Y[keep], A[keep])
 
 
-# backward calls that leave the slice sum of dW to the launch of dA, in slices of 64 x 64 and of 128 x 128 tiles, and calls that have
-# none: the form of a product, and with it the order of a binary32 sum, is that of the separate calls
-@pytest.mark.parametrize("M,N,K", [(2048, 192, 352), (976, 208, 560), (4240, 1360, 224), (2736, 432, 1312), (4992, 1056, 672)])
+# backward calls that leave the slice sum of dW to the launch of dA, in slices of 64 x 64 and of 128 x 128 tiles (with groups of waves
+# for dA, for dW, for both and for neither), and calls that have none: the form of a product, and with it the order of a binary32
+# sum, is that of the separate calls
+@pytest.mark.parametrize("M,N,K", [(2048, 192, 352), (976, 208, 560), (4240, 1360, 224), (2736, 432, 1312), (4992, 1056, 672),
+                                   (6432, 208, 304), (4304, 320, 288), (7296, 1968, 448), (5920, 1936, 608), (4080, 2000, 752)])
 @pytest.mark.parametrize("kind", [L.INT8, L.E5M2, L.E4M3])
 def test_backward_in_one_call_equals_the_separate_calls_where_a_slice_sum_rides(M, N, K, kind):
     say("sum rides", M, N, K, L.KIND_NAMES[kind])

@@ -13,9 +13,9 @@ P256, P128, P128_G2, P128x192, P64, P64_G2, P64_G4 = range(7)
 WRAP = """
 #include "srq_plan.hpp"
 using namespace srq;
-extern "C" void plan(size_t P, size_t Q, size_t R, int pipe, int leaves, unsigned* o) {
+extern "C" void plan(size_t P, size_t Q, size_t R, int pipe, int leaves, unsigned rides, unsigned* o) {
   const Plan pl = plan_for(P, Q, R, pipe);
-  const Launch l = choose_launch(pl, P, Q, pipe == PIPE_BF16 ? 2 * R : R, pipe, leaves);
+  const Launch l = choose_launch(pl, P, Q, pipe == PIPE_BF16 ? 2 * R : R, pipe, leaves, rides);
   o[0] = pl.nsplit; o[1] = l.form; o[2] = l.nsplit; o[3] = l.k_per_split; o[4] = l.ring;
 }
 """
@@ -28,11 +28,11 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(d / "plan.cpp"), "-o", str(d / "plan.so")],
                    check=True)
     lib = C.CDLL(str(d / "plan.so"))
-    lib.plan.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_int, C.c_void_p]
+    lib.plan.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_int, C.c_uint, C.c_void_p]
 
-    def f(P, Q, R, pipe, leaves=False):
+    def f(P, Q, R, pipe, leaves=False, rides=0):
         o = (C.c_uint * 5)()
-        lib.plan(P, Q, R, pipe, leaves, o)
+        lib.plan(P, Q, R, pipe, leaves, rides, o)
         return dict(planned_slices=o[0], form=o[1], slices=o[2], k_per_split=o[3], ring=o[4])
     return f
 
@@ -93,3 +93,17 @@ def test_groups_of_waves_leave_lds_for_quantizers_of_another_stream(plan, pipe):
                         assert room >= 3 * QUANTIZER_LDS, (P, Q, R, leaves, p)
                         seen.add((p["form"], p["ring"]))
     assert {(P128_G2, 3), (P64_G2, 3), (P64_G2, 4)} <= seen
+
+
+# input gradients that carry the slice sum of the weight gradient (us of both products without groups of waves, with)
+@pytest.mark.parametrize("M,N,K,pipe,plain,groups", [
+    (5328, 3104, 736, F16C, 58.1, 64.1), (7296, 1968, 448, F16C, 37.6, 41.5), (6416, 2496, 560, F16W, 48.8, 52.8),
+    (7296, 1968, 448, I8, 31.5, 33.8), (3824, 9344, 192, I8, 39.5, 41.9), (6064, 1488, 320, I8, 25.1, 27.7),
+    (4304, 320, 288, F16W, 15.6, 17.0), (9504, 544, 112, F16C, 17.5, 19.1), (2320, 96, 560, BF16, 10.9, 11.4),
+    (6784, 4016, 432, F16C, 60.7, 56.9), (6512, 5264, 480, F16W, 81.9, 76.6), (10304, 5440, 288, I8, 65.0, 61.9),
+    (5248, 3008, 448, I8, 36.5, 31.8), (2816, 272, 368, I8, 11.6, 10.0), (4832, 1488, 320, F16C, 27.5, 23.6),
+    (9360, 2528, 176, I8, 33.7, 29.0)])
+def test_launches_that_carry_a_slice_sum_leave_room_for_it(plan, M, N, K, pipe, plain, groups):
+    rides = plan(N, K, M, pipe, leaves=True)["slices"]
+    assert rides > 1
+    assert (plan(M, K, N, pipe, rides=rides)["form"] in (P128_G2, P64_G2, P64_G4)) == (groups < plain)
