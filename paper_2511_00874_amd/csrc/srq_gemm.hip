@@ -208,8 +208,10 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
 // has one wave per SIMD, which nothing covers while it waits for LDS or at the barrier (2048 x 2048 x 4096 int8, with the
 // loads of the stages left out 17.8 us, with the matrix work left out 24.0, together 25.4); the groups put two there and a
 // longer ring of stages keeps more loads in flight (with four, 17.4 with the matrix work left out, 23.8 in all; with three 23.1).
-template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1>
-__global__ __launch_bounds__(WGM* WGN* KG * 64) void gemm_nt_kernel(GemmParams g, SliceSum rider, uint32_t gemm_blocks) {
+// SETS = 2 (one group): two sets of accumulators, for the first and the second half of the sub-steps of every stage, added at the
+// end: the sums of two groups of waves, in the same order.
+template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1, int SETS = 1>
+__global__ __launch_bounds__(WGM* WGN* KG * 64, SETS) void gemm_nt_kernel(GemmParams g, SliceSum rider, uint32_t gemm_blocks) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   if (blockIdx.x >= gemm_blocks) {
     if (rider.is_int) slice_sum<true>(rider, blockIdx.x - gemm_blocks, gridDim.x - gemm_blocks);
@@ -230,6 +232,7 @@ __global__ __launch_bounds__(WGM* WGN* KG * 64) void gemm_nt_kernel(GemmParams g
   constexpr int FC = sizeof(raw_t) / 16;  // 16-byte chunks a lane reads per sub-step
   constexpr int KSUB = BK / MMA::KSTEP / KG;  // sub-steps of a stage that a wave multiplies
   static_assert(KSUB >= 1, "every group has a sub-step");
+  static_assert(SETS == 1 || (KG == 1 && SETS == 2 && KSUB % 2 == 0), "two sets stand for two groups");
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);  // the same, known to be uniform
@@ -317,13 +320,16 @@ __global__ __launch_bounds__(WGM* WGN* KG * 64) void gemm_nt_kernel(GemmParams g
     return f;
   };
 
-  acc_t acc[TM][TN];
+  acc_t acc_set[SETS][TM][TN];
+  auto& acc = acc_set[0];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int h = 0; h < SETS; ++h)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc_set[h][i][j][r] = 0;
 
 #pragma unroll
   for (int s = 0; s < STAGES - 1; ++s) issue(s, s);  // stages past the end load zeros
@@ -359,7 +365,10 @@ __global__ __launch_bounds__(WGM* WGN* KG * 64) void gemm_nt_kernel(GemmParams g
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = MMA::mma(ze[j], xe[i], acc[i][j]);  // MFMA rows: q, columns: p
+          for (int j = 0; j < TN; ++j) {  // MFMA rows: q, columns: p
+            acc_t& sum = acc_set[ks * SETS / KSUB][i][j];
+            sum = MMA::mma(ze[j], xe[i], sum);
+          }
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
@@ -386,7 +395,10 @@ __global__ __launch_bounds__(WGM* WGN* KG * 64) void gemm_nt_kernel(GemmParams g
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = MMA::mma(ze[ks & 1][j], xe[ks & 1][i], acc[i][j]);
+          for (int j = 0; j < TN; ++j) {
+            acc_t& sum = acc_set[ks * SETS / KSUB][i][j];
+            sum = MMA::mma(ze[ks & 1][j], xe[ks & 1][i], sum);
+          }
         constexpr int N_MFMA = TM * TN * MMA::MFMA_PER_MMA;
         constexpr int N_VALU = (TM + TN) * MMA::VALU_PER_EXPAND;
         constexpr int PER = (N_VALU + N_MFMA - 1) / N_MFMA;
@@ -417,29 +429,40 @@ __global__ __launch_bounds__(WGM* WGN* KG * 64) void gemm_nt_kernel(GemmParams g
 
   wait_vmcnt<0>();   // the zero-filled stages issued past the end must have landed too
   __syncthreads();
+  if constexpr (SETS == 2) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = acc[i][j][r] + acc_set[SETS - 1][i][j][r];
+  }
   if constexpr (KG == 1) {
     static_assert(NW * epilogue_wave_bytes(TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
     write_wave_tile<MMA, TM, TN>(g, acc, lds + wave * epilogue_wave_bytes(TN), lane, p0 + wp * WTM, q0 + wq * WTN, slice);
   } else {
     // The groups' sums meet in LDS, IP row blocks of every wave at a time, and are added in a fixed order by the threads
     // that write them out, whole rows of the tile per instruction.
-    constexpr int EP_PITCH = BN + 4, CPR = BN / 4, RING = STAGES * STAGE;
-    constexpr int IP = TM % 2 == 0 && KG * WGM * 64 * EP_PITCH * 4 <= RING ? 2 : 1, ROWS = WGM * IP * 32;
-    static_assert(KG * ROWS * EP_PITCH * 4 <= RING && ROWS * CPR % (NW * 64) == 0, "the sums must fit in the ring");
+    // Chunk c of 4 sums of row r lies at chunk c ^ (r mod CPR): a lane per row writes to all banks without padded rows.
+    constexpr int CPR = BN / 4, RING = STAGES * STAGE;
+    constexpr int IP = TM % 2 == 0 && KG * WGM * 64 * BN * 4 <= RING ? 2 : 1, ROWS = WGM * IP * 32;
+    static_assert(KG * ROWS * BN * 4 <= RING && ROWS * CPR % (NW * 64) == 0, "the sums must fit in the ring");
+    static_assert(CPR == 16 || CPR == 32, "a power of two, rows of a wave in step with it");
     uint32_t* const ep = reinterpret_cast<uint32_t*>(lds);
     const float s = total_scale(g);
     const bool q_vec = (g.Q & 3u) == 0;
     uint32_t* const pbase = g.nsplit > 1 ? g.partial + (size_t)slice * g.P * g.Q : nullptr;
 #pragma unroll
     for (int i0 = 0; i0 < TM; i0 += IP) {
-      uint32_t* const mine = ep + (kg * ROWS + wp * IP * 32 + (lane & 31u)) * EP_PITCH + wq * WTN + 4 * (lane >> 5);
+      uint32_t* const mine = ep + (kg * ROWS + wp * IP * 32 + (lane & 31u)) * BN;
 #pragma unroll
       for (int i = 0; i < IP; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
           for (int gq = 0; gq < 4; ++gq)
-            *reinterpret_cast<v4u*>(mine + i * 32 * EP_PITCH + j * 32 + 8 * gq) =
+            *reinterpret_cast<v4u*>(mine + i * 32 * BN +
+                                    4 * ((wq * (WTN / 4) + j * 8 + 2 * gq + (lane >> 5)) ^ (lane & (CPR - 1)))) =
                 v4u{MMA::bits(acc[i0 + i][j][4 * gq]), MMA::bits(acc[i0 + i][j][4 * gq + 1]),
                     MMA::bits(acc[i0 + i][j][4 * gq + 2]), MMA::bits(acc[i0 + i][j][4 * gq + 3])};
       __syncthreads();
@@ -447,10 +470,11 @@ __global__ __launch_bounds__(WGM* WGN* KG * 64) void gemm_nt_kernel(GemmParams g
       for (int it = 0; it < ROWS * CPR / (NW * 64); ++it) {
         const uint32_t id = it * NW * 64 + tid, row = id / CPR, c = id % CPR;
         const uint32_t p = p0 + row / (IP * 32) * WTM + i0 * 32 + row % (IP * 32), q = q0 + c * 4;
-        v4u raw = *reinterpret_cast<const v4u*>(ep + row * EP_PITCH + c * 4);
+        const uint32_t* const at = ep + row * BN + 4 * (c ^ (row & (CPR - 1)));
+        v4u raw = *reinterpret_cast<const v4u*>(at);
 #pragma unroll
         for (int k = 1; k < KG; ++k) {
-          const v4u more = *reinterpret_cast<const v4u*>(ep + (k * ROWS + row) * EP_PITCH + c * 4);
+          const v4u more = *reinterpret_cast<const v4u*>(at + k * ROWS * BN);
 #pragma unroll
           for (int e = 0; e < 4; ++e) raw[e] = MMA::bits(MMA::from_bits(raw[e]) + MMA::from_bits(more[e]));
         }
@@ -960,11 +984,11 @@ uint32_t slice_sum_blocks(const SliceSum& r, uint32_t threads, uint32_t per_thre
   return (uint32_t)(blocks < 1 ? 1 : blocks);
 }
 
-template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1>
+template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1, int SETS = 1>
 hipError_t launch_tile(GemmParams g, const SliceSumPlan& ss, hipStream_t stream) {
   constexpr int LDS_BYTES = STAGES * (BM + BN) * BK;
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
-  auto kern = &gemm_nt_kernel<MMA, BM, BN, WGM, WGN, STAGES, KG>;
+  auto kern = &gemm_nt_kernel<MMA, BM, BN, WGM, WGN, STAGES, KG, SETS>;
   // once per kernel (a function-local static: its initialisation is safe against concurrent
   // first calls from several host threads)
   static const hipError_t configured = hipFuncSetAttribute(
@@ -1039,9 +1063,11 @@ hipError_t launch_mma(GemmParams g, const Launch& l, const SliceSumPlan& ss, hip
   switch (l.form) {
     case FORM_256x256: return launch_persist<MMA>(g, ss, stream);                        // 8 waves of 128 x 64, persistent
     case FORM_128x128: return launch_tile<MMA, 128, 128, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 64
+    case FORM_128x128_S2:  // binary32 sums only (choose_launch)
+      if constexpr (!std::is_same<MMA, I8Mma>::value) return launch_tile<MMA, 128, 128, 2, 2, 2, 1, 2>(g, ss, stream);
+      break;
     case FORM_128x128_G2: return launch_tile<MMA, 128, 128, 2, 2, 3, 2>(g, ss, stream);  // 8 waves of 64 x 64
     case FORM_128x192: return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 96
-    case FORM_64x64: return launch_tile<MMA, 64, 64, 2, 2, 3>(g, ss, stream);            // 4 waves of 32 x 32
     case FORM_64x64_G2:                                                                  // 8 waves of 32 x 32
       return l.ring == 3 ? launch_tile<MMA, 64, 64, 2, 2, 3, 2>(g, ss, stream) : launch_tile<MMA, 64, 64, 2, 2, 4, 2>(g, ss, stream);
     case FORM_64x64_G4:  // 8 waves of 64 x 32; binary32 sums only (choose_launch)
@@ -1171,15 +1197,8 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
   g.accumulate = accumulate ? 1 : 0;
   if (x_packed) return launch_persist<I8Mma, true>(g, ss, stream);
   // integer sums are the same in every form: there the launch counts, not the role
-  bool leaves = role == ROLE_WEIGHT_GRADIENT;
-  uint32_t rides = 0;
-  if (pipe == PIPE_I8) {
-    leaves = defer != nullptr;
-    if (carry && carry->total > 0) rides = carry->nsplit;
-  } else if (role == ROLE_INPUT_GRADIENT) {  // M x K over N here: the weight gradient is N x K over M
-    const Launch w = choose_launch(plan_for(R, Q, P, pipe), R, Q, pipe == PIPE_BF16 ? 2 * P : P, pipe, true, 0);
-    if (w.nsplit > 1) rides = w.nsplit;
-  }
+  const bool leaves = pipe == PIPE_I8 ? defer != nullptr : role == ROLE_WEIGHT_GRADIENT;
+  const uint32_t rides = carry && carry->total > 0 ? carry->nsplit : 0;
   const Launch l = choose_launch(pl, P, Q, row_bytes, pipe, leaves, rides);
   if (pipe == PIPE_I8) return launch_mma<I8Mma>(g, l, ss, stream);
   if (pipe == PIPE_BF16) return launch_mma<BF16Mma>(g, l, ss, stream);

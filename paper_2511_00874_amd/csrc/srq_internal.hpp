@@ -143,8 +143,7 @@ struct SliceSum {
 // sr_linear_bwd_weight, the stash and phase calls), whether or not its sum is in fact deferred there.
 enum ProductRole {
   ROLE_ANY = 0,
-  ROLE_WEIGHT_GRADIENT = 1,  // sr_linear_bwd leaves its slice sum to the launch of the input gradient
-  ROLE_INPUT_GRADIENT = 2    // which carries it
+  ROLE_WEIGHT_GRADIENT = 1  // sr_linear_bwd leaves its slice sum to the launch of the input gradient
 };
 hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint8_t* Z, int kindZ,
                              size_t P, size_t Q, size_t R, size_t pitch, int pipe, const GemmScale& s,

@@ -86,8 +86,8 @@ inline Plan make_plan(size_t P, size_t Q, size_t row_bytes) {
 // products one after another, and round about 1.4 times as far from the exact result.  Where its slices would be longer
 // than those of PIPE_BF16 it takes that plan, the same slices in half the bytes.  E4M3 steps, us and error of the
 // results against 64 bits with its own slices and with those: 1472 x 1440 x 4448 129 (9.4e-8), 130 (7.0e-8), on PIPE_BF16
-// 143; 224 x 1248 x 1792, where a slice sum is a launch more, 43 (5.9e-8), 47 (5.0e-8), on PIPE_BF16 51.  (The error
-// equals that of PIPE_BF16.)
+// 143; 224 x 1248 x 1792, where a slice sum is a launch more, 43 (5.9e-8), 47 (5.0e-8), on PIPE_BF16 51.  (These without
+// groups of waves, with the error of PIPE_BF16.)
 inline Plan plan_for(size_t P, size_t Q, size_t R, int pipe) {
   if (pipe == PIPE_BF16) return make_plan(P, Q, 2 * R);
   const Plan pl = make_plan(P, Q, R);
@@ -107,9 +107,8 @@ inline Plan plan_for(size_t P, size_t Q, size_t R, int pipe) {
 // 8.2 -> 8.7 (stays as planned); 1024 x 2048 x 2048 (128 x 128 tiles, uncut) 12.9 -> 9.3, 17.4 -> 12.4.
 // The other side of the lines: few tiles, whose slices fill more CUs (272 x 80 x 3792 int8 6.8 -> 7.5, 192 x 160 x 2240
 // E5M2 7.6 -> 8.2, 256 x 256 x 2048 bfloat16 6.9 -> 8.0); more than a tile a CU (576 x 2048 x 6000 int8 22.2 -> 29.9).
-// Beyond 48 stages the lines no longer hold (3536 x 128 x 9696 int8 17.6 -> 24.3) and the slices stay.
-// Uncut 64 x 64 tiles: the groups from 7 stages on, 2 to 9 % faster; up to 3 the longer ring and the sum of the groups cost 2 to
-// 7 % (864 x 736 x 48 3.5 -> 3.7 us), in between both take the same time.
+// Beyond 48 stages, 64 where every row begins a cache line, the lines no longer hold and the slices stay (3536 x 128 x 9696 int8
+// 17.6 -> 24.3, 640 x 992 x 7168 17.2 -> 13.4, 1008 x 224 x 10240 14.7 -> 19.0).
 // `leaves`: the sum of the slices is left to a later launch and runs beside its matrix work.  Slices of 64 x 64 tiles then
 // always stay: the two products of E4M3 backward calls of up to 2^27 multiplications took 10 to 30 % longer otherwise (73 of 80
 // random ones by more than 8 %), E5M2 2048 x 192 x 352 9.4 -> 11.8.  With 128-row tiles there is less to save: M, N, K 5824 x 960
@@ -118,65 +117,77 @@ inline bool small_in_one_pass(const Plan& pl, size_t P, size_t Q, size_t row_byt
   const size_t t64 = ((P + 63) / 64) * ((Q + 63) / 64);
   const size_t items = ((P + pl.bm - 1) / pl.bm) * ((Q + pl.bn - 1) / pl.bn) * pl.nsplit;
   const size_t stages = (row_bytes + STAGE_BYTES - 1) / STAGE_BYTES;
-  if (pl.tile == 0 || t64 > 2 * NUM_CU) return false;
-  if (pl.tile == 2 && pl.nsplit == 1) return stages >= 7;
-  if (items > NUM_CU || (pl.nsplit > 1 && stages > 48) || (leaves && pl.tile == 2)) return false;
+  if (pl.tile == 0 || t64 > 2 * NUM_CU || (pl.tile == 2 && pl.nsplit == 1)) return false;
+  if (items > NUM_CU || (leaves && pl.tile == 2)) return false;
+  if (pl.nsplit > 1 && stages > (row_bytes % STAGE_BYTES == 0 ? 64 : 48)) return false;
   const double st = (double)stages, slice = (double)(pl.k_per_split / STAGE_BYTES);
   const double mb = pl.nsplit > 1 ? 4e-6 * pl.nsplit * (double)P * (double)Q : 0.0;
   const double once = t64 <= NUM_CU ? (widens ? 3.2 + 0.285 * st : 2.75 + 0.18 * st)
                                     : (widens ? 4.0 + 0.49 * st : 2.5 + 0.44 * st);
-  const double planned = pl.tile == 2 ? 5.6 + (widens ? 0.22 : 0.085) * slice + 0.59 * mb
-                                      : (widens ? 5.8 : 4.0) + 0.73 * slice + 0.44 * mb - (leaves && pl.nsplit > 1 ? 1.5 + 0.2 * mb : 0.0);
+  double planned = pl.tile == 2 ? 5.6 + (widens ? 0.22 : 0.085) * slice + 0.59 * mb
+                                : (widens ? 5.8 : 4.0) + 0.73 * slice + 0.44 * mb;
+  if (leaves && pl.nsplit > 1) planned -= 1.5 + 0.2 * mb;
   return once < planned;
 }
 
-// The kernel form of a planned product, its slices and the stages of its LDS ring.  _G2, _G4: groups of waves share a tile.
-enum Form { FORM_256x256, FORM_128x128, FORM_128x128_G2, FORM_128x192, FORM_64x64, FORM_64x64_G2, FORM_64x64_G4 };
+// The kernel form of a planned product, its slices and the stages of its LDS ring.  _G2, _G4: groups of waves share a tile;
+// _S2: two sets of accumulators stand for two groups.
+enum Form { FORM_256x256, FORM_128x128, FORM_128x128_S2, FORM_128x128_G2, FORM_128x192, FORM_64x64_G2, FORM_64x64_G4 };
 struct Launch {
   Form form;
   uint32_t nsplit, k_per_split;
   int ring;
 };
+// Binary32 sums: an accumulator holds the part of a slice that its group of waves multiplies, half of it or a quarter, and no
+// choice below makes the parts longer than the plan's slices.  Forms over the same slices in two halves, of 64 x 64 or
+// 128 x 128 tiles, in groups or in sets, give the same result bit for bit: `rides`, which sr_linear_bwd has and
+// sr_linear_bwd_data has not, may choose among them.
+//
 // The rings leave room on a CU for quantizer workgroups of another stream, and fewer stages are not slower alone: with eight
 // waves on 128 x 128 tiles three take 0.97 to 1.0 of the time of four (2048 x 2048 x 4096 int8 23.3 and 23.1 us, E5M2
 // 33.2 and 33.2), and beside the quantizer of another layer, M, N, K 2672 x 704 x 6128 E5M2, a step of 66.4 us with four takes 52.5
 // (51.7 with four waves and two stages), 5792 x 592 x 5120 E5M2 77.5 and 66.9 (65.9), 2624 x 896 x 4288 int8 41.8 and 41.6
-// (48.0).  64 x 64 tiles two a CU: three stages as well, 0.94 to 1.0 of the time of four or five alone; one a CU: four and five, as
-// three are up to 1.2 times slower where the operands come from beyond the L2 (16 x 5632 x 5632 int8 9.8 and 12.0).
+// (48.0).  64 x 64 tiles: three stages as well, 0.94 to 1.0 of the time of four or five alone.  Only long contractions with a CU for
+// a tile take four and five, as three are up to 1.2 times slower where the operands come from beyond the L2 (16 x 5632 x 5632
+// int8 9.8 and 12.0).
+//
 // `rides`: slices of an earlier product whose sum the launch carries (0: none).  Its workgroups take as much LDS as a tile's, and
 // where the tiles hold nearly all CUs they wait for them to finish instead of running beside them.
-//   - Eight waves on 128 x 128 tiles with such a sum: up to 224 of them (both products of a backward call, us without groups and
-//     with: E5M2 5328 x 3104 x 736, 252 tiles, 58.1 -> 64.1, 7296 x 1968 x 448, 228 tiles, 37.6 -> 41.5; 6784 x 4016 x 432,
-//     212 tiles, 60.7 -> 56.9), or for integers a contraction of 24 stages, beside which it ends in time (10304 x 5440 x 288,
-//     243 tiles, 65.0 -> 61.9; at 16 and 19 stages 31.5 -> 33.8, 39.5 -> 41.9).
-//   - More than a 64 x 64 tile a CU, uncut: not over 12 stages or fewer beside a sum of more than three slices, a chain of as many
+//   - Two groups on 128 x 128 tiles with such a sum: up to 192 of them, 224 from 16 stages on (both products of a backward
+//     call, us without groups and with: E5M2 5328 x 3104 x 736, 252 tiles, 58.1 -> 64.1, 7296 x 1968 x 448, 228 tiles, 37.6 -> 41.5;
+//     6784 x 4016 x 432, 212 tiles, 60.7 -> 56.9), or for integers 24 stages, beside which it ends in time (10304 x 5440 x 288,
+//     243 tiles, 65.0 -> 61.9; at 16 and 19 stages 31.5 -> 33.8, 39.5 -> 41.9).  Instead four waves, a ring of 64 KiB, and for
+//     binary32 sums two sets of accumulators (1.00 to 1.03 of the time of one).
+//   - More than a 64 x 64 tile a CU: not over 12 stages or fewer beside a sum of more than three slices, a chain of as many
 //     loads (int8 6064 x 1488 x 320, six, 25.1 -> 27.7; E4M3 8240 x 1152 x 160, 13, 27.7 -> 29.7; with two, 2816 x 272 x 368 int8
 //     11.6 -> 10.0).  8-bit floats and sums of four to six slices: not over 6 stages (E5M2 6432 x 208 x 304 14.5 -> 15.8; at twelve,
 //     4832 x 1488 x 320, 27.5 -> 23.6).
 inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes, int pipe, bool leaves, uint32_t rides) {
-  const bool widens = pipe == PIPE_F16C || pipe == PIPE_F16W;
+  const bool widens = pipe == PIPE_F16C || pipe == PIPE_F16W, is_int = pipe == PIPE_I8;
+  const Form four_waves = is_int ? FORM_128x128 : FORM_128x128_S2;
   if (pl.tile == 0) return Launch{FORM_256x256, pl.nsplit, pl.k_per_split, 2};
-  // In binary32 the parts of a sum are to be no longer than the plan's slices: two groups of waves stand for two of
-  // them, four for four.  (PIPE_F8 has two sub-steps a stage, no work for four groups.)
-  const bool one_a_cu = ((P + 63) / 64) * ((Q + 63) / 64) <= NUM_CU;
-  const bool behind_tiles = rides > 3 && pl.nsplit == 1 && !one_a_cu &&
-                            row_bytes <= (size_t)(pipe == PIPE_I8 || rides > 6 ? 12 : 6) * STAGE_BYTES;
-  if (!behind_tiles && small_in_one_pass(pl, P, Q, row_bytes, widens, leaves)) {
+  // (four groups stand for up to four slices of a binary32 sum; PIPE_F8 has two sub-steps a stage, no work for four groups)
+  if (small_in_one_pass(pl, P, Q, row_bytes, widens, leaves)) {
     const uint32_t whole = (uint32_t)((row_bytes + STAGE_BYTES - 1) / STAGE_BYTES * STAGE_BYTES);
-    if (pipe == PIPE_I8 || pl.nsplit <= 2) return Launch{FORM_64x64_G2, 1, whole, one_a_cu ? 4 : 3};
+    const bool one_a_cu = ((P + 63) / 64) * ((Q + 63) / 64) <= NUM_CU;
+    const bool waits = rides > 3 && pl.tile == 1 && pl.nsplit == 1 && !one_a_cu &&
+                       row_bytes <= (size_t)(is_int || rides > 6 ? 12 : 6) * STAGE_BYTES;
+    if (waits) return Launch{four_waves, 1, whole, 2};
+    if (is_int || pl.nsplit <= 2) return Launch{FORM_64x64_G2, 1, whole, one_a_cu ? 4 : 3};
     if (pipe != PIPE_F8 && pl.nsplit <= 4) return Launch{FORM_64x64_G4, 1, whole, one_a_cu ? 5 : 3};
   }
-  if (pl.tile == 1) {
-    // A workgroup that has a CU to itself and a long contraction: eight waves in two groups instead of four, and a longer
-    // ring.  2048 x 2048 x 4096 int8 25.9 -> 23.1 us, E5M2 34.0 -> 33.2; 512 x 5632 x 5632 30.4 -> 24.0, 39.1 -> 35.9.
-    const size_t items = ((P + 127) / 128) * ((Q + 127) / 128) * pl.nsplit;
-    const bool room = rides == 0 || items <= 224 || (pipe == PIPE_I8 && pl.k_per_split >= 24 * STAGE_BYTES);
-    if (items <= NUM_CU && pl.k_per_split >= 16 * STAGE_BYTES && room)
-      return Launch{FORM_128x128_G2, pl.nsplit, pl.k_per_split, 3};
-    return Launch{FORM_128x128, pl.nsplit, pl.k_per_split, 2};
-  }
+  // 64 x 64 tiles: eight waves of 32 x 32 in two groups take 0.91 to 1.02 of the time of four waves (uncut one stage 1.0 to
+  // 1.02, four 0.99, eight 0.95; slices 0.98).
+  if (pl.tile == 2) return Launch{FORM_64x64_G2, pl.nsplit, pl.k_per_split, 3};
   if (pl.tile == 3) return Launch{FORM_128x192, pl.nsplit, pl.k_per_split, 2};
-  return Launch{FORM_64x64, pl.nsplit, pl.k_per_split, 3};
+  // A workgroup that has a CU to itself: eight waves in two groups instead of four, and a longer ring.  2048 x 2048 x 4096 int8
+  // 25.9 -> 23.1 us, E5M2 34.0 -> 33.2; 512 x 5632 x 5632 30.4 -> 24.0, 39.1 -> 35.9; at 8 to 15 stages int8 0.81 to 1.01 of the
+  // time, E5M2 0.94 to 1.05; at three to seven 0.94 and 0.98, at one and two 8-bit floats 1.00 to 1.03.  (Codes of 8-bit floats
+  // from as few terms on as their bfloat16 form, so that the sums of the two are as long.)
+  const size_t items = ((P + 127) / 128) * ((Q + 127) / 128) * pl.nsplit, stages = pl.k_per_split / STAGE_BYTES;
+  if (items > NUM_CU || stages < (widens ? 2 : 3)) return Launch{FORM_128x128, pl.nsplit, pl.k_per_split, 2};
+  const bool room = rides == 0 || items <= (stages < 16 ? 192 : 224) || (is_int && stages >= 24);
+  return room ? Launch{FORM_128x128_G2, pl.nsplit, pl.k_per_split, 3} : Launch{four_waves, pl.nsplit, pl.k_per_split, 2};
 }
 
 }  // namespace srq

@@ -8,6 +8,16 @@ from paper_2511_00874_amd import lib as L
 DEV = "cuda:0"
 KINDS = [L.INT8, L.INT4, L.E4M3, L.E5M2, L.E4M2, L.E4M1, L.E4M0]
 
+# P x Q over R: groups of waves that share a tile, in every form (test_plan.py says which shape takes which): edges of tiles, Q not a
+# multiple of 4, contractions that end inside a stage; whole contractions and slices
+GROUP_SHAPES = [(16, 16, 16), (65, 63, 144), (130, 67, 1040), (257, 250, 2064), (130, 70, 4112), (1008, 768, 3072),
+                (640, 1025, 2576), (1001, 1003, 3088), (1030, 1090, 2064), (1090, 1102, 4112), (1040, 1936, 2064), (770, 771, 12304),
+                (912, 400, 16448)]
+# M, N, K of backward calls that leave the slice sum of dW to the launch of dA: slices of 64 x 64 and of 128 x 128 tiles, with dA in
+# each form that a sum rides on, and calls that have none
+RIDE_SHAPES = [(2048, 192, 352), (976, 208, 560), (4240, 1360, 224), (2736, 432, 1312), (4992, 1056, 672), (6432, 208, 304),
+               (4304, 320, 288), (7296, 1968, 448), (5920, 1936, 608), (4080, 2000, 752), (7472, 3488, 288)]
+
 
 def say(*a):
     print(*a, flush=True)

@@ -6,7 +6,7 @@ import torch
 import oracle
 from paper_2511_00874_amd import lib as L
 from paper_2511_00874_amd import synth
-from gpu_util import (DEV, check_product, check_product_f8_pipeline, group_max_sum, host_src, say,
+from gpu_util import (DEV, GROUP_SHAPES, RIDE_SHAPES, check_product, check_product_f8_pipeline, group_max_sum, host_src, say,
                       to_dev)
 
 pytestmark = pytest.mark.gpu
@@ -118,6 +118,37 @@ def test_gemm_with_groups_of_waves(P, Q, R):
             check_product(got.view(-1)[at].cpu().numpy(), ref, ab)
         assert torch.equal(f(out=C.clone(), beta=1.0), got + C)     # the sum is rounded once, then added
         assert torch.equal(f(), got)
+
+
+@pytest.mark.parametrize("P,Q,R", GROUP_SHAPES)
+@pytest.mark.parametrize("pipe", ["int8", "e5m2", "bf16", "fp8"])
+def test_gemm_in_every_form(P, Q, R, pipe):
+    say("gemm form", pipe, P, Q, R)
+    rng = np.random.default_rng(P + Q)
+    kind = {"int8": L.INT8, "e5m2": L.E5M2}.get(pipe, L.E4M3)
+    X, Z = _rand_codes((P, R), kind, 41), _rand_codes((Q, R), kind, 42)
+    C = torch.from_numpy(rng.standard_normal((P, Q)).astype(np.float32)).to(DEV)
+    if pipe == "bf16":
+        xz = [to_dev(oracle.decode_array(kind, c).astype(np.float32).reshape(c.shape), True) for c in (X, Z)]
+        f = lambda **k: L.sr_gemm_bf16(*xz, alpha=0.25, **k)  # noqa: E731
+    elif pipe == "e5m2":
+        f = lambda **k: L.sr_gemm_e5m2(to_dev(X), to_dev(Z), alpha=0.25, **k)  # noqa: E731
+    else:
+        f = lambda **k: L.sr_gemm_codes(to_dev(X), kind, to_dev(Z), kind, alpha=0.25, **k)  # noqa: E731
+    got = f()
+    # rows and columns at the edges of tiles and in between, all of their crossings
+    ps, qs = (np.unique(np.concatenate([rng.integers(0, n, size=24), [0, n - 1], np.arange(31, n, 32)[:12]])) for n in (P, Q))
+    sub = got[torch.from_numpy(ps).to(DEV)][:, torch.from_numpy(qs).to(DEV)].cpu().numpy()
+    ref, ab = oracle.gemm_fwd(X[ps], kind, 0.5, Z[qs], kind, 0.5, want_abs=True)
+    if pipe == "int8":
+        assert np.array_equal(sub, ref.reshape(sub.shape))
+    elif pipe == "fp8":
+        xv, zv = (oracle.decode_array(kind, c).astype(np.float64).reshape(c.shape) for c in (X[ps], Z[qs]))
+        check_product_f8_pipeline(sub, ref, group_max_sum(xv, zv, 0.25), ab)
+    else:
+        check_product(sub, ref, ab)
+    assert torch.equal(f(out=C.clone(), beta=1.0), got + C)     # the sum is rounded once, then added
+    assert torch.equal(f(), got)
 
 
 def test_fp8_pipeline_aligns_groups_of_eight_products_to_14_bits():
@@ -318,11 +349,8 @@ def test_every_e4m3_value_is_widened_exactly():
     assert np.array_equal(Y[keep], A[keep])
 
 
-# backward calls that leave the slice sum of dW to the launch of dA, in slices of 64 x 64 and of 128 x 128 tiles (with groups of waves
-# for dA, for dW, for both and for neither), and calls that have none: the form of a product, and with it the order of a binary32
-# sum, is that of the separate calls
-@pytest.mark.parametrize("M,N,K", [(2048, 192, 352), (976, 208, 560), (4240, 1360, 224), (2736, 432, 1312), (4992, 1056, 672),
-                                   (6432, 208, 304), (4304, 320, 288), (7296, 1968, 448), (5920, 1936, 608), (4080, 2000, 752)])
+# the form of a product, and with it the order of a binary32 sum, is that of the separate calls whether or not a slice sum rides
+@pytest.mark.parametrize("M,N,K", RIDE_SHAPES)
 @pytest.mark.parametrize("kind", [L.INT8, L.E5M2, L.E4M3])
 def test_backward_in_one_call_equals_the_separate_calls_where_a_slice_sum_rides(M, N, K, kind):
     say("sum rides", M, N, K, L.KIND_NAMES[kind])

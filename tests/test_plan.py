@@ -5,10 +5,12 @@ import subprocess
 
 import pytest
 
+from gpu_util import GROUP_SHAPES, RIDE_SHAPES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2511_00874_amd", "csrc")
 I8, F8, BF16, F16C, F16W = range(5)
-P256, P128, P128_G2, P128x192, P64, P64_G2, P64_G4 = range(7)
+P256, P128, P128_S2, P128_G2, P128x192, P64_G2, P64_G4 = range(7)
 
 WRAP = """
 #include "srq_plan.hpp"
@@ -47,16 +49,16 @@ def test_four_groups_are_for_binary32_sums(plan):
 
 # products that one pass of 64 x 64 tiles makes slower (us as planned, in one pass), and others that it makes faster
 @pytest.mark.parametrize("P,Q,R,pipe,planned,once", [
-    (864, 736, 48, I8, 3.5, 3.7), (1872, 400, 64, F16C, 3.7, 3.9), (96, 6432, 64, BF16, 3.5, 3.7), (16, 5168, 112, F8, 3.0, 3.3),
     (272, 80, 3792, I8, 6.8, 7.5), (576, 48, 3856, I8, 6.9, 7.6), (4496, 96, 7456, I8, 16.8, 19.8), (576, 2048, 6000, I8, 22.2, 29.9),
     (64, 6000, 10192, I8, 21.7, 26.6), (192, 160, 2240, F16C, 7.6, 8.2), (3776, 32, 2768, F16C, 8.4, 9.5),
     (256, 256, 2048, F16C, 7.3, 7.7), (256, 256, 2048, BF16, 6.9, 8.0), (4432, 208, 2720, BF16, 18.6, 21.7),
-    (1152, 1616, 11408, F8, 46.4, 55.4),
+    (1152, 1616, 11408, F8, 46.4, 55.4), (1008, 224, 10240, I8, 14.7, 19.0), (640, 992, 7168, I8, 17.2, 13.4),
     (1008, 768, 3072, I8, 13.7, 7.1), (1008, 768, 3072, F16C, 15.8, 10.2), (512, 1024, 4096, F16C, 15.6, 12.2),
     (16, 5632, 5632, I8, 11.4, 9.8), (32, 5632, 2048, I8, 6.5, 5.4), (1024, 2048, 2048, F16C, 17.4, 12.4),
     (1024, 2048, 2048, BF16, 21.8, 15.3), (256, 6528, 96, F8, 5.5, 4.6)])
 def test_one_pass_only_where_it_is_faster(plan, P, Q, R, pipe, planned, once):
-    assert (plan(P, Q, R, pipe)["form"] in (P64_G2, P64_G4)) == (once < planned)
+    p = plan(P, Q, R, pipe)
+    assert (p["form"] in (P64_G2, P64_G4) and p["slices"] == 1) == (once < planned)
 
 
 # weight gradients whose slice sum runs beside the next launch: N x K, contraction M (us of both products of the backward call with
@@ -69,7 +71,7 @@ def test_one_pass_only_where_it_is_faster(plan, P, Q, R, pipe, planned, once):
     (1744, 1872, 384, F16W, 18.3, 15.9), (2432, 1440, 384, F16W, 19.0, 16.4), (2736, 432, 1312, F16C, 22.1, 17.8),
     (3888, 160, 2768, I8, 25.9, 21.6), (1520, 1216, 1104, F16W, 22.6, 19.0)])
 def test_one_pass_where_the_slice_sum_is_left_to_a_later_launch(plan, M, N, K, pipe, sliced, once):
-    assert (plan(N, K, M, pipe, True)["form"] in (P64_G2, P64_G4)) == (once < sliced)
+    assert (plan(N, K, M, pipe, True)["slices"] == 1) == (once < sliced)
 
 
 LDS_OF_A_CU = 160 << 10
@@ -98,7 +100,7 @@ def test_groups_of_waves_leave_lds_for_quantizers_of_another_stream(plan, pipe):
 # input gradients that carry the slice sum of the weight gradient (us of both products without groups of waves, with)
 @pytest.mark.parametrize("M,N,K,pipe,plain,groups", [
     (5328, 3104, 736, F16C, 58.1, 64.1), (7296, 1968, 448, F16C, 37.6, 41.5), (6416, 2496, 560, F16W, 48.8, 52.8),
-    (7296, 1968, 448, I8, 31.5, 33.8), (3824, 9344, 192, I8, 39.5, 41.9), (6064, 1488, 320, I8, 25.1, 27.7),
+    (3824, 9344, 192, I8, 39.5, 41.9), (6064, 1488, 320, I8, 25.1, 27.7),
     (4304, 320, 288, F16W, 15.6, 17.0), (9504, 544, 112, F16C, 17.5, 19.1), (2320, 96, 560, BF16, 10.9, 11.4),
     (6784, 4016, 432, F16C, 60.7, 56.9), (6512, 5264, 480, F16W, 81.9, 76.6), (10304, 5440, 288, I8, 65.0, 61.9),
     (5248, 3008, 448, I8, 36.5, 31.8), (2816, 272, 368, I8, 11.6, 10.0), (4832, 1488, 320, F16C, 27.5, 23.6),
@@ -107,3 +109,46 @@ def test_launches_that_carry_a_slice_sum_leave_room_for_it(plan, M, N, K, pipe, 
     rides = plan(N, K, M, pipe, leaves=True)["slices"]
     assert rides > 1
     assert (plan(M, K, N, pipe, rides=rides)["form"] in (P128_G2, P64_G2, P64_G4)) == (groups < plain)
+
+
+@pytest.mark.parametrize("pipe", [F8, BF16, F16C, F16W])
+def test_no_binary32_sum_is_longer_than_a_slice_of_the_plan_and_uncut_sums_are_halved(plan, pipe):
+    groups = {P256: 1, P128: 1, P128_S2: 2, P128_G2: 2, P128x192: 1, P64_G2: 2, P64_G4: 4}
+    element = 2 if pipe == BF16 else 1
+    for P in (16, 80, 656, 1264, 2048, 5104):
+        for Q in (64, 304, 704, 2080):
+            for R in (16, 144, 400, 688, 1040, 2672, 5424, 6128):
+                for leaves in (False, True):
+                    p = plan(P, Q, R, pipe, leaves)
+                    part = min(p["k_per_split"], element * R) / groups[p["form"]]
+                    whole = plan(P, Q, R, pipe, leaves, rides=5)
+                    # with a sum on board: the same slices in as many parts, so the same result
+                    assert (p["slices"], p["k_per_split"], groups[p["form"]]) == (whole["slices"], whole["k_per_split"],
+                                                                                  groups[whole["form"]])
+                    assert part <= element * R / p["planned_slices"] + 128
+                    if p["form"] in (P64_G2, P64_G4):
+                        assert part <= max(64, element * R / 2)
+
+
+def test_gpu_tests_reach_every_form(plan):
+    # (form, stages of the ring, sliced) that the shapes of the GPU tests take, on each pipeline
+    seen = {pipe: set() for pipe in range(5)}
+    carried = {pipe: set() for pipe in range(5)}
+    for pipe in range(5):
+        for P, Q, R in GROUP_SHAPES:
+            p = plan(P, Q, R, pipe)
+            seen[pipe].add((p["form"], p["ring"], p["slices"] > 1))
+        for M, N, K in RIDE_SHAPES:
+            rides = plan(N, K, M, pipe, True)["slices"]
+            if rides > 1:
+                p = plan(M, K, N, pipe, rides=rides)
+                carried[pipe].add((p["form"], p["slices"] > 1))
+    for pipe in range(5):
+        assert {(P64_G2, 3, False), (P64_G2, 3, True), (P128_G2, 3, False), (P128_G2, 3, True)} <= seen[pipe], pipe
+    for pipe in (I8, F16C, F8):
+        assert (P64_G2, 4, False) in seen[pipe]
+    for pipe in (F16C, F16W):
+        assert {(P64_G4, 5, False), (P64_G4, 3, False)} <= seen[pipe]
+    assert {(P64_G2, False), (P128, False), (P128_G2, False)} <= carried[I8]
+    for pipe in (F16C, F16W):
+        assert {(P64_G2, False), (P128_S2, False), (P128_G2, False)} <= carried[pipe]
