@@ -110,7 +110,7 @@ typedef struct {
  * value is a binary16 number), on the f16 matrix pipeline.  For a smaller product of any other
  * pair the quantizer writes each grid value as a bfloat16 number and the product runs on the bf16
  * matrix pipeline.  The two pipelines group the contraction differently, so their binary32 sums
- * can differ in the last bits; neither is less precise.
+ * can differ in the last bits; their errors are of the same size.
  * With SRQ_FLAG_F8_PIPELINE set on BOTH operands' quantizers the one-byte codes go to the fp8
  * matrix pipeline at twice the rate.  That hardware adds the products of each run of 8
  * consecutive contraction indices after aligning them to the largest one and truncating to 14

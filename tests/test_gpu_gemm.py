@@ -370,8 +370,10 @@ def test_backward_in_one_call_equals_the_separate_calls_where_a_slice_sum_rides(
 
 
 # weight gradients whose bfloat16 form cuts the contraction into more slices than the code form would by its own
-# count, on each tile shape, and one whose slices end inside a stage of 128 codes
-@pytest.mark.parametrize("M,N,K", [(2064, 1296, 560), (2064, 1488, 1296), (1600, 1152, 176), (1600, 1296, 560)])
+# count, on each tile shape, and one whose slices end inside a stage of 128 codes; and two that reach 16 stages of 128 bytes in the
+# bfloat16 form only
+@pytest.mark.parametrize("M,N,K", [(2064, 1296, 560), (2064, 1488, 1296), (1600, 1152, 176), (1600, 1296, 560),
+                                   (1536, 1776, 2224), (3968, 2144, 544)])
 @pytest.mark.parametrize("pair", [(L.E4M3, L.E4M3), (L.E5M2, L.E4M3)])
 def test_code_products_are_no_less_precise_than_the_bfloat16_form(M, N, K, pair):
     # grid values and scale 1: the quantizers pass them through.  Both products are exact and both sum in
