@@ -235,8 +235,8 @@ int sr_linear_bwd_phase(float* dA, float* dW, const void* dY, int dtypedY, const
  * W in their source precision, applies Eq. 1 (the thresholds of an element are fixed by its
  * index, so the codes are the ones sr_quantize gives) and multiplies from LDS; no quantized
  * operand is written to memory and no workspace is needed.  An element is rounded again by every
- * output tile that uses it, so the call is meant for outputs of a few tiles (small M and N);
- * on large shapes it is many times slower than sr_linear_fwd and exists there to be measured.
+ * output tile that uses it, so the call is meant for short contractions (K <= 128) and at most some 256 tiles of
+ * 64 x 64; on large shapes it is many times slower than sr_linear_fwd and exists there to be measured.
  * Formats: qA_fwd and qW_fwd both integer (results equal to sr_linear_fwd bit for bit: the int32
  * sums are exact), or both SRQ_E5M2 (exact products, binary32 sums; SRQ_FLAG_F8_PIPELINE is
  * ignored); any other pair, and SRQ_NONE, is SRQ_ERR_UNSUPPORTED.  M, N, K multiples of 16.  Y must not share

@@ -246,9 +246,10 @@ int run_linear(float* out, const void* x, int dtx, size_t xr, size_t xc, int x_t
   hipStream_t s = static_cast<hipStream_t>(stream);
   // A short contraction and few 64 x 64 tiles: rounding inside the product (no codes in memory, one launch instead of
   // two) although an element is rounded once for every tile that uses it.  One stage (R <= 128): up to a tile a CU --
-  // 64 x 128 x 128 5.0 against 6.4 us with two launches, 512 x 512 x 128 5.3 against 6.8, 1024 x 1024 x 128 6.2 against
-  // 7.4, 4096 x 256 x 128 6.6 against 7.5.  Two stages: only where the call is as long as its launches -- 128 x 128 x 256
-  // 7.2 against 6.8 us on the GPU, and a launch less to wait for; 128 x 128 x 384 9.5 against 7.3.  Integer pairs
+  // 64 x 128 x 128 5.3 against 6.6 us with two launches, 512 x 512 x 128 5.6 against 6.9, 1024 x 1024 x 128 6.4 against
+  // 7.6, 16384 x 64 x 128 6.4 against 8.2.  Two stages: only where the call is as long as its launches -- 128 x 128 x 256
+  // 7.6 against 7.0 us on the GPU, but 7.4 against 9.8 a call from the host in a row and 21.0 against 21.4 for one that is waited
+  // for; 256 x 256 x 144 8.9 against 6.9, 128 x 128 x 384 9.9 against 7.5 (9.6 against 9.7 in a row, 23.5 against 21.9).  Integer pairs
   // only: their results are the same bit for bit in both forms.  Not where the result lies over a source: a workgroup
   // would write elements that another has yet to read, while the two launches read all of the sources first.
   const size_t tiles = ((P + 63) / 64) * ((Q + 63) / 64);

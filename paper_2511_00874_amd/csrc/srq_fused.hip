@@ -10,10 +10,10 @@
 // The price is that an element is rounded again by every tile that uses it: A once per tile
 // column, W once per tile row.  One Philox block and eight passes through Eq. 1 are about 200
 // vector operations for eight elements, against the 32 x 32 x 32 MFMA those eight codes share
-// with 2040 others, so the kernel is bound by the vector ALU as soon as the output has more than
-// a few tiles.  It pays where the tensors are used once or twice and the contraction is short -- an
-// output of a few tiles, where it also saves a launch -- and that is where sr_linear_fwd selects
-// it; sr_linear_fwd_fused runs it on any shape so that the crossover can be measured.
+// with 2040 others, so the kernel is bound by the vector ALU.  What it saves is a launch and the codes'
+// way through memory.  That is worth more as long as the tiles are at most one a CU, which round side by side, and the
+// contraction is one stage (two where the whole call is as long as its launches): sr_linear_fwd
+// selects it there, sr_linear_fwd_fused runs it on any shape so that the crossover can be measured.
 #include "srq_device.hpp"
 #include "srq_internal.hpp"
 #include "srq_mma.hpp"
