@@ -351,22 +351,28 @@ def test_every_e4m3_value_is_widened_exactly():
 
 # the form of a product, and with it the order of a binary32 sum, is that of the separate calls whether or not a slice sum rides
 @pytest.mark.parametrize("M,N,K", RIDE_SHAPES)
-@pytest.mark.parametrize("kind", [L.INT8, L.E5M2, L.E4M3])
-def test_backward_in_one_call_equals_the_separate_calls_where_a_slice_sum_rides(M, N, K, kind):
-    say("sum rides", M, N, K, L.KIND_NAMES[kind])
+@pytest.mark.parametrize("kind,flags", [(L.INT8, 0), (L.E5M2, 0), (L.E4M3, 0), (L.E4M3, L.FLAG_F8_PIPELINE)])
+def test_backward_in_one_call_equals_the_separate_calls_where_a_slice_sum_rides(M, N, K, kind, flags):
+    say("sum rides", M, N, K, L.KIND_NAMES[kind], flags)
     A, W, dY = synth.single_layer(M, N, K, 23, std_dy=1e-3)
     A, W, dY = to_dev(A), to_dev(W, True), to_dev(dY)
-    q = [L.Quant(kind, oracle.absmax_scale(host_src(t), kind), 4, i << 24) for i, t in enumerate((dY, W, A))]
+    q = [L.Quant(kind, oracle.absmax_scale(host_src(t), kind), 4, i << 24, flags=flags) for i, t in enumerate((dY, W, A))]
     dA, dW = L.sr_linear_bwd(dY, W, A, *q)
     assert torch.equal(dA, L.sr_linear_bwd_data(dY, W, q[0], q[1]))
     assert torch.equal(dW, L.sr_linear_bwd_weight(dY, A, q[0], q[2]))
+    qf = [L.Quant(L.INT8, oracle.absmax_scale(host_src(t), L.INT8), 5) for t in (A, W)]
+    _, stash = L.sr_linear_fwd_stash(A, W, *qf, q[2], q[1])
     dW2 = dW.clone()
-    dA2, _ = L.sr_linear_bwd(dY, W, A, *q, out_dW=dW2, beta=1.0)
+    dA2, _ = L.sr_linear_bwd_stashed(dY, stash, K, *q, out_dW=dW2, beta=1.0)
     assert torch.equal(dA2, dA) and torch.equal(dW2, dW + dW)
-    idx = np.random.default_rng(5).integers(0, N * K, size=2000).astype(np.uint64)
+    if flags:
+        return    # its own bar: test_gemm_in_every_form
     oq = [oracle.Quant(kind, qq.scale, 4, i << 24) for i, qq in enumerate(q)]
-    ref, ab = oracle.linear_bwd_weight(host_src(dY), host_src(A), oq[0], oq[2], want_abs=True, at=idx)
-    check_product(dW.view(-1).cpu().numpy()[idx.astype(np.int64)], ref, ab)
+    for got, f, (x, qx), (z, qz) in ((dW, oracle.linear_bwd_weight, (dY, oq[0]), (A, oq[2])),
+                                     (dA, oracle.linear_bwd_data, (dY, oq[0]), (W, oq[1]))):
+        idx = np.random.default_rng(5).integers(0, got.numel(), size=2000).astype(np.uint64)
+        ref, ab = f(host_src(x), host_src(z), qx, qz, want_abs=True, at=idx)
+        check_product(got.view(-1).cpu().numpy()[idx.astype(np.int64)], ref, ab)
 
 
 # weight gradients whose bfloat16 form cuts the contraction into more slices than the code form would by its own
