@@ -147,9 +147,12 @@ struct Launch {
 // waves on 128 x 128 tiles three take 0.97 to 1.0 of the time of four (2048 x 2048 x 4096 int8 23.3 and 23.1 us, E5M2
 // 33.2 and 33.2), and beside the quantizer of another layer, M, N, K 2672 x 704 x 6128 E5M2, a step of 66.4 us with four takes 52.5
 // (51.7 with four waves and two stages), 5792 x 592 x 5120 E5M2 77.5 and 66.9 (65.9), 2624 x 896 x 4288 int8 41.8 and 41.6
-// (48.0).  64 x 64 tiles: three stages as well, 0.94 to 1.0 of the time of four or five alone.  Only long contractions with a CU for
+// (48.0).  64 x 64 tiles: three stages as well, 0.94 to 1.0 of the time of four or five alone.  Only longer contractions with a CU for
 // a tile take four and five, as three are up to 1.2 times slower where the operands come from beyond the L2 (16 x 5632 x 5632
-// int8 9.8 and 12.0).
+// int8 9.8 and 12.0): in one pass, and from eight stages on, except where the codes are widened, which covers the loads (quantizer
+// and product, us, with three and four, at 8, 10, 11 and 16 stages: int8 128 x 1136 x 992 9.5 and 9.2, 128 x 1760 x 1280 10.5 and 10.3,
+// 16 x 80 x 1296 9.1 and 8.4, bfloat16 values 16 x 224 x 1952 12.0 and 11.3; codes 64 x 1504 x 1616 12.9 and 13.1; at one to three
+// stages four take 1.00 to 1.02 of the time of three).
 //
 // `rides`: slices of an earlier product whose sum the launch carries (0: none).  Its workgroups take as much LDS as a tile's, and
 // where the tiles hold nearly all CUs they wait for them to finish instead of running beside them.
@@ -178,7 +181,11 @@ inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes
   }
   // 64 x 64 tiles: eight waves of 32 x 32 in two groups take 0.91 to 1.02 of the time of four waves (uncut one stage 1.0 to
   // 1.02, four 0.99, eight 0.95; slices 0.98).
-  if (pl.tile == 2) return Launch{FORM_64x64_G2, pl.nsplit, pl.k_per_split, 3};
+  if (pl.tile == 2) {
+    const bool one_a_cu = ((P + 63) / 64) * ((Q + 63) / 64) * pl.nsplit <= NUM_CU;
+    const int ring = one_a_cu && !widens && rides == 0 && pl.k_per_split >= 8 * STAGE_BYTES ? 4 : 3;
+    return Launch{FORM_64x64_G2, pl.nsplit, pl.k_per_split, ring};
+  }
   if (pl.tile == 3) return Launch{FORM_128x192, pl.nsplit, pl.k_per_split, 2};
   // A workgroup that has a CU to itself: eight waves in two groups instead of four, and a longer ring.  2048 x 2048 x 4096 int8
   // 25.9 -> 23.1 us, E5M2 34.0 -> 33.2; 512 x 5632 x 5632 30.4 -> 24.0, 39.1 -> 35.9; at 8 to 15 stages int8 0.81 to 1.01 of the
