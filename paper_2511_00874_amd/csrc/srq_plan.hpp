@@ -102,13 +102,19 @@ inline Plan plan_for(size_t P, size_t Q, size_t R, int pipe) {
 // 128-row tiles, where the output is so small that the chip holds all of those tiles at once, two a CU: nothing is written
 // out twice and no sum is left to a second launch.  Times of both in microseconds from straight lines through some 900
 // products of random sizes, each repeated in a graph (st: stages; mb: megabytes of partial sums; `widens`: 8-bit floats on the
-// f16 pipeline, twice the matrix work a stage).  As planned and this way, int8 and E5M2: 1008 x 768 x 3072 (three slices)
-// 13.7 -> 7.1, 15.8 -> 10.2; 512 x 1024 x 4096 (four) 13.3 -> 8.1, 15.6 -> 12.2; 32 x 4240 x 2448 (64 x 64 tiles, two) 6.9 -> 6.0,
-// 8.2 -> 8.7 (stays as planned); 1024 x 2048 x 2048 (128 x 128 tiles, uncut) 12.9 -> 9.3, 17.4 -> 12.4.
-// The other side of the lines: few tiles, whose slices fill more CUs (272 x 80 x 3792 int8 6.8 -> 7.5, 192 x 160 x 2240
-// E5M2 7.6 -> 8.2, 256 x 256 x 2048 bfloat16 6.9 -> 8.0); more than a tile a CU (576 x 2048 x 6000 int8 22.2 -> 29.9).
-// Beyond 48 stages, 64 where every row begins a cache line, the lines no longer hold and the slices stay (3536 x 128 x 9696 int8
-// 17.6 -> 24.3, 640 x 992 x 7168 17.2 -> 13.4, 1008 x 224 x 10240 14.7 -> 19.0).
+// f16 pipeline, twice the matrix work a stage), and 1.5 more for the second launch: in a graph it costs the GPU no more than its
+// sum, but 3.5 us where small calls follow one another from the host and it is the host that they wait for.  As planned and
+// this way, int8 and E5M2: 1008 x 768 x 3072 (three slices) 13.7 -> 7.1, 15.8 -> 10.2; 512 x 1024 x 4096 (four) 13.3 -> 8.1,
+// 15.6 -> 12.2; 32 x 4240 x 2448 (64 x 64 tiles, two) 6.9 -> 6.0, 8.2 -> 8.7; 1024 x 2048 x 2048 (128 x 128 tiles, uncut)
+// 12.9 -> 9.3, 17.4 -> 12.4.  The other side of the lines: more than a tile a CU (576 x 2048 x 6000 int8 22.2 -> 29.9).
+// Whole calls with absmax and quantizers, in a row, waited for and in a graph: 48 x 1072 x 1664 E4M3 25.7, 37.4, 19.2 -> 20.9,
+// 37.9, 20.2; 208 x 224 x 3248 int8 26.4, 36.9, 19.1 -> 22.7, 39.3, 22.0.  Over 420 random shapes the rule loses 0.35 us a call
+// against the better form in a graph and 0.3 in a row (0.23 and 0.67 if the launch is not counted).
+// Beyond some length the lines no longer hold and the slices stay: 64 stages where every row begins a cache line; otherwise
+// 28 where 64 x 64 tiles are planned, 24 with codes to widen, and 40 where 128-row tiles are (3536 x 128 x 9696 int8 17.6 -> 24.3,
+// 640 x 992 x 7168 17.2 -> 13.4, 1008 x 224 x 10240 14.7 -> 19.0; with the quantizers, whose codes come from beyond the L2,
+// 496 x 304 x 6864 17.3 -> 32.3, 240 x 240 x 3984 19.8 -> 27.2, 848 x 320 x 3408 E5M2 17.2 -> 21.8; int8 at 28 to 36 and 36 to 48
+// stages, the middle half: 64 x 64 tiles 2.3 to 4.8 and 4.2 to 8.7 us more, 128-row tiles 1.6 less to 1.2 more and 0.9 to 2.9 more).
 // `leaves`: the sum of the slices is left to a later launch and runs beside its matrix work.  Slices of 64 x 64 tiles then
 // always stay: the two products of E4M3 backward calls of up to 2^27 multiplications took 10 to 30 % longer otherwise (73 of 80
 // random ones by more than 8 %), E5M2 2048 x 192 x 352 9.4 -> 11.8.  With 128-row tiles there is less to save: M, N, K 5824 x 960
@@ -119,14 +125,14 @@ inline bool small_in_one_pass(const Plan& pl, size_t P, size_t Q, size_t row_byt
   const size_t stages = (row_bytes + STAGE_BYTES - 1) / STAGE_BYTES;
   if (pl.tile == 0 || t64 > 2 * NUM_CU || (pl.tile == 2 && pl.nsplit == 1)) return false;
   if (items > NUM_CU || (leaves && pl.tile == 2)) return false;
-  if (pl.nsplit > 1 && stages > (row_bytes % STAGE_BYTES == 0 ? 64 : 48)) return false;
+  if (pl.nsplit > 1 && stages > (row_bytes % STAGE_BYTES == 0 ? 64u : pl.tile != 2 ? 40u : widens ? 24u : 28u)) return false;
   const double st = (double)stages, slice = (double)(pl.k_per_split / STAGE_BYTES);
   const double mb = pl.nsplit > 1 ? 4e-6 * pl.nsplit * (double)P * (double)Q : 0.0;
   const double once = t64 <= NUM_CU ? (widens ? 3.2 + 0.285 * st : 2.75 + 0.18 * st)
                                     : (widens ? 4.0 + 0.49 * st : 2.5 + 0.44 * st);
   double planned = pl.tile == 2 ? 5.6 + (widens ? 0.22 : 0.085) * slice + 0.59 * mb
                                 : (widens ? 5.8 : 4.0) + 0.73 * slice + 0.44 * mb;
-  if (leaves && pl.nsplit > 1) planned -= 1.5 + 0.2 * mb;
+  if (pl.nsplit > 1) planned += leaves ? -1.5 - 0.2 * mb : 1.5;
   return once < planned;
 }
 
