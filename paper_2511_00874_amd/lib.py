@@ -131,14 +131,14 @@ def _dev(t):
 # The handle of the current device's current stream.  torch.cuda.current_stream().cuda_stream makes a stream object and
 # looks up the device for it (4 us a call, as much as a kernel launch); the raw handle comes without either where this torch
 # has the two calls.
-_current_device = getattr(torch._C, "_cuda_getDevice", None)
-_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+if hasattr(torch._C, "_cuda_getDevice") and hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    _current_device, _current_raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
 
-
-def _stream():
-    if _current_device is None or _current_raw_stream is None:
+    def _stream():
+        return _current_raw_stream(_current_device())
+else:
+    def _stream():
         return torch.cuda.current_stream().cuda_stream
-    return _current_raw_stream(_current_device())
 
 
 class Quant:
