@@ -52,6 +52,13 @@ __device__ __forceinline__ int cvt_flr(float x) {
   return r;
 }
 
+// u within [-q, q], q the same for the whole wave: one instruction, which the compiler forms only of constants
+__device__ __forceinline__ int clamp_to(int u, int q) {
+  int r;
+  asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(u), "s"(-q), "v"(q));
+  return r;
+}
+
 // What is added to U before the shift: 65535 - r16 for stochastic rounding (r16 the element's
 // 16 random bits), 32768 for round-to-nearest.
 constexpr uint32_t RTN_ADDEND = 32768u;
@@ -111,7 +118,7 @@ __device__ __forceinline__ uint32_t quantize_elem(float x, const InvScale& s, ui
     const int QI = KIND == SRQ_INTX ? s.sub_qi : (G::qmax << 16);
     const float y16 = __fmul_rn(x, s.inv16);                            // t * 2^16, D = 1
     int u = ROUND == SRQ_SR ? cvt_rpi(y16) : cvt_flr(y16);              // saturating
-    u = min(max(u, -QI), QI);                                           // clamp t to +-Qmax
+    u = clamp_to(u, QI);                                                // clamp t to +-Qmax
     const int q = (u + (int)addend) >> 16;
     code = AS_BF16 ? __float_as_uint((float)q) >> 16 : (uint32_t)q;     // (at most 7 significant bits)
     if (FIX_NAN && x != x) code = 0u;
@@ -172,6 +179,121 @@ __device__ __forceinline__ uint32_t pack4_nibbles(const uint32_t (&c)[4]) {
   return (c[0] & 0xFu) | ((c[1] & 0xFu) << 4) | ((c[2] & 0xFu) << 8) | ((c[3] & 0xFu) << 12);
 }
 
+// ---- four elements to a word of four byte codes --------------------------------------------------
+// r0 holds the random bits of elements 0 and 1 (low half first), r1 those of 2 and 3, as they come out of Philox; for
+// round-to-nearest (sr = false) both are RTN_WORD, whose halves give the addend 32768.  (sr is uniform; where it is a constant the
+// other form folds away.)
+//
+// What bounds the rounding is the vector ALU (a wave instruction is 2 to 2.7 cycles for plain binary32 and logic operations,
+// 4.4 for most others, 5.2 for a 32 x 32 -> 64 multiply-add, 8.4 for the conversions below), so it is counted in cycles of a wave
+// for 8 elements a lane, Philox (183) included: int8 513 -> 457, E5M2 837 -> 651, E4M3 814 -> 642 against code by code.
+//
+// Integers: the code is byte 2 of U + addend, so the byte permutes that pack the word also take the place of the shifts.
+//
+// E4M3 and E5M2: v_cvt_sr_fp8_f32 / v_cvt_sr_bf8_f32 add the top 20 / 21 bits of a seed to the fraction of |t| below the
+// kept bits and cut.  That is Eq. 1 exactly where t is a normal number of the grid.  With F the 24-bit significand of |t| and
+// 16 + b fraction bits below the kept ones (b = 5 for E5M2, 4 for E4M3), U of the rule above is (F + 2^(b-1)) >> b for t > 0 and
+// -((F + 2^(b-1) - 1) >> b) for t < 0, hence
+//     t > 0:  |q| = (F + ((65535 - r) << b) + 2^(b-1)) >> (16 + b)
+//     t < 0:  |q| = (F + (r << b) + 2^(b-1) - 1) >> (16 + b)
+// and the two seeds are each other's complement: (~r) << 16 | 0x8000, inverted where t is negative.  Round-to-nearest lacks the
+// half of U: the seed 0x80000000 by the same rule.  (The bits of an inverted seed below the ones that are added do not matter.)
+// A product that is +0 or -0 becomes +0 in the fused add of +0, which has code 0.  Left to the general rule, for
+// the rare lanes that hold one: subnormals of the grid, a negative product that rounds to -0, and NaN.
+constexpr uint32_t RTN_WORD = 0x7FFF7FFFu;
+
+template <int KIND>
+__device__ __forceinline__ uint32_t quantize_word(float x0, float x1, float x2, float x3, const InvScale& s, uint32_t r0,
+                                                  uint32_t r1, bool sr) {
+  const float x[4] = {x0, x1, x2, x3};
+  if constexpr (KIND == SRQ_E4M3 || KIND == SRQ_E5M2) {
+    constexpr float QM = Grid<KIND>::qmax, LEAST = KIND == SRQ_E5M2 ? 0x1p-14f : 0x1p-6f;  // smallest normal number
+    const uint32_t n0 = ~r0, n1 = ~r1, add_half = sr ? 0x8000u : 0u;
+    const uint32_t seed[4] = {(n0 << 16) | add_half, (n0 & 0xFFFF0000u) | add_half, (n1 << 16) | add_half,
+                              (n1 & 0xFFFF0000u) | add_half};
+    float t[4];
+    int sd[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      t[e] = __builtin_amdgcn_fmed3f(__builtin_fmaf(x[e], s.inv, 0.0f), -QM, QM);
+      sd[e] = (int)seed[e] ^ ((int)__float_as_uint(t[e]) >> 31);
+    }
+    int w = 0;
+    if constexpr (KIND == SRQ_E5M2) {
+      w = __builtin_amdgcn_cvt_sr_bf8_f32(t[0], sd[0], w, 0);
+      w = __builtin_amdgcn_cvt_sr_bf8_f32(t[1], sd[1], w, 1);
+      w = __builtin_amdgcn_cvt_sr_bf8_f32(t[2], sd[2], w, 2);
+      w = __builtin_amdgcn_cvt_sr_bf8_f32(t[3], sd[3], w, 3);
+    } else {
+      w = __builtin_amdgcn_cvt_sr_fp8_f32(t[0], sd[0], w, 0);
+      w = __builtin_amdgcn_cvt_sr_fp8_f32(t[1], sd[1], w, 1);
+      w = __builtin_amdgcn_cvt_sr_fp8_f32(t[2], sd[2], w, 2);
+      w = __builtin_amdgcn_cvt_sr_fp8_f32(t[3], sd[3], w, 3);
+    }
+    const bool nan = __builtin_isunordered(x0, x1) || __builtin_isunordered(x2, x3);
+    const float least = fminf(fminf(fabsf(t[0]), fabsf(t[1])), fminf(fabsf(t[2]), fabsf(t[3])));
+    if (!(least >= LEAST) || nan) {  // a zero, or one of those
+      bool general = nan;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) general = general || (__float_as_uint(t[e]) != 0u && fabsf(t[e]) < LEAST);
+      if (general) {
+#pragma unroll 1
+        for (int e = 0; e < 4; ++e) {  // (a loop: rare code that should not take the room of common code)
+          const float xe = e == 0 ? x0 : e == 1 ? x1 : e == 2 ? x2 : x3;
+          const uint32_t n = e < 2 ? n0 : n1, add = (e & 1) ? n >> 16 : n & 0xFFFFu;
+          const uint32_t c = sr ? quantize_elem<KIND, SRQ_SR>(xe, s, add) : quantize_elem<KIND, SRQ_RTN>(xe, s, add);
+          w = (int)(((uint32_t)w & ~(0xFFu << (8 * e))) | (c & 0xFFu) << (8 * e));
+        }
+      }
+    }
+    return (uint32_t)w;
+  } else {
+    uint32_t add[4], c[4];
+    sr_addends(r0, r1, add);
+    if constexpr (Grid<KIND>::is_float) {
+      if (sr) quantize_quad<KIND, SRQ_SR, false>(c, x0, x1, x2, x3, s, add);
+      else quantize_quad<KIND, SRQ_RTN, false>(c, x0, x1, x2, x3, s, add);
+      return pack4_bytes(c);
+    } else {
+      const int QI = KIND == SRQ_INTX ? s.sub_qi : (Grid<KIND>::qmax << 16);
+      int u[4];
+      if (sr) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] = cvt_rpi(__fmul_rn(x[e], s.inv16));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] = cvt_flr(__fmul_rn(x[e], s.inv16));
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c[e] = (uint32_t)clamp_to(u[e], QI) + add[e];
+      if (__builtin_isunordered(x0, x1) || __builtin_isunordered(x2, x3)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (x[e] != x[e]) c[e] = 0u;
+      }
+      const uint32_t lo = __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0602u), hi = __builtin_amdgcn_perm(c[3], c[2], 0x0c0c0602u);
+      return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+    }
+  }
+}
+
+// Two words of byte codes -> one of nibbles (elements 0-7, element 0 in bits 3:0).
+__device__ __forceinline__ uint32_t pack8_nibbles(uint32_t lo, uint32_t hi) {
+  lo = (lo & 0x0F0F0F0Fu) | ((lo >> 4) & 0x00F000F0u);  // bytes 0 and 2 hold the pairs
+  hi = (hi & 0x0F0F0F0Fu) | ((hi >> 4) & 0x00F000F0u);
+  return __builtin_amdgcn_perm(hi, lo, 0x06040200u);
+}
+
+// Four words of four bytes, rows -> columns (eight byte permutes).
+__device__ __forceinline__ void turn4x4(uint32_t r0, uint32_t r1, uint32_t r2, uint32_t r3, uint32_t (&c)[4]) {
+  const uint32_t a0 = __builtin_amdgcn_perm(r1, r0, 0x05010400u), a1 = __builtin_amdgcn_perm(r1, r0, 0x07030602u);
+  const uint32_t b0 = __builtin_amdgcn_perm(r3, r2, 0x05010400u), b1 = __builtin_amdgcn_perm(r3, r2, 0x07030602u);
+  c[0] = __builtin_amdgcn_perm(b0, a0, 0x05040100u);
+  c[1] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
+  c[2] = __builtin_amdgcn_perm(b1, a1, 0x05040100u);
+  c[3] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+}
+
 __device__ __forceinline__ float bf16_to_f32(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 
 // 1 / scale, correctly rounded, from a host value or a device-resident one.
@@ -198,13 +320,22 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+// A pointer that is known to point to global memory.  One that was read out of a structure in memory is generic to the compiler,
+// whose flat instructions take no scalar base and are waited for together with those of the LDS.
+template <class T>
+using global_ptr = __attribute__((address_space(1))) T*;
+template <class T>
+__device__ __forceinline__ global_ptr<T> as_global(T* p) { return (global_ptr<T>)p; }
+
 // A 16-byte load of a source tensor: streaming, or cached for one that is small enough to be met again in
 // the last-level cache (the load policy in srq_internal.hpp).
 template <bool CACHED, class T>
-__device__ __forceinline__ T load_source(const T* p) {
+__device__ __forceinline__ T load_source(global_ptr<const T> p) {
   if constexpr (CACHED) return *p;
   else return __builtin_nontemporal_load(p);
 }
+template <bool CACHED, class T>
+__device__ __forceinline__ T load_source(const T* p) { return load_source<CACHED, T>(as_global(p)); }
 
 // Load the 8 elements of group g (element index 8g..8g+7) as binary32; lanes beyond n read 0.
 template <int SRC, bool CACHED = false>
@@ -262,70 +393,93 @@ __device__ __forceinline__ void quantize_group(uint32_t (&c)[8], const float (&v
   for (int j = 0; j < 4; ++j) { c[j] = lo4[j]; c[4 + j] = hi4[j]; }
 }
 
-// ---- one wave, 512 consecutive binary32 elements, fully coalesced ---------------------------
-// Lane L loads elements 4L..4L+3 of the chunk and 256+4L..256+4L+3: two 16-byte loads, each a
-// contiguous kilobyte across the wave.  A lane therefore holds one half of Philox group L/2 and
-// one half of group 32 + L/2.  The even lane of a pair draws the block of the first group, the
-// odd lane the block of the second, and they trade the two words the other needs through a
-// quad permute: one Philox block per 8 elements, as in the layout-free definition.
+// The random words of a Philox block, or what stands for them in round-to-nearest.
+__device__ __forceinline__ void round_words(bool sr, uint64_t block, uint32_t k0, uint32_t k1, uint32_t (&w)[4]) {
+  if (sr) philox_block(block, k0, k1, w);
+  else w[0] = w[1] = w[2] = w[3] = RTN_WORD;
+}
+
+// One group to two words of byte codes.
+template <int KIND>
+__device__ __forceinline__ u32x2 quantize_group_words(const float (&v)[8], const InvScale& s, uint64_t block, uint32_t k0,
+                                                      uint32_t k1, bool sr) {
+  uint32_t w[4];
+  round_words(sr, block, k0, k1, w);
+  return u32x2{quantize_word<KIND>(v[0], v[1], v[2], v[3], s, w[0], w[1], sr),
+               quantize_word<KIND>(v[4], v[5], v[6], v[7], s, w[2], w[3], sr)};
+}
+
+// v_permlane32_swap: the upper 32 lanes of a and the lower 32 of b change places.
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+
+// For lanes L and L + 32 that hold the two halves of each of two groups: the lower lane passes the block of the first
+// group and the upper lane that of the second; w[0], w[1] become this lane's words of the first group, w[2], w[3] of the second.
+__device__ __forceinline__ void round_words_of_pair(bool sr, uint64_t block, uint32_t k0, uint32_t k1, uint32_t (&w)[4]) {
+  round_words(sr, block, k0, k1, w);
+  if (sr) {
+    swap_halves(w[0], w[2]);
+    swap_halves(w[1], w[3]);
+  }
+}
+
+// ---- one wave, 512 consecutive binary32 elements ---------------------------------------------
+// 64 groups of 8.  Lane L < 32 loads the first quad of groups L and 32 + L, lane 32 + L the second quads: two 16-byte
+// loads, each a contiguous kilobyte across the wave.  The lower lane draws the Philox block of the first group, the upper one that
+// of the second, and one swap of wave halves per word hands out the words (a swap is 8 cycles where trading between
+// neighbouring lanes took two moves and two selects, 18).  The codes go the same way: after another swap
+// a lane holds a whole group and writes 8 bytes.
 constexpr int CHUNK = 512;
 
-// store modes: 0 one byte per element, 1 nibbles, 2 bfloat16 (values as in StoreMode)
 // Stores that write through the L2 (system-scope cache policy) without the streaming hint: the
 // line does not stay dirty in the L2 (nothing left to flush when the kernel ends) but is still
 // allocated in the last-level cache for the kernel that reads it next.
 __device__ __forceinline__ void store_through16(void* p, const u32x4& v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" : : "v"(p), "v"(v) : "memory");
 }
-__device__ __forceinline__ void store_through8(void* p, const u32x2& v) {
+__device__ __forceinline__ void store_through8(global_ptr<uint8_t> p, const u32x2& v) {
   asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1" : : "v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store_through4(void* p, uint32_t v) {
   asm volatile("global_store_dword %0, %1, off sc0 sc1" : : "v"(p), "v"(v) : "memory");
 }
 
-template <int KIND, int ROUND, int STORE, bool CACHED = false>
+// store modes: 0 one byte per element, 1 nibbles, 2 bfloat16 (values as in StoreMode)
+template <int KIND, int STORE, bool CACHED = false>
 __device__ __forceinline__ void quantize_chunk_f32(uint8_t* __restrict__ out, const float* __restrict__ x,
                                                    size_t chunk, uint32_t lane, const InvScale& s, uint32_t k0,
-                                                   uint32_t k1, uint64_t counter_offset) {
-  constexpr bool AS_BF16 = STORE == 2;
-  const size_t e0 = chunk * CHUNK + 4 * lane;  // first element of this lane's first quad
+                                                   uint32_t k1, uint64_t counter_offset, bool sr) {
+  const uint32_t half = lane >> 5, l = lane & 31u;
+  const size_t e0 = chunk * CHUNK + 8 * l + 4 * half;  // first element of this lane's first quad
   const f32x4 a = load_source<CACHED>(reinterpret_cast<const f32x4*>(x + e0));
   const f32x4 b = load_source<CACHED>(reinterpret_cast<const f32x4*>(x + e0 + 256));
-  uint32_t addA[4], addB[4];
-  if constexpr (ROUND == SRQ_SR) {
-    const bool odd = lane & 1u;
-    uint32_t w[4];
-    philox_block(counter_offset + chunk * (CHUNK / 8) + (odd ? 32u : 0u) + (lane >> 1), k0, k1, w);
-    // Even lane: its first quad is the first half of its own block (words 0,1), its second quad
-    // the first half of the odd neighbour's block.  Odd lane: first quad = second half (words
-    // 2,3) of the even neighbour's block, second quad = second half of its own.
-    const uint32_t nb0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[0], 0xB1, 0xF, 0xF, true);  // lane ^ 1
-    const uint32_t nb1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[1], 0xB1, 0xF, 0xF, true);
-    const uint32_t nb2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[2], 0xB1, 0xF, 0xF, true);
-    const uint32_t nb3 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[3], 0xB1, 0xF, 0xF, true);
-    sr_addends(odd ? nb2 : w[0], odd ? nb3 : w[1], addA);
-    sr_addends(odd ? w[2] : nb0, odd ? w[3] : nb1, addB);
+  uint32_t w[4];
+  round_words_of_pair(sr, counter_offset + chunk * (CHUNK / 8) + lane, k0, k1, w);
+  const size_t g0 = chunk * CHUNK + 8 * lane;  // the group this lane writes
+  if constexpr (STORE == 2) {
+    uint32_t addA[4], addB[4], ca[4], cb[4];
+    sr_addends(w[0], w[1], addA);
+    sr_addends(w[2], w[3], addB);
+    if (sr) {
+      quantize_quad<KIND, SRQ_SR, true>(ca, a.x, a.y, a.z, a.w, s, addA);
+      quantize_quad<KIND, SRQ_SR, true>(cb, b.x, b.y, b.z, b.w, s, addB);
+    } else {
+      quantize_quad<KIND, SRQ_RTN, true>(ca, a.x, a.y, a.z, a.w, s, addA);
+      quantize_quad<KIND, SRQ_RTN, true>(cb, b.x, b.y, b.z, b.w, s, addB);
+    }
+    uint32_t a0 = ca[0] | (ca[1] << 16), a1 = ca[2] | (ca[3] << 16), b0 = cb[0] | (cb[1] << 16), b1 = cb[2] | (cb[3] << 16);
+    swap_halves(a0, b0);
+    swap_halves(a1, b1);
+    __builtin_nontemporal_store(u32x4{a0, a1, b0, b1}, as_global(reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + g0)));
   } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) addA[j] = addB[j] = RTN_ADDEND;  // Def. 2
-  }
-  uint32_t ca[4], cb[4];
-  quantize_quad<KIND, ROUND, AS_BF16>(ca, a.x, a.y, a.z, a.w, s, addA);
-  quantize_quad<KIND, ROUND, AS_BF16>(cb, b.x, b.y, b.z, b.w, s, addB);
-  if constexpr (STORE == 1) {
-    uint16_t* o = reinterpret_cast<uint16_t*>(out + e0 / 2);
-    o[0] = (uint16_t)pack4_nibbles(ca);
-    o[64] = (uint16_t)pack4_nibbles(cb);
-  } else if constexpr (STORE == 2) {
-    u32x2* o = reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(out) + e0);
-    const u32x2 va = {ca[0] | (ca[1] << 16), ca[2] | (ca[3] << 16)}, vb = {cb[0] | (cb[1] << 16), cb[2] | (cb[3] << 16)};
-    __builtin_nontemporal_store(va, o);
-    __builtin_nontemporal_store(vb, o + 64);
-  } else {
-    uint32_t* o = reinterpret_cast<uint32_t*>(out + e0);
-    __builtin_nontemporal_store(pack4_bytes(ca), o);
-    __builtin_nontemporal_store(pack4_bytes(cb), o + 64);
+    uint32_t wa = quantize_word<KIND>(a.x, a.y, a.z, a.w, s, w[0], w[1], sr);
+    uint32_t wb = quantize_word<KIND>(b.x, b.y, b.z, b.w, s, w[2], w[3], sr);
+    swap_halves(wa, wb);
+    if constexpr (STORE == 1) __builtin_nontemporal_store(pack8_nibbles(wa, wb), as_global(reinterpret_cast<uint32_t*>(out + g0 / 2)));
+    else __builtin_nontemporal_store(u32x2{wa, wb}, as_global(reinterpret_cast<u32x2*>(out + g0)));
   }
 }
 

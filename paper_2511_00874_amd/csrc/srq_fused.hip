@@ -49,18 +49,15 @@ __device__ __forceinline__ void stage_codes(uint8_t* tile, const FusedOperand& o
   for (uint32_t g = threadIdx.x; g < ROWS * 16u; g += 256u) {
     const uint32_t r = g >> 4, kg = g & 15u;
     const uint32_t row = row0 + r, k = k0 + kg * 8u;
-    uint32_t c[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};  // beyond the tensor: zeros
+    u32x2 c = {0u, 0u};  // beyond the tensor: zeros
     if (row < op.rows && k < R) {
       const size_t group = ((size_t)row * R + k) >> 3;  // R % 16 == 0: a group never leaves its row
       float v[8];
       if (op.dtype == SRQ_F32) load_group<SRQ_F32>(v, op.x, group, n);
       else load_group<SRQ_BF16>(v, op.x, group, n);
-      if (op.round == SRQ_SR) quantize_group<KIND, SRQ_SR, false>(c, v, s, block0 + group, key0, key1);
-      else quantize_group<KIND, SRQ_RTN, false>(c, v, s, block0 + group, key0, key1);
+      c = quantize_group_words<KIND>(v, s, block0 + group, key0, key1, op.round == SRQ_SR);
     }
-    const uint32_t lo[4] = {c[0], c[1], c[2], c[3]}, hi[4] = {c[4], c[5], c[6], c[7]};
-    const u32x2 w = {pack4_bytes(lo), pack4_bytes(hi)};
-    *reinterpret_cast<u32x2*>(tile + r * BK + (swizzled_chunk(r, kg >> 1) << 4) + (kg & 1u) * 8u) = w;
+    *reinterpret_cast<u32x2*>(tile + r * BK + (swizzled_chunk(r, kg >> 1) << 4) + (kg & 1u) * 8u) = c;
   }
 }
 
@@ -87,15 +84,12 @@ __device__ __forceinline__ void stage_codes_ahead(uint8_t* tile, const FusedOper
     for (uint32_t a = 0; a < 2; ++a) {
       const uint32_t r = (g0 + a * NT) >> 4, kg = (g0 + a * NT) & 15u;
       const uint32_t row = row0 + r, k = k0 + kg * 8u;
-      uint32_t c[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+      u32x2 c = {0u, 0u};
       if (row < op.rows && k < R) {
         const size_t group = ((size_t)row * R + k) >> 3;
-        if (op.round == SRQ_SR) quantize_group<KIND, SRQ_SR, false>(c, v[a], s, block0 + group, key0, key1);
-        else quantize_group<KIND, SRQ_RTN, false>(c, v[a], s, block0 + group, key0, key1);
+        c = quantize_group_words<KIND>(v[a], s, block0 + group, key0, key1, op.round == SRQ_SR);
       }
-      const uint32_t lo[4] = {c[0], c[1], c[2], c[3]}, hi[4] = {c[4], c[5], c[6], c[7]};
-      const u32x2 w = {pack4_bytes(lo), pack4_bytes(hi)};
-      *reinterpret_cast<u32x2*>(tile + r * BK + (swizzled_chunk(r, kg >> 1) << 4) + (kg & 1u) * 8u) = w;
+      *reinterpret_cast<u32x2*>(tile + r * BK + (swizzled_chunk(r, kg >> 1) << 4) + (kg & 1u) * 8u) = c;
     }
   }
 }

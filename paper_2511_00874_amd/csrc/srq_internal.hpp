@@ -86,6 +86,8 @@ struct QuantJobs {
   QuantJob job[QUANT_JOBS_MAX];
 };
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream);
+// its second half where some quantizer rounds to nearest (mixed: and some stochastically), jobs filled in
+hipError_t launch_jobs_to_nearest(const QuantJobs& jobs, uint32_t blocks, bool cached, bool mixed, hipStream_t stream);
 
 // Several per-tensor scales in two launches: up to ABSMAX_MAX distinct tensors and
 // ABSMAX_MAX scales (a tensor may feed several formats).

@@ -9,17 +9,6 @@ namespace {
 
 constexpr int QBLOCK = 256;
 
-__device__ __forceinline__ uint32_t pack_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-  const uint32_t q[4] = {a, b, c, d};
-  return pack4_bytes(q);
-}
-__device__ __forceinline__ uint32_t pack_nibbles(const uint32_t (&c)[8]) {
-  uint32_t r = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) r |= (c[j] & 0xFu) << (4 * j);
-  return r;
-}
-
 // ---- same-layout output -------------------------------------------------------------------
 template <int KIND, int SRC, int ROUND, int STORE>
 __global__ __launch_bounds__(QBLOCK) void quantize_flat_kernel(uint8_t* __restrict__ out,
@@ -34,12 +23,11 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_kernel(uint8_t* __restri
   const size_t stride = (size_t)gridDim.x * QBLOCK;
   for (size_t g = (size_t)blockIdx.x * QBLOCK + threadIdx.x; g < ngroups; g += stride) {
     float v[8];
-    uint32_t c[8];
     load_group<SRC>(v, x, g, n);
-    quantize_group<KIND, ROUND, false>(c, v, inv, counter_offset + g, k0, k1);
+    const u32x2 c = quantize_group_words<KIND>(v, inv, counter_offset + g, k0, k1, ROUND == SRQ_SR);
     const size_t base = g * 8;
     if constexpr (STORE == STORE_NIBBLE) {
-      const uint32_t word = pack_nibbles(c);
+      const uint32_t word = pack8_nibbles(c.x, c.y);
       if (base + 8 <= n) {
         __builtin_nontemporal_store(word, reinterpret_cast<uint32_t*>(out + base / 2));
       } else {
@@ -47,12 +35,11 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_kernel(uint8_t* __restri
       }
     } else {
       if (base + 8 <= n) {
-        u32x2 word = {pack_bytes(c[0], c[1], c[2], c[3]), pack_bytes(c[4], c[5], c[6], c[7])};
-        __builtin_nontemporal_store(word, reinterpret_cast<u32x2*>(out + base));
+        __builtin_nontemporal_store(c, reinterpret_cast<u32x2*>(out + base));
       } else {
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          if (base + j < n) out[base + j] = (uint8_t)c[j];
+          if (base + j < n) out[base + j] = (uint8_t)(c[j / 4] >> (8 * (j % 4)));
       }
     }
   }
@@ -71,8 +58,8 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_f32_kernel(uint8_t* __re
   const uint32_t lane = threadIdx.x & 63u;
   const size_t waves = (size_t)gridDim.x * (QBLOCK / 64);
   for (size_t c = (size_t)blockIdx.x * (QBLOCK / 64) + (threadIdx.x >> 6); c < nchunks; c += waves)
-    quantize_chunk_f32<KIND, ROUND, STORE>(out, x, c, lane, inv, (uint32_t)seed, (uint32_t)(seed >> 32),
-                                           counter_offset);
+    quantize_chunk_f32<KIND, STORE>(out, x, c, lane, inv, (uint32_t)seed, (uint32_t)(seed >> 32), counter_offset,
+                                    ROUND == SRQ_SR);
 }
 
 // ---- transposed output --------------------------------------------------------------------
@@ -82,9 +69,9 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_f32_kernel(uint8_t* __re
 // lines on the store side.
 //   - A thread takes a piece that is several rows deep, so the codes of neighbouring rows, which are
 //     neighbours in the output, are packed in registers and go to LDS a word (or two) at a time.
-//     binary32: 4 columns x 8 rows (a 16-byte load per row; the lanes of a pair hold the two halves of
-//     each Philox group, the even lane draws the blocks of the first four rows, the odd lane those
-//     of the last four, and they trade two words per block).  bfloat16: 8 columns x 4 rows.  All loads of
+//     binary32: 4 columns x 8 rows (a 16-byte load per row; lanes L and L + 32 hold the two halves of
+//     each Philox group, the lower one draws the blocks of the even rows, the upper one those of the odd rows,
+//     and they trade words by swaps of wave halves).  bfloat16: 8 columns x 4 rows.  All loads of
 //     a piece are issued before its first code is made.
 //   - A run whose length or place is not a multiple of 16 bytes (a row count that is not one) leaves
 //     16 bytes at a time from the first multiple of four on, put together from LDS words by a byte
@@ -96,10 +83,11 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_f32_kernel(uint8_t* __re
 //     40 / 41 / 42 us, 65536 x 4096 241 / 227 / 229.)
 // Against the form before (a group of 8 codes per thread, byte-wise LDS writes, 128-row tiles, a ragged
 // run byte by byte): 12289 x 3080 bfloat16 -> int8 82 -> 35 us, binary32 99 -> 47; 12288 x 3080 binary32
-// 52 -> 41 (189 MB: 4.6 TB/s); 65536 x 4096 binary32 311 -> 227 (5.9 TB/s), bfloat16 162 -> 130.
-//   - At most 64 registers (the launch bounds): a wave of it then fits on a SIMD beside two of the persistent product
+// 52 -> 41 (189 MB: 4.6 TB/s); 65536 x 4096 binary32 311 -> 227 (5.9 TB/s), bfloat16 162 -> 130.  With the codes of a quad made
+// as one word (quantize_word): 12289 x 3080 bfloat16 -> E5M2 38.2 -> 33.8 us.
+//   - At most 64 registers: a wave of it then fits on a SIMD beside two of the persistent product
 //     kernel, so that on a second stream it runs beside a product and not behind it.  That takes no more than to
-//     recompute the addresses of the store side (opaque); alone it is as fast.  Six calls on 16384 x 4096 beside int8 products
+//     recompute the addresses of both sides (opaque) and to round a row at a time; alone it is as fast.  Six calls on 16384 x 4096 beside int8 products
 //     of 8192 cubed, us a call at 94 registers and at 64: binary32 490 and 177, bfloat16 478 and 145.
 constexpr int TC = 64;
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at a multiple of four
@@ -107,7 +95,7 @@ constexpr uint32_t TBAND = 16;
 constexpr uint32_t TRANSPOSE_GRID = 1u << 20;  // workgroups per launch at most; the rest of the tiles by a loop
 
 template <int KIND, int SRC, int ROUND, int STORE, int TR>
-__global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
+__global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
     uint8_t* __restrict__ out, const void* __restrict__ x, uint32_t rows, uint32_t cols, float scale,
     const float* scale_dev, int kind, uint64_t seed, uint64_t counter_host, const uint64_t* counter_dev) {
   static_assert(STORE == STORE_BYTE || STORE == STORE_NIBBLE, "codes");
@@ -136,8 +124,10 @@ __global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
     static_assert(PIECES >= 1, "a piece per thread");
 #pragma unroll 1
     for (int it = 0; it < PIECES; ++it) {
-      const uint32_t id = it * QBLOCK + threadIdx.x;
-      const uint32_t cl = (id % (TC / PC)) * PC, rl = (id / (TC / PC)) * PR;
+      // binary32: lanes L and L + 32 hold the two halves of each Philox group of their rows
+      const uint32_t tid = opaque(threadIdx.x), id = it * QBLOCK + tid, lane = tid & 63u, half = lane >> 5;
+      const uint32_t cl = F32 ? (lane & 7u) * 8 + half * 4 : (id % (TC / PC)) * PC;
+      const uint32_t rl = F32 ? ((id >> 6) * 4 + ((lane >> 3) & 3u)) * PR : (id / (TC / PC)) * PR;
       const uint32_t col = c0 + cl, row = r0 + rl;
       const bool col_ok = col < cols;  // cols % 8 == 0: a piece never straddles the edge
       const size_t e0 = (size_t)row * cols + col;
@@ -149,49 +139,52 @@ __global__ __launch_bounds__(QBLOCK, 8) void quantize_transpose_kernel(
         if constexpr (F32) raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(static_cast<const float*>(x) + e));
         else raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(x) + e));
       }
-      uint32_t c[PR][PC];
       if constexpr (F32) {
-        const bool odd = threadIdx.x & 1u;
+        uint32_t c[PR];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          uint32_t addA[4], addB[4];  // rows i and i + 4
-          if constexpr (ROUND == SRQ_SR) {
-            uint32_t w[4];
-            philox_block(ctr + (e0 + (size_t)(odd ? i + 4 : i) * cols) / 8, k0, k1, w);
-            const uint32_t s0 = odd ? w[0] : w[2], s1 = odd ? w[1] : w[3];  // what the other lane needs
-            const uint32_t t0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s0, 0xB1, 0xF, 0xF, true);  // lane ^ 1
-            const uint32_t t1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s1, 0xB1, 0xF, 0xF, true);
-            sr_addends(odd ? t0 : w[0], odd ? t1 : w[1], addA);
-            sr_addends(odd ? w[2] : t0, odd ? w[3] : t1, addB);
-          } else {
+        for (int i = 0; i < PR; i += 2) {
+          __builtin_amdgcn_sched_barrier(0);  // (two pairs of rows at once would not fit the registers)
+          uint32_t w[4];
+          round_words_of_pair(ROUND == SRQ_SR, ctr + (e0 + (size_t)(i + half) * cols) / 8, k0, k1, w);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) addA[e] = addB[e] = RTN_ADDEND;
+          for (int h = 0; h < 2; ++h) {
+            c[i + h] = quantize_word<KIND>(__uint_as_float(raw[i + h].x), __uint_as_float(raw[i + h].y),
+                                           __uint_as_float(raw[i + h].z), __uint_as_float(raw[i + h].w), inv, w[2 * h],
+                                           w[2 * h + 1], ROUND == SRQ_SR);
+            __builtin_amdgcn_sched_barrier(0);
           }
-          quantize_quad<KIND, ROUND, false>(c[i], __uint_as_float(raw[i].x), __uint_as_float(raw[i].y),
-                                            __uint_as_float(raw[i].z), __uint_as_float(raw[i].w), inv, addA);
-          quantize_quad<KIND, ROUND, false>(c[i + 4], __uint_as_float(raw[i + 4].x), __uint_as_float(raw[i + 4].y),
-                                            __uint_as_float(raw[i + 4].z), __uint_as_float(raw[i + 4].w), inv, addB);
+        }
+        uint32_t upper[4], lower[4];
+        turn4x4(c[0], c[1], c[2], c[3], upper);
+        turn4x4(c[4], c[5], c[6], c[7], lower);
+#pragma unroll
+        for (int e = 0; e < PC; ++e) {
+          uint8_t* const dst = tile + (cl + e) * PITCH + rl / DIV;
+          if constexpr (STORE == STORE_NIBBLE) *reinterpret_cast<uint32_t*>(dst) = pack8_nibbles(upper[e], lower[e]);
+          else *reinterpret_cast<u32x2*>(dst) = u32x2{upper[e], lower[e]};
         }
       } else {
+        u32x2 c[PR];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < PR; ++i) {
           float v[8];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             v[2 * e] = bf16_to_f32(raw[i][e] & 0xFFFFu);
             v[2 * e + 1] = bf16_to_f32(raw[i][e] >> 16);
           }
-          quantize_group<KIND, ROUND, false>(c[i], v, inv, ctr + (e0 + (size_t)i * cols) / 8, k0, k1);
+          c[i] = quantize_group_words<KIND>(v, inv, ctr + (e0 + (size_t)i * cols) / 8, k0, k1, ROUND == SRQ_SR);
         }
-      }
 #pragma unroll
-      for (int e = 0; e < PC; ++e) {
-        uint8_t* const dst = tile + (cl + e) * PITCH + rl / DIV;
+        for (int h = 0; h < 2; ++h) {
+          uint32_t q[4];
+          turn4x4(c[0][h], c[1][h], c[2][h], c[3][h], q);
 #pragma unroll
-        for (int h = 0; h < PR; h += 4) {
-          const uint32_t q[4] = {c[h][e], c[h + 1][e], c[h + 2][e], c[h + 3][e]};
-          if constexpr (STORE == STORE_NIBBLE) *reinterpret_cast<uint16_t*>(dst + h / 2) = (uint16_t)pack4_nibbles(q);
-          else *reinterpret_cast<uint32_t*>(dst + h) = pack4_bytes(q);
+          for (int e = 0; e < 4; ++e) {
+            uint8_t* const dst = tile + (cl + 4 * h + e) * PITCH + rl / DIV;
+            if constexpr (STORE == STORE_NIBBLE) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)pack8_nibbles(q[e], 0u);
+            else *reinterpret_cast<uint32_t*>(dst) = q[e];
+          }
         }
       }
     }

@@ -32,8 +32,8 @@ def _form(kind):
     return 2, lambda P, Q, R: L.raw.sr_gemm_bf16_workspace_bytes(P, Q, R)
 
 
-def _expect(t, kind, q, transpose, es):
-    codes = oracle.quantize(host_src(t), kind, q.scale, q.seed, q.counter_offset)
+def _expect(t, kind, q, transpose, es, mode=oracle.SR):
+    codes = oracle.quantize(host_src(t), kind, q.scale, q.seed, q.counter_offset, mode)
     if transpose:
         codes = np.ascontiguousarray(codes.T)
     if es == 1:
@@ -90,6 +90,58 @@ def test_many_row_bands_with_a_ragged_last_group():
     # a band of 16 rows make one full group and one of six bands, the last of them partial
     say("workspace codes, 4752 rows")
     _run(4752, 144, 208, L.INT8, seed=5, w_bf16=True)
+
+
+# Launches whose quantizers all round to nearest, and launches of both modes, are kernels of their own; the sources span
+# 40 binades with zeros of both signs, infinities and NaN, so that a quad holds numbers that the 8-bit conversions round,
+# subnormals of the grid and numbers that underflow, and the scale is not that of the largest element (saturation).
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("modes", [(L.SR, L.SR, L.SR), (L.RTN, L.RTN, L.RTN), (L.SR, L.RTN, L.SR)])
+def test_codes_of_mixed_rounding_and_wide_ranges(kind, modes):
+    M, N, K, seed = 144, 80, 208, 21
+    say("workspace codes, modes", L.KIND_NAMES[kind], modes)
+    rng = np.random.default_rng(kind)
+
+    def wide(shape):
+        x = (rng.standard_normal(shape) * np.exp2(rng.uniform(-38, 2, shape))).astype(np.float32)
+        flat = x.reshape(-1)
+        at = rng.permutation(flat.size)[:96]
+        flat[at] = np.resize(np.float32([0.0, -0.0, np.inf, -np.inf, np.nan, 1e-40, -1e-40, 3e38]), 96)
+        return x
+
+    A, W, dY = to_dev(wide((M, K))), to_dev(wide((N, K)), True), to_dev(wide((M, N)))
+    oq, lq, off = {}, {}, 0
+    for name, t, mode in (("dY", dY, modes[0]), ("W", W, modes[1]), ("A", A, modes[2])):
+        scale = float(np.float32(2.0 / L.QMAX[kind]))
+        oq[name] = oracle.Quant(kind, scale, seed, off)
+        lq[name] = L.Quant(kind, scale, seed, off, round_mode=mode)
+        off += (t.numel() + 7) // 8
+    es, slices = _form(kind)
+    mode_of = dict(zip(("dY", "W", "A"), modes))
+    ws = torch.zeros(L.sr_linear_workspace_bytes(L.OP_BWD, M, N, K), dtype=torch.uint8, device=A.device)
+    L.sr_linear_bwd(dY, W, A, lq["dY"], lq["W"], lq["A"], workspace=ws)
+    o_wt = _up(M * N * es)
+    o_dyt = o_wt + _up(K * N * es) + _up(slices(M, K, N))
+    o_at = o_dyt + _up(N * M * es)
+    for what, name, t, off_b, tr in (("Q(dY)", "dY", dY, 0, False), ("Q(W)^T", "W", W, o_wt, True),
+                                     ("Q(dY)^T", "dY", dY, o_dyt, True), ("Q(A)^T", "A", A, o_at, True)):
+        want = _expect(t, kind, oq[name], tr, es, mode_of[name])
+        got = _piece(ws, off_b, want.size)
+        if es == 2:  # NaN has a payload of its own in each
+            got, want = (x.view(np.uint16) for x in (got, want))
+            nan = (want & 0x7FFF) > 0x7F80
+            assert np.all((got[nan] & 0x7FFF) > 0x7F80)
+            got, want = got[~nan], want[~nan]
+        assert np.array_equal(got, want), what
+    # integer codes in the source layout beside the transposed ones (the stash call): both of A's quantizers
+    q8 = L.Quant(L.INT8, 0.02, seed, 5000, round_mode=modes[1])
+    q8w = L.Quant(L.INT8, 0.02, seed, 9000, round_mode=modes[0])
+    ws = torch.zeros(L.sr_linear_workspace_bytes(L.OP_FWD_STASH, M, N, K), dtype=torch.uint8, device=A.device)
+    _, stash = L.sr_linear_fwd_stash(A, W, q8, q8w, lq["A"], lq["W"], workspace=ws)
+    q = oracle.Quant(L.INT8, 0.02, seed, 5000)
+    assert np.array_equal(_piece(ws, 0, M * K), _expect(A, L.INT8, q, False, 1, modes[1])), "Q(A) forward"
+    if es == 1:
+        assert np.array_equal(_piece(stash, 0, M * K), _expect(A, kind, oq["A"], True, 1, modes[2])), "stash"
 
 
 def _nib16(codes):
