@@ -18,6 +18,10 @@
 
 namespace srq {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
 // ---- Philox4x32-10 (Salmon et al., SC'11), counter (block_lo, block_hi, 0, 0) ----------
 // The key schedule is wave-uniform, so it lives in scalar registers; only the two 32x32->64
 // multiplies and the xors per round are vector work.
@@ -186,7 +190,8 @@ __device__ __forceinline__ uint32_t pack4_nibbles(const uint32_t (&c)[4]) {
 //
 // What bounds the rounding is the vector ALU (a wave instruction is 2 to 2.7 cycles for plain binary32 and logic operations,
 // 4.4 for most others, 5.2 for a 32 x 32 -> 64 multiply-add, 8.4 for the conversions below), so it is counted in cycles of a wave
-// for 8 elements a lane, Philox (183) included: int8 513 -> 457, E5M2 837 -> 651, E4M3 814 -> 642 against code by code.
+// for 8 elements a lane, Philox (183) included: int8 513 -> 457, E5M2 837 -> 651, E4M3 814 -> 642 against
+// code by code (a word at a time; quantize_octet has one branch where two words have two).
 //
 // Integers: the code is byte 2 of U + addend, so the byte permutes that pack the word also take the place of the shifts.
 //
@@ -202,78 +207,109 @@ __device__ __forceinline__ uint32_t pack4_nibbles(const uint32_t (&c)[4]) {
 // the rare lanes that hold one: subnormals of the grid, a negative product that rounds to -0, and NaN.
 constexpr uint32_t RTN_WORD = 0x7FFF7FFFu;
 
+// Formats whose codes come out of the conversions a word at a time.
+template <int KIND>
+constexpr bool BY_CONVERSION = KIND == SRQ_E4M3 || KIND == SRQ_E5M2;
+
+// Four elements by conversion; t: their clamped grid coordinates.
+template <int KIND>
+__device__ __forceinline__ uint32_t convert_word(const float (&x)[4], float (&t)[4], const InvScale& s, uint32_t r0, uint32_t r1,
+                                                 bool sr) {
+  constexpr float QM = Grid<KIND>::qmax;
+  const uint32_t n0 = ~r0, n1 = ~r1, add_half = sr ? 0x8000u : 0u;
+  const uint32_t seed[4] = {(n0 << 16) | add_half, (n0 & 0xFFFF0000u) | add_half, (n1 << 16) | add_half,
+                            (n1 & 0xFFFF0000u) | add_half};
+  int sd[4], w = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    t[e] = __builtin_amdgcn_fmed3f(__builtin_fmaf(x[e], s.inv, 0.0f), -QM, QM);
+    sd[e] = (int)seed[e] ^ ((int)__float_as_uint(t[e]) >> 31);
+  }
+  if constexpr (KIND == SRQ_E5M2) {
+    w = __builtin_amdgcn_cvt_sr_bf8_f32(t[0], sd[0], w, 0);
+    w = __builtin_amdgcn_cvt_sr_bf8_f32(t[1], sd[1], w, 1);
+    w = __builtin_amdgcn_cvt_sr_bf8_f32(t[2], sd[2], w, 2);
+    w = __builtin_amdgcn_cvt_sr_bf8_f32(t[3], sd[3], w, 3);
+  } else {
+    w = __builtin_amdgcn_cvt_sr_fp8_f32(t[0], sd[0], w, 0);
+    w = __builtin_amdgcn_cvt_sr_fp8_f32(t[1], sd[1], w, 1);
+    w = __builtin_amdgcn_cvt_sr_fp8_f32(t[2], sd[2], w, 2);
+    w = __builtin_amdgcn_cvt_sr_fp8_f32(t[3], sd[3], w, 3);
+  }
+  return (uint32_t)w;
+}
+
+// Four elements of the other formats.
 template <int KIND>
 __device__ __forceinline__ uint32_t quantize_word(float x0, float x1, float x2, float x3, const InvScale& s, uint32_t r0,
                                                   uint32_t r1, bool sr) {
+  static_assert(!BY_CONVERSION<KIND>, "quantize_octet");
   const float x[4] = {x0, x1, x2, x3};
-  if constexpr (KIND == SRQ_E4M3 || KIND == SRQ_E5M2) {
-    constexpr float QM = Grid<KIND>::qmax, LEAST = KIND == SRQ_E5M2 ? 0x1p-14f : 0x1p-6f;  // smallest normal number
-    const uint32_t n0 = ~r0, n1 = ~r1, add_half = sr ? 0x8000u : 0u;
-    const uint32_t seed[4] = {(n0 << 16) | add_half, (n0 & 0xFFFF0000u) | add_half, (n1 << 16) | add_half,
-                              (n1 & 0xFFFF0000u) | add_half};
-    float t[4];
-    int sd[4];
+  uint32_t add[4], c[4];
+  sr_addends(r0, r1, add);
+  if constexpr (Grid<KIND>::is_float) {
+    if (sr) quantize_quad<KIND, SRQ_SR, false>(c, x0, x1, x2, x3, s, add);
+    else quantize_quad<KIND, SRQ_RTN, false>(c, x0, x1, x2, x3, s, add);
+    return pack4_bytes(c);
+  } else {
+    const int QI = KIND == SRQ_INTX ? s.sub_qi : (Grid<KIND>::qmax << 16);
+    int u[4];
+    if (sr) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      t[e] = __builtin_amdgcn_fmed3f(__builtin_fmaf(x[e], s.inv, 0.0f), -QM, QM);
-      sd[e] = (int)seed[e] ^ ((int)__float_as_uint(t[e]) >> 31);
-    }
-    int w = 0;
-    if constexpr (KIND == SRQ_E5M2) {
-      w = __builtin_amdgcn_cvt_sr_bf8_f32(t[0], sd[0], w, 0);
-      w = __builtin_amdgcn_cvt_sr_bf8_f32(t[1], sd[1], w, 1);
-      w = __builtin_amdgcn_cvt_sr_bf8_f32(t[2], sd[2], w, 2);
-      w = __builtin_amdgcn_cvt_sr_bf8_f32(t[3], sd[3], w, 3);
+      for (int e = 0; e < 4; ++e) u[e] = cvt_rpi(__fmul_rn(x[e], s.inv16));
     } else {
-      w = __builtin_amdgcn_cvt_sr_fp8_f32(t[0], sd[0], w, 0);
-      w = __builtin_amdgcn_cvt_sr_fp8_f32(t[1], sd[1], w, 1);
-      w = __builtin_amdgcn_cvt_sr_fp8_f32(t[2], sd[2], w, 2);
-      w = __builtin_amdgcn_cvt_sr_fp8_f32(t[3], sd[3], w, 3);
-    }
-    const bool nan = __builtin_isunordered(x0, x1) || __builtin_isunordered(x2, x3);
-    const float least = fminf(fminf(fabsf(t[0]), fabsf(t[1])), fminf(fabsf(t[2]), fabsf(t[3])));
-    if (!(least >= LEAST) || nan) {  // a zero, or one of those
-      bool general = nan;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) general = general || (__float_as_uint(t[e]) != 0u && fabsf(t[e]) < LEAST);
-      if (general) {
+      for (int e = 0; e < 4; ++e) u[e] = cvt_flr(__fmul_rn(x[e], s.inv16));
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c[e] = (uint32_t)clamp_to(u[e], QI) + add[e];
+    if (__builtin_isunordered(x0, x1) || __builtin_isunordered(x2, x3)) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (x[e] != x[e]) c[e] = 0u;
+    }
+    const uint32_t lo = __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0602u), hi = __builtin_amdgcn_perm(c[3], c[2], 0x0c0c0602u);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+  }
+}
+
+// Eight elements, x and y four each, with their four random words: two words of codes.  (One test for the rare cases of all eight:
+// branches keep the compiler from moving work across them.)
+template <int KIND>
+__device__ __forceinline__ u32x2 quantize_octet(const float (&x)[4], const float (&y)[4], const InvScale& s, const uint32_t (&r)[4],
+                                                bool sr) {
+  if constexpr (!BY_CONVERSION<KIND>) {
+    return u32x2{quantize_word<KIND>(x[0], x[1], x[2], x[3], s, r[0], r[1], sr),
+                 quantize_word<KIND>(y[0], y[1], y[2], y[3], s, r[2], r[3], sr)};
+  } else {
+    constexpr float LEAST = KIND == SRQ_E5M2 ? 0x1p-14f : 0x1p-6f;  // smallest normal number
+    float t[2][4];
+    uint32_t w[2] = {convert_word<KIND>(x, t[0], s, r[0], r[1], sr), convert_word<KIND>(y, t[1], s, r[2], r[3], sr)};
+    float least = fabsf(t[0][0]);
+    bool nan = false;
+#pragma unroll
+    for (int e = 1; e < 8; ++e) least = fminf(least, fabsf(t[e / 4][e % 4]));
+#pragma unroll
+    for (int e = 0; e < 4; e += 2) nan = nan || __builtin_isunordered(x[e], x[e + 1]) || __builtin_isunordered(y[e], y[e + 1]);
+    if (!(least >= LEAST) || nan) {  // a zero, or one of those
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float(&v)[4] = h ? y : x;
+        bool general = __builtin_isunordered(v[0], v[1]) || __builtin_isunordered(v[2], v[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) general = general || (__float_as_uint(t[h][e]) != 0u && fabsf(t[h][e]) < LEAST);
+        if (general) {
 #pragma unroll 1
-        for (int e = 0; e < 4; ++e) {  // (a loop: rare code that should not take the room of common code)
-          const float xe = e == 0 ? x0 : e == 1 ? x1 : e == 2 ? x2 : x3;
-          const uint32_t n = e < 2 ? n0 : n1, add = (e & 1) ? n >> 16 : n & 0xFFFFu;
-          const uint32_t c = sr ? quantize_elem<KIND, SRQ_SR>(xe, s, add) : quantize_elem<KIND, SRQ_RTN>(xe, s, add);
-          w = (int)(((uint32_t)w & ~(0xFFu << (8 * e))) | (c & 0xFFu) << (8 * e));
+          for (int e = 0; e < 4; ++e) {  // (a loop: rare code that should not take the room of common code)
+            const float ve = e == 0 ? v[0] : e == 1 ? v[1] : e == 2 ? v[2] : v[3];
+            const uint32_t n = ~r[2 * h + e / 2], add = (e & 1) ? n >> 16 : n & 0xFFFFu;
+            const uint32_t c = sr ? quantize_elem<KIND, SRQ_SR>(ve, s, add) : quantize_elem<KIND, SRQ_RTN>(ve, s, add);
+            w[h] = (w[h] & ~(0xFFu << (8 * e))) | (c & 0xFFu) << (8 * e);
+          }
         }
       }
     }
-    return (uint32_t)w;
-  } else {
-    uint32_t add[4], c[4];
-    sr_addends(r0, r1, add);
-    if constexpr (Grid<KIND>::is_float) {
-      if (sr) quantize_quad<KIND, SRQ_SR, false>(c, x0, x1, x2, x3, s, add);
-      else quantize_quad<KIND, SRQ_RTN, false>(c, x0, x1, x2, x3, s, add);
-      return pack4_bytes(c);
-    } else {
-      const int QI = KIND == SRQ_INTX ? s.sub_qi : (Grid<KIND>::qmax << 16);
-      int u[4];
-      if (sr) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) u[e] = cvt_rpi(__fmul_rn(x[e], s.inv16));
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) u[e] = cvt_flr(__fmul_rn(x[e], s.inv16));
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) c[e] = (uint32_t)clamp_to(u[e], QI) + add[e];
-      if (__builtin_isunordered(x0, x1) || __builtin_isunordered(x2, x3)) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (x[e] != x[e]) c[e] = 0u;
-      }
-      const uint32_t lo = __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0602u), hi = __builtin_amdgcn_perm(c[3], c[2], 0x0c0c0602u);
-      return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-    }
+    return u32x2{w[0], w[1]};
   }
 }
 
@@ -316,10 +352,6 @@ __device__ __forceinline__ uint64_t first_block(uint64_t counter_offset, const u
 }
 
 // ---- groups of 8 consecutive elements (one Philox block) -----------------------------------
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
 // A pointer that is known to point to global memory.  One that was read out of a structure in memory is generic to the compiler,
 // whose flat instructions take no scalar base and are waited for together with those of the LDS.
 template <class T>
@@ -405,8 +437,7 @@ __device__ __forceinline__ u32x2 quantize_group_words(const float (&v)[8], const
                                                       uint32_t k1, bool sr) {
   uint32_t w[4];
   round_words(sr, block, k0, k1, w);
-  return u32x2{quantize_word<KIND>(v[0], v[1], v[2], v[3], s, w[0], w[1], sr),
-               quantize_word<KIND>(v[4], v[5], v[6], v[7], s, w[2], w[3], sr)};
+  return quantize_octet<KIND>({v[0], v[1], v[2], v[3]}, {v[4], v[5], v[6], v[7]}, s, w, sr);
 }
 
 // v_permlane32_swap: the upper 32 lanes of a and the lower 32 of b change places.
@@ -418,12 +449,22 @@ __device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
 
 // For lanes L and L + 32 that hold the two halves of each of two groups: the lower lane passes the block of the first
 // group and the upper lane that of the second; w[0], w[1] become this lane's words of the first group, w[2], w[3] of the second.
-__device__ __forceinline__ void round_words_of_pair(bool sr, uint64_t block, uint32_t k0, uint32_t k1, uint32_t (&w)[4]) {
-  round_words(sr, block, k0, k1, w);
-  if (sr) {
-    swap_halves(w[0], w[2]);
-    swap_halves(w[1], w[3]);
-  }
+__device__ __forceinline__ void round_words_of_pair(uint64_t block, uint32_t k0, uint32_t k1, uint32_t (&w)[4]) {
+  philox_block(block, k0, k1, w);
+  swap_halves(w[0], w[2]);
+  swap_halves(w[1], w[3]);
+}
+// The same for neighbouring lanes: the even one passes the block of the first group, the odd one that of the second.
+__device__ __forceinline__ void round_words_of_neighbours(uint64_t block, uint32_t k0, uint32_t k1, uint32_t (&w)[4], bool odd) {
+  philox_block(block, k0, k1, w);
+  const uint32_t n0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[0], 0xB1, 0xF, 0xF, true);  // lane ^ 1
+  const uint32_t n1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[1], 0xB1, 0xF, 0xF, true);
+  const uint32_t n2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[2], 0xB1, 0xF, 0xF, true);
+  const uint32_t n3 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w[3], 0xB1, 0xF, 0xF, true);
+  w[0] = odd ? n2 : w[0];
+  w[1] = odd ? n3 : w[1];
+  w[2] = odd ? w[2] : n0;
+  w[3] = odd ? w[3] : n1;
 }
 
 // ---- one wave, 512 consecutive binary32 elements ---------------------------------------------
@@ -443,7 +484,7 @@ __device__ __forceinline__ void store_through16(void* p, const u32x4& v) {
 __device__ __forceinline__ void store_through8(global_ptr<uint8_t> p, const u32x2& v) {
   asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1" : : "v"(p), "v"(v) : "memory");
 }
-__device__ __forceinline__ void store_through4(void* p, uint32_t v) {
+__device__ __forceinline__ void store_through4(global_ptr<uint8_t> p, uint32_t v) {
   asm volatile("global_store_dword %0, %1, off sc0 sc1" : : "v"(p), "v"(v) : "memory");
 }
 
@@ -457,7 +498,8 @@ __device__ __forceinline__ void quantize_chunk_f32(uint8_t* __restrict__ out, co
   const f32x4 a = load_source<CACHED>(reinterpret_cast<const f32x4*>(x + e0));
   const f32x4 b = load_source<CACHED>(reinterpret_cast<const f32x4*>(x + e0 + 256));
   uint32_t w[4];
-  round_words_of_pair(sr, counter_offset + chunk * (CHUNK / 8) + lane, k0, k1, w);
+  if (sr) round_words_of_pair(counter_offset + chunk * (CHUNK / 8) + lane, k0, k1, w);
+  else w[0] = w[1] = w[2] = w[3] = RTN_WORD;
   const size_t g0 = chunk * CHUNK + 8 * lane;  // the group this lane writes
   if constexpr (STORE == 2) {
     uint32_t addA[4], addB[4], ca[4], cb[4];
@@ -475,8 +517,8 @@ __device__ __forceinline__ void quantize_chunk_f32(uint8_t* __restrict__ out, co
     swap_halves(a1, b1);
     __builtin_nontemporal_store(u32x4{a0, a1, b0, b1}, as_global(reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + g0)));
   } else {
-    uint32_t wa = quantize_word<KIND>(a.x, a.y, a.z, a.w, s, w[0], w[1], sr);
-    uint32_t wb = quantize_word<KIND>(b.x, b.y, b.z, b.w, s, w[2], w[3], sr);
+    const u32x2 c = quantize_octet<KIND>({a.x, a.y, a.z, a.w}, {b.x, b.y, b.z, b.w}, s, w, sr);
+    uint32_t wa = c.x, wb = c.y;
     swap_halves(wa, wb);
     if constexpr (STORE == 1) __builtin_nontemporal_store(pack8_nibbles(wa, wb), as_global(reinterpret_cast<uint32_t*>(out + g0 / 2)));
     else __builtin_nontemporal_store(u32x2{wa, wb}, as_global(reinterpret_cast<u32x2*>(out + g0)));

@@ -87,8 +87,8 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_f32_kernel(uint8_t* __re
 // as one word (quantize_word): 12289 x 3080 bfloat16 -> E5M2 38.2 -> 33.8 us.
 //   - At most 64 registers: a wave of it then fits on a SIMD beside two of the persistent product
 //     kernel, so that on a second stream it runs beside a product and not behind it.  That takes no more than to
-//     recompute the addresses of both sides (opaque) and to round a row at a time; alone it is as fast.  Six calls on 16384 x 4096 beside int8 products
-//     of 8192 cubed, us a call at 94 registers and at 64: binary32 490 and 177, bfloat16 478 and 145.
+//     recompute the addresses of both sides (opaque) and to round a row at a time; alone it is as fast.  Six calls on 16384 x 4096
+//     beside int8 products of 8192 cubed, us a call at 94 registers and at 64: binary32 490 and 177, bfloat16 478 and 145.
 constexpr int TC = 64;
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at a multiple of four
 constexpr uint32_t TBAND = 16;
@@ -145,14 +145,15 @@ __global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
         for (int i = 0; i < PR; i += 2) {
           __builtin_amdgcn_sched_barrier(0);  // (two pairs of rows at once would not fit the registers)
           uint32_t w[4];
-          round_words_of_pair(ROUND == SRQ_SR, ctr + (e0 + (size_t)(i + half) * cols) / 8, k0, k1, w);
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            c[i + h] = quantize_word<KIND>(__uint_as_float(raw[i + h].x), __uint_as_float(raw[i + h].y),
-                                           __uint_as_float(raw[i + h].z), __uint_as_float(raw[i + h].w), inv, w[2 * h],
-                                           w[2 * h + 1], ROUND == SRQ_SR);
-            __builtin_amdgcn_sched_barrier(0);
-          }
+          if constexpr (ROUND == SRQ_SR) round_words_of_pair(ctr + (e0 + (size_t)(i + half) * cols) / 8, k0, k1, w);
+          else w[0] = w[1] = w[2] = w[3] = RTN_WORD;
+          const u32x2 q = quantize_octet<KIND>({__uint_as_float(raw[i].x), __uint_as_float(raw[i].y), __uint_as_float(raw[i].z),
+                                                __uint_as_float(raw[i].w)},
+                                               {__uint_as_float(raw[i + 1].x), __uint_as_float(raw[i + 1].y),
+                                                __uint_as_float(raw[i + 1].z), __uint_as_float(raw[i + 1].w)},
+                                               inv, w, ROUND == SRQ_SR);
+          c[i] = q.x;
+          c[i + 1] = q.y;
         }
         uint32_t upper[4], lower[4];
         turn4x4(c[0], c[1], c[2], c[3], upper);

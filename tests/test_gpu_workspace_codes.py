@@ -144,6 +144,27 @@ def test_codes_of_mixed_rounding_and_wide_ranges(kind, modes):
         assert np.array_equal(_piece(stash, 0, M * K), _expect(A, kind, oq["A"], True, 1, modes[2])), "stash"
 
 
+# rows and columns that end inside a tile, in its first half and by one group of 16; one tile and several bands; the scale takes some
+# elements into the subnormals of the formats and some to saturation
+@pytest.mark.parametrize("M,N,K,kind", [(16, 16, 16, L.E5M2), (80, 1040, 144, L.E5M2), (2192, 208, 336, L.E5M2),
+                                        (4240, 16, 80, L.E5M2), (272, 1040, 528, L.E4M3), (2096, 144, 464, L.E4M3)])
+@pytest.mark.parametrize("fwd", [L.INT8, L.INT4])
+def test_stash_codes_of_two_quantizers(M, N, K, kind, fwd):
+    say("stash, two quantizers", M, N, K, L.KIND_NAMES[kind], L.KIND_NAMES[fwd])
+    rng = np.random.default_rng(M + N)
+    A, W = ((rng.standard_normal(s) * np.exp2(rng.uniform(-24, 3, s))).astype(np.float32) for s in ((M, K), (N, K)))
+    for w_bf16 in (True, False):
+        tA, tW = to_dev(A, not w_bf16), to_dev(W, w_bf16)
+        oq = [oracle.Quant(k, s, 17, 1000 * i) for i, (k, s) in enumerate(((fwd, 0.03), (fwd, 0.04), (kind, 0.01), (kind, 0.02)))]
+        lq = [L.Quant(q.kind, q.scale, q.seed, q.counter_offset) for q in oq]
+        ws = torch.zeros(L.sr_linear_workspace_bytes(L.OP_FWD_STASH, M, N, K), dtype=torch.uint8, device=tA.device)
+        _, stash = L.sr_linear_fwd_stash(tA, tW, *lq, workspace=ws)
+        assert np.array_equal(_piece(ws, 0, M * K), _expect(tA, fwd, oq[0], False, 1)), "Q(A)"
+        assert np.array_equal(_piece(ws, _up(M * K), N * K), _expect(tW, fwd, oq[1], False, 1)), "Q(W)"
+        assert np.array_equal(_piece(stash, 0, M * K), _expect(tA, kind, oq[2], True, 1)), "Q(A)^T"
+        assert np.array_equal(_piece(stash, _up(2 * M * K), N * K), _expect(tW, kind, oq[3], True, 1)), "Q(W)^T"
+
+
 def _nib16(codes):
     """Two 4-bit values per byte: byte j of every 8 holds elements j (low nibble) and j + 8 (high nibble)
     of a run of 16 along the last axis."""
