@@ -192,6 +192,15 @@ int launch_backward_products(float* dA, float* dW, const uint8_t* dy_rm, const u
                              size_t M, size_t N, size_t K, const ProductPlan& pd, const ProductPlan& pw, float beta,
                              void* gws_d, void* gws_w, hipStream_t s, bool packed_rm = false,
                              bool packed_t = false) {
+  if (!packed_rm && !packed_t && pd.pipe == pw.pipe) {
+    const GemmScale sw{1.0f, qdY->scale, qA->scale, qdY->scale_dev, qA->scale_dev};
+    const GemmScale sd{1.0f, qdY->scale, qW->scale, qdY->scale_dev, qW->scale_dev};
+    const PairedProduct w{dW, dy_t, a_t, qA->kind, N, K, M, sw, beta == 1.0f, gws_w};
+    const PairedProduct d{dA, dy_rm, w_t, qW->kind, M, K, N, sd, false, gws_d};
+    bool done;
+    const hipError_t e = launch_gemm_pair(w, d, qdY->kind, pd.pipe, s, done);
+    if (done || e != hipSuccess) return e == hipSuccess ? SRQ_OK : SRQ_ERR_HIP;
+  }
   SliceSum sum_w{};
   int st = launch_product(dW, dy_t, qdY, a_t, qA, N, K, M, pw, beta, gws_w, s, ROLE_WEIGHT_GRADIENT, nullptr,
                           &sum_w, packed_t);

@@ -197,12 +197,7 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
   }
 }
 
-// Besides its tiles a launch can carry the slice sum of an EARLIER product (`rider`, complete when
-// this launch starts): memory-bound work that runs beside the matrix work, in the resident slots
-// the tiles leave free and in the tail of the launch, instead of in a launch of its own.  (Its workgroups are given the LDS of a
-// tile's: the launch chooses a form that leaves such slots, see choose_launch.)
-// Workgroups [0, gemm_blocks) multiply, the rest sum.  (Measured against this: the rider groups
-// spread through the launch, every fourth group of 8 -- slower.)
+// One tile of a product: workgroup `block` of its tiles, `lds` a ring of STAGES stages.
 // KG > 1: KG groups of WGM x WGN waves share the tile.  Each group multiplies its own sub-steps of every stage, and the
 // groups' sums are added through LDS at the end.  For workgroups that are few: a CU with a single workgroup of four waves
 // has one wave per SIMD, which nothing covers while it waits for LDS or at the barrier (2048 x 2048 x 4096 int8, with the
@@ -210,14 +205,8 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
 // longer ring of stages keeps more loads in flight (with four, 17.4 with the matrix work left out, 23.8 in all; with three 23.1).
 // SETS = 2 (one group): two sets of accumulators, for the first and the second half of the sub-steps of every stage, added at the
 // end: the sums of two groups of waves, in the same order.
-template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1, int SETS = 1>
-__global__ __launch_bounds__(WGM* WGN* KG * 64, SETS) void gemm_nt_kernel(GemmParams g, SliceSum rider, uint32_t gemm_blocks) {
-  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-  if (blockIdx.x >= gemm_blocks) {
-    if (rider.is_int) slice_sum<true>(rider, blockIdx.x - gemm_blocks, gridDim.x - gemm_blocks);
-    else slice_sum<false>(rider, blockIdx.x - gemm_blocks, gridDim.x - gemm_blocks);
-    return;
-  }
+template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG, int SETS>
+__device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block, uint8_t* lds) {
   constexpr int NG = WGM * WGN, NW = NG * KG;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile (p x q)
   constexpr int TM = WTM / 32, TN = WTN / 32;
@@ -250,7 +239,7 @@ __global__ __launch_bounds__(WGM* WGN* KG * 64, SETS) void gemm_nt_kernel(GemmPa
   // contraction of a few panels, instead of on every slice of its tiles.
   constexpr uint32_t GROUP = 8;
   const uint32_t ntiles = g.tiles_p * g.tiles_q, nwork = ntiles * g.nsplit, chunk = (nwork + 7u) >> 3;
-  const uint32_t work = (blockIdx.x & 7u) * chunk + (blockIdx.x >> 3);
+  const uint32_t work = (block & 7u) * chunk + (block >> 3);
   if (work >= nwork) return;  // padding of the last XCD's range (whole workgroup leaves)
   const uint32_t slice = work / ntiles, tile = work - slice * ntiles;
   const uint32_t band = tile / (GROUP * g.tiles_q), band_p = band * GROUP;
@@ -483,6 +472,42 @@ __global__ __launch_bounds__(WGM* WGN* KG * 64, SETS) void gemm_nt_kernel(GemmPa
       if (i0 + IP < TM) __syncthreads();
     }
   }
+}
+
+// Besides its tiles a launch can carry the slice sum of an EARLIER product (`rider`, complete when
+// this launch starts): memory-bound work that runs beside the matrix work, in the resident slots
+// the tiles leave free and in the tail of the launch, instead of in a launch of its own.  (Its workgroups are given the LDS of a
+// tile's: the launch chooses a form that leaves such slots, see choose_launch.)
+// Workgroups [0, gemm_blocks) multiply, the rest sum.  (Measured against this: the rider groups
+// spread through the launch, every fourth group of 8 -- slower.)
+template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1, int SETS = 1>
+__global__ __launch_bounds__(WGM* WGN* KG * 64, SETS) void gemm_nt_kernel(GemmParams g, SliceSum rider, uint32_t gemm_blocks) {
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  if (blockIdx.x >= gemm_blocks) {
+    if (rider.is_int) slice_sum<true>(rider, blockIdx.x - gemm_blocks, gridDim.x - gemm_blocks);
+    else slice_sum<false>(rider, blockIdx.x - gemm_blocks, gridDim.x - gemm_blocks);
+    return;
+  }
+  product_tile<MMA, BM, BN, WGM, WGN, STAGES, KG, SETS>(g, blockIdx.x, lds);
+}
+
+// Two products in one launch: the uncut weight and input gradients of a layer.  Workgroups [0, blocks_a) multiply the first (the
+// one with the longer tiles), the rest the second, in tiles of one size, so that both fill the same slots: the stores of one's tiles go out
+// beside the matrix work of the other's, a product of few tiles leaves no CU idle, and there is one start and one end instead of two.
+// choose_pair says where that is faster.  The results are bit for bit those of the products in launches of their own.
+template <int WGM_, int WGN_, int KG_, int SETS_>
+struct Waves {
+  static constexpr int WGM = WGM_, WGN = WGN_, KG = KG_, SETS = SETS_, THREADS = WGM * WGN * KG * 64;
+};
+template <class MMA, int BM, int BN, int STAGES, class WA, class WB>
+__global__ __launch_bounds__(WA::THREADS, (WA::SETS > WB::SETS ? WA::SETS : WB::SETS)) void gemm_pair_kernel(GemmParams a, GemmParams b,
+                                                                                                         uint32_t blocks_a) {
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  static_assert(WA::THREADS == WB::THREADS, "one launch");
+  if (blockIdx.x < blocks_a)
+    product_tile<MMA, BM, BN, WA::WGM, WA::WGN, STAGES, WA::KG, WA::SETS>(a, blockIdx.x, lds);
+  else
+    product_tile<MMA, BM, BN, WB::WGM, WB::WGN, STAGES, WB::KG, WB::SETS>(b, blockIdx.x - blocks_a, lds);
 }
 
 // ---- 256 x 256 tiles, workgroups that stay -------------------------------------------------------
@@ -984,6 +1009,19 @@ uint32_t slice_sum_blocks(const SliceSum& r, uint32_t threads, uint32_t per_thre
   return (uint32_t)(blocks < 1 ? 1 : blocks);
 }
 
+// The slice sum of a product (nothing to sum if it is not cut).
+template <class MMA>
+SliceSum own_slice_sum(const GemmParams& g) {
+  SliceSum own{};
+  if (g.nsplit > 1) {
+    own.partial = g.partial; own.out = g.out; own.nsplit = g.nsplit; own.total = (size_t)g.P * g.Q;
+    own.s = GemmScale{g.alpha, g.sx, g.sz, g.sx_dev, g.sz_dev};
+    own.accumulate = g.accumulate;
+    own.is_int = std::is_same<typename MMA::acc_t, v16i>::value ? 1 : 0;
+  }
+  return own;
+}
+
 template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG = 1, int SETS = 1>
 hipError_t launch_tile(GemmParams g, const SliceSumPlan& ss, hipStream_t stream) {
   constexpr int LDS_BYTES = STAGES * (BM + BN) * BK;
@@ -1006,13 +1044,7 @@ hipError_t launch_tile(GemmParams g, const SliceSumPlan& ss, hipStream_t stream)
   kern<<<dim3(gemm_blocks + carry_blocks), WGM * WGN * KG * 64, LDS_BYTES, stream>>>(g, carry, gemm_blocks);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  SliceSum own{};
-  if (g.nsplit > 1) {
-    own.partial = g.partial; own.out = g.out; own.nsplit = g.nsplit; own.total = (size_t)g.P * g.Q;
-    own.s = GemmScale{g.alpha, g.sx, g.sz, g.sx_dev, g.sz_dev};
-    own.accumulate = g.accumulate;
-    own.is_int = std::is_same<typename MMA::acc_t, v16i>::value ? 1 : 0;
-  }
+  const SliceSum own = own_slice_sum<MMA>(g);
   if (ss.defer) {
     *ss.defer = own;
   } else if (own.total > 0) {
@@ -1040,13 +1072,7 @@ hipError_t launch_persist(GemmParams g, const SliceSumPlan& ss, hipStream_t stre
   kern<<<dim3(8 * slots), 512, LDS_BYTES, stream>>>(g, carry);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  SliceSum own{};
-  if (g.nsplit > 1) {
-    own.partial = g.partial; own.out = g.out; own.nsplit = g.nsplit; own.total = (size_t)g.P * g.Q;
-    own.s = GemmScale{g.alpha, g.sx, g.sz, g.sx_dev, g.sz_dev};
-    own.accumulate = g.accumulate;
-    own.is_int = std::is_same<typename MMA::acc_t, v16i>::value ? 1 : 0;
-  }
+  const SliceSum own = own_slice_sum<MMA>(g);
   if (ss.defer) {
     *ss.defer = own;
   } else if (own.total > 0) {
@@ -1076,6 +1102,51 @@ hipError_t launch_mma(GemmParams g, const Launch& l, const SliceSumPlan& ss, hip
       break;
   }
   return hipErrorInvalidValue;
+}
+
+template <class MMA, int BM, int BN, int STAGES, class WA, class WB>
+hipError_t launch_pair(GemmParams a, GemmParams b, hipStream_t stream) {
+  constexpr int LDS_BYTES = STAGES * (BM + BN) * BK;
+  auto kern = &gemm_pair_kernel<MMA, BM, BN, STAGES, WA, WB>;
+  static const hipError_t configured = hipFuncSetAttribute(
+      reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+  if (configured != hipSuccess) return configured;
+  uint32_t blocks[2];
+  GemmParams* const both[2] = {&a, &b};
+  for (int i = 0; i < 2; ++i) {
+    GemmParams& g = *both[i];
+    g.tiles_p = (g.P + BM - 1) / BM;
+    g.tiles_q = (g.Q + BN - 1) / BN;
+    blocks[i] = (g.tiles_p * g.tiles_q * g.nsplit + 7) / 8 * 8;
+  }
+  kern<<<dim3(blocks[0] + blocks[1]), WA::THREADS, LDS_BYTES, stream>>>(a, b, blocks[0]);
+  hipError_t e = hipGetLastError();
+  for (int i = 0; i < 2 && e == hipSuccess; ++i)
+    if (both[i]->nsplit > 1) e = launch_slice_sum(own_slice_sum<MMA>(*both[i]), stream);
+  return e;
+}
+
+// wa, wb: sets of accumulators (128 x 128 tiles) or groups of waves (64 x 64) of the two products
+template <class MMA>
+hipError_t launch_pair_mma(const GemmParams& a, const GemmParams& b, PairForm form, int wa, int wb, hipStream_t stream) {
+  constexpr bool IS_INT = std::is_same<MMA, I8Mma>::value;
+  using One = Waves<2, 2, 1, 1>;
+  using Two = Waves<2, 2, 1, 2>;
+  using G2 = Waves<2, 2, 2, 1>;
+  if (form == PAIR_128x128) {
+    if constexpr (IS_INT) {
+      return launch_pair<MMA, 128, 128, 2, One, One>(a, b, stream);
+    } else {
+      if (wa == 1) return wb == 1 ? launch_pair<MMA, 128, 128, 2, One, One>(a, b, stream) : launch_pair<MMA, 128, 128, 2, One, Two>(a, b, stream);
+      return wb == 1 ? launch_pair<MMA, 128, 128, 2, Two, One>(a, b, stream) : launch_pair<MMA, 128, 128, 2, Two, Two>(a, b, stream);
+    }
+  }
+  if constexpr (BK / MMA::KSTEP >= 4 && !IS_INT) {
+    using G4 = Waves<1, 2, 4, 1>;
+    if (wa == 4) return wb == 4 ? launch_pair<MMA, 64, 64, 3, G4, G4>(a, b, stream) : launch_pair<MMA, 64, 64, 3, G4, G2>(a, b, stream);
+    if (wb == 4) return launch_pair<MMA, 64, 64, 3, G2, G4>(a, b, stream);
+  }
+  return launch_pair<MMA, 64, 64, 3, G2, G2>(a, b, stream);
 }
 
 // Tiles and contraction slices of gemm_cut3_kernel, by the same model: 128 x 128 tiles of four waves,
@@ -1175,6 +1246,46 @@ bool gemm_operands_addressable(size_t P, size_t Q, size_t R, int pipe) {
   return (P + 256) * rb < (1ull << 31) && (Q + 256) * rb < (1ull << 31);
 }
 
+namespace {
+
+// Runs f.template operator()<MMA>() with the matrix pipeline of `pipe` for operands of these kinds.
+template <class F>
+hipError_t with_pipeline(int pipe, int kindX, int kindZ, const F& f) {
+  if (pipe == PIPE_I8) return f(I8Mma{});
+  if (pipe == PIPE_BF16) return f(BF16Mma{});
+  // the Z operand is the first MFMA operand, X the second
+  const int fx = kindX == SRQ_E5M2, fz = kindZ == SRQ_E5M2;
+  if (pipe == PIPE_F16C || pipe == PIPE_F16W) {
+    if (!fz && !fx) return f(F8F16Mma<0, 0>{});
+    if (!fz && fx) return f(F8F16Mma<0, 1>{});
+    if (fz && !fx) return f(F8F16Mma<1, 0>{});
+    return f(F8F16Mma<1, 1>{});
+  }
+  if (!fz && !fx) return f(F8Mma<0, 0>{});
+  if (!fz && fx) return f(F8Mma<0, 1>{});
+  if (fz && !fx) return f(F8Mma<1, 0>{});
+  return f(F8Mma<1, 1>{});
+}
+
+GemmParams product_params(float* out, const uint8_t* X, const uint8_t* Z, size_t P, size_t Q, size_t row_bytes, size_t pitch,
+                          const GemmScale& s, bool accumulate, void* workspace, bool x_packed) {
+  GemmParams g;
+  g.out = out;
+  g.partial = static_cast<uint32_t*>(workspace);
+  g.X = X; g.Z = Z;
+  g.P = (uint32_t)P; g.Q = (uint32_t)Q; g.R = (uint32_t)row_bytes;
+  g.pitch = (uint32_t)pitch;
+  g.pitch_x = (uint32_t)(x_packed ? pitch / 2 : pitch);
+  g.k_per_split = 0;
+  g.nsplit = 1;
+  g.tiles_p = g.tiles_q = 0;
+  g.alpha = s.alpha; g.sx = s.sx; g.sz = s.sz; g.sx_dev = s.sx_dev; g.sz_dev = s.sz_dev;
+  g.accumulate = accumulate ? 1 : 0;
+  return g;
+}
+
+}  // namespace
+
 hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint8_t* Z, int kindZ,
                              size_t P, size_t Q, size_t R, size_t pitch, int pipe, const GemmScale& s,
                              bool accumulate, void* workspace, hipStream_t stream, ProductRole role,
@@ -1183,37 +1294,35 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
   const size_t row_bytes = pipe == PIPE_BF16 ? 2 * R : R;
   const Plan pl = plan_for(P, Q, R, pipe);
   if (x_packed && !(pipe == PIPE_I8 && pl.tile == 0)) return hipErrorInvalidValue;  // see gemm_takes_packed_x
-  GemmParams g;
-  g.out = out;
-  g.partial = static_cast<uint32_t*>(workspace);
-  g.X = X; g.Z = Z;
-  g.P = (uint32_t)P; g.Q = (uint32_t)Q; g.R = (uint32_t)row_bytes;
-  g.pitch = (uint32_t)pitch;
-  g.pitch_x = (uint32_t)(x_packed ? pitch / 2 : pitch);
+  GemmParams g = product_params(out, X, Z, P, Q, row_bytes, pitch, s, accumulate, workspace, x_packed);
   g.k_per_split = pl.k_per_split;
   g.nsplit = pl.nsplit;
-  g.tiles_p = g.tiles_q = 0;
-  g.alpha = s.alpha; g.sx = s.sx; g.sz = s.sz; g.sx_dev = s.sx_dev; g.sz_dev = s.sz_dev;
-  g.accumulate = accumulate ? 1 : 0;
   if (x_packed) return launch_persist<I8Mma, true>(g, ss, stream);
   // integer sums are the same in every form: there the launch counts, not the role
   const bool leaves = pipe == PIPE_I8 ? defer != nullptr : role == ROLE_WEIGHT_GRADIENT;
   const uint32_t rides = carry && carry->total > 0 ? carry->nsplit : 0;
   const Launch l = choose_launch(pl, P, Q, row_bytes, pipe, leaves, rides);
-  if (pipe == PIPE_I8) return launch_mma<I8Mma>(g, l, ss, stream);
-  if (pipe == PIPE_BF16) return launch_mma<BF16Mma>(g, l, ss, stream);
-  // the Z operand is the first MFMA operand, X the second
-  const int fx = kindX == SRQ_E5M2, fz = kindZ == SRQ_E5M2;
-  if (pipe == PIPE_F16C || pipe == PIPE_F16W) {
-    if (!fz && !fx) return launch_mma<F8F16Mma<0, 0>>(g, l, ss, stream);
-    if (!fz && fx) return launch_mma<F8F16Mma<0, 1>>(g, l, ss, stream);
-    if (fz && !fx) return launch_mma<F8F16Mma<1, 0>>(g, l, ss, stream);
-    return launch_mma<F8F16Mma<1, 1>>(g, l, ss, stream);
-  }
-  if (!fz && !fx) return launch_mma<F8Mma<0, 0>>(g, l, ss, stream);
-  if (!fz && fx) return launch_mma<F8Mma<0, 1>>(g, l, ss, stream);
-  if (fz && !fx) return launch_mma<F8Mma<1, 0>>(g, l, ss, stream);
-  return launch_mma<F8Mma<1, 1>>(g, l, ss, stream);
+  return with_pipeline(pipe, kindX, kindZ, [&](auto mma) { return launch_mma<decltype(mma)>(g, l, ss, stream); });
+}
+
+hipError_t launch_gemm_pair(const PairedProduct& w, const PairedProduct& d, int kindX, int pipe, hipStream_t stream, bool& done) {
+  done = false;
+  if (pipe == PIPE_BF16 || (pipe != PIPE_I8 && (w.kindZ == SRQ_E5M2) != (d.kindZ == SRQ_E5M2))) return hipSuccess;
+  const Pair p = choose_pair(w.R, w.P, w.Q, pipe);  // M, N, K
+  if (p.form == PAIR_NONE) return hipSuccess;
+  GemmParams gw = product_params(w.out, w.X, w.Z, w.P, w.Q, w.R, w.R, w.s, w.accumulate, w.partial, false);
+  GemmParams gd = product_params(d.out, d.X, d.Z, d.P, d.Q, d.R, d.R, d.s, d.accumulate, d.partial, false);
+  gw.nsplit = p.w.nsplit;
+  gw.k_per_split = p.w.k_per_split;
+  gd.nsplit = p.d.nsplit;
+  gd.k_per_split = p.d.k_per_split;
+  done = true;
+  return with_pipeline(pipe, kindX, w.kindZ, [&](auto mma) {
+    using MMA = decltype(mma);
+    if constexpr (std::is_same<MMA, BF16Mma>::value) return hipErrorInvalidValue;
+    else return p.weight_first ? launch_pair_mma<MMA>(gw, gd, p.form, p.w.waves, p.d.waves, stream)
+                               : launch_pair_mma<MMA>(gd, gw, p.form, p.d.waves, p.w.waves, stream);
+  });
 }
 
 hipError_t launch_slice_sum(const SliceSum& r, hipStream_t stream) {

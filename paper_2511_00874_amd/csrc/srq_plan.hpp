@@ -203,4 +203,111 @@ inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes
   return room ? Launch{FORM_128x128_G2, pl.nsplit, pl.k_per_split, 3} : Launch{four_waves, pl.nsplit, pl.k_per_split, 2};
 }
 
+// The two products of a backward call, dW (N x K, contraction M) and dA (M x K, contraction N), in one launch of tiles of
+// one size, each over the slices that it is planned with (sums of slices follow in launches of their own).  Not where one takes
+// the 256 x 256 tiles, and only forms in which an accumulator of a binary32 sum holds the same part of the contraction as in a
+// launch of its own (sets of accumulators stand for two groups of waves on 128 x 128 tiles; 64 x 64 tiles have two or four groups): the
+// results are the same bit for bit.
+//
+// Two launches leave the chip idle twice while their last tiles are written, and a product of few tiles leaves CUs idle for all of its
+// time.  Both products from codes, us in two launches and in one: M, N, K 4096 x 2048 x 2048 int8 44.1 -> 39.5 (E5M2, not taken,
+// 67.8 -> 69.9: three tiles a CU in one launch, 128 x 192 tiles in two); 2432 x 4240 x 1216 E5M2 59.3 -> 54.0; 1008 x 3072 x 768
+// E5M2 22.1 -> 14.6 (64 x 64); 2048 x 1200 x 1200 E5M2 24.6 -> 18.0.  Straight lines fitted to 640 calls of random sizes say which is
+// faster; 128 x 128 tiles that are not all on the chip at once have to gain more, as a round of few tiles at the end costs most (534 tiles
+// of 12976 x 2384 x 384 int8 46.0 -> 54.7, not taken).
+// Over 1440 other calls, 0.80 of the time of two launches on average where one is taken, 2 % of them more than 2 % slower.
+// Never 128 x 128 where a product has at most 128 rows (4144 x 80 x 784 E5M2 12.3 -> 15.0: alone it takes 64 x 64 tiles), nor where the
+// results do not fit the last-level cache, whose writes then bound both (30656 x 112 x 5760 int8 170 -> 200).
+constexpr size_t PAIR_MAX_RESULTS = (size_t)64 << 20;  // of 4 bytes
+enum PairForm { PAIR_NONE, PAIR_128x128, PAIR_64x64 };
+struct Paired {
+  int waves;  // sets of accumulators (128 x 128 tiles of four waves) or groups of waves (64 x 64 of eight)
+  uint32_t nsplit, k_per_split;
+};
+struct Pair {
+  PairForm form;
+  bool weight_first;  // the product with the longer tiles goes first
+  Paired w, d;
+};
+struct PairLines {  // microseconds: constant, per stage (of a tile, by form, or of all tiles a CU), of the last tiles to end beyond an even
+                    // share, MB of results, MB of partial sums, a sum; most of the separate launches' time that is worth a pair of
+                    // 128 x 128 tiles
+  double apart, group128, group64_one, group64_two, load_apart128, last_apart128, load_apart192, last_apart192, out, partial, sum;
+  double pair128, load128, last128, out128, partial128, sum128;
+  double pair64, load64, partial64, sum64;
+  double worth128;
+};
+constexpr PairLines PAIR_LINES[2] = {
+    {5.7, 0.51, 0.21, 0.42, 0.53, 0.56, 0.70, 0.51, 0.15, 0.55, 1.5, 3.2, 0.57, 0.44, 0.07, 0.43, 1.7, 4.2, 0.27, 0.42, 1.7, 0.93},
+    {6.7, 0.77, 0.27, 0.46, 0.78, 0.82, 1.21, 0.39, 0.13, 0.38, 2.3, 3.7, 0.92, 0.24, 0.05, 0.34, 2.6, 4.8, 0.31, 0.36, 1.7, 0.88}};  // widened
+// Stages until the last of n1 tiles of s1 stages and then n2 of s2 <= s1 ends, where `slots` of them run at a time.
+inline uint64_t stages_to_end(uint64_t n1, uint64_t s1, uint64_t n2, uint64_t s2, uint64_t slots) {
+  const uint64_t full = n1 / slots * s1, late = n1 % slots, first_end = full + (late ? s1 : 0);
+  const uint64_t even = (n1 * s1 + n2 * s2 + slots - 1) / slots;
+  uint64_t lo = even > first_end ? even : first_end, hi = lo + s2;  // (an even share and one tile are enough)
+  while (lo < hi) {
+    const uint64_t t = (lo + hi) / 2;
+    if (late * ((t - first_end) / s2) + (slots - late) * ((t - full) / s2) >= n2) hi = t;
+    else lo = t + 1;
+  }
+  return lo;
+}
+inline Pair choose_pair(size_t M, size_t N, size_t K, int pipe) {
+  const bool is_int = pipe == PIPE_I8;
+  if (pipe == PIPE_BF16 || (M + N) * K > PAIR_MAX_RESULTS) return Pair{PAIR_NONE, false, {1, 1, 0}, {1, 1, 0}};
+  const PairLines& c = PAIR_LINES[pipe == PIPE_F16C || pipe == PIPE_F16W];
+  const Launch l[2] = {choose_launch(plan_for(N, K, M, pipe), N, K, M, pipe, true, 0),
+                       choose_launch(plan_for(M, K, N, pipe), M, K, N, pipe, false, 0)};
+  Pair p{PAIR_NONE, l[0].k_per_split >= l[1].k_per_split, {1, l[0].nsplit, l[0].k_per_split}, {1, l[1].nsplit, l[1].k_per_split}};
+  if (l[0].form == FORM_256x256 || l[1].form == FORM_256x256) return p;
+  constexpr uint64_t SLOTS = 2 * NUM_CU;  // workgroups of four waves that are on the chip at a time
+  const size_t rows[2] = {N, M};
+  bool sets = M > 128 && N > 128, groups = true;  // the forms that keep the sums as they are
+  int halves[2], parts[2];
+  uint64_t n128[2], stages[2];
+  double apart = c.apart, out = 0.0, partial = 0.0, sums = 0.0, load64 = 0.0;
+  for (int i = 0; i < 2; ++i) {
+    const Form f = l[i].form;
+    const bool two = f == FORM_128x128_G2 || f == FORM_128x128_S2 || f == FORM_64x64_G2;
+    halves[i] = two && !is_int ? 2 : 1;
+    parts[i] = f == FORM_64x64_G4 ? 4 : 2;
+    sets = sets && f != FORM_64x64_G4;
+    groups = groups && (two || is_int || f == FORM_64x64_G4);
+    stages[i] = (l[i].k_per_split + STAGE_BYTES - 1) / STAGE_BYTES;
+    const auto tiles = [&](size_t bm, size_t bn) { return (uint64_t)((rows[i] + bm - 1) / bm) * ((K + bn - 1) / bn) * l[i].nsplit; };
+    const uint64_t t64 = tiles(64, 64);
+    n128[i] = tiles(128, 128);
+    const double s = (double)stages[i], mb = 4e-6 * (double)rows[i] * (double)K;
+    load64 += (double)t64 * s / NUM_CU;
+    if (f == FORM_128x128_G2) apart += c.group128 * s;
+    else if (f == FORM_64x64_G2 || f == FORM_64x64_G4)
+      apart += (t64 <= NUM_CU ? c.group64_one : c.group64_two * (t64 > SLOTS ? (double)t64 / SLOTS : 1.0)) * s;
+    else {
+      const uint64_t t = f == FORM_128x192 ? tiles(128, 192) : n128[i];
+      const double load = (double)t * s / NUM_CU, last = (double)((t + SLOTS - 1) / SLOTS) * s - 0.5 * load;
+      apart += f == FORM_128x192 ? c.load_apart192 * load + c.last_apart192 * last : c.load_apart128 * load + c.last_apart128 * last;
+    }
+    out += mb;
+    if (l[i].nsplit > 1) {
+      partial += l[i].nsplit * mb;
+      sums += 1.0;
+      if (i == 1) apart += c.sum;  // (the other one's sum rides)
+    }
+  }
+  apart += c.out * out + c.partial * partial;
+  const int a = p.weight_first ? 0 : 1, b = 1 - a;
+  const double load128 = (double)(n128[0] * stages[0] + n128[1] * stages[1]) / NUM_CU;
+  const double last = (double)stages_to_end(n128[a], stages[a], n128[b], stages[b], SLOTS) - 0.5 * load128;
+  const double t128 = c.pair128 + c.load128 * load128 + c.last128 * last + c.out128 * out + c.partial128 * partial + c.sum128 * sums;
+  const double t64 = c.pair64 + c.load64 * load64 + c.partial64 * partial + c.sum64 * sums;
+  const bool at_once = n128[0] + n128[1] <= SLOTS;
+  const bool small = groups && (!sets || t64 <= t128);
+  const double worth = (small ? 0.95 : at_once ? 1.0 : c.worth128) * (sums > 0.0 ? 0.95 : 1.0);
+  if (!(sets || groups) || (small ? t64 : t128) >= worth * apart) return p;
+  p.form = small ? PAIR_64x64 : PAIR_128x128;
+  p.w.waves = small ? parts[0] : halves[0];
+  p.d.waves = small ? parts[1] : halves[1];
+  return p;
+}
+
 }  // namespace srq

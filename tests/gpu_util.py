@@ -18,6 +18,12 @@ GROUP_SHAPES = [(16, 16, 16), (65, 63, 144), (130, 67, 1040), (257, 250, 2064), 
 RIDE_SHAPES = [(2048, 192, 352), (976, 208, 560), (4240, 1360, 224), (2736, 432, 1312), (4992, 1056, 672), (6432, 208, 304),
                (4304, 320, 288), (7296, 1968, 448), (5920, 1936, 608), (4080, 2000, 752), (7472, 3488, 288)]
 
+# M, N, K of backward calls whose two products go in one launch: tiles of both sizes, either product first, sets and groups of either, slices
+# of either or both, rows and columns that end inside a tile (test_plan.py says what which shape takes)
+PAIR_SHAPES = [(16, 16, 16), (528, 16, 16), (16, 528, 16), (1008, 3072, 768), (592, 5584, 704), (2000, 2272, 1392),
+               (1440, 1040, 3664), (784, 144, 4752), (5408, 144, 672), (4592, 5008, 80), (5104, 784, 288), (144, 3008, 1184),
+               (1696, 144, 2016), (3344, 3536, 128), (2000, 4352, 16), (6192, 3888, 16), (3408, 3648, 80)]
+
 
 def say(*a):
     print(*a, flush=True)

@@ -6,8 +6,8 @@ import torch
 import oracle
 from paper_2511_00874_amd import lib as L
 from paper_2511_00874_amd import synth
-from gpu_util import (DEV, GROUP_SHAPES, RIDE_SHAPES, check_product, check_product_f8_pipeline, group_max_sum, host_src, say,
-                      to_dev)
+from gpu_util import (DEV, GROUP_SHAPES, PAIR_SHAPES, RIDE_SHAPES, check_product, check_product_f8_pipeline, group_max_sum,
+                      host_src, say, to_dev)
 
 pytestmark = pytest.mark.gpu
 
@@ -373,6 +373,27 @@ def test_backward_in_one_call_equals_the_separate_calls_where_a_slice_sum_rides(
         idx = np.random.default_rng(5).integers(0, got.numel(), size=2000).astype(np.uint64)
         ref, ab = f(host_src(x), host_src(z), qx, qz, want_abs=True, at=idx)
         check_product(got.view(-1).cpu().numpy()[idx.astype(np.int64)], ref, ab)
+
+
+@pytest.mark.parametrize("M,N,K", PAIR_SHAPES)
+@pytest.mark.parametrize("kind,kind_dy,flags", [(L.INT8, L.INT8, 0), (L.E5M2, L.E5M2, 0), (L.E4M3, L.E5M2, 0),
+                                                (L.E4M3, L.E4M3, L.FLAG_F8_PIPELINE)])
+def test_backward_products_in_one_launch_equal_the_separate_calls(M, N, K, kind, kind_dy, flags):
+    say("pair", M, N, K, L.KIND_NAMES[kind], L.KIND_NAMES[kind_dy], flags)
+    A, W, dY = synth.single_layer(M, N, K, 29, std_dy=1e-3)
+    A, W, dY = to_dev(A), to_dev(W, True), to_dev(dY)
+    q = [L.Quant(k, oracle.absmax_scale(host_src(t), k), 4, i << 24, flags=flags)
+         for i, (t, k) in enumerate(((dY, kind_dy), (W, kind), (A, kind)))]
+    want_dA, want_dW = L.sr_linear_bwd_data(dY, W, q[0], q[1]), L.sr_linear_bwd_weight(dY, A, q[0], q[2])
+    dA, dW = L.sr_linear_bwd(dY, W, A, *q)
+    assert torch.equal(dA, want_dA) and torch.equal(dW, want_dW)
+    dW2 = dW.clone()
+    L.sr_linear_bwd(dY, W, A, *q, out_dW=dW2, beta=1.0)
+    assert torch.equal(dW2, dW + dW)
+    qf = [L.Quant(L.INT8, oracle.absmax_scale(host_src(t), L.INT8), 5) for t in (A, W)]
+    _, stash = L.sr_linear_fwd_stash(A, W, *qf, q[2], q[1])
+    dA3, dW3 = L.sr_linear_bwd_stashed(dY, stash, K, *q)
+    assert torch.equal(dA3, want_dA) and torch.equal(dW3, want_dW)
 
 
 # weight gradients whose bfloat16 form cuts the contraction into more slices than the code form would by its own

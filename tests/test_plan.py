@@ -5,7 +5,7 @@ import subprocess
 
 import pytest
 
-from gpu_util import GROUP_SHAPES, RIDE_SHAPES
+from gpu_util import GROUP_SHAPES, PAIR_SHAPES, RIDE_SHAPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2511_00874_amd", "csrc")
@@ -20,6 +20,11 @@ extern "C" void plan(size_t P, size_t Q, size_t R, int pipe, int leaves, unsigne
   const Launch l = choose_launch(pl, P, Q, pipe == PIPE_BF16 ? 2 * R : R, pipe, leaves, rides);
   o[0] = pl.nsplit; o[1] = l.form; o[2] = l.nsplit; o[3] = l.k_per_split; o[4] = l.ring;
 }
+extern "C" void pair(size_t M, size_t N, size_t K, int pipe, unsigned* o) {
+  const Pair p = choose_pair(M, N, K, pipe);
+  const unsigned v[] = {(unsigned)p.form, p.weight_first, (unsigned)p.w.waves, p.w.nsplit, p.w.k_per_split, (unsigned)p.d.waves, p.d.nsplit, p.d.k_per_split};
+  for (int i = 0; i < 8; ++i) o[i] = v[i];
+}
 """
 
 
@@ -31,12 +36,54 @@ def plan(tmp_path_factory):
                    check=True)
     lib = C.CDLL(str(d / "plan.so"))
     lib.plan.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_int, C.c_uint, C.c_void_p]
+    lib.pair.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_void_p]
+
+    def pair(M, N, K, pipe):
+        o = (C.c_uint * 8)()
+        lib.pair(M, N, K, pipe, o)
+        return dict(zip(("form", "weight_first", "waves_w", "slices_w", "k_w", "waves_d", "slices_d", "k_d"), o))
 
     def f(P, Q, R, pipe, leaves=False, rides=0):
         o = (C.c_uint * 5)()
         lib.plan(P, Q, R, pipe, leaves, rides, o)
         return dict(planned_slices=o[0], form=o[1], slices=o[2], k_per_split=o[3], ring=o[4])
+    f.pair = pair
     return f
+
+
+def test_pairs_keep_the_sums_of_the_launches_they_replace(plan):
+    # over random calls: a pair has the slices of the separate launches, and in binary32 as many partial sums in them; no pair for
+    # bfloat16 operands or 256 x 256 tiles
+    import random
+    rng = random.Random(5)
+    taken = 0
+    for _ in range(4000):
+        M, N, K = (16 * int(2 ** rng.uniform(0, 9)) for _ in range(3))
+        for pipe in range(5):
+            p = plan.pair(M, N, K, pipe)
+            w, d = plan(N, K, M, pipe, True), plan(M, K, N, pipe)
+            if pipe == BF16 or P256 in (w["form"], d["form"]):
+                assert p["form"] == 0
+            if p["form"] == 0:
+                continue
+            taken += 1
+            for which, l in (("w", w), ("d", d)):
+                assert (p["slices_" + which], p["k_" + which]) == (l["slices"], l["k_per_split"])
+                if pipe != I8:
+                    parts = 4 if l["form"] == P64_G4 else 2 if l["form"] in (P128_S2, P128_G2, P64_G2) else 1
+                    assert p["waves_" + which] == parts
+                assert p["waves_" + which] in ((1, 2) if p["form"] == 1 else (2, 4))
+    assert taken > 4000
+
+
+def test_pair_shapes_cover_the_forms(plan):
+    seen = {pipe: {(p["form"], p["waves_w"], p["waves_d"], p["weight_first"], p["slices_w"] > 1, p["slices_d"] > 1)
+                   for p in (plan.pair(*s, pipe) for s in PAIR_SHAPES)} for pipe in (I8, F8, F16C)}
+    for pipe in seen:
+        assert {f[0] for f in seen[pipe]} >= {1, 2} and {f[3] for f in seen[pipe]} == {0, 1}
+        assert any(f[4] for f in seen[pipe]) and any(f[5] for f in seen[pipe])
+    assert {f[1:3] for f in seen[F16C] if f[0] == 1} == {(1, 1), (1, 2), (2, 1), (2, 2)}
+    assert {f[1:3] for f in seen[F16C] if f[0] == 2} == {(2, 2), (2, 4), (4, 2), (4, 4)}
 
 
 def test_four_groups_are_for_binary32_sums(plan):
