@@ -145,6 +145,30 @@ def test_absmax_scale_finds_the_maximum_wherever_it_is(n, bf16):
         assert s == (1.0 if where is None else float(np.float32(abs(v)) / np.float32(127)))
 
 
+# Inf and NaN of every payload take no part, beside the largest finite value, in either half of a bfloat16 word; values whose
+# neighbour in that word has all its bits set; nothing but Inf and NaN; batched and alone
+@pytest.mark.parametrize("n", [2, 9, 4103, 65536, 262159])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_absmax_scale_of_finite_values_beside_others(n, bf16):
+    bits = [0x7F800000, 0xFF800000, 0x7FFF0000, 0xFF810000, 0x7FC00000, 0xFFFF0000]
+    if not bf16:
+        bits += [0x7F800001, 0xFFFFFFFF]
+    others = np.array(bits, np.uint32).view(np.float32)
+    for big in (np.uint32(0x7F7F0000).view(np.float32), np.float32(1.0), np.float32(2.0 ** -130), None):
+        for at in (0, 1, n // 2, n - 1):
+            y = np.resize(others, n)
+            if big is not None:
+                y[at] = -big if at % 2 else big
+                y[(at + 1) % n] = np.float32(0.0) if at % 3 else others[-1]
+            say("absmax beside Inf and NaN", n, "bf16" if bf16 else "f32", big, at)
+            high = (y.view(np.uint32) >> 16).astype(np.uint16).view(np.int16)
+            x = torch.from_numpy(high).view(torch.bfloat16).to(DEV) if bf16 else to_dev(y)
+            want = 1.0 if big is None else max(float(np.float32(big) / np.float32(127)), 2.0 ** -100)
+            out = torch.empty(1, device=DEV)
+            L.sr_absmax_scales([(x, L.INT8, out)])
+            assert float(L.sr_absmax_scale(x, L.INT8).item()) == want and float(out.item()) == want
+
+
 @pytest.mark.parametrize("kind", [L.INT8, L.E5M2, L.E4M3])
 def test_vanishing_tensor_gets_the_floored_scale_not_saturation(kind):
     # max|x| / Qmax below 2^-100: both absmax entry points floor the step there, and the codes
