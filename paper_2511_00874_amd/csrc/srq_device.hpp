@@ -97,6 +97,9 @@ __host__ __device__ constexpr bool kind_is_e4mx(int kind) { return kind >= SRQ_E
 // second, integer quantizer rides along with another format's pass over the same tensor.
 constexpr int SRQ_INTX = 101;
 template <> struct Grid<SRQ_INTX> { static constexpr bool is_float = false; static constexpr int qmax = 0; };  // InvScale::sub_qi
+// E4M3 whose codes come out of the conversions (below); the same codes.
+constexpr int SRQ_E4M3_CONV = 102;
+template <> struct Grid<SRQ_E4M3_CONV> : Grid<SRQ_E4M3> {};
 
 // Per-tensor constants of the multiply that produces the grid coordinate.
 struct InvScale {
@@ -207,9 +210,12 @@ __device__ __forceinline__ uint32_t pack4_nibbles(const uint32_t (&c)[4]) {
 // the rare lanes that hold one: subnormals of the grid, a negative product that rounds to -0, and NaN.
 constexpr uint32_t RTN_WORD = 0x7FFF7FFFu;
 
-// Formats whose codes come out of the conversions a word at a time.
+// Formats whose codes come out of the conversions a word at a time.  E4M3 only where a launch is long: its smallest normal number is
+// 2^-15 of the largest, so some 6 % of the waves hold an element of the general rule, and a short launch waits for that one wave, whose
+// code is not in the instruction cache (a normal tensor of 1024 x 2048 binary32 3.7 -> 4.2 us, bfloat16 4.2 -> 5.7; of 16384 x 8192
+// 109.9 -> 102.3, 89.4 -> 71.4).  For E5M2 that is 2^-30: tensors of any size gain.
 template <int KIND>
-constexpr bool BY_CONVERSION = KIND == SRQ_E4M3 || KIND == SRQ_E5M2;
+constexpr bool BY_CONVERSION = KIND == SRQ_E4M3_CONV || KIND == SRQ_E5M2;
 
 // Four elements by conversion; t: their clamped grid coordinates.
 template <int KIND>

@@ -192,8 +192,8 @@ __global__ __launch_bounds__(QBLOCK) void quantize_dual_kernel(QuantJobs jobs) {
     if (j.dtype == SRQ_F32) dual_tile<SRQ_E5M2, true, CACHED>(job, local, tile);
     else dual_tile<SRQ_E5M2, false, CACHED>(job, local, tile);
   } else {
-    if (j.dtype == SRQ_F32) dual_tile<SRQ_E4M3, true, CACHED>(job, local, tile);
-    else dual_tile<SRQ_E4M3, false, CACHED>(job, local, tile);
+    if (j.dtype == SRQ_F32) dual_tile<SRQ_E4M3_CONV, true, CACHED>(job, local, tile);
+    else dual_tile<SRQ_E4M3_CONV, false, CACHED>(job, local, tile);
   }
 }
 

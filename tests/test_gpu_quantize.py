@@ -145,6 +145,27 @@ def test_absmax_scale_finds_the_maximum_wherever_it_is(n, bf16):
         assert s == (1.0 if where is None else float(np.float32(abs(v)) / np.float32(127)))
 
 
+# E4M3 tensors of at least 2^24 elements take their codes from the conversion instructions, smaller ones do not: halves of a tensor,
+# each below the line, against the whole; zeros, subnormals of the grid, NaN, Inf and saturating values among the elements
+@pytest.mark.parametrize("rows,cols", [(4096, 4096), (4100, 4104), (2, (1 << 23) + 8)])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("mode", [L.SR, L.RTN])
+def test_large_e4m3_tensor_has_the_codes_of_its_halves(rows, cols, bf16, mode):
+    say("E4M3 of 2^24 elements", rows, cols, bf16, mode)
+    g = torch.Generator(DEV).manual_seed(7)
+    x = torch.randn(rows, cols, device=DEV, generator=g) * torch.exp2(torch.rand(rows, cols, device=DEV, generator=g) * 24 - 20)
+    x.view(-1)[::997] = float("nan")
+    x.view(-1)[1::1009] = 0.0
+    x.view(-1)[2::1013] = -0.0
+    x.view(-1)[3::1019] = -float("inf")
+    x = x.to(torch.bfloat16) if bf16 else x
+    half = rows // 2
+    q = [L.Quant(L.E4M3, 0.01, 3, o, round_mode=mode) for o in (0, half * cols // 8)]
+    want = torch.cat([L.sr_quantize(x[:half], q[0]).view(half, cols), L.sr_quantize(x[half:], q[1]).view(half, cols)])
+    assert torch.equal(L.sr_quantize(x, q[0]).view(rows, cols), want)
+    assert torch.equal(L.sr_quantize(x, q[0], transpose_out=True).view(cols, rows), want.t())
+
+
 # Inf and NaN of every payload take no part, beside the largest finite value, in either half of a bfloat16 word; values whose
 # neighbour in that word has all its bits set; nothing but Inf and NaN; batched and alone
 @pytest.mark.parametrize("n", [2, 9, 4103, 65536, 262159])
