@@ -380,7 +380,9 @@ __global__ void absmax_finish_kernel(float* scale, float qmax) {
 // to the workspace (plain stores: nothing to initialise).  Launch 2: one block per tensor folds
 // that tensor's partials and writes the scales requested of it (several formats may share one
 // tensor).
-__global__ __launch_bounds__(QBLOCK) void absmax_multi_kernel(AbsmaxBatch b) {
+// At most 64 registers, as the scales are computed beside the products of another layer (70, the compiler's choice, cost 1.4 % of the
+// two-stream step).
+__global__ __launch_bounds__(QBLOCK, 8) void absmax_multi_kernel(AbsmaxBatch b) {
   int t = 0;
 #pragma unroll
   for (int i = 1; i < ABSMAX_MAX; ++i)
