@@ -293,7 +293,10 @@ __device__ __forceinline__ uint32_t absmax_pieces(const void* __restrict__ x, si
 #pragma unroll
     for (int j = 0; j < 8; ++j) a[j] = load_source<CACHED>(p + i + j * (size_t)nt);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) fold(a[j]);
+    for (int j = 0; j < 8; ++j) {
+      if (j % 2 == 0) __builtin_amdgcn_sched_barrier(0);  // (all keys at once take registers)
+      fold(a[j]);
+    }
   }
   for (; i + 3 * (size_t)nt < gf; i += 4 * (size_t)nt) {
     const u32x4 a = load_source<CACHED>(p + i), b = load_source<CACHED>(p + i + nt);
