@@ -513,9 +513,11 @@ hipError_t dispatch_src_round(void* codes, const void* x, size_t rows, size_t co
                            : launch_one<KIND, SRQ_BF16, SRQ_RTN, STORE>(codes, x, rows, cols, tr, a, s);
 }
 
-// E4M3 by conversion (BY_CONVERSION) from here on.  us without and with, binary32 / bfloat16: 2048 x 4096 8.6 and 8.5 / 9.4 and 9.5, turned
-// 9.8 and 10.0 / 8.8 and 9.6; 4096 x 4096 15.5 and 14.7 / 14.3 and 12.6, turned 17.8 and 17.7 / 15.3 and 15.5; 8192 x 4096 28.5 and
-// 27.5 / 24.5 and 20.9, turned 34.3 and 34.0 / 26.5 and 25.0.
+// E4M3 by conversion (BY_CONVERSION) from here on.  us without and with, for a normal tensor / one with 1 % of outliers / values over
+// 40 binades: 2^24 elements, rows of 4096, binary32 17.2 -> 14.5 / 16.7 -> 15.0 / 15.5 -> 14.9, turned 17.8 -> 17.0 / 17.8 -> 17.3 / 17.7 ->
+// 17.3, bfloat16 14.1 -> 11.3 / 14.2 -> 13.2 / 14.2 -> 13.2, turned 15.3 -> 12.3 / 15.3 -> 14.2 / 15.3 -> 14.2; 2^28 elements binary32 215 -> 217 /
+// 218 -> 216 / 215 -> 220 (HBM; the spread of the times is 2 %), bfloat16 170 -> 140 / 173 -> 155 / 168 -> 161.  Half as many elements, normal,
+// bfloat16 turned: 8.8 and 9.6.
 constexpr size_t E4M3_CONV_ELEMENTS = (size_t)1 << 24;
 
 }  // namespace

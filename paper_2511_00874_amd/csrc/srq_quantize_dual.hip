@@ -4,8 +4,10 @@
 // registers have no room for it.)
 //
 // What bounds it is the vector ALU, two Philox blocks for eight elements, beside the loads.  The stochastic conversions
-// (quantize_octet) take a third of the ALU work off.  Forward quantizers of GPT-2's second linear (8192 x 3072 and 768 x 3072, 165
-// MB) 40.3 -> 34.6 us, of its first 16.5 -> 13.2, of 4096 x 2048 and 2048 x 2048 20.2 -> 16.8.
+// (quantize_octet) take a third of the ALU work off, less where a tensor holds subnormals of the grid.  us of the forward quantizers, E5M2 and
+// E4M3 of normal tensors / E4M3 of an activation with 1 % of outliers / of one over 40 binades: GPT-2's second linear (8192 x 3072 and
+// 768 x 3072, 165 MB) 38.3 -> 34.6, 38.8 -> 35.1 / 38.2 -> 36.5 / 37.7 -> 36.5; 1008 x 768 and 3072 x 768 9.0 -> 7.4, 9.1 -> 7.6 / 9.1 -> 7.7 /
+// 9.1 -> 7.8; 4096 x 2048 and 2048 x 2048 20.0 -> 17.1, 20.5 -> 17.5 / 19.9 -> 18.3 / 20.0 -> 18.4.
 // Not for large tensors or other jobs: with one quantizer, or two of integers, there is less to save than this order of the reads costs
 // (8192 x 3072 E5M2 in both layouts 27.6 -> 28.7 us; 65536 x 2048, rows a power of two apart, int4 108 -> 143).
 #include <cstddef>

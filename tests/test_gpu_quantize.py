@@ -166,6 +166,64 @@ def test_large_e4m3_tensor_has_the_codes_of_its_halves(rows, cols, bf16, mode):
     assert torch.equal(L.sr_quantize(x, q[0], transpose_out=True).view(cols, rows), want.t())
 
 
+# Codes that come out of the conversion instructions, about the smallest normal number of the grid: values of 2^-12 to 2^4 of it, of
+# both signs, whose last bits decide ties of the 16 random bits, against the oracle; every rounding of a wave meets both rules
+@pytest.mark.parametrize("kind,n", [(L.E5M2, 1 << 18), (L.E4M3, 1 << 24)])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("mode", [L.SR, L.RTN])
+def test_converted_codes_about_the_smallest_normal_number(kind, n, bf16, mode):
+    say("codes about the smallest normal number", L.KIND_NAMES[kind], bf16, mode)
+    least, step = (2.0 ** -6, 2.0 ** -9) if kind == L.E4M3 else (2.0 ** -14, 2.0 ** -16)
+    rng = np.random.default_rng(kind)
+    x = (least * rng.standard_normal(n, np.float32) * np.exp2(rng.uniform(-12, 4, n))).astype(np.float32)
+    ties = rng.integers(-(1 << 22), 1 << 22, n // 4)  # multiples of 2^-17 and 2^-21 of the spacing of the subnormals
+    x[::4] = ties.astype(np.float32) * np.float32(step * 2.0 ** -17)
+    x[2::8] = ties[::2].astype(np.float32) * np.float32(step * 2.0 ** -21)
+    x[1::997], x[3::1009], x[5::1013] = np.nan, 0.0, -0.0
+    xd = to_dev(x, bf16)
+    got = L.sr_quantize(xd, L.Quant(kind, 1.0, 5, 9, round_mode=mode)).cpu().numpy()
+    assert np.array_equal(got, oracle_codes(xd, kind, 1.0, 5, 9, mode))
+
+
+def _graph_us(f, calls=4, repeats=9):
+    f()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(calls):
+            f()
+    times = []
+    for _ in range(repeats + 1):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        graph.replay()
+        end.record()
+        end.synchronize()
+        times.append(start.elapsed_time(end) * 1e3 / calls)
+    return min(times[1:])
+
+
+# E4M3 and E5M2 codes of a large tensor take no longer than the codes of E4M2, which no conversion makes, whatever the values: neither
+# where 1 % of outliers or a range of 40 binades put nearly every wave among the subnormals, nor where half of the elements are
+# zero.  (A tenth for the spread of such times; a loop over the elements of those waves took 1.25 to 1.8 times as long.)
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("transpose", [False, True])
+@pytest.mark.parametrize("values", ["normal", "outliers", "half zero", "40 binades"])
+def test_converted_codes_take_no_longer_than_code_by_code_whatever_the_values(bf16, transpose, values):
+    rows, cols = 1 << 14, 1 << 13
+    x = synth.outlier_tensor_torch(rows * cols, 5, DEV, outlier_frac=0.01 if values == "outliers" else 0.0).view(rows, cols)
+    if values == "half zero":
+        x = x.clamp_(min=0.0)
+    elif values == "40 binades":
+        x *= torch.exp2(-40 * torch.rand(rows, cols, device=DEV, generator=torch.Generator(DEV).manual_seed(6)))
+    x = x.to(torch.bfloat16) if bf16 else x
+    out = torch.empty(rows * cols, dtype=torch.uint8, device=DEV)
+    q = {k: L.Quant(k, L.sr_absmax_scale(x, k), 3) for k in (L.E4M2, L.E4M3, L.E5M2)}
+    us = {k: _graph_us(lambda: L.sr_quantize(x, q[k], transpose_out=transpose, out=out)) for k in q}
+    say("us of a kind", bf16, transpose, values, us)
+    assert max(us[L.E4M3], us[L.E5M2]) <= 1.1 * us[L.E4M2]
+
+
 # Inf and NaN of every payload take no part, beside the largest finite value, in either half of a bfloat16 word; values whose
 # neighbour in that word has all its bits set; nothing but Inf and NaN; batched and alone
 @pytest.mark.parametrize("n", [2, 9, 4103, 65536, 262159])
