@@ -6,8 +6,8 @@
 // What bounds it is the vector ALU, two Philox blocks for eight elements, beside the loads.  The stochastic conversions
 // (quantize_octet) take a third of the ALU work off, less where a tensor holds subnormals of the grid.  us of the forward quantizers, E5M2 and
 // E4M3 of normal tensors / E4M3 of an activation with 1 % of outliers / of one over 40 binades: GPT-2's second linear (8192 x 3072 and
-// 768 x 3072, 165 MB) 38.3 -> 34.6, 38.8 -> 35.1 / 38.2 -> 36.5 / 37.7 -> 36.5; 1008 x 768 and 3072 x 768 9.0 -> 7.4, 9.1 -> 7.6 / 9.1 -> 7.7 /
-// 9.1 -> 7.8; 4096 x 2048 and 2048 x 2048 20.0 -> 17.1, 20.5 -> 17.5 / 19.9 -> 18.3 / 20.0 -> 18.4.
+// 768 x 3072, 165 MB) 38.3 -> 33.1, 38.8 -> 33.6 / 38.2 -> 37.1 / 37.7 -> 36.5; 1008 x 768 and 3072 x 768 9.0 -> 6.8, 9.1 -> 7.0 / 9.1 -> 7.2 /
+// 9.1 -> 7.0; 4096 x 2048 and 2048 x 2048 20.0 -> 16.9, 20.5 -> 17.4 / 19.9 -> 17.5 / 20.0 -> 17.3.
 // Not for large tensors or other jobs: with one quantizer, or two of integers, there is less to save than this order of the reads costs
 // (8192 x 3072 E5M2 in both layouts 27.6 -> 28.7 us; 65536 x 2048, rows a power of two apart, int4 108 -> 143).
 #include <cstddef>
@@ -61,9 +61,11 @@ __device__ __forceinline__ global_ptr<T> uniform_ptr(T* p) {
 
 // A thread takes pieces of four neighbouring rows, neighbours in the output, so that codes go to LDS a word at a time, and loads a row of
 // the next piece as soon as the present one has left its registers; the stores of a piece go out after those loads (a wave waits for
-// loads and stores in the order they were issued).  binary32: 4 columns; lanes L and L + 32 hold the two halves of each Philox
-// group, so that a swap of wave halves hands out the random words of two rows and another one makes 8-byte pieces of the integer codes.
-// bfloat16: 8 columns, a group a row.
+// loads and stores in the order they were issued).  The two steps are written out, one with those loads and one without: in a loop the
+// compiler sees loads in flight at its end, too, and where the registers of the LDS reads fall together with theirs it waits
+// for everything, the stores that write through included (8192 x 3072 and 768 x 3072 34.8 instead of 33.1 us).
+// binary32: 4 columns; lanes L and L + 32 hold the two halves of each Philox group, so that a swap of wave halves hands out the random
+// words of two rows and another one makes 8-byte pieces of the integer codes.  bfloat16: 8 columns, a group a row.
 template <int KIND, bool F32, bool CACHED>
 __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t* tile) {
   const QuantJob j = read_job(job);
@@ -97,9 +99,8 @@ __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t
   const uint64_t ctr = uniform(first_block(j.counter_offset, j.counter_dev));
   const uint64_t ctr2 = uniform(first_block(j.counter_offset2, j.counter_dev2));
   const uint32_t steps_end = min(TR, rows - r0);
-#pragma unroll 1
-  for (uint32_t r = 0; r < steps_end; r += STEP) {
-    const bool more = r + STEP < steps_end, inside = col_ok && r0 + rl + r < rows;
+  auto step = [&](uint32_t r, auto more) __attribute__((always_inline)) {
+    const bool inside = col_ok && r0 + rl + r < rows;
     const QuantJob p = read_job(job, true);
     const uint32_t k0 = (uint32_t)p.seed, k1 = (uint32_t)(p.seed >> 32), m0 = (uint32_t)p.seed2, m1 = (uint32_t)(p.seed2 >> 32);
     const size_t group_step = (e_tile + (size_t)r * cols) / 8;
@@ -121,7 +122,7 @@ __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t
         const u32x2 q2 = quantize_octet<SRQ_INTX>(x, y, inv2, w, true);
         out2[i] = q2.x;
         out2[i + 1] = q2.y;
-        if (more) {
+        if constexpr (more.value) {
           load(r + STEP, i);
           load(r + STEP, i + 1);
         }
@@ -152,7 +153,6 @@ __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t
         }
         c[i] = quantize_group_words<KIND>(f, inv, ctr + group + group_off, k0, k1, true);
         const u32x2 q2 = quantize_group_words<SRQ_INTX>(f, inv2, ctr2 + group + group_off, m0, m1, true);
-        if (more) load(r + STEP, i);
         if (inside) *reinterpret_cast<global_ptr<u32x2>>(uniform_ptr(p.out2 + group * 8) + group_off * 8) = q2;
       }
 #pragma unroll
@@ -163,7 +163,16 @@ __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t
         for (int e = 0; e < 4; ++e) *reinterpret_cast<uint32_t*>(dst + (4 * h + e) * PITCH) = q[e];
       }
     }
+  };
+  static_assert(STEP == TR || 2 * STEP == TR, "one step or two");
+  uint32_t r = 0;
+  if constexpr (STEP < TR) {
+    if (steps_end > STEP) {
+      step(0u, std::true_type{});
+      r = STEP;
+    }
   }
+  step(r, std::false_type{});
   __syncthreads();
   const QuantJob o = read_job(job, true);
 #pragma unroll
