@@ -218,7 +218,14 @@ inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes
 // Over 1440 other calls, 0.80 of the time of two launches on average where one is taken, 2 % of them more than 2 % slower.
 // Never 128 x 128 where a product has at most 128 rows (4144 x 80 x 784 E5M2 12.3 -> 15.0: alone it takes 64 x 64 tiles), nor where the
 // results do not fit the last-level cache, whose writes then bound both (30656 x 112 x 5760 int8 170 -> 200).
+// Where the results are written for longer than they are multiplied (integers; the line for 64 x 64 tiles has no term for that) larger
+// tiles write faster.  With more than 64 MB of results a pair takes 128 x 128 tiles where it can (2496 x 192 x 10192, us apart, on 64 x 64 and
+// on 128 x 128 tiles 44.0, 43.4, 33.4; 240 x 2928 x 6736 40.5, 37.2, 30.6; 33 calls 0.77 to 1.01 of the time of 64 x 64; with 30 to 60 MB
+// 0.89 to 1.3).  With more than 96 MB no 64 x 64 tiles take the place of slices of 128 x 128 (5648 x 96 x 10688 69.5 -> 86.0, 16 x 8192 x 4096
+// 39.0 -> 44.0; of 11 such calls 7 lost, 1.04 on average), but for weight gradients in 16 slices or more, whose sum would ride on the input
+// gradient and delay it (32768 x 16 x 1024 64.2 -> 43.3, 99808 x 16 x 256 86.7 -> 47.0).
 constexpr size_t PAIR_MAX_RESULTS = (size_t)64 << 20;  // of 4 bytes
+constexpr double PAIR_LARGE_MB = 64.0, PAIR_LARGE_CUT_MB = 96.0;
 enum PairForm { PAIR_NONE, PAIR_128x128, PAIR_64x64 };
 struct Paired {
   int waves;  // sets of accumulators (128 x 128 tiles of four waves) or groups of waves (64 x 64 of eight)
@@ -294,6 +301,8 @@ inline Pair choose_pair(size_t M, size_t N, size_t K, int pipe) {
       if (i == 1) apart += c.sum;  // (the other one's sum rides)
     }
   }
+  const auto cut = [](const Launch& l) { return l.form == FORM_128x128_G2 && l.nsplit > 1; };
+  if (out > PAIR_LARGE_CUT_MB && (cut(l[0]) || cut(l[1])) && l[0].nsplit < 16) groups = false;
   apart += c.out * out + c.partial * partial;
   const int a = p.weight_first ? 0 : 1, b = 1 - a;
   const double load128 = (double)(n128[0] * stages[0] + n128[1] * stages[1]) / NUM_CU;
@@ -301,7 +310,7 @@ inline Pair choose_pair(size_t M, size_t N, size_t K, int pipe) {
   const double t128 = c.pair128 + c.load128 * load128 + c.last128 * last + c.out128 * out + c.partial128 * partial + c.sum128 * sums;
   const double t64 = c.pair64 + c.load64 * load64 + c.partial64 * partial + c.sum64 * sums;
   const bool at_once = n128[0] + n128[1] <= SLOTS;
-  const bool small = groups && (!sets || t64 <= t128);
+  const bool small = groups && (!sets || (t64 <= t128 && out <= PAIR_LARGE_MB));
   const double worth = (small ? 0.95 : at_once ? 1.0 : c.worth128) * (sums > 0.0 ? 0.95 : 1.0);
   if (!(sets || groups) || (small ? t64 : t128) >= worth * apart) return p;
   p.form = small ? PAIR_64x64 : PAIR_128x128;

@@ -76,6 +76,22 @@ def test_pairs_keep_the_sums_of_the_launches_they_replace(plan):
     assert taken > 4000
 
 
+# integer products whose results are written for longer than they are multiplied (us of both in launches of their own, and in one launch
+# of 64 x 64 and of 128 x 128 tiles, where these can be taken)
+@pytest.mark.parametrize("M,N,K,apart,small,large", [
+    (8192, 16, 4096, 42.6, 47.3, None), (16, 8192, 4096, 39.0, 44.0, None), (5648, 96, 10688, 69.5, 86.0, None),
+    (96, 58384, 1104, 82.9, 96.4, None), (128, 10240, 3392, 47.7, 53.6, None), (80, 7600, 4000, 41.0, 44.3, None),
+    (32768, 16, 1024, 64.2, 43.3, None), (99808, 16, 256, 86.7, 47.0, None), (65536, 32, 512, 94.5, 52.9, None),
+    (672, 16, 61424, 61.0, 49.8, None), (4096, 64, 8192, 44.1, 37.2, None), (48, 1328, 20560, 38.9, 31.6, None),
+    (80, 768, 22816, 26.4, 22.5, None), (12912, 16, 1088, 28.1, 22.3, None),
+    (2496, 192, 10192, 44.0, 43.4, 33.4), (240, 2928, 6736, 40.5, 37.2, 30.6), (192, 1360, 10512, 27.5, 25.4, 20.8),
+    (192, 256, 114336, 58.9, 67.5, 54.5), (160, 1984, 3584, 15.5, 12.7, 16.7), (1024, 3632, 1088, 30.1, 22.6, 29.6)])
+def test_pairs_of_large_results_take_the_tiles_that_write_them_faster(plan, M, N, K, apart, small, large):
+    times = {0: apart, 1: large, 2: small}
+    form = plan.pair(M, N, K, I8)["form"]
+    assert times[form] == min(t for t in times.values() if t)
+
+
 def test_pair_shapes_cover_the_forms(plan):
     seen = {pipe: {(p["form"], p["waves_w"], p["waves_d"], p["weight_first"], p["slices_w"] > 1, p["slices_d"] > 1)
                    for p in (plan.pair(*s, pipe) for s in PAIR_SHAPES)} for pipe in (I8, F8, F16C)}
