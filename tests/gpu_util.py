@@ -14,9 +14,11 @@ GROUP_SHAPES = [(16, 16, 16), (65, 63, 144), (130, 67, 1040), (257, 250, 2064), 
                 (640, 1025, 2576), (1001, 1003, 3088), (1030, 1090, 2064), (1090, 1102, 4112), (1040, 1936, 2064), (770, 771, 12304),
                 (912, 400, 16448)]
 # M, N, K of backward calls that leave the slice sum of dW to the launch of dA: slices of 64 x 64 and of 128 x 128 tiles, with dA in
-# each form that a sum rides on, and calls that have none
+# each form that a sum rides on, and calls that have none.  Some take both products in one launch on some pipelines, where no sum
+# rides; the last four leave one that does for each form and pipeline (test_plan.py).
 RIDE_SHAPES = [(2048, 192, 352), (976, 208, 560), (4240, 1360, 224), (2736, 432, 1312), (4992, 1056, 672), (6432, 208, 304),
-               (4304, 320, 288), (7296, 1968, 448), (5920, 1936, 608), (4080, 2000, 752), (7472, 3488, 288)]
+               (4304, 320, 288), (7296, 1968, 448), (5920, 1936, 608), (4080, 2000, 752), (7472, 3488, 288),
+               (2048, 656, 416), (2048, 848, 400), (1488, 416, 608), (4352, 528, 336)]
 
 # M, N, K of backward calls whose two products go in one launch: tiles of both sizes, either product first, sets and groups of either, slices
 # of either or both, rows and columns that end inside a tile (test_plan.py says what which shape takes)
