@@ -137,6 +137,7 @@ int check_dims(size_t M, size_t N, size_t K) {
 struct ProductPlan {
   int pipe;
   size_t es, x_bytes, z_bytes, gemm_bytes;
+  Plan cut;  // made once a call: some microseconds of the host for long contractions
 };
 
 // e5m2_call = false: an operand of the product is shared with another one that has an E4M3-family
@@ -152,7 +153,8 @@ int plan_product(ProductPlan& pp, const srq_quant* qx, const srq_quant* qz, size
   pp.es = pp.pipe == PIPE_BF16 ? 2 : 1;
   pp.x_bytes = align_up(P * R * pp.es, WS_ALIGN);
   pp.z_bytes = align_up(Q * R * pp.es, WS_ALIGN);
-  pp.gemm_bytes = align_up(gemm_workspace_bytes(P, Q, R, pp.pipe), WS_ALIGN);
+  pp.cut = plan_for(P, Q, R, pp.pipe);
+  pp.gemm_bytes = align_up(partial_bytes(pp.cut, P, Q), WS_ALIGN);
   return SRQ_OK;
 }
 
@@ -178,7 +180,7 @@ int launch_product(float* out, const uint8_t* xc, const srq_quant* qx, const uin
   // packed 4-bit X: the kernel multiplies 16 * value, the factor goes into alpha (a power of two: exact)
   GemmScale sc{x_packed ? 0.0625f : 1.0f, qx->scale, qz->scale, qx->scale_dev, qz->scale_dev};
   return launch_gemm_codes(out, xc, qx->kind, zc, qz->kind, P, Q, R, R * pp.es, pp.pipe, sc, beta == 1.0f, gws,
-                           s, role, carry, defer, x_packed) == hipSuccess
+                           s, role, carry, defer, x_packed, &pp.cut) == hipSuccess
              ? SRQ_OK
              : SRQ_ERR_HIP;
 }
@@ -195,8 +197,8 @@ int launch_backward_products(float* dA, float* dW, const uint8_t* dy_rm, const u
   if (!packed_rm && !packed_t && pd.pipe == pw.pipe) {
     const GemmScale sw{1.0f, qdY->scale, qA->scale, qdY->scale_dev, qA->scale_dev};
     const GemmScale sd{1.0f, qdY->scale, qW->scale, qdY->scale_dev, qW->scale_dev};
-    const PairedProduct w{dW, dy_t, a_t, qA->kind, N, K, M, sw, beta == 1.0f, gws_w};
-    const PairedProduct d{dA, dy_rm, w_t, qW->kind, M, K, N, sd, false, gws_d};
+    const PairedProduct w{dW, dy_t, a_t, qA->kind, N, K, M, sw, beta == 1.0f, gws_w, pw.cut};
+    const PairedProduct d{dA, dy_rm, w_t, qW->kind, M, K, N, sd, false, gws_d, pd.cut};
     bool done;
     const hipError_t e = launch_gemm_pair(w, d, qdY->kind, pd.pipe, s, done);
     if (done || e != hipSuccess) return e == hipSuccess ? SRQ_OK : SRQ_ERR_HIP;

@@ -1233,8 +1233,7 @@ hipError_t launch_cut3(GemmParams g, hipStream_t stream) {
 }  // namespace
 
 size_t gemm_workspace_bytes(size_t P, size_t Q, size_t R, int pipe) {
-  const Plan pl = plan_for(P, Q, R, pipe);
-  return pl.nsplit > 1 ? (size_t)pl.nsplit * P * Q * sizeof(uint32_t) : 0;
+  return partial_bytes(plan_for(P, Q, R, pipe), P, Q);
 }
 
 bool gemm_takes_packed_x(size_t P, size_t Q, size_t R, int pipe) {
@@ -1289,10 +1288,10 @@ GemmParams product_params(float* out, const uint8_t* X, const uint8_t* Z, size_t
 hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint8_t* Z, int kindZ,
                              size_t P, size_t Q, size_t R, size_t pitch, int pipe, const GemmScale& s,
                              bool accumulate, void* workspace, hipStream_t stream, ProductRole role,
-                             const SliceSum* carry, SliceSum* defer, bool x_packed) {
+                             const SliceSum* carry, SliceSum* defer, bool x_packed, const Plan* plan) {
   const SliceSumPlan ss{carry, defer};
   const size_t row_bytes = pipe == PIPE_BF16 ? 2 * R : R;
-  const Plan pl = plan_for(P, Q, R, pipe);
+  const Plan pl = plan ? *plan : plan_for(P, Q, R, pipe);
   if (x_packed && !(pipe == PIPE_I8 && pl.tile == 0)) return hipErrorInvalidValue;  // see gemm_takes_packed_x
   GemmParams g = product_params(out, X, Z, P, Q, row_bytes, pitch, s, accumulate, workspace, x_packed);
   g.k_per_split = pl.k_per_split;
@@ -1308,7 +1307,7 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
 hipError_t launch_gemm_pair(const PairedProduct& w, const PairedProduct& d, int kindX, int pipe, hipStream_t stream, bool& done) {
   done = false;
   if (pipe == PIPE_BF16 || (pipe != PIPE_I8 && (w.kindZ == SRQ_E5M2) != (d.kindZ == SRQ_E5M2))) return hipSuccess;
-  const Pair p = choose_pair(w.R, w.P, w.Q, pipe);  // M, N, K
+  const Pair p = choose_pair(w.R, w.P, w.Q, pipe, w.plan, d.plan);  // M, N, K
   if (p.form == PAIR_NONE) return hipSuccess;
   GemmParams gw = product_params(w.out, w.X, w.Z, w.P, w.Q, w.R, w.R, w.s, w.accumulate, w.partial, false);
   GemmParams gd = product_params(d.out, d.X, d.Z, d.P, d.Q, d.R, d.R, d.s, d.accumulate, d.partial, false);

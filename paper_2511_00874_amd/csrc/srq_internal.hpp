@@ -152,7 +152,9 @@ enum ProductRole {
 hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint8_t* Z, int kindZ,
                              size_t P, size_t Q, size_t R, size_t pitch, int pipe, const GemmScale& s,
                              bool accumulate, void* workspace, hipStream_t stream, ProductRole role = ROLE_ANY,
-                             const SliceSum* carry = nullptr, SliceSum* defer = nullptr, bool x_packed = false);
+                             const SliceSum* carry = nullptr, SliceSum* defer = nullptr, bool x_packed = false,
+                             const Plan* plan = nullptr);
+// (plan: plan_for of this product, where the caller has it already)
 // Both backward products of a layer in one launch where choose_pair says so (`done`; otherwise nothing is launched): the same
 // results, bit for bit, as from launch_gemm_codes, the weight gradient with its role.  One byte per element, rows without gaps.
 struct PairedProduct {
@@ -163,6 +165,7 @@ struct PairedProduct {
   GemmScale s;
   bool accumulate;
   void* partial;  // room for its slices, as launch_gemm_codes takes it
+  Plan plan;      // plan_for of it
 };
 hipError_t launch_gemm_pair(const PairedProduct& weight, const PairedProduct& data, int kindX, int pipe, hipStream_t stream, bool& done);
 // x_packed: X holds 4-bit integers two per byte -- byte j of every 8 holds elements j (low nibble)

@@ -81,6 +81,11 @@ inline Plan make_plan(size_t P, size_t Q, size_t row_bytes) {
   return best;
 }
 
+// Bytes of the partial sums of a planned product.
+inline size_t partial_bytes(const Plan& pl, size_t P, size_t Q) {
+  return pl.nsplit > 1 ? (size_t)pl.nsplit * P * Q * sizeof(uint32_t) : 0;
+}
+
 // The plan of a product on one of the pipelines.  PIPE_F16W has half the row bytes of PIPE_BF16, and by its own
 // count would cut long contractions into half as many slices: every accumulator would then sum twice as many
 // products one after another, and round about 1.4 times as far from the exact result.  Where its slices would be longer
@@ -259,12 +264,12 @@ inline uint64_t stages_to_end(uint64_t n1, uint64_t s1, uint64_t n2, uint64_t s2
   }
   return lo;
 }
-inline Pair choose_pair(size_t M, size_t N, size_t K, int pipe) {
+// plan_w, plan_d: the products' plans (plan_for), which take more time than the choice
+inline Pair choose_pair(size_t M, size_t N, size_t K, int pipe, const Plan& plan_w, const Plan& plan_d) {
   const bool is_int = pipe == PIPE_I8;
   if (pipe == PIPE_BF16 || (M + N) * K > PAIR_MAX_RESULTS) return Pair{PAIR_NONE, false, {1, 1, 0}, {1, 1, 0}};
   const PairLines& c = PAIR_LINES[pipe == PIPE_F16C || pipe == PIPE_F16W];
-  const Launch l[2] = {choose_launch(plan_for(N, K, M, pipe), N, K, M, pipe, true, 0),
-                       choose_launch(plan_for(M, K, N, pipe), M, K, N, pipe, false, 0)};
+  const Launch l[2] = {choose_launch(plan_w, N, K, M, pipe, true, 0), choose_launch(plan_d, M, K, N, pipe, false, 0)};
   Pair p{PAIR_NONE, l[0].k_per_split >= l[1].k_per_split, {1, l[0].nsplit, l[0].k_per_split}, {1, l[1].nsplit, l[1].k_per_split}};
   if (l[0].form == FORM_256x256 || l[1].form == FORM_256x256) return p;
   constexpr uint64_t SLOTS = 2 * NUM_CU;  // workgroups of four waves that are on the chip at a time

@@ -13,6 +13,7 @@ I8, F8, BF16, F16C, F16W = range(5)
 P256, P128, P128_S2, P128_G2, P128x192, P64_G2, P64_G4 = range(7)
 
 WRAP = """
+#include <chrono>
 #include "srq_plan.hpp"
 using namespace srq;
 extern "C" void plan(size_t P, size_t Q, size_t R, int pipe, int leaves, unsigned rides, unsigned* o) {
@@ -21,9 +22,29 @@ extern "C" void plan(size_t P, size_t Q, size_t R, int pipe, int leaves, unsigne
   o[0] = pl.nsplit; o[1] = l.form; o[2] = l.nsplit; o[3] = l.k_per_split; o[4] = l.ring;
 }
 extern "C" void pair(size_t M, size_t N, size_t K, int pipe, unsigned* o) {
-  const Pair p = choose_pair(M, N, K, pipe);
+  const Pair p = choose_pair(M, N, K, pipe, plan_for(N, K, M, pipe), plan_for(M, K, N, pipe));
   const unsigned v[] = {(unsigned)p.form, p.weight_first, (unsigned)p.w.waves, p.w.nsplit, p.w.k_per_split, (unsigned)p.d.waves, p.d.nsplit, p.d.k_per_split};
   for (int i = 0; i < 8; ++i) o[i] = v[i];
+}
+// nanoseconds of the plans of a backward call, and of what chooses between one launch and two beside them
+extern "C" void host_time(size_t M, size_t N, size_t K, int pipe, double* o) {
+  const auto now = [] { return std::chrono::duration<double, std::nano>(std::chrono::steady_clock::now().time_since_epoch()).count(); };
+  unsigned sum = 0;
+  o[0] = o[1] = 1e30;
+  for (int r = 0; r < 20; ++r) {
+    const double start = now();
+    Plan w, d;
+    for (int i = 0; i < 100; ++i) {
+      w = plan_for(N + i % 2 * 16, K, M, pipe), d = plan_for(M, K, N + i % 2 * 16, pipe);
+      sum += w.nsplit + d.nsplit;
+    }
+    const double between = now();
+    for (int i = 0; i < 100; ++i) sum += choose_pair(M, N + i % 2 * 16, K, pipe, w, d).form;
+    const double end = now();
+    if (between - start < o[0]) o[0] = between - start;
+    if (end - between < o[1]) o[1] = end - between;
+  }
+  o[0] /= 100, o[1] /= 100, o[2] = sum;
 }
 """
 
@@ -36,7 +57,7 @@ def plan(tmp_path_factory):
                    check=True)
     lib = C.CDLL(str(d / "plan.so"))
     lib.plan.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_int, C.c_uint, C.c_void_p]
-    lib.pair.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_void_p]
+    lib.pair.argtypes = lib.host_time.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_void_p]
 
     def pair(M, N, K, pipe):
         o = (C.c_uint * 8)()
@@ -47,7 +68,7 @@ def plan(tmp_path_factory):
         o = (C.c_uint * 5)()
         lib.plan(P, Q, R, pipe, leaves, rides, o)
         return dict(planned_slices=o[0], form=o[1], slices=o[2], k_per_split=o[3], ring=o[4])
-    f.pair = pair
+    f.pair, f.host_time = pair, lib.host_time
     return f
 
 
@@ -74,6 +95,15 @@ def test_pairs_keep_the_sums_of_the_launches_they_replace(plan):
                     assert p["waves_" + which] == parts
                 assert p["waves_" + which] in ((1, 2) if p["form"] == 1 else (2, 4))
     assert taken > 4000
+
+
+# a backward call makes its two plans once, and what is added to them is less than a microsecond (it was the time of two more plans)
+@pytest.mark.parametrize("M,N,K,pipe", [(1008, 3072, 768, F16C), (4096, 2048, 2048, I8), (16384, 256, 256, F16W), (65536, 256, 512, F16W)])
+def test_choosing_a_pair_costs_little_host_time(plan, M, N, K, pipe):
+    ns = (C.c_double * 3)()
+    plan.host_time(M, N, K, pipe, ns)
+    print("ns of the plans and of the choice", M, N, K, pipe, list(ns)[:2])
+    assert ns[1] < 1000
 
 
 # integer products whose results are written for longer than they are multiplied (us of both in launches of their own, and in one launch
