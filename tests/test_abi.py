@@ -6,9 +6,11 @@ import ctypes as C
 import itertools
 import os
 import re
+import struct
 import subprocess
 import sys
 
+import msgpack
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -197,3 +199,34 @@ def test_import_without_the_raw_stream_calls(lib):
             "except RuntimeError as e: assert 'device tensors' in str(e), e\n"
             "else: raise AssertionError('a host tensor was accepted')\n")
     subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
+
+
+def _kernels(path):
+    """Kernel name -> what the compiler notes of it, from the code objects inside a library."""
+    blob, out, at = open(path, "rb").read(), {}, 0
+    while (at := blob.find(b"\x7fELF", at + 1)) >= 0:
+        elf = blob[at:]
+        if elf[4] != 2 or struct.unpack_from("<H", elf, 18)[0] != 224:  # 64 bits, AMDGPU
+            continue
+        sections, size, count = *struct.unpack_from("<Q", elf, 40), *struct.unpack_from("<HH", elf, 58)
+        for i in range(count):
+            _, kind, _, _, note, length = struct.unpack_from("<IIQQQQ", elf, sections + i * size)
+            end = note + length if kind == 7 else note  # SHT_NOTE
+            while note < end:
+                name, desc, tag = struct.unpack_from("<III", elf, note)
+                text = note + 12 + (name + 3) // 4 * 4
+                if tag == 32:  # NT_AMDGPU_METADATA
+                    out.update((k[".name"], k) for k in msgpack.unpackb(elf[text:text + desc])["amdhsa.kernels"])
+                note = text + (desc + 3) // 4 * 4
+    return out
+
+
+def test_memory_bound_kernels_hold_at_most_64_registers(lib):
+    # a wave of them then fits on a SIMD beside two of a product kernel on another stream; beyond that they wait for its end
+    kernels = _kernels(lib.LIB_PATH)
+    for part in ("quantize_flat", "quantize_transpose", "quantize_jobs", "quantize_dual", "absmax_multi"):
+        of = {n: k for n, k in kernels.items() if part in n}
+        assert of, part
+        for name, k in of.items():
+            assert k[".vgpr_count"] <= 64 and k[".agpr_count"] == 0, name
+            assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
