@@ -181,10 +181,6 @@ __device__ __forceinline__ uint32_t pack4_bytes(const uint32_t (&c)[4]) {
   const uint32_t hi = __builtin_amdgcn_perm(c[3], c[2], 0x0c0c0400u);
   return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
-// low nibbles of four codes -> 16 bits (c0 in bits 3:0)
-__device__ __forceinline__ uint32_t pack4_nibbles(const uint32_t (&c)[4]) {
-  return (c[0] & 0xFu) | ((c[1] & 0xFu) << 4) | ((c[2] & 0xFu) << 8) | ((c[3] & 0xFu) << 12);
-}
 
 // ---- four elements to a word of four byte codes --------------------------------------------------
 // r0 holds the random bits of elements 0 and 1 (low half first), r1 those of 2 and 3, as they come out of Philox; for

@@ -129,8 +129,8 @@ __device__ __forceinline__ void transpose_path(const QuantJob& j, uint32_t local
   if (j.dtype == SRQ_F32) {
     // 16 lanes x 16 bytes cover the 64 columns of one tile row: a wave loads 4 rows per
     // instruction, fully used lines.  A lane holds a quad (half a Philox group) of row rA and
-    // one of row rA + 64; the even lane of a pair draws the block of the first group, the odd
-    // lane the block of the second, and they trade two words (as in quantize_chunk_f32).
+    // one of row rA + TR / 2; the even lane of a pair draws the block of the first group, the odd
+    // lane the block of the second, and they trade two words (round_words_of_neighbours).
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const bool odd = lane & 1u;
     const uint32_t cq = (lane & 15u) * 4;                    // first column of the quad in the tile

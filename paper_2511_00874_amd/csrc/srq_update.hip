@@ -64,13 +64,9 @@ __global__ __launch_bounds__(UBLOCK) void update_bf16_kernel(uint16_t* __restric
     uint32_t addA[4], addB[4];
     if (ROUND == SRQ_SR) {
       uint32_t x[4];
-      philox_block(counter_offset + c * (CHUNK / 8) + (odd ? 32u : 0u) + (lane >> 1), k0, k1, x);
-      const uint32_t nb0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[0], 0xB1, 0xF, 0xF, true);  // lane ^ 1
-      const uint32_t nb1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[1], 0xB1, 0xF, 0xF, true);
-      const uint32_t nb2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[2], 0xB1, 0xF, 0xF, true);
-      const uint32_t nb3 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[3], 0xB1, 0xF, 0xF, true);
-      sr_addends(odd ? nb2 : x[0], odd ? nb3 : x[1], addA);
-      sr_addends(odd ? x[2] : nb0, odd ? x[3] : nb1, addB);
+      round_words_of_neighbours(counter_offset + c * (CHUNK / 8) + (odd ? 32u : 0u) + (lane >> 1), k0, k1, x, odd);
+      sr_addends(x[0], x[1], addA);
+      sr_addends(x[2], x[3], addB);
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j) addA[j] = addB[j] = RTN_ADDEND;
