@@ -165,6 +165,9 @@ __global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
           else *reinterpret_cast<u32x2*>(dst) = u32x2{upper[e], lower[e]};
         }
       } else {
+        // by conversion: words of codes, turned; others: the codes, or the sums that hold them, of four rows, whose bytes are then
+        // picked by column (24 byte permutes instead of 40)
+        uint32_t sum[PR][2][4];
         u32x2 c[PR];
 #pragma unroll
         for (int i = 0; i < PR; ++i) {
@@ -174,17 +177,43 @@ __global__ __launch_bounds__(QBLOCK) void quantize_transpose_kernel(
             v[2 * e] = bf16_to_f32(raw[i][e] & 0xFFFFu);
             v[2 * e + 1] = bf16_to_f32(raw[i][e] >> 16);
           }
-          c[i] = quantize_group_words<KIND>(v, inv, ctr + (e0 + (size_t)i * cols) / 8, k0, k1, ROUND == SRQ_SR);
+          const uint64_t block = ctr + (e0 + (size_t)i * cols) / 8;
+          if constexpr (BY_CONVERSION<KIND>) {
+            c[i] = quantize_group_words<KIND>(v, inv, block, k0, k1, ROUND == SRQ_SR);
+          } else if constexpr (Grid<KIND>::is_float) {
+            uint32_t code[8];
+            quantize_group<KIND, ROUND, false>(code, v, inv, block, k0, k1);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sum[i][e / 4][e % 4] = code[e];
+          } else {
+            uint32_t w[4];
+            round_words(ROUND == SRQ_SR, block, k0, k1, w);
+            integer_sums<KIND>(sum[i], {v[0], v[1], v[2], v[3]}, {v[4], v[5], v[6], v[7]}, inv, w, ROUND == SRQ_SR);
+          }
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           uint32_t q[4];
-          turn4x4(c[0][h], c[1][h], c[2][h], c[3][h], q);
+          if constexpr (BY_CONVERSION<KIND>) {
+            turn4x4(c[0][h], c[1][h], c[2][h], c[3][h], q);
+          } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < 4; ++e) {
+              const uint32_t col[4] = {sum[0][h][e], sum[1][h][e], sum[2][h][e], sum[3][h][e]};
+              q[e] = Grid<KIND>::is_float ? pack4_bytes(col) : signed_bytes(col);
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < 4; e += 2) {
             uint8_t* const dst = tile + (cl + 4 * h + e) * PITCH + rl / DIV;
-            if constexpr (STORE == STORE_NIBBLE) *reinterpret_cast<uint16_t*>(dst) = (uint16_t)pack8_nibbles(q[e], 0u);
-            else *reinterpret_cast<uint32_t*>(dst) = q[e];
+            if constexpr (STORE == STORE_NIBBLE) {
+              const uint32_t n = pack8_nibbles(q[e], q[e + 1]);
+              *reinterpret_cast<uint16_t*>(dst) = (uint16_t)n;
+              *reinterpret_cast<uint16_t*>(dst + PITCH) = (uint16_t)(n >> 16);
+            } else {
+              *reinterpret_cast<uint32_t*>(dst) = q[e];
+              *reinterpret_cast<uint32_t*>(dst + PITCH) = q[e + 1];
+            }
           }
         }
       }

@@ -166,6 +166,25 @@ def test_large_e4m3_tensor_has_the_codes_of_its_halves(rows, cols, bf16, mode):
     assert torch.equal(L.sr_quantize(x, q[0], transpose_out=True).view(cols, rows), want.t())
 
 
+# NaN of either sign in every place of a group of eight, alone and beside others, has the code 0 and leaves its neighbours theirs
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("mode", [L.SR, L.RTN])
+def test_codes_of_nan_in_every_place(kind, bf16, mode):
+    x = synth.gaussian((1040, 72), 1.0, 11)
+    flat = x.reshape(-1)
+    for g in range(0, flat.size // 8, 3):
+        flat[8 * g + g // 3 % 8] = np.nan if g % 2 else -np.nan
+    flat[64:72] = np.nan
+    flat[80:88:2] = -np.nan
+    xd = to_dev(x, bf16)
+    q = L.Quant(kind, 3.0 / L.QMAX[kind], 3, 7, round_mode=mode)
+    say("NaN in every place", L.KIND_NAMES[kind], bf16, mode)
+    assert np.array_equal(L.sr_quantize(xd, q).cpu().numpy(), oracle_codes(xd, kind, q.scale, 3, 7, mode))
+    assert np.array_equal(L.sr_quantize(xd, q, transpose_out=True).cpu().numpy(),
+                          oracle_codes(xd, kind, q.scale, 3, 7, mode, transpose=True))
+
+
 # Codes that come out of the conversion instructions, about the smallest normal number of the grid: values of 2^-12 to 2^4 of it, of
 # both signs, whose last bits decide ties of the 16 random bits, against the oracle; every rounding of a wave meets both rules
 @pytest.mark.parametrize("kind,n", [(L.E5M2, 1 << 18), (L.E4M3, 1 << 24)])
