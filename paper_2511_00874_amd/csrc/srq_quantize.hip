@@ -84,7 +84,7 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_f32_kernel(uint8_t* __re
 // Against the form before (a group of 8 codes per thread, byte-wise LDS writes, 128-row tiles, a ragged
 // run byte by byte): 12289 x 3080 bfloat16 -> int8 82 -> 35 us, binary32 99 -> 47; 12288 x 3080 binary32
 // 52 -> 41 (189 MB: 4.6 TB/s); 65536 x 4096 binary32 311 -> 227 (5.9 TB/s), bfloat16 162 -> 130.  With the codes of a quad made
-// as one word (quantize_word): 12289 x 3080 bfloat16 -> E5M2 38.2 -> 33.8 us.
+// as one word: 12288 x 3080 bfloat16 -> E5M2 32.8 -> 28.6 us, 65536 x 4096 186 -> 151.
 //   - At most 64 registers: a wave of it then fits on a SIMD beside two of the persistent product
 //     kernel, so that on a second stream it runs beside a product and not behind it.  That takes no more than to
 //     recompute the addresses of both sides (opaque) and to round a row at a time; alone it is as fast.  Six calls on 16384 x 4096
@@ -542,12 +542,13 @@ hipError_t dispatch_src_round(void* codes, const void* x, size_t rows, size_t co
                            : launch_one<KIND, SRQ_BF16, SRQ_RTN, STORE>(codes, x, rows, cols, tr, a, s);
 }
 
-// E4M3 by conversion (BY_CONVERSION) from here on.  us without and with, for a normal tensor / one with 1 % of outliers / values over
-// 40 binades: 2^24 elements, rows of 4096, binary32 17.2 -> 14.5 / 16.7 -> 15.0 / 15.5 -> 14.9, turned 17.8 -> 17.0 / 17.8 -> 17.3 / 17.7 ->
-// 17.3, bfloat16 14.1 -> 11.3 / 14.2 -> 13.2 / 14.2 -> 13.2, turned 15.3 -> 12.3 / 15.3 -> 14.2 / 15.3 -> 14.2; 2^28 elements binary32 215 -> 217 /
-// 218 -> 216 / 215 -> 220 (HBM; the spread of the times is 2 %), bfloat16 170 -> 140 / 173 -> 155 / 168 -> 161.  Half as many elements, normal,
-// bfloat16 turned: 8.8 and 9.6.
-constexpr size_t E4M3_CONV_ELEMENTS = (size_t)1 << 24;
+// E4M3 by conversion (BY_CONVERSION) from here on, where a tensor of any values is no slower.  us without and with, for a normal tensor / one
+// with 1 % of outliers / values over 40 binades: 2^20 elements binary32 turned 4.1 -> 3.8 / 4.1 -> 4.2 / 4.1 -> 4.2; 2^22, rows of 2048, binary32
+// 5.2 -> 4.7 / 5.3 -> 5.1 / 5.3 -> 5.1, turned 5.9 -> 5.1 / 5.9 -> 5.6 / 5.9 -> 5.7, bfloat16 6.7 -> 6.0 / 6.7 -> 6.5 / 6.7 -> 6.5, turned 5.8 ->
+// 4.9 / 5.8 -> 5.4 / 5.8 -> 5.4; 2^24, rows of 4096, binary32 17.2 -> 14.5 / 16.7 -> 15.0 / 15.5 -> 14.9, bfloat16 14.1 -> 11.3 / 14.2 -> 13.2 /
+// 14.2 -> 13.2, turned 15.3 -> 12.3 / 15.3 -> 14.2 / 15.3 -> 14.2; 2^28 binary32 215 -> 217 / 218 -> 216 / 215 -> 220 (HBM; the times spread
+// by 2 %), bfloat16 170 -> 140 / 173 -> 155 / 168 -> 161.
+constexpr size_t E4M3_CONV_ELEMENTS = (size_t)1 << 22;
 
 }  // namespace
 

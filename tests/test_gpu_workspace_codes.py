@@ -92,7 +92,8 @@ def test_many_row_bands_with_a_ragged_last_group():
     _run(4752, 144, 208, L.INT8, seed=5, w_bf16=True)
 
 
-# Launches whose quantizers all round to nearest, and launches of both modes, are kernels of their own; the sources span
+# Launches whose quantizers all round to nearest, and launches of both modes: the mode is a branch of a job, and saved float codes have a
+# kernel of their own only where both quantizers round stochastically; the sources span
 # 40 binades with zeros of both signs, infinities and NaN, so that a quad holds numbers that the 8-bit conversions round,
 # subnormals of the grid and numbers that underflow, and the scale is not that of the largest element (saturation).
 @pytest.mark.parametrize("kind", KINDS)
