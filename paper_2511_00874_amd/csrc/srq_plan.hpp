@@ -221,6 +221,10 @@ inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes
 // faster; 128 x 128 tiles that are not all on the chip at once have to gain more, as a round of few tiles at the end costs most (534 tiles
 // of 12976 x 2384 x 384 int8 46.0 -> 54.7, not taken).
 // Over 1440 other calls, 0.80 of the time of two launches on average where one is taken, 2 % of them more than 2 % slower.
+// Beside the quantizers of another layer on a second stream (a graph each; the forms with two sets of accumulators leave these no
+// registers, so that they wait for a workgroup's end, but that comes sooner) still 0.89 to 1.07 of the time of both streams, 0.975 on
+// average of 48: N x K 3072 x 768, E5M2, at 1008, 2048, 3072, 4096 tokens 43.8, 58.1, 78.8, 93.8 -> 44.5, 52.5, 70.2, 89.7 (products alone
+// 38.4, 50.1, 65.6, 74.2 -> 31.0, 42.8, 58.2, 66.8); the worst, 2048 x 2048 on the fp8 pipeline at 2048, 58.8 -> 63.1 (47.1 -> 42.0).
 // Never 128 x 128 where a product has at most 128 rows (4144 x 80 x 784 E5M2 12.3 -> 15.0: alone it takes 64 x 64 tiles), nor where the
 // results do not fit the last-level cache, whose writes then bound both (30656 x 112 x 5760 int8 170 -> 200).
 // Where the results are written for longer than they are multiplied (integers; the line for 64 x 64 tiles has no term for that) larger

@@ -6,8 +6,8 @@
 // What bounds it is the vector ALU, two Philox blocks for eight elements, beside the loads.  The stochastic conversions
 // (quantize_octet) take a third of the ALU work off, less where a tensor holds subnormals of the grid.  us of the forward quantizers, E5M2 and
 // E4M3 of normal tensors / E4M3 of an activation with 1 % of outliers / of one over 40 binades: GPT-2's second linear (8192 x 3072 and
-// 768 x 3072, 165 MB) 38.3 -> 33.1, 38.8 -> 33.6 / 38.2 -> 37.1 / 37.7 -> 36.5; 1008 x 768 and 3072 x 768 9.0 -> 6.8, 9.1 -> 7.0 / 9.1 -> 7.2 /
-// 9.1 -> 7.0; 4096 x 2048 and 2048 x 2048 20.0 -> 16.9, 20.5 -> 17.4 / 19.9 -> 17.5 / 20.0 -> 17.3.
+// 768 x 3072, 165 MB) 39.3 -> 32.3, 39.9 -> 33.0 / 39.7 -> 34.4 / 39.0 -> 35.2; 1008 x 768 and 3072 x 768 9.2 -> 6.6, 9.4 -> 6.8 / 9.4 -> 6.9 /
+// 9.2 -> 6.8; 4096 x 2048 and 2048 x 2048 20.3 -> 16.5, 21.1 -> 16.9 / 20.0 -> 17.2 / 20.0 -> 17.1.
 // Not for large tensors or other jobs: with one quantizer, or two of integers, there is less to save than this order of the reads costs
 // (8192 x 3072 E5M2 in both layouts 27.6 -> 28.7 us; 65536 x 2048, rows a power of two apart, int4 108 -> 143).
 #include <cstddef>
