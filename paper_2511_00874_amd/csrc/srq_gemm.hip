@@ -11,6 +11,7 @@
 //                                                     binary16 number, the operands are widened in
 //                                                     registers
 //   E4M3/E5M2 codes     v_mfma_f32_32x32x64_f8f6f4    fp8 pipeline (aligns groups of 8 products)
+// The 256 x 256 tiles multiply in MFMA tiles of 16 x 16 and twice that depth (srq_mma.hpp), the others in 32 x 32.
 //
 // Kernel shape.  A workgroup owns a BM x BN output tile, its waves a WGM x WGN grid of
 // sub-tiles made of 32x32 MFMA tiles.  The contraction advances BK = 128 bytes per stage.
@@ -530,6 +531,18 @@ __global__ __launch_bounds__(WA::THREADS, (WA::SETS > WB::SETS ? WA::SETS : WB::
 // the buffer of its last stage is the staging area of the epilogue (the other one is receiving the
 // next tile's first stage); it is handed back to the ring by the barrier of the next stage.
 // Every loop bound below is uniform over the workgroup, so all waves meet at every barrier.
+//
+// What bounds it: the chip's power as much as its pipes (operands of zeros run 1.3 times as fast), and the operands on their
+// way into LDS and out of it again (a stage is 64 KiB in and 192 KiB out for 2048 cycles of MFMAs a SIMD).  Hence MFMA
+// tiles of 16 x 16, under which the clock is higher (the fp8 pipeline excepted), and LDS reads one at a time between the
+// MFMAs.  int8, us before (32 x 32 tiles, all fragments of a sub-step read at its start) and now, Gaussian codes:
+// 8192 x 2048 x 5632 84.9 -> 77.7 (79.2 -> 76.4 with the reads spread), 8192^3 450 -> 411, 65536 x 2048 x 5632 671 -> 645,
+// 65536 x 2048 x 2048 264 -> 250, 65536 x 5632 x 2048 719 -> 683; with packed 4-bit X 65536 x 5632 x 2048 700 -> 680.  Whole steps:
+// 65536 x 5632 x 2048 2834 -> 2768, 8192 x 2048 x 5632 E4M3 641 -> 603.  Errors against 64 bits of the 8-bit float products are what
+// they were (0.9997 to 1.0003 of it over 8 large shapes).  Measured against it, all slower or equal: the two waves of a SIMD
+// taking turns at LDS and at the MFMAs, a barrier between the turns, with half stages of 64 bytes (rows of 64 bytes
+// come in at 0.75 of the rate of 128) or quarters of the tile, loads two and a half stages ahead: 0.98 to 1.05 of the time; operand
+// rows stored in blocks of 8 or 256 so that a load is one piece, or 128 bytes apart beyond the row: 0.97 to 1.01.
 struct TileItem {
   uint32_t valid, p0, q0, slice, kbeg, kend;
 };
@@ -544,7 +557,7 @@ template <class MMA, bool XP>
 __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, SliceSum rider) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   constexpr int BM = 256, BN = 256, WGN = 4, NW = 8, NLOAD = 4;
-  constexpr int WTM = 128, WTN = 64, TM = WTM / 32, TN = WTN / 32;
+  constexpr int WTM = 128, WTN = 64, T = MMA::TILE, TM = WTM / T, TN = WTN / T, HM = TM / 2;
   constexpr int STAGE = (BM + BN) * BK;
   // DMA instructions per loader wave and stage (an instruction covers 8 rows of 128 bytes, or 16 packed rows of 64)
   constexpr int XL = XP ? BM / 16 / NLOAD : BM / 8 / NLOAD, ZL = BN / 8 / NLOAD;
@@ -554,8 +567,10 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
   using frag_t = typename MMA::frag_t;
   using raw_t = typename MMA::raw_t;
   constexpr int FC = sizeof(raw_t) / 16;
-  constexpr int KSUB = BK / MMA::KSTEP;
-  static_assert(!XP || (FC == 1 && sizeof(frag_t) == 16 && MMA::KSTEP == 32), "packed X: the int8 pipeline only");
+  constexpr int KS = BK / MMA::KSTEP;  // sub-steps of a stage
+  constexpr int LG = 64 / T;           // lane groups that read a sub-step
+  static_assert(HM == TN, "a fragment of Z is fetched beside every fragment of half the X rows");
+  static_assert(!XP || (FC == 1 && T == 16 && KS == 2 && sizeof(frag_t) == 16), "packed X: the int8 pipeline only");
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -626,73 +641,118 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
                 (i & 1) ? (live1 ? zvoff + kc1 + i * 8 * g.pitch : OOB) : (live0 ? zvoff + kc0 + i * 8 * g.pitch : OOB));
   };
 
-  const uint32_t swz = ((lane >> 1) & 7u) ^ ((lane >> 5) * FC);
-  uint32_t xoff[KSUB * FC], zoff[KSUB * FC];
-#pragma unroll
-  for (int t = 0; t < KSUB * FC; ++t) {
-    const uint32_t tt = (t / FC) * 2 * FC + (t % FC);
-    xoff[t] = (wp * WTM + (lane & 31u)) * BK + ((swz ^ tt) << 4);
-    zoff[t] = BM * BK + (wq * WTN + (lane & 31u)) * BK + ((swz ^ tt) << 4);
-  }
-  // packed X: 8 bytes per lane and MFMA (16 elements), row pitch 64, chunk ks of row r at ks ^ ((r >> 2) & 3)
-  uint32_t xoffp[KSUB];
-#pragma unroll
-  for (int ks = 0; ks < KSUB; ++ks)
-    xoffp[ks] = (wp * WTM + (lane & 31u)) * 64u + ((((uint32_t)ks ^ (lane >> 2)) & 3u) << 4) + 8u * (lane >> 5);
-  auto load_frag = [&](const uint8_t* stage, const uint32_t (&off)[KSUB * FC], int sub, int ks) {
+  // Operand reads: lane (row = lane % T, group = lane / T) takes FC chunks of a sub-step, logical chunk
+  // (ks * LG + group) * FC + c.  Packed X: the 16 bytes of a lane group are two runs of 16 elements, one for each
+  // sub-step, so Z's chunk there is 2 * group + ks; row pitch 64, chunk c of row r at c ^ ((r >> 2) & 3).
+  constexpr uint32_t KS_XOR = XP ? 16u : 16u * LG * FC;
+  const uint32_t zoff = BM * BK + (wq * WTN + lane % T) * BK + ((((lane >> 1) & 7u) ^ ((lane / T) * (XP ? 2 : FC))) << 4);
+  const uint32_t xoff = XP ? (wp * WTM + lane % T) * 64u + ((((lane / T) ^ (lane >> 2)) & 3u) << 4)
+                           : (wp * WTM + lane % T) * BK + ((((lane >> 1) & 7u) ^ ((lane / T) * FC)) << 4);
+  auto load_frag = [&](const uint8_t* at, uint32_t off) {
     raw_t f;
 #pragma unroll
     for (int c = 0; c < FC; ++c) {
-      const v4i part = *reinterpret_cast<const v4i*>(stage + off[ks * FC + c] + sub * 32 * BK);
+      const v4i part = *reinterpret_cast<const v4i*>(at + (off ^ (c * 16u)));
       f[4 * c + 0] = part[0]; f[4 * c + 1] = part[1]; f[4 * c + 2] = part[2]; f[4 * c + 3] = part[3];
     }
     return f;
   };
 
   acc_t acc[TM][TN];
-    // fragments are read one sub-step ahead (two, as in gemm_nt_kernel, is no faster here and costs 24
-  // registers): at 219 VGPRs two waves of this kernel leave a SIMD 64 registers, enough for one wave
-  // of the quantizer or absmax kernels, so a memory-bound launch on another stream runs BESIDE this
-  // kernel on the same CUs instead of behind it
-  constexpr int PF = 1;
+  // A stage is a row of units: a sub-step of half the wave's X rows.  A unit's fragments of X are read one by one into the
+  // registers that the unit before has just left, and the next sub-step's fragments of Z beside them: LDS reads spread
+  // between the MFMAs, and few enough registers (216) that two waves of this kernel leave a SIMD 64, enough for one wave
+  // of the quantizer or absmax kernels: a memory-bound launch on another stream runs BESIDE this kernel on the same CUs
+  // instead of behind it.
   auto compute = [&](uint32_t buf) {
-    const uint8_t* stage = lds + buf * STAGE;
-    typename std::conditional<XP, v2i, raw_t>::type xf[PF + 1][TM];
-    raw_t zf[PF + 1][TN];
-    auto fetch = [&](int ks) {
+    const uint8_t* const stage = lds + buf * STAGE;
+    if constexpr (!XP) {
+      raw_t xf[HM], zf[2][TN];
+      auto fetch_x = [&](int u, int i) { xf[i] = load_frag(stage + ((u & 1) * HM + i) * T * BK, xoff ^ ((u >> 1) * KS_XOR)); };
+      auto fetch_z = [&](int ks, int j) { zf[ks & 1][j] = load_frag(stage + j * T * BK, zoff ^ (ks * KS_XOR)); };
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        if constexpr (XP) xf[ks % (PF + 1)][i] = *reinterpret_cast<const v2i*>(stage + xoffp[ks] + i * 32 * 64);
-        else xf[ks % (PF + 1)][i] = load_frag(stage, xoff, i, ks);
-      }
+      for (int j = 0; j < TN; ++j) fetch_z(0, j);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) zf[ks % (PF + 1)][j] = load_frag(stage, zoff, j, ks);
-    };
-#pragma unroll
-    for (int ks = 0; ks < PF && ks < KSUB; ++ks) fetch(ks);
-#pragma unroll
-    for (int ks = 0; ks < KSUB; ++ks) {
-      if (ks + PF < KSUB) fetch(ks + PF);
+      for (int i = 0; i < HM; ++i) fetch_x(0, i);
       __builtin_amdgcn_sched_barrier(0);
-      frag_t xe[TM], ze[TN];
+      frag_t xe[2], ze[TN];  // (plain copies unless the pipeline widens its operands)
+      if constexpr (MMA::WIDENS) xe[0] = MMA::expand_x(xf[0]);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        if constexpr (XP) {
-          // byte j of the 8 holds elements j (low nibble) and j + 8 (high nibble): four words of 16 * value
-          const v2i x = xf[ks % (PF + 1)][i];
-          const int hi = (int)0xF0F0F0F0u;
-          xe[i] = frag_t{(x[0] << 4) & hi, (x[1] << 4) & hi, x[0] & hi, x[1] & hi};
-        } else {
-          xe[i] = MMA::expand_x(xf[ks % (PF + 1)][i]);
+      for (int u = 0; u < 2 * KS; ++u) {
+        if ((u & 1) == 0) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j) ze[j] = MMA::expand_z(zf[(u >> 1) & 1][j]);
+        }
+#pragma unroll
+        for (int i = 0; i < HM; ++i) {
+          if constexpr (MMA::WIDENS) {  // the next fragment is widened beside the MFMAs of this one
+            if (i + 1 < HM || u + 1 < 2 * KS) xe[(i + 1) & 1] = MMA::expand_x(xf[(i + 1) % HM]);
+          } else {
+            xe[i & 1] = MMA::expand_x(xf[i]);
+          }
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            acc_t& sum = acc[(u & 1) * HM + i][j];
+            sum = MMA::mma(ze[j], xe[i & 1], sum);
+          }
+          if constexpr (MMA::WIDENS) {
+            constexpr int N_MFMA = TN * MMA::MFMA_PER_MMA;
+#pragma unroll
+            for (int m = 0; m < N_MFMA; ++m) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x002, (MMA::VALU_PER_EXPAND + N_MFMA - 1) / N_MFMA, 0);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (u + 1 < 2 * KS) fetch_x(u + 1, i);
+          if ((u & 1) == 0 && u + 2 < 2 * KS) fetch_z((u >> 1) + 1, i);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
+    } else {
+      // Packed X: 32 elements a lane and fragment, all of a stage's read at its start; the halves (h) and sub-steps (ks) in
+      // the order (0,0) (1,0) (1,1) (0,1), so that Z is read once.  Fragment n + 1 of the sixteen is widened beside the
+      // MFMAs of fragment n (widened a unit at a time, before its MFMAs: 6 % slower, as much as the tiles of 16 gain).
+      raw_t xf[2][HM], zf[TN];
+      auto fetch_z = [&](int ks, int j) { zf[j] = load_frag(stage + j * T * BK, zoff ^ (ks * KS_XOR)); };
+      auto widen = [&](int n) {
+        const int ks = n >> 3, h = ((n >> 2) & 1) ^ ks, i = n & 3;
+        // byte j of the 8 of a run holds elements j (low nibble) and j + 8 (high nibble): four words of 16 * value
+        const int x0 = xf[h][i][2 * ks], x1 = xf[h][i][2 * ks + 1], hi = (int)0xF0F0F0F0u;
+        return frag_t{(x0 << 4) & hi, (x1 << 4) & hi, x0 & hi, x1 & hi};
+      };
 #pragma unroll
-      for (int j = 0; j < TN; ++j) ze[j] = MMA::expand_z(zf[ks % (PF + 1)][j]);
+      for (int j = 0; j < TN; ++j) fetch_z(0, j);
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = MMA::mma(ze[j], xe[i], acc[i][j]);
+        for (int i = 0; i < HM; ++i) xf[h][i] = load_frag(stage + (h * HM + i) * T * 64, xoff);
       __builtin_amdgcn_sched_barrier(0);
+      frag_t xe[2];
+      xe[0] = widen(0);
+#pragma unroll
+      for (int n = 0; n < 16; ++n) {
+        const int ks = n >> 3, h = ((n >> 2) & 1) ^ ks, i = n & 3;
+        if (n < 15) xe[(n + 1) & 1] = widen(n + 1);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          acc_t& sum = acc[h * HM + i][j];
+          sum = MMA::mma(zf[j], xe[n & 1], sum);
+          if (n == 7) {  // the last MFMA that reads this fragment of the first sub-step
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_z(1, j);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        if (n != 7) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   };
 
@@ -717,7 +777,7 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+          for (int r = 0; r < T * T / 64; ++r) acc[i][j][r] = 0;
       const int ktiles = (int)((cur.kend - cur.kbeg + BK - 1) / BK);
       for (int kt = 0; kt < ktiles; ++kt) {
         if (loader) wait_vmcnt<0>();  // stage gs has landed (the only DMAs in flight)
@@ -735,24 +795,26 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
       // whole tile inside the output, rows 16-byte aligned, nothing to add to: plain row stores
       const bool fast = q_vec && !g.accumulate && cur.p0 + BM <= g.P && cur.q0 + BN <= g.Q;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        // MFMA result register r of lane l: q = 8 (r / 4) + 4 (l / 32) + r % 4, p = l % 32.
+      for (int i = 0; i < WTM / 32; ++i) {
+        // MFMA result register r of lane l: q = 4 LG (r / 4) + 4 (l / T) + r % 4, p = l % T.
         // Final results are converted and scaled here, by the wave that computed them (all eight
         // share that work); partial results of a slice go out as raw accumulator bits.
         const uint32_t le = opaque(lane);
-        uint8_t* const mine = stg + wave_u * EP_WAVE + (le & 31u) * (WTN * 4);
+        uint8_t* const mine = stg + wave_u * EP_WAVE;
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int h = 0; h < 32 / T; ++h)
 #pragma unroll
-          for (int gq = 0; gq < 4; ++gq) {
-            const uint32_t c = j * 8 + 2 * gq + (le >> 5);
-            v4u w;
+          for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-              w[e] = pbase ? MMA::bits(acc[i][j][4 * gq + e])
-                           : __float_as_uint(__fmul_rn(MMA::to_f32(acc[i][j][4 * gq + e]), s));
-            *reinterpret_cast<v4u*>(mine + ((c ^ (le & 15u)) << 4)) = w;
-          }
+            for (int gq = 0; gq < T / 4 / LG; ++gq) {
+              const acc_t& sum = acc[i * (32 / T) + h][j];
+              const uint32_t row = h * T + le % T, c = j * (T / 4) + gq * LG + le / T;
+              v4u w;
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                w[e] = pbase ? MMA::bits(sum[4 * gq + e]) : __float_as_uint(__fmul_rn(MMA::to_f32(sum[4 * gq + e]), s));
+              *reinterpret_cast<v4u*>(mine + row * (WTN * 4) + ((c ^ (row & 15u)) << 4)) = w;
+            }
         // the wave reads back what it has just written (its LDS instructions complete in order) and
         // writes whole rows of its band
         __builtin_amdgcn_wave_barrier();
@@ -1017,7 +1079,7 @@ SliceSum own_slice_sum(const GemmParams& g) {
     own.partial = g.partial; own.out = g.out; own.nsplit = g.nsplit; own.total = (size_t)g.P * g.Q;
     own.s = GemmScale{g.alpha, g.sx, g.sz, g.sx_dev, g.sz_dev};
     own.accumulate = g.accumulate;
-    own.is_int = std::is_same<typename MMA::acc_t, v16i>::value ? 1 : 0;
+    own.is_int = std::is_base_of<I8Mma, MMA>::value ? 1 : 0;
   }
   return own;
 }
@@ -1056,8 +1118,9 @@ hipError_t launch_tile(GemmParams g, const SliceSumPlan& ss, hipStream_t stream)
 
 // The 256 x 256 tiles on workgroups that stay (gemm_nt_persist_kernel): one workgroup per CU, or
 // fewer if there is less work.
-template <class MMA, bool XP = false>
+template <class MMA32, bool XP = false>
 hipError_t launch_persist(GemmParams g, const SliceSumPlan& ss, hipStream_t stream) {
+  using MMA = typename Tiles16<MMA32>::type;
   constexpr int LDS_BYTES = 2 * (256 + 256) * BK;
   auto kern = &gemm_nt_persist_kernel<MMA, XP>;
   static const hipError_t configured = hipFuncSetAttribute(
