@@ -11,10 +11,10 @@
 //                                                     binary16 number, the operands are widened in
 //                                                     registers
 //   E4M3/E5M2 codes     v_mfma_f32_32x32x64_f8f6f4    fp8 pipeline (aligns groups of 8 products)
-// The 256 x 256 tiles multiply in MFMA tiles of 16 x 16 and twice that depth (srq_mma.hpp), the others in 32 x 32.
+// Most kernels multiply in MFMA tiles of 16 x 16 and twice that depth, under which the chip clocks higher (srq_mma.hpp).
 //
 // Kernel shape.  A workgroup owns a BM x BN output tile, its waves a WGM x WGN grid of
-// sub-tiles made of 32x32 MFMA tiles.  The contraction advances BK = 128 bytes per stage.
+// sub-tiles made of MFMA tiles.  The contraction advances BK = 128 bytes per stage.
 // Operand tiles go from global memory straight into LDS (buffer_load ... lds, 16 bytes per
 // lane, no registers in between) through a ring of STAGES buffers, so the loads of the next
 // stages are in flight while the current one is multiplied; out-of-range rows and the tail of
@@ -155,18 +155,19 @@ __device__ __forceinline__ void store_quad(const GemmParams& g, uint32_t* pbase,
   }
 }
 
-// Epilogue of a wave: its TM x TN block of 32 x 32 MFMA results, first row p0 and column q0 of the output.
-// MFMA result register r of lane l: MFMA row 8*(r/4) + 4*(l/32) + r%4 (a q), MFMA column l%32 (a p).
+// Epilogue of a wave: its TM x TN block of T x T MFMA results, first row p0 and column q0 of the output.
+// MFMA result register r of lane l: MFMA row 4 * LG * (r / 4) + 4 * (l / T) + r % 4 (a q), MFMA column l % T (a p); LG = 64 / T.
 // The wave turns its block through its own piece of LDS (`stage`), a band of 32 p-rows at a time (of
 // at most 96 columns), so that every global store instruction writes whole rows of the band.
-constexpr int epilogue_columns(int TN) { return 32 * (TN <= 3 ? TN : TN % 3 == 0 ? 3 : 2); }
-constexpr int epilogue_wave_bytes(int TN) { return 32 * (epilogue_columns(TN) + 4) * 4; }
+constexpr int epilogue_columns(int cols) { return cols <= 96 ? cols : cols % 96 == 0 ? 96 : 64; }
+constexpr int epilogue_wave_bytes(int cols) { return 32 * (epilogue_columns(cols) + 4) * 4; }
 
 template <class MMA, int TM, int TN>
 __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typename MMA::acc_t (&acc)[TM][TN], uint8_t* stage,
                                                 uint32_t lane, uint32_t p0, uint32_t q0, uint32_t slice) {
-  constexpr int COLS = epilogue_columns(TN), JB = COLS / 32;
-  static_assert(TN % JB == 0, "whole bands");
+  constexpr int T = MMA::TILE, LG = 64 / T, IB = 32 / T;
+  constexpr int COLS = epilogue_columns(TN * T), JB = COLS / T;
+  static_assert(TN % JB == 0 && TM % IB == 0, "whole bands");
   constexpr int EP_PITCH = COLS + 4;                  // floats; +4 staggers the banks
   constexpr int CPR = COLS / 4;                       // 16-byte chunks per band row
   constexpr int EP_ITERS = 32 * CPR / 64;
@@ -175,17 +176,20 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
   const bool q_vec = (g.Q & 3u) == 0;
   uint32_t* const pbase = g.nsplit > 1 ? g.partial + (size_t)slice * g.P * g.Q : nullptr;
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
+  for (int i0 = 0; i0 < TM; i0 += IB) {
 #pragma unroll
     for (int j0 = 0; j0 < TN; j0 += JB) {
 #pragma unroll
-      for (int j = 0; j < JB; ++j)
+      for (int i = 0; i < IB; ++i)
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq)
-          *reinterpret_cast<v4u*>(ep + (lane & 31u) * EP_PITCH + j * 32 + 8 * gq + 4 * (lane >> 5)) =
-              v4u{MMA::bits(acc[i][j0 + j][4 * gq]), MMA::bits(acc[i][j0 + j][4 * gq + 1]),
-                  MMA::bits(acc[i][j0 + j][4 * gq + 2]), MMA::bits(acc[i][j0 + j][4 * gq + 3])};
-      const uint32_t pb = p0 + i * 32, qb = q0 + j0 * 32;
+        for (int j = 0; j < JB; ++j)
+#pragma unroll
+          for (int gq = 0; gq < T / 4 / LG; ++gq) {
+            const typename MMA::acc_t& sum = acc[i0 + i][j0 + j];
+            *reinterpret_cast<v4u*>(ep + (i * T + lane % T) * EP_PITCH + j * T + 4 * (gq * LG + lane / T)) =
+                v4u{MMA::bits(sum[4 * gq]), MMA::bits(sum[4 * gq + 1]), MMA::bits(sum[4 * gq + 2]), MMA::bits(sum[4 * gq + 3])};
+          }
+      const uint32_t pb = p0 + i0 * T, qb = q0 + j0 * T;
 #pragma unroll
       for (int it = 0; it < EP_ITERS; ++it) {
         const uint32_t id = it * 64 + lane, row = id / CPR, c = id % CPR;
@@ -206,11 +210,18 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
 // longer ring of stages keeps more loads in flight (with four, 17.4 with the matrix work left out, 23.8 in all; with three 23.1).
 // SETS = 2 (one group): two sets of accumulators, for the first and the second half of the sub-steps of every stage, added at the
 // end: the sums of two groups of waves, in the same order.
-template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG, int SETS>
+template <class PIPE, int BM, int BN, int WGM, int WGN, int STAGES, int KG, int SETS>
 __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block, uint8_t* lds) {
+  // MFMA tiles of 16 x 16 (srq_mma.hpp) but for two cases: four groups, which have a sub-step of 32 bytes each, and codes to widen
+  // in more than one set of sums, where half a stage is a single sub-step, nothing is left to widen beside, and they are
+  // slower (2048 x 2048 x 4096 E5M2, two groups, 38.5 -> 41.5 us; with the groups taking turns at LDS and the MFMAs 43.5).  Forms
+  // that agree bit for bit have tiles of one size: their sums round differently, though to the same error.  Kernels, us, 32 x 32 and
+  // 16 x 16: int8 4096 x 2048 x 2048 24.4 -> 23.0, both its backward products in a pair 39.6 -> 38.4, 8192 x 768 x 3072 31.5 -> 30.6,
+  // 2432 x 4240 x 1216 24.6 -> 21.7; E5M2 8192 x 768 x 3072 47.3 -> 43.5 and 43.1 -> 43.4 in two runs.
+  using MMA = typename std::conditional<PIPE::WIDENS ? KG * SETS == 1 : KG <= 2, typename Tiles16<PIPE>::type, PIPE>::type;
   constexpr int NG = WGM * WGN, NW = NG * KG;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile (p x q)
-  constexpr int TM = WTM / 32, TN = WTN / 32;
+  constexpr int T = MMA::TILE, LG = 64 / T, TM = WTM / T, TN = WTN / T;
   constexpr int STAGE = (BM + BN) * BK;
   constexpr int XL = BM / 8 / NW, ZL = BN / 8 / NW;  // wave-level DMA instructions per stage
   constexpr int LPW = XL + ZL;
@@ -290,21 +301,15 @@ __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block
                 (i & 1) ? (zlive1 ? zvoff + zc1 + i * 8 * g.pitch : OOB) : (zlive0 ? zvoff + zc0 + i * 8 * g.pitch : OOB));
   };
 
-  // operand reads: lane (row = lane % 32, kgroup = lane / 32) takes FC chunks per MFMA;
-  // physical chunk = logical ^ ((row >> 1) & 7), and logical = t | kgroup * FC with t a constant
-  const uint32_t swz = ((lane >> 1) & 7u) ^ ((lane >> 5) * FC);
-  uint32_t xoff[KSUB * FC], zoff[KSUB * FC];
-#pragma unroll
-  for (int t = 0; t < KSUB * FC; ++t) {
-    const uint32_t tt = (t / FC + kg * KSUB) * 2 * FC + (t % FC);
-    xoff[t] = (wp * WTM + (lane & 31u)) * BK + ((swz ^ tt) << 4);
-    zoff[t] = BM * BK + (wq * WTN + (lane & 31u)) * BK + ((swz ^ tt) << 4);
-  }
-  auto load_frag = [&](const uint8_t* stage, const uint32_t (&off)[KSUB * FC], int sub, int ks) {
+  // operand reads: lane (row = lane % T, group = lane / T) takes FC chunks per sub-step, logical chunk
+  // (sub-step * LG + group) * FC + c; physical chunk = logical ^ ((row >> 1) & 7)
+  const uint32_t swz = ((lane >> 1) & 7u) ^ ((kg * KSUB * LG + lane / T) * FC);
+  const uint32_t xoff = (wp * WTM + lane % T) * BK + (swz << 4), zoff = BM * BK + (wq * WTN + lane % T) * BK + (swz << 4);
+  auto load_frag = [&](const uint8_t* at, uint32_t off) {
     raw_t f;
 #pragma unroll
     for (int c = 0; c < FC; ++c) {
-      const v4i part = *reinterpret_cast<const v4i*>(stage + off[ks * FC + c] + sub * 32 * BK);
+      const v4i part = *reinterpret_cast<const v4i*>(at + (off ^ (c * 16u)));
       f[4 * c + 0] = part[0]; f[4 * c + 1] = part[1]; f[4 * c + 2] = part[2]; f[4 * c + 3] = part[3];
     }
     return f;
@@ -319,83 +324,124 @@ __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc_set[h][i][j][r] = 0;
+        for (int r = 0; r < T * T / 64; ++r) acc_set[h][i][j][r] = 0;
 
 #pragma unroll
   for (int s = 0; s < STAGES - 1; ++s) issue(s, s);  // stages past the end load zeros
 
-  // one stage: the fragments of the sub-steps up to PF ahead are fetched before sub-step ks is
-  // multiplied; the scheduling barriers pin that order (the LDS latency then hides behind the
-  // MFMAs) and bound the number of live fragments (registers)
-  constexpr int PF = KSUB > 2 ? 2 : 1;
+  // one stage
   auto compute = [&](int buf) {
-    const uint8_t* stage = lds + buf * STAGE;
-    raw_t xf[PF + 1][TM], zf[PF + 1][TN];
-    auto fetch = [&](int ks) {
+    const uint8_t* const stage = lds + buf * STAGE;
+    if constexpr (T == 16) {
+      // After the MFMAs of an X fragment the next sub-step's fragments are read one by one into the registers that have
+      // just come free.  Fragments that have to be widened (VALU) are, one ahead, between the MFMAs of the one before, those of Z
+      // between the first ones that do without them.  The scheduling barriers pin that order.
+      raw_t xf[TM], zf[2][TN];
+      auto fetch_x = [&](int ks, int i) { xf[i] = load_frag(stage + i * T * BK, xoff ^ (ks * LG * FC * 16u)); };
+      auto fetch_z = [&](int ks, int j) { zf[ks & 1][j] = load_frag(stage + j * T * BK, zoff ^ (ks * LG * FC * 16u)); };
+      fetch_z(0, 0);
+      fetch_x(0, 0);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) xf[ks % (PF + 1)][i] = load_frag(stage, xoff, i, ks);
+      for (int j = 1; j < TN; ++j) fetch_z(0, j);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) zf[ks % (PF + 1)][j] = load_frag(stage, zoff, j, ks);
-    };
-#pragma unroll
-    for (int ks = 0; ks < PF && ks < KSUB; ++ks) fetch(ks);
-    // the interleaved widening below keeps two widened operand sets live: it fits the register file beside wave
-    // tiles of up to 64 x 96
-    constexpr bool INTERLEAVE = MMA::WIDENS && TM * TN <= 6;
-    if constexpr (!INTERLEAVE) {
+      for (int i = 1; i < TM; ++i) fetch_x(0, i);
+      __builtin_amdgcn_sched_barrier(0);
+      frag_t xe[2], ze[TN];  // (plain copies unless the pipeline widens its operands)
+      if constexpr (MMA::WIDENS) {
+        xe[0] = MMA::expand_x(xf[0]);
+        ze[0] = MMA::expand_z(zf[0][0]);
+      }
 #pragma unroll
       for (int ks = 0; ks < KSUB; ++ks) {
-        if (ks + PF < KSUB) fetch(ks + PF);
-        __builtin_amdgcn_sched_barrier(0);
-        frag_t xe[TM], ze[TN];  // (a plain copy unless the pipeline widens its operands)
+        if constexpr (!MMA::WIDENS) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) xe[i] = MMA::expand_x(xf[ks % (PF + 1)][i]);
+          for (int j = 0; j < TN; ++j) ze[j] = MMA::expand_z(zf[ks & 1][j]);
+        }
 #pragma unroll
-        for (int j = 0; j < TN; ++j) ze[j] = MMA::expand_z(zf[ks % (PF + 1)][j]);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
+          const int n = ks * TM + i;
+          const bool turn = i + 1 == TM && ks + 1 < KSUB;
+          if constexpr (MMA::WIDENS) {
+            if (n + 1 < KSUB * TM) xe[(n + 1) & 1] = MMA::expand_x(xf[(i + 1) % TM]);
+          } else {
+            xe[n & 1] = MMA::expand_x(xf[i]);
+          }
 #pragma unroll
           for (int j = 0; j < TN; ++j) {  // MFMA rows: q, columns: p
             acc_t& sum = acc_set[ks * SETS / KSUB][i][j];
-            sum = MMA::mma(ze[j], xe[i], sum);
+            sum = MMA::mma(ze[j], xe[n & 1], sum);
+            if constexpr (MMA::WIDENS) {
+              if (i == 0 && j + 1 < TN) ze[j + 1] = MMA::expand_z(zf[ks & 1][j + 1]);
+              if (turn && TM > 1 && j == 0) ze[0] = MMA::expand_z(zf[(ks + 1) & 1][0]);
+            }
           }
-        __builtin_amdgcn_sched_barrier(0);
+          if constexpr (MMA::WIDENS) {
+            constexpr int N_MFMA = TN * MMA::MFMA_PER_MMA, V = MMA::VALU_PER_EXPAND;
+            const int valu = V + (i == 0 ? (TN - 1) * V : 0) + (turn ? V : 0);
+#pragma unroll
+            for (int m = 0; m < N_MFMA; ++m) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              if (valu > 4 * N_MFMA) __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
+              else if (valu > 3 * N_MFMA) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+              else if (valu > N_MFMA) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+              else __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (ks + 1 < KSUB) {
+            fetch_x(ks + 1, i);
+#pragma unroll
+            for (int j = i * TN / TM; j < (i + 1) * TN / TM; ++j) fetch_z(ks + 1, j);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       }
     } else {
-      // Operands are widened in registers (VALU) before they are multiplied.  A wave issues in
-      // order, so widening a whole sub-step and then multiplying it would leave the matrix pipe
-      // idle during the widening: instead the operands of sub-step ks + 1 are widened while the
-      // MFMAs of sub-step ks are issued, a few VALU operations after each MFMA (the scheduling
-      // groups below pin that interleaving).
-      frag_t xe[2][TM], ze[2][TN];
+      // The fragments of the sub-steps up to PF ahead are fetched before sub-step ks is multiplied; the scheduling barriers
+      // pin that order (the LDS latency then hides behind the MFMAs) and bound the number of live fragments (registers).
+      constexpr int PF = KSUB > 2 ? 2 : 1;
+      raw_t xf[PF + 1][TM], zf[PF + 1][TN];
+      auto fetch = [&](int ks) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) xe[0][i] = MMA::expand_x(xf[0][i]);
+        for (int i = 0; i < TM; ++i) xf[ks % (PF + 1)][i] = load_frag(stage + i * T * BK, xoff ^ (ks * LG * FC * 16u));
 #pragma unroll
-      for (int j = 0; j < TN; ++j) ze[0][j] = MMA::expand_z(zf[0][j]);
+        for (int j = 0; j < TN; ++j) zf[ks % (PF + 1)][j] = load_frag(stage + j * T * BK, zoff ^ (ks * LG * FC * 16u));
+      };
+#pragma unroll
+      for (int ks = 0; ks < PF && ks < KSUB; ++ks) fetch(ks);
+      // Operands are widened in registers (VALU) before they are multiplied.  A wave issues in order, so widening a whole
+      // sub-step and then multiplying it would leave the matrix pipe idle during the widening: instead the operands of
+      // sub-step ks + 1 are widened while the MFMAs of sub-step ks are issued, a few VALU operations after each MFMA (the
+      // scheduling groups below pin that interleaving).  Two widened operand sets fit the register file beside these wave tiles.
+      constexpr int SETS_X = MMA::WIDENS ? 2 : 1;
+      frag_t xe[SETS_X][TM], ze[SETS_X][TN];
+      auto widen = [&](int ks) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) xe[ks % SETS_X][i] = MMA::expand_x(xf[ks % (PF + 1)][i]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) ze[ks % SETS_X][j] = MMA::expand_z(zf[ks % (PF + 1)][j]);
+      };
+      if constexpr (MMA::WIDENS) widen(0);
 #pragma unroll
       for (int ks = 0; ks < KSUB; ++ks) {
         if (ks + PF < KSUB) fetch(ks + PF);
         __builtin_amdgcn_sched_barrier(0);
-        if (ks + 1 < KSUB) {
-#pragma unroll
-          for (int i = 0; i < TM; ++i) xe[(ks + 1) & 1][i] = MMA::expand_x(xf[(ks + 1) % (PF + 1)][i]);
-#pragma unroll
-          for (int j = 0; j < TN; ++j) ze[(ks + 1) & 1][j] = MMA::expand_z(zf[(ks + 1) % (PF + 1)][j]);
-        }
+        if constexpr (!MMA::WIDENS) widen(ks);  // (plain copies)
+        else if (ks + 1 < KSUB) widen(ks + 1);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
             acc_t& sum = acc_set[ks * SETS / KSUB][i][j];
-            sum = MMA::mma(ze[ks & 1][j], xe[ks & 1][i], sum);
+            sum = MMA::mma(ze[ks % SETS_X][j], xe[ks % SETS_X][i], sum);
           }
-        constexpr int N_MFMA = TM * TN * MMA::MFMA_PER_MMA;
-        constexpr int N_VALU = (TM + TN) * MMA::VALU_PER_EXPAND;
-        constexpr int PER = (N_VALU + N_MFMA - 1) / N_MFMA;
+        if constexpr (MMA::WIDENS) {
+          constexpr int N_MFMA = TM * TN * MMA::MFMA_PER_MMA, N_VALU = (TM + TN) * MMA::VALU_PER_EXPAND;
 #pragma unroll
-        for (int m = 0; m < N_MFMA; ++m) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // one MFMA
-          __builtin_amdgcn_sched_group_barrier(0x002, PER, 0);  // then up to PER VALU operations
+          for (int m = 0; m < N_MFMA; ++m) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                             // one MFMA
+            __builtin_amdgcn_sched_group_barrier(0x002, (N_VALU + N_MFMA - 1) / N_MFMA, 0);  // then a few VALU operations
+          }
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -425,17 +471,17 @@ __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = acc[i][j][r] + acc_set[SETS - 1][i][j][r];
+        for (int r = 0; r < T * T / 64; ++r) acc[i][j][r] = acc[i][j][r] + acc_set[SETS - 1][i][j][r];
   }
   if constexpr (KG == 1) {
-    static_assert(NW * epilogue_wave_bytes(TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
-    write_wave_tile<MMA, TM, TN>(g, acc, lds + wave * epilogue_wave_bytes(TN), lane, p0 + wp * WTM, q0 + wq * WTN, slice);
+    static_assert(NW * epilogue_wave_bytes(WTN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
+    write_wave_tile<MMA, TM, TN>(g, acc, lds + wave * epilogue_wave_bytes(WTN), lane, p0 + wp * WTM, q0 + wq * WTN, slice);
   } else {
     // The groups' sums meet in LDS, IP row blocks of every wave at a time, and are added in a fixed order by the threads
     // that write them out, whole rows of the tile per instruction.
     // Chunk c of 4 sums of row r lies at chunk c ^ (r mod CPR): a lane per row writes to all banks without padded rows.
     constexpr int CPR = BN / 4, RING = STAGES * STAGE;
-    constexpr int IP = TM % 2 == 0 && KG * WGM * 64 * BN * 4 <= RING ? 2 : 1, ROWS = WGM * IP * 32;
+    constexpr int IP = WTM % 64 == 0 && KG * WGM * 64 * BN * 4 <= RING ? 2 : 1, ROWS = WGM * IP * 32;
     static_assert(KG * ROWS * BN * 4 <= RING && ROWS * CPR % (NW * 64) == 0, "the sums must fit in the ring");
     static_assert(CPR == 16 || CPR == 32, "a power of two, rows of a wave in step with it");
     uint32_t* const ep = reinterpret_cast<uint32_t*>(lds);
@@ -443,18 +489,19 @@ __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block
     const bool q_vec = (g.Q & 3u) == 0;
     uint32_t* const pbase = g.nsplit > 1 ? g.partial + (size_t)slice * g.P * g.Q : nullptr;
 #pragma unroll
-    for (int i0 = 0; i0 < TM; i0 += IP) {
-      uint32_t* const mine = ep + (kg * ROWS + wp * IP * 32 + (lane & 31u)) * BN;
+    for (int i0 = 0; i0 < WTM / 32; i0 += IP) {
+      uint32_t* const mine = ep + (kg * ROWS + wp * IP * 32) * BN;
 #pragma unroll
-      for (int i = 0; i < IP; ++i)
+      for (int i = 0; i < IP * 32 / T; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int gq = 0; gq < 4; ++gq)
-            *reinterpret_cast<v4u*>(mine + i * 32 * BN +
-                                    4 * ((wq * (WTN / 4) + j * 8 + 2 * gq + (lane >> 5)) ^ (lane & (CPR - 1)))) =
-                v4u{MMA::bits(acc[i0 + i][j][4 * gq]), MMA::bits(acc[i0 + i][j][4 * gq + 1]),
-                    MMA::bits(acc[i0 + i][j][4 * gq + 2]), MMA::bits(acc[i0 + i][j][4 * gq + 3])};
+          for (int gq = 0; gq < T / 4 / LG; ++gq) {
+            const acc_t& sum = acc[i0 * 32 / T + i][j];
+            const uint32_t row = i * T + lane % T, c = wq * (WTN / 4) + j * (T / 4) + gq * LG + lane / T;
+            *reinterpret_cast<v4u*>(mine + row * BN + 4 * (c ^ (row & (CPR - 1)))) =
+                v4u{MMA::bits(sum[4 * gq]), MMA::bits(sum[4 * gq + 1]), MMA::bits(sum[4 * gq + 2]), MMA::bits(sum[4 * gq + 3])};
+          }
       __syncthreads();
 #pragma unroll
       for (int it = 0; it < ROWS * CPR / (NW * 64); ++it) {
@@ -470,7 +517,7 @@ __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block
         }
         if (p < g.P && q < g.Q) store_quad<MMA>(g, pbase, p, q, raw, s, q_vec);
       }
-      if (i0 + IP < TM) __syncthreads();
+      if (i0 + IP < WTM / 32) __syncthreads();
     }
   }
 }
@@ -670,22 +717,28 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
       raw_t xf[HM], zf[2][TN];
       auto fetch_x = [&](int u, int i) { xf[i] = load_frag(stage + ((u & 1) * HM + i) * T * BK, xoff ^ ((u >> 1) * KS_XOR)); };
       auto fetch_z = [&](int ks, int j) { zf[ks & 1][j] = load_frag(stage + j * T * BK, zoff ^ (ks * KS_XOR)); };
+      fetch_z(0, 0);
+      fetch_x(0, 0);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) fetch_z(0, j);
+      for (int j = 1; j < TN; ++j) fetch_z(0, j);
 #pragma unroll
-      for (int i = 0; i < HM; ++i) fetch_x(0, i);
+      for (int i = 1; i < HM; ++i) fetch_x(0, i);
       __builtin_amdgcn_sched_barrier(0);
       frag_t xe[2], ze[TN];  // (plain copies unless the pipeline widens its operands)
-      if constexpr (MMA::WIDENS) xe[0] = MMA::expand_x(xf[0]);
+      if constexpr (MMA::WIDENS) {
+        xe[0] = MMA::expand_x(xf[0]);
+        ze[0] = MMA::expand_z(zf[0][0]);
+      }
 #pragma unroll
       for (int u = 0; u < 2 * KS; ++u) {
-        if ((u & 1) == 0) {
+        if (!MMA::WIDENS && (u & 1) == 0) {
 #pragma unroll
           for (int j = 0; j < TN; ++j) ze[j] = MMA::expand_z(zf[(u >> 1) & 1][j]);
         }
 #pragma unroll
         for (int i = 0; i < HM; ++i) {
-          if constexpr (MMA::WIDENS) {  // the next fragment is widened beside the MFMAs of this one
+          const bool first = (u & 1) == 0 && i == 0, turn = (u & 1) == 1 && i + 1 == HM && u + 1 < 2 * KS;
+          if constexpr (MMA::WIDENS) {  // the next fragments are widened beside the MFMAs of these
             if (i + 1 < HM || u + 1 < 2 * KS) xe[(i + 1) & 1] = MMA::expand_x(xf[(i + 1) % HM]);
           } else {
             xe[i & 1] = MMA::expand_x(xf[i]);
@@ -694,13 +747,19 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
           for (int j = 0; j < TN; ++j) {
             acc_t& sum = acc[(u & 1) * HM + i][j];
             sum = MMA::mma(ze[j], xe[i & 1], sum);
+            if constexpr (MMA::WIDENS) {
+              if (first && j + 1 < TN) ze[j + 1] = MMA::expand_z(zf[(u >> 1) & 1][j + 1]);
+              if (turn && j == 0) ze[0] = MMA::expand_z(zf[((u >> 1) + 1) & 1][0]);
+            }
           }
           if constexpr (MMA::WIDENS) {
             constexpr int N_MFMA = TN * MMA::MFMA_PER_MMA;
 #pragma unroll
             for (int m = 0; m < N_MFMA; ++m) {
               __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-              __builtin_amdgcn_sched_group_barrier(0x002, (MMA::VALU_PER_EXPAND + N_MFMA - 1) / N_MFMA, 0);
+              if (first) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+              else if (turn) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+              else __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
             }
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -1045,8 +1104,8 @@ __global__ __launch_bounds__(NW * 64, TWO ? 2 : 1) void gemm_cut3_kernel(GemmPar
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[0][j][r] = __fadd_rn(acc[0][j][r], low[j][r]);
   }
-  static_assert(NW * epilogue_wave_bytes(TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
-  write_wave_tile<BF16Mma, 1, TN>(g, acc, lds + wave * epilogue_wave_bytes(TN), lane, p0 + wave * 32, q0, slice);
+  static_assert(NW * epilogue_wave_bytes(32 * TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
+  write_wave_tile<BF16Mma, 1, TN>(g, acc, lds + wave * epilogue_wave_bytes(32 * TN), lane, p0 + wave * 32, q0, slice);
 }
 
 // The slice sum in a launch of its own.
