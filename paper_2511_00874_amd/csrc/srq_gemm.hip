@@ -962,7 +962,7 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
 // X is binary32 as the caller has it; the bf16 pipeline multiplies it exactly once it is cut into three
 // bfloat16 numbers that sum to it: p0 its top 8 significand bits, p1 the top 8 of the remainder, p2 what
 // is left (binary32 has 24 bits; both subtractions are exact; a non-finite x gives a NaN part).  The
-// cut is made in registers, between the LDS read and the MFMAs: 32 x 16 values cost a wave 44 vector
+// cut is made in registers, between the LDS read and the MFMAs: 512 values cost a wave 44 vector
 // operations and feed 3 TN MFMAs, so a wave owns 32 rows and ALL columns of the workgroup's tile (no
 // other wave cuts the same values), and the vector work hides behind the matrix work of the other
 // waves of the SIMD.  The matrix pipe bounds it: three products per value are what exactness costs.
@@ -1000,7 +1000,7 @@ __device__ __forceinline__ void cut3(const v4f (&x)[2], v4i (&plane)[3]) {
 // 7.1e-8 with two, 10976 x 1760 x 3312 5.4e-7 and 1.4e-7.  Twice the accumulators are 189 registers instead of 125,
 // two workgroups per CU instead of three: 8192 x 3072 x 768 forward and input gradient 233 us against 253, 16384 x 4096
 // x 1024 737 against 774.  Three stages in that ring (147 KiB of LDS): 251 and 767.  make_cut3_plan says which.
-template <int NW, int TN, int STAGES, bool TWO>
+template <class MMA, int NW, int TN, int STAGES, bool TWO>
 __global__ __launch_bounds__(NW * 64, TWO ? 2 : 1) void gemm_cut3_kernel(GemmParams g) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   constexpr int BM = 32 * NW, BN = 32 * TN;
@@ -1047,19 +1047,25 @@ __global__ __launch_bounds__(NW * 64, TWO ? 2 : 1) void gemm_cut3_kernel(GemmPar
     for (int i = 0; i < ZL; ++i) lds_dma16(zrsrc, zs + i * 1024, k < kend ? zvoff + i * 16 * g.pitch + k : OOB);
   };
 
-  // operand reads: lane (row = lane % 32, kgroup = lane / 32) takes 8 elements of the contraction
-  uint32_t xoff[4], zoff[2];
+  // operand reads: lane (row = lane % T, group = lane / T) takes 8 elements of the contraction.  A wave's 32 rows of a stage are
+  // two fragments: two sub-steps (32 x 32 MFMA tiles) or two blocks of 16 rows (16 x 16, a stage deep)
+  constexpr int T = MMA::TILE, KS = T / 16, RT = 32 / T, CN = BN / T;
+  using acc_t = typename MMA::acc_t;
+  uint32_t xoff[4], zoff[KS];
 #pragma unroll
   for (int t = 0; t < 4; ++t)
-    xoff[t] = (wave * 32 + (lane & 31u)) * XROW + ((((t >> 1) * 4 + (t & 1) + (lane >> 5) * 2) ^ ((lane >> 1) & 7u)) << 4);
+    xoff[t] = (wave * 32 + (KS == 1 ? (t >> 1) * 16 : 0) + lane % T) * XROW +
+              (((2 * (lane / T) + (t & 1) + (KS == 2 ? (t >> 1) * 4 : 0)) ^ ((lane >> 1) & 7u)) << 4);
 #pragma unroll
-  for (int t = 0; t < 2; ++t) zoff[t] = BM * XROW + (lane & 31u) * ZROW + (((2 * t + (lane >> 5)) ^ ((lane >> 2) & 3u)) << 4);
+  for (int t = 0; t < KS; ++t) zoff[t] = BM * XROW + (lane % T) * ZROW + (((2 * t + lane / T) ^ ((lane >> 2) & 3u)) << 4);
 
-  v16f acc[1][TN], low[TWO ? TN : 1];
+  acc_t acc[RT][CN], low[TWO ? RT : 1][TWO ? CN : 1];
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[0][j][r] = low[TWO ? j : 0][r] = 0.0f;
+    for (int j = 0; j < CN; ++j)
+#pragma unroll
+      for (int r = 0; r < T * T / 64; ++r) acc[i][j][r] = low[TWO ? i : 0][TWO ? j : 0][r] = 0.0f;
 
 #pragma unroll
   for (int s = 0; s < STAGES - 1; ++s) issue(s, s);  // stages past the end load zeros
@@ -1073,24 +1079,27 @@ __global__ __launch_bounds__(NW * 64, TWO ? 2 : 1) void gemm_cut3_kernel(GemmPar
         issue(kt + STAGES - 1, (s + STAGES - 1) % STAGES);
         const uint8_t* const stage = lds + s * STAGE;
         v4f x[2][2];
-        v4i z[2][TN];
+        v4i z[KS][CN];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          x[ks][0] = *reinterpret_cast<const v4f*>(stage + xoff[2 * ks]);
-          x[ks][1] = *reinterpret_cast<const v4f*>(stage + xoff[2 * ks + 1]);
+        for (int n = 0; n < 2; ++n) {
+          x[n][0] = *reinterpret_cast<const v4f*>(stage + xoff[2 * n]);
+          x[n][1] = *reinterpret_cast<const v4f*>(stage + xoff[2 * n + 1]);
+          if (n < KS) {
 #pragma unroll
-          for (int j = 0; j < TN; ++j) z[ks][j] = *reinterpret_cast<const v4i*>(stage + zoff[ks] + j * 32 * ZROW);
+            for (int j = 0; j < CN; ++j) z[n][j] = *reinterpret_cast<const v4i*>(stage + zoff[n] + j * T * ZROW);
+          }
         }
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
+        for (int n = 0; n < 2; ++n) {
+          const int i = n % RT, ks = n % KS;
           v4i plane[3];
-          cut3(x[ks], plane);
+          cut3(x[n], plane);
 #pragma unroll
           for (int b = 2; b >= 0; --b)  // small parts first
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-              v16f& sum = TWO && b > 0 ? low[TWO ? j : 0] : acc[0][j];
-              sum = BF16Mma::mma(z[ks][j], plane[b], sum);
+            for (int j = 0; j < CN; ++j) {
+              acc_t& sum = TWO && b > 0 ? low[TWO ? i : 0][TWO ? j : 0] : acc[i][j];
+              sum = MMA::mma(z[ks][j], plane[b], sum);
             }
         }
       }
@@ -1100,12 +1109,14 @@ __global__ __launch_bounds__(NW * 64, TWO ? 2 : 1) void gemm_cut3_kernel(GemmPar
   __syncthreads();
   if constexpr (TWO) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[0][j][r] = __fadd_rn(acc[0][j][r], low[j][r]);
+      for (int j = 0; j < CN; ++j)
+#pragma unroll
+        for (int r = 0; r < T * T / 64; ++r) acc[i][j][r] = __fadd_rn(acc[i][j][r], low[i][j][r]);
   }
   static_assert(NW * epilogue_wave_bytes(32 * TN) <= STAGES * STAGE, "epilogue staging must fit in the operand ring");
-  write_wave_tile<BF16Mma, 1, TN>(g, acc, lds + wave * epilogue_wave_bytes(32 * TN), lane, p0 + wave * 32, q0, slice);
+  write_wave_tile<MMA, RT, CN>(g, acc, lds + wave * epilogue_wave_bytes(32 * TN), lane, p0 + wave * 32, q0, slice);
 }
 
 // The slice sum in a launch of its own.
@@ -1333,10 +1344,10 @@ Cut3Plan make_cut3_plan(size_t P, size_t Q, size_t R, size_t partial_bytes) {
   return best;
 }
 
-template <int NW, int TN, int STAGES, bool TWO>
+template <class MMA, int NW, int TN, int STAGES, bool TWO>
 hipError_t launch_cut3(GemmParams g, hipStream_t stream) {
   constexpr int LDS_BYTES = STAGES * (32 * NW * 128 + 32 * TN * 64);
-  auto kern = &gemm_cut3_kernel<NW, TN, STAGES, TWO>;
+  auto kern = &gemm_cut3_kernel<MMA, NW, TN, STAGES, TWO>;
   static const hipError_t configured = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
   if (configured != hipSuccess) return configured;
@@ -1465,8 +1476,12 @@ hipError_t launch_gemm_f32_bf16(float* out, const float* X, const uint16_t* Z, s
   g.k_per_split = pl.k_per_split;
   g.nsplit = pl.nsplit;
   g.alpha = s.alpha; g.sx = s.sx; g.sz = s.sz; g.sx_dev = s.sx_dev; g.sz_dev = s.sz_dev;
-  if (pl.two) return pl.kind == 0 ? launch_cut3<4, 4, 2, true>(g, stream) : launch_cut3<2, 2, 3, true>(g, stream);
-  return pl.kind == 0 ? launch_cut3<4, 4, 2, false>(g, stream) : launch_cut3<2, 2, 3, false>(g, stream);
+  // MFMA tiles of 16 x 16 where the chip is full of 128 x 128 tiles and its clock counts; the small ones wait for LDS, the
+  // cut and their stores instead, and take 32 x 32 (forward and input gradient, int8 weights, us with 32 x 32 and 16 x 16:
+  // 8192 x 3072 x 768 220.7 and 208.9, 16384 x 4096 x 1024 696 and 646; 736 x 688 x 1744 46.5 and 48.2, 496 x 496 x 352 29.0 and
+  // 30.2; error against 64 bits 3.68e-7 and 3.65e-7 at the first, 6.012e-7 and 5.989e-7 at the second)
+  if (pl.two) return pl.kind == 0 ? launch_cut3<BF16Mma16, 4, 4, 2, true>(g, stream) : launch_cut3<BF16Mma, 2, 2, 3, true>(g, stream);
+  return pl.kind == 0 ? launch_cut3<BF16Mma16, 4, 4, 2, false>(g, stream) : launch_cut3<BF16Mma, 2, 2, 3, false>(g, stream);
 }
 
 }  // namespace srq
