@@ -165,6 +165,11 @@ class Quant:
         return srq_quant(self.kind, self.round_mode, value, flags, scale_dev, self.seed & (2**64 - 1), offset)
 
 
+def _q(q):
+    """A quantizer as the C entry points take it; one that is marshalled already stays as it is."""
+    return q if type(q) is srq_quant else q.c()
+
+
 def sr_absmax_scale(x, kind, out=None):
     """Device tensor holding max|x| / Qmax(kind) (1 if x is all zero)."""
     if out is None:
@@ -194,6 +199,19 @@ def sr_absmax_scales(requests):
     AbsmaxBatch(requests).run()
 
 
+def absmax_scales(pairs):
+    """The scales of [(tensor, kind)] in two launches: one tensor that holds them in order (a view of its own for each
+    costs as much as a launch)."""
+    count = len(pairs)
+    out = torch.empty(count, dtype=torch.float32, device=pairs[0][0].device)
+    at = _dev(out)
+    reqs = (srq_absmax_req * count)(*[(_dev(x), _dtype(x), kind, x.numel(), at + 4 * i) for i, (x, kind) in enumerate(pairs)])
+    need = _lib.sr_absmax_workspace_bytes(reqs, count)
+    ws = torch.empty(max(need, 4), dtype=torch.uint8, device=out.device)
+    _check(_lib.sr_absmax_scales(reqs, count, ws.data_ptr(), ws.numel(), _stream()))
+    return out
+
+
 def sr_linear_stash_bytes(M, N, K):
     return _lib.sr_linear_stash_bytes(M, N, K)
 
@@ -208,8 +226,8 @@ def sr_linear_fwd_stash(A, W, qA, qW, qA_bwd, qW_bwd, stash=None, out=None, work
     if stash is None:
         stash = torch.empty(sr_linear_stash_bytes(M, N, K), dtype=torch.uint8, device=A.device)
     ws = _ws(OP_FWD_STASH, M, N, K, workspace, A.device)
-    _check(_lib.sr_linear_fwd_stash_phase(_dev(out), _dev(A), _dtype(A), _dev(W), _dtype(W), M, N, K, C.byref(qA.c()),
-                                          C.byref(qW.c()), C.byref(qA_bwd.c()), C.byref(qW_bwd.c()), _dev(stash),
+    _check(_lib.sr_linear_fwd_stash_phase(_dev(out), _dev(A), _dtype(A), _dev(W), _dtype(W), M, N, K, _q(qA),
+                                          _q(qW), _q(qA_bwd), _q(qW_bwd), _dev(stash),
                                           stash.numel(), _dev(ws), ws.numel(), phase, _stream()))
     return out, stash
 
@@ -223,8 +241,8 @@ def sr_linear_bwd_stashed(dY, stash, K, qdY, qW, qA, out_dA=None, out_dW=None, b
     if out_dW is None:
         out_dW = torch.empty((N, K), dtype=torch.float32, device=dY.device)
     ws = _ws(OP_BWD_STASHED, M, N, K, workspace, dY.device)
-    _check(_lib.sr_linear_bwd_stashed_phase(_dev(out_dA), _dev(out_dW), _dev(dY), _dtype(dY), M, N, K, C.byref(qdY.c()),
-                                            C.byref(qW.c()), C.byref(qA.c()), _dev(stash), stash.numel(), beta, _dev(ws),
+    _check(_lib.sr_linear_bwd_stashed_phase(_dev(out_dA), _dev(out_dW), _dev(dY), _dtype(dY), M, N, K, _q(qdY),
+                                            _q(qW), _q(qA), _dev(stash), stash.numel(), beta, _dev(ws),
                                             ws.numel(), phase, _stream()))
     return out_dA, out_dW
 
@@ -245,7 +263,7 @@ def sr_quantize(x, q, transpose_out=False, out=None):
     if out is None:
         out = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=x.device)[:nbytes]
     _check(_lib.sr_quantize(_dev(out), _dev(x), _dtype(x), rows, cols, int(bool(transpose_out)),
-                            C.byref(q.c()), _stream()))
+                            _q(q), _stream()))
     return out
 
 
@@ -315,14 +333,14 @@ def sr_linear_fwd(A, W, qA, qW, out=None, workspace=None, phase=None):
     M, K = A.shape
     N = W.shape[0]
     if phase is not None:
-        _check(_lib.sr_linear_fwd_phase(_dev(out), _dev(A), _dtype(A), _dev(W), _dtype(W), M, N, K, C.byref(qA.c()),
-                                        C.byref(qW.c()), _dev(workspace), workspace.numel(), phase, _stream()))
+        _check(_lib.sr_linear_fwd_phase(_dev(out), _dev(A), _dtype(A), _dev(W), _dtype(W), M, N, K, _q(qA),
+                                        _q(qW), _dev(workspace), workspace.numel(), phase, _stream()))
         return out
     if out is None:
         out = torch.empty((M, N), dtype=torch.float32, device=A.device)
     ws = _ws(OP_FWD_WEIGHT_ONLY if qA.kind == NONE else OP_FWD, M, N, K, workspace, A.device)
     _check(_lib.sr_linear_fwd(_dev(out), _dev(A), _dtype(A), _dev(W), _dtype(W), M, N, K,
-                              C.byref(qA.c()), C.byref(qW.c()), _dev(ws), ws.numel(), _stream()))
+                              _q(qA), _q(qW), _dev(ws), ws.numel(), _stream()))
     return out
 
 
@@ -332,7 +350,7 @@ def sr_linear_fwd_static(A, W, qA, qW, out):
     M, K = A.shape
     N = W.shape[0]
     _check(_lib.sr_linear_fwd_static(_dev(out), _dev(A), _dtype(A), _dev(W), _dtype(W), M, N, K,
-                                     C.byref(qA.c()), C.byref(qW.c()), _stream()))
+                                     _q(qA), _q(qW), _stream()))
     return out
 
 
@@ -343,7 +361,7 @@ def sr_linear_fwd_fused(A, W, qA, qW, out=None):
     if out is None:
         out = torch.empty((M, N), dtype=torch.float32, device=A.device)
     _check(_lib.sr_linear_fwd_fused(_dev(out), _dev(A), _dtype(A), _dev(W), _dtype(W), M, N, K,
-                                    C.byref(qA.c()), C.byref(qW.c()), _stream()))
+                                    _q(qA), _q(qW), _stream()))
     return out
 
 
@@ -355,7 +373,7 @@ def sr_linear_bwd_data(dY, W, qdY, qW, out=None, workspace=None):
         out = torch.empty((M, K), dtype=torch.float32, device=dY.device)
     ws = _ws(OP_BWD_DATA_WEIGHT_ONLY if qdY.kind == NONE else OP_BWD_DATA, M, N, K, workspace, dY.device)
     _check(_lib.sr_linear_bwd_data(_dev(out), _dev(dY), _dtype(dY), _dev(W), _dtype(W), M, N, K,
-                                   C.byref(qdY.c()), C.byref(qW.c()), _dev(ws), ws.numel(), _stream()))
+                                   _q(qdY), _q(qW), _dev(ws), ws.numel(), _stream()))
     return out
 
 
@@ -367,7 +385,7 @@ def sr_linear_bwd_weight(dY, A, qdY, qA, out=None, beta=0.0, workspace=None):
         out = torch.empty((N, K), dtype=torch.float32, device=dY.device)
     ws = _ws(OP_BWD_WEIGHT, M, N, K, workspace, dY.device)
     _check(_lib.sr_linear_bwd_weight(_dev(out), _dev(dY), _dtype(dY), _dev(A), _dtype(A), M, N, K,
-                                     C.byref(qdY.c()), C.byref(qA.c()), beta, _dev(ws), ws.numel(),
+                                     _q(qdY), _q(qA), beta, _dev(ws), ws.numel(),
                                      _stream()))
     return out
 
@@ -379,7 +397,7 @@ def sr_linear_bwd(dY, W, A, qdY, qW, qA, out_dA=None, out_dW=None, beta=0.0, wor
     K = W.shape[1]
     if phase is not None:
         _check(_lib.sr_linear_bwd_phase(_dev(out_dA), _dev(out_dW), _dev(dY), _dtype(dY), _dev(W), _dtype(W), _dev(A),
-                                        _dtype(A), M, N, K, C.byref(qdY.c()), C.byref(qW.c()), C.byref(qA.c()), beta,
+                                        _dtype(A), M, N, K, _q(qdY), _q(qW), _q(qA), beta,
                                         _dev(workspace), workspace.numel(), phase, _stream()))
         return out_dA, out_dW
     if out_dA is None:
@@ -388,6 +406,6 @@ def sr_linear_bwd(dY, W, A, qdY, qW, qA, out_dA=None, out_dW=None, beta=0.0, wor
         out_dW = torch.empty((N, K), dtype=torch.float32, device=dY.device)
     ws = _ws(OP_BWD, M, N, K, workspace, dY.device)
     _check(_lib.sr_linear_bwd(_dev(out_dA), _dev(out_dW), _dev(dY), _dtype(dY), _dev(W), _dtype(W), _dev(A),
-                              _dtype(A), M, N, K, C.byref(qdY.c()), C.byref(qW.c()), C.byref(qA.c()), beta,
+                              _dtype(A), M, N, K, _q(qdY), _q(qW), _q(qA), beta,
                               _dev(ws), ws.numel(), _stream()))
     return out_dA, out_dW

@@ -14,12 +14,21 @@ from . import lib as L
 # the widest layer used here (32000 outputs in the two-byte form).  Token chunks are independent
 # in Y and dA; dW accumulates over them (beta = 1), which is also how micro-batches accumulate.
 MAX_ROWS = 16384
+MASK64 = 2**64 - 1
 NOQ = L.Quant(L.NONE, 1.0)  # the identity quantizer of the weight-only objective
 
 
 def _rows(t, r0, r1):
     """Rows r0 .. r1 - 1 of t; t itself where that is all of them (a view costs as much as a kernel launch)."""
     return t if r0 == 0 and r1 == t.shape[0] else t[r0:r1]
+
+
+def _matrix(x, cols):
+    """x as a dense binary32 matrix of `cols` columns; x itself where it is one (each of the three steps costs as much as a
+    launch, also where it changes nothing)."""
+    if x.dim() == 2 and x.shape[1] == cols and x.dtype is torch.float32 and x.is_contiguous():
+        return x
+    return x.reshape(-1, cols).contiguous().float()
 
 
 class SRLinearFn(torch.autograd.Function):
@@ -34,18 +43,18 @@ class SRLinearFn(torch.autograd.Function):
     def forward(ctx, x, layer):
         ctx.layer = layer
         ctx.shape = x.shape
-        a = x.reshape(-1, x.shape[-1]).contiguous().float()
+        a = _matrix(x, x.shape[-1])
         y, ctx.saved = layer._forward(a)
         if "stash" not in ctx.saved:  # the backward pass quantizes (or multiplies) the activation itself
             ctx.save_for_backward(a)
-        return y.reshape(*x.shape[:-1], layer.out_features)
+        return y if x.dim() == 2 else y.reshape(*x.shape[:-1], layer.out_features)
 
     @staticmethod
     def backward(ctx, dy):
         a = ctx.saved_tensors[0] if ctx.saved_tensors else None
         layer = ctx.layer
-        da = layer._backward(dy.reshape(-1, layer.out_features).contiguous().float(), a, ctx.saved)
-        return da.reshape(ctx.shape), None
+        da = layer._backward(_matrix(dy, layer.out_features), a, ctx.saved)
+        return da if len(ctx.shape) == 2 else da.reshape(ctx.shape), None
 
 
 OBJECTIVES = ("five", "weight_only", "qat")
@@ -91,14 +100,33 @@ class SRLinear(torch.nn.Module):
         self.seed, self.position, self.round_mode = seed, 0, round_mode
         self.ws = None
 
-    def _q(self, name, scale, position):
-        return L.Quant(self.kinds[name], scale, seed=self.seed, counter_offset=position, round_mode=self.round_mode)
+    _sizes = None  # bytes that calls of so many rows need
 
-    def _scales(self, n):
-        return torch.empty(n, dtype=torch.float32, device=self.weight.device)
+    def _size(self, op, M):
+        """Bytes of workspace for a call of M rows, or of its stash (op None).  A query plans the products anew: up to 256
+        answers are kept."""
+        sizes = self._sizes
+        if sizes is None or len(sizes) >= 256:
+            sizes = self._sizes = {}
+        key = (op, M, self.out_features, self.in_features)
+        need = sizes.get(key)
+        if need is None:
+            need = sizes[key] = L.sr_linear_stash_bytes(*key[1:]) if op is None else L.sr_linear_workspace_bytes(*key)
+        return need
+
+    def _q(self, name, scales, i, position):
+        """The quantizer of `name` with the i-th of `scales`, in the form of the C interface: for calls while `scales` lives."""
+        return L.srq_quant(self.kinds[name], self.round_mode, 0.0, 0, scales.data_ptr() + 4 * i, self.seed & MASK64,
+                           position & MASK64)
+
+    @staticmethod
+    def _q_saved(saved):
+        """The weights' quantizer of a forward pass for its backward pass (everything but the address of its scale is kept)."""
+        i, kind, rounding, seed, position = saved["w"]
+        return L.srq_quant(kind, rounding, 0.0, 0, saved["scales"].data_ptr() + 4 * i, seed, position)
 
     def _workspace(self, op, M):
-        need = L.sr_linear_workspace_bytes(op, M, self.out_features, self.in_features)
+        need = self._size(op, M)
         if self.ws is None or self.ws.numel() < need:
             self.ws = torch.empty(need, dtype=torch.uint8, device=self.weight.device)
         return self.ws
@@ -109,29 +137,30 @@ class SRLinear(torch.nn.Module):
         N = self.out_features
         w = self.weight
         qat = self.objective == "qat"
-        sc = self._scales(2)                          # W, and (qat) A for the backward pass
-        reqs = [(w, self.kinds["W_fwd"], sc[0:1])]
+        pairs = [(w, self.kinds["W_fwd"])]            # W, and (qat) A for the backward pass
         if qat:
-            reqs.append((a, self.kinds["A_bwd"], sc[1:2]))
-        L.sr_absmax_scales(reqs)
-        saved = {"qw": self._q("W_fwd", sc[0:1], self.position)}  # the same copy serves the backward pass
+            pairs.append((a, self.kinds["A_bwd"]))
+        sc = L.absmax_scales(pairs)
+        qw = self._q("W_fwd", sc, 0, self.position)   # the same copy serves the backward pass
+        saved = {"scales": sc, "w": (0, qw.kind, qw.round, qw.seed, qw.counter_offset)}
         self.position += (N * K + 7) // 8
         if qat:
-            saved["sA"], saved["pos_a"] = sc[1:2], self.position
+            saved["a"] = 1, self.position
             self.position += (M * K + 7) // 8
         y = torch.empty((M, N), dtype=torch.float32, device=a.device)
         for r0 in range(0, M, MAX_ROWS):
             r1 = min(M, r0 + MAX_ROWS)
-            L.sr_linear_fwd(_rows(a, r0, r1), w, NOQ, saved["qw"], out=_rows(y, r0, r1),
+            L.sr_linear_fwd(_rows(a, r0, r1), w, NOQ, qw, out=_rows(y, r0, r1),
                             workspace=self._workspace(L.OP_FWD_WEIGHT_ONLY, r1 - r0))
         return y, saved
 
     def _backward_weight_only(self, dy, a, saved):
         M, N = dy.shape
         da = torch.empty((M, self.in_features), dtype=torch.float32, device=dy.device)
+        qw = self._q_saved(saved)
         for r0 in range(0, M, MAX_ROWS):
             r1 = min(M, r0 + MAX_ROWS)
-            L.sr_linear_bwd_data(_rows(dy, r0, r1), self.weight, NOQ, saved["qw"], out=_rows(da, r0, r1),
+            L.sr_linear_bwd_data(_rows(dy, r0, r1), self.weight, NOQ, qw, out=_rows(da, r0, r1),
                                  workspace=self._workspace(L.OP_BWD_DATA_WEIGHT_ONLY, r1 - r0))
         if self.have_grad:
             self.dW.addmm_(dy.t(), a)
@@ -146,19 +175,20 @@ class SRLinear(torch.nn.Module):
         M, K = a.shape
         N = self.out_features
         w = self.weight
-        sc = self._scales(4)
-        L.sr_absmax_scales([(a, self.kinds["A_fwd"], sc[0:1]), (w, self.kinds["W_fwd"], sc[1:2]),
-                            (a, self.kinds["A_bwd"], sc[2:3]), (w, self.kinds["W_bwd"], sc[3:4])])
+        sc = L.absmax_scales([(a, self.kinds["A_fwd"]), (w, self.kinds["W_fwd"]), (a, self.kinds["A_bwd"]),
+                              (w, self.kinds["W_bwd"])])
         # every tensor gets its own stretch of the stream (in blocks of 8 elements); a chunk that
         # starts at row r0 continues where the rows before it would have drawn, so the codes do
         # not depend on the chunking.  The backward quantizers of A and W get theirs now.
         a_blocks, w_blocks = (M * K + 7) // 8, (N * K + 7) // 8
-        pos_w, pos_a = self.position, self.position + w_blocks
-        saved = {"sA": sc[2:3], "pos_a": pos_a + a_blocks,
-                 "qw": self._q("W_bwd", sc[3:4], pos_a + 2 * a_blocks)}
-        self.position = pos_a + 2 * a_blocks + w_blocks
+        pos_w = self.position
+        pos_a = pos_w + w_blocks
+        pos_a_bwd = pos_a + a_blocks
+        pos_w_bwd = pos_a_bwd + a_blocks
+        self.__dict__["position"] = pos_w_bwd + w_blocks  # (Module.__setattr__ would look for parameters and modules first)
+        qw, qw_bwd = self._q("W_fwd", sc, 1, pos_w), self._q("W_bwd", sc, 3, pos_w_bwd)
+        saved = {"scales": sc, "a": (2, pos_a_bwd), "w": (3, qw_bwd.kind, qw_bwd.round, qw_bwd.seed, qw_bwd.counter_offset)}
         y = torch.empty((M, N), dtype=torch.float32, device=a.device)
-        qw = self._q("W_fwd", sc[1:2], pos_w)
         # integer forward formats: the same pass over A and W also writes the codes of their backward
         # quantizers (one stash per chunk of rows), and the activation itself need not be kept
         stash = self.kinds["A_fwd"] in (L.INT8, L.INT4)
@@ -166,11 +196,12 @@ class SRLinear(torch.nn.Module):
             saved["stash"] = []
         for r0 in range(0, M, MAX_ROWS):
             r1 = min(M, r0 + MAX_ROWS)
-            qa = self._q("A_fwd", sc[0:1], pos_a + (r0 * K) // 8)
+            qa = self._q("A_fwd", sc, 0, pos_a + (r0 * K) // 8)
             if stash:
-                qa_bwd = self._q("A_bwd", saved["sA"], saved["pos_a"] + (r0 * K) // 8)
-                _, st = L.sr_linear_fwd_stash(_rows(a, r0, r1), w, qa, qw, qa_bwd, saved["qw"], out=_rows(y, r0, r1),
-                                              workspace=self._workspace(L.OP_FWD_STASH, r1 - r0))
+                qa_bwd = self._q("A_bwd", sc, 2, pos_a_bwd + (r0 * K) // 8)
+                st = torch.empty(self._size(None, r1 - r0), dtype=torch.uint8, device=a.device)
+                L.sr_linear_fwd_stash(_rows(a, r0, r1), w, qa, qw, qa_bwd, qw_bwd, stash=st, out=_rows(y, r0, r1),
+                                      workspace=self._workspace(L.OP_FWD_STASH, r1 - r0))
                 saved["stash"].append(st)
             else:
                 L.sr_linear_fwd(_rows(a, r0, r1), w, qa, qw, out=_rows(y, r0, r1),
@@ -185,23 +216,23 @@ class SRLinear(torch.nn.Module):
         M, N = dy.shape
         K = self.in_features
         w = self.weight
-        sdy = self._scales(1)
-        L.sr_absmax_scales([(dy, self.kinds["dY_bwd"], sdy)])
+        sdy = L.absmax_scales([(dy, self.kinds["dY_bwd"])])
         da = torch.empty((M, K), dtype=torch.float32, device=dy.device)
         pos_dy = self.position
-        self.position += (M * N + 7) // 8
+        self.__dict__["position"] = pos_dy + (M * N + 7) // 8
+        scales, (i_a, pos_a), qw = saved["scales"], saved["a"], self._q_saved(saved)
         for i, r0 in enumerate(range(0, M, MAX_ROWS)):
             r1 = min(M, r0 + MAX_ROWS)
-            qdy = self._q("dY_bwd", sdy, pos_dy + (r0 * N) // 8)
-            qa = self._q("A_bwd", saved["sA"], saved["pos_a"] + (r0 * K) // 8)
+            qdy = self._q("dY_bwd", sdy, 0, pos_dy + (r0 * N) // 8)
+            qa = self._q("A_bwd", scales, i_a, pos_a + (r0 * K) // 8)
             beta = 1.0 if self.have_grad else 0.0
             if "stash" in saved:
-                L.sr_linear_bwd_stashed(_rows(dy, r0, r1), saved["stash"][i], K, qdy, saved["qw"], qa,
+                L.sr_linear_bwd_stashed(_rows(dy, r0, r1), saved["stash"][i], K, qdy, qw, qa,
                                         out_dA=_rows(da, r0, r1), out_dW=self.dW, beta=beta, workspace=self._workspace(L.OP_BWD_STASHED, r1 - r0))
             else:
-                L.sr_linear_bwd(_rows(dy, r0, r1), w, _rows(a, r0, r1), qdy, saved["qw"], qa,
+                L.sr_linear_bwd(_rows(dy, r0, r1), w, _rows(a, r0, r1), qdy, qw, qa,
                                 out_dA=_rows(da, r0, r1), out_dW=self.dW, beta=beta, workspace=self._workspace(L.OP_BWD, r1 - r0))
-            self.have_grad = True
+            self.__dict__["have_grad"] = True
         return da
 
     def forward(self, x):
