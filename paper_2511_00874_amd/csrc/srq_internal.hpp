@@ -86,10 +86,11 @@ struct QuantJobs {
   QuantJob job[QUANT_JOBS_MAX];
 };
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream);
-// Those of them whose jobs are all of one sort, which has a kernel of its own (srq_quantize_dual.hip): E4M3 or E5M2 codes turned and
-// the codes of a second, integer quantizer as the source lies, both rounding stochastically, in tiles of DUAL_TILE_ROWS rows.
-constexpr uint32_t DUAL_TILE_ROWS = 128;
-hipError_t launch_quantize_duals(const QuantJobs& jobs, uint32_t blocks, bool cached, hipStream_t stream);
+// Those of them whose jobs are all of one sort, which has a kernel of its own (srq_quantize_dual.hip): E4M3 or E5M2 codes turned,
+// rounding stochastically, in tiles of TURN_TILE_ROWS rows, alone, with the same codes as the source lies, or with the codes of a
+// second, integer quantizer that rounds stochastically.
+constexpr uint32_t TURN_TILE_ROWS = 128;
+hipError_t launch_quantize_turned(const QuantJobs& jobs, uint32_t blocks, bool cached, hipStream_t stream);
 
 // Several per-tensor scales in two launches: up to ABSMAX_MAX distinct tensors and
 // ABSMAX_MAX scales (a tensor may feed several formats).

@@ -1,15 +1,19 @@
-// The operand quantizers of a forward pass that also saves its operands for the backward pass, where that takes 8-bit floats: every
-// element of A and W goes through two quantizers, its E4M3 or E5M2 code is written turned, its integer code as the source lies.
-// (Such a launch of quantize_jobs_kernel, with two quantizers by conversion and by permutes; a kernel of its own because that one's
-// registers have no room for it.)
+// The operand quantizers that write E4M3 or E5M2 codes turned: of a forward pass that also saves its operands for the backward pass
+// (every element of A and W goes through two quantizers, its integer code is written as the source lies), and of a backward pass (an
+// output gradient in both layouts; A and W, turned only).  (Such launches of quantize_jobs_kernel, by conversion and by permutes; a
+// kernel of its own because that one's registers have no room for it.)
 //
-// What bounds it is the vector ALU, two Philox blocks for eight elements, beside the loads.  The stochastic conversions
-// (quantize_octet) take a third of the ALU work off, less where a tensor holds subnormals of the grid.  us of the forward quantizers, E5M2 and
-// E4M3 of normal tensors / E4M3 of an activation with 1 % of outliers / of one over 40 binades: GPT-2's second linear (8192 x 3072 and
-// 768 x 3072, 165 MB) 39.3 -> 32.3, 39.9 -> 33.0 / 39.7 -> 34.4 / 39.0 -> 35.2; 1008 x 768 and 3072 x 768 9.2 -> 6.6, 9.4 -> 6.8 / 9.4 -> 6.9 /
-// 9.2 -> 6.8; 4096 x 2048 and 2048 x 2048 20.3 -> 16.5, 21.1 -> 16.9 / 20.0 -> 17.2 / 20.0 -> 17.1.
-// Not for large tensors or other jobs: with one quantizer, or two of integers, there is less to save than this order of the reads costs
-// (8192 x 3072 E5M2 in both layouts 27.6 -> 28.7 us; 65536 x 2048, rows a power of two apart, int4 108 -> 143).
+// What bounds it is the vector ALU, one or two Philox blocks for eight elements, beside the loads.  The stochastic conversions
+// (quantize_octet) take a third of the ALU work off, less where a tensor holds subnormals of the grid; codes go to LDS four at a time instead
+// of one, and the same-layout codes leave in pieces of 8 bytes.  us, before and now:
+//   two quantizers, E5M2 and E4M3 of normal tensors / E4M3 of an activation with 1 % of outliers / of one over 40 binades: GPT-2's second
+//   linear (8192 x 3072 and 768 x 3072, 165 MB) 39.3 -> 32.3, 39.9 -> 33.0 / 39.7 -> 34.4 / 39.0 -> 35.2; 1008 x 768 and 3072 x 768
+//   9.2 -> 6.6, 9.4 -> 6.8 / 9.4 -> 6.9 / 9.2 -> 6.8; 4096 x 2048 and 2048 x 2048 20.3 -> 16.5, 21.1 -> 16.9 / 20.0 -> 17.2 / 20.0 -> 17.1;
+//   one quantizer in both layouts, E5M2, binary32 and bfloat16: 4096 x 2048 11.8 -> 10.3, 11.6 -> 9.2; 8192 x 2048 23.0 -> 19.1, 18.5 ->
+//   14.3; 8192 x 3072 28.5 -> 27.1, 26.3 -> 21.4; 65536 x 256 20.8 -> 19.0, 19.9 -> 15.9; the three of a backward call, 1008 x 3072 and
+//   3072 x 3072 16.7 -> 13.5, 8192 x 2048 and 2048 x 2048 38.6 -> 33.2, 16384 x 1024 and 1024 x 1024 35.4 -> 35.5 (bfloat16 16.6 -> 12.4,
+//   35.9 -> 24.9, 31.9 -> 24.3).  E4M3 within 2 % of these.  Not so binary32 rows 16 KiB apart (turn_strided).
+// Not for large tensors (65536 x 2048, rows a power of two apart, int4 108 -> 143) or integers turned, where there is less to save.
 #include <cstddef>
 #include <type_traits>
 
@@ -20,7 +24,7 @@ namespace srq {
 namespace {
 
 constexpr int QBLOCK = 256;
-constexpr uint32_t TC = 64, TR = DUAL_TILE_ROWS;  // tile: TR source rows x TC source columns
+constexpr uint32_t TC = 64, TR = TURN_TILE_ROWS;  // tile: TR source rows x TC source columns
 constexpr uint32_t PITCH = TR + 4;                // the words a wave instruction writes to LDS fall on all 64 banks
 constexpr uint32_t BAND_GROUP = 32;               // tile order as there
 
@@ -66,8 +70,9 @@ __device__ __forceinline__ global_ptr<T> uniform_ptr(T* p) {
 // for everything, the stores that write through included (8192 x 3072 and 768 x 3072 34.8 instead of 33.1 us).
 // binary32: 4 columns; lanes L and L + 32 hold the two halves of each Philox group, so that a swap of wave halves hands out the random
 // words of two rows and another one makes 8-byte pieces of the integer codes.  bfloat16: 8 columns, a group a row.
-template <int KIND, bool F32, bool CACHED>
-__device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t* tile) {
+enum Second { SECOND_INT, SECOND_SAME, SECOND_NONE };  // what is written as the source lies: integer codes, the same codes, nothing
+template <int KIND, bool F32, Second SECOND, bool CACHED>
+__device__ __forceinline__ void turn_tile(job_words job, uint32_t local, uint8_t* tile) {
   const QuantJob j = read_job(job);
   const uint32_t tiles_x = (j.cols + TC - 1) / TC, tiles_y = (j.rows + TR - 1) / TR;
   const uint32_t band0 = local / (BAND_GROUP * tiles_x) * BAND_GROUP, within = local - band0 * tiles_x;
@@ -95,9 +100,14 @@ __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t
 #pragma unroll
   for (int i = 0; i < 4; ++i) load(0, i);
   // (the first loads are under way before the scales are waited for)
-  const InvScale inv = uniform(inv_scale(j.scale, j.scale_dev, j.kind)), inv2 = uniform(inv_scale(j.scale2, j.scale_dev2, j.kind2));
+  const InvScale inv = uniform(inv_scale(j.scale, j.scale_dev, j.kind));
   const uint64_t ctr = uniform(first_block(j.counter_offset, j.counter_dev));
-  const uint64_t ctr2 = uniform(first_block(j.counter_offset2, j.counter_dev2));
+  InvScale inv2 = inv;
+  uint64_t ctr2 = 0;
+  if constexpr (SECOND == SECOND_INT) {
+    inv2 = uniform(inv_scale(j.scale2, j.scale_dev2, j.kind2));
+    ctr2 = uniform(first_block(j.counter_offset2, j.counter_dev2));
+  }
   const uint32_t steps_end = min(TR, rows - r0);
   auto step = [&](uint32_t r, auto more) __attribute__((always_inline)) {
     const bool inside = col_ok && r0 + rl + r < rows;
@@ -118,10 +128,15 @@ __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t
         const u32x2 q = quantize_octet<KIND>(x, y, inv, w, true);
         c[i] = q.x;
         c[i + 1] = q.y;
-        round_words_of_pair(ctr2 + group + group_off, m0, m1, w);
-        const u32x2 q2 = quantize_octet<SRQ_INTX>(x, y, inv2, w, true);
-        out2[i] = q2.x;
-        out2[i + 1] = q2.y;
+        if constexpr (SECOND == SECOND_INT) {
+          round_words_of_pair(ctr2 + group + group_off, m0, m1, w);
+          const u32x2 q2 = quantize_octet<SRQ_INTX>(x, y, inv2, w, true);
+          out2[i] = q2.x;
+          out2[i + 1] = q2.y;
+        } else {
+          out2[i] = q.x;
+          out2[i + 1] = q.y;
+        }
         if constexpr (more.value) {
           load(r + STEP, i);
           load(r + STEP, i + 1);
@@ -129,7 +144,7 @@ __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < 4; i += 2) {
+      for (int i = 0; i < (SECOND == SECOND_NONE ? 0 : 4); i += 2) {
         swap_halves(out2[i], out2[i + 1]);  // this lane: the whole group of its row
         const global_ptr<uint8_t> o = uniform_ptr(p.out2 + (group_step + (size_t)i * gstep) * 8) + group_off * 8;
         const u32x2 q2 = {out2[i], out2[i + 1]};
@@ -152,8 +167,9 @@ __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t
           f[2 * e + 1] = bf16_to_f32(v[i][e] >> 16);
         }
         c[i] = quantize_group_words<KIND>(f, inv, ctr + group + group_off, k0, k1, true);
-        const u32x2 q2 = quantize_group_words<SRQ_INTX>(f, inv2, ctr2 + group + group_off, m0, m1, true);
-        if (inside) *reinterpret_cast<global_ptr<u32x2>>(uniform_ptr(p.out2 + group * 8) + group_off * 8) = q2;
+        u32x2 q2 = c[i];
+        if constexpr (SECOND == SECOND_INT) q2 = quantize_group_words<SRQ_INTX>(f, inv2, ctr2 + group + group_off, m0, m1, true);
+        if (SECOND != SECOND_NONE && inside) *reinterpret_cast<global_ptr<u32x2>>(uniform_ptr(p.out2 + group * 8) + group_off * 8) = q2;
       }
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -187,6 +203,20 @@ __device__ __forceinline__ void dual_tile(job_words job, uint32_t local, uint8_t
   }
 }
 
+template <int KIND, bool CACHED>
+__device__ __forceinline__ void turn_job(const QuantJob& j, job_words job, uint32_t local, uint8_t* tile) {
+  if (j.out2 && j.kind2) {
+    if (j.dtype == SRQ_F32) turn_tile<KIND, true, SECOND_INT, CACHED>(job, local, tile);
+    else turn_tile<KIND, false, SECOND_INT, CACHED>(job, local, tile);
+  } else if (j.out2) {
+    if (j.dtype == SRQ_F32) turn_tile<KIND, true, SECOND_SAME, CACHED>(job, local, tile);
+    else turn_tile<KIND, false, SECOND_SAME, CACHED>(job, local, tile);
+  } else {
+    if (j.dtype == SRQ_F32) turn_tile<KIND, true, SECOND_NONE, CACHED>(job, local, tile);
+    else turn_tile<KIND, false, SECOND_NONE, CACHED>(job, local, tile);
+  }
+}
+
 // At most 64 registers: a wave fits on a SIMD beside two of the persistent product kernel.
 template <bool CACHED>
 __global__ __launch_bounds__(QBLOCK) void quantize_dual_kernel(QuantJobs jobs) {
@@ -199,18 +229,13 @@ __global__ __launch_bounds__(QBLOCK) void quantize_dual_kernel(QuantJobs jobs) {
                         (offsetof(QuantJobs, job) + (size_t)ji * sizeof(QuantJob)) / 4;
   const QuantJob j = read_job(job);
   const uint32_t local = blockIdx.x - j.first_block;
-  if (j.kind == SRQ_E5M2) {
-    if (j.dtype == SRQ_F32) dual_tile<SRQ_E5M2, true, CACHED>(job, local, tile);
-    else dual_tile<SRQ_E5M2, false, CACHED>(job, local, tile);
-  } else {
-    if (j.dtype == SRQ_F32) dual_tile<SRQ_E4M3_CONV, true, CACHED>(job, local, tile);
-    else dual_tile<SRQ_E4M3_CONV, false, CACHED>(job, local, tile);
-  }
+  if (j.kind == SRQ_E5M2) turn_job<SRQ_E5M2, CACHED>(j, job, local, tile);
+  else turn_job<SRQ_E4M3_CONV, CACHED>(j, job, local, tile);
 }
 
 }  // namespace
 
-hipError_t launch_quantize_duals(const QuantJobs& jobs, uint32_t blocks, bool cached, hipStream_t stream) {
+hipError_t launch_quantize_turned(const QuantJobs& jobs, uint32_t blocks, bool cached, hipStream_t stream) {
   if (cached) quantize_dual_kernel<true><<<blocks, QBLOCK, 0, stream>>>(jobs);
   else quantize_dual_kernel<false><<<blocks, QBLOCK, 0, stream>>>(jobs);
   return hipGetLastError();

@@ -329,12 +329,19 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
 
 }  // namespace
 
+// Binary32 rows a multiple of 16 KiB apart: the sixteen rows that a wave instruction of launch_quantize_turned's kernel reads a piece of
+// then share a few memory channels, and many tiles of them wait for each other where the four neighbouring rows of
+// quantize_jobs_kernel do not (one quantizer, E5M2 in both layouts, us there and here: rows x 4096 at 2048 rows 11.8 and 11.5, 3072 14.4 and
+// 15.5, 4096 21.5 and 27.5, 6144 28.8 and 36.7; x 8192 at 2048 27.6 and 23.6, 3072 32.4 and 32.8; at 4096 rows x 4160 21.3 and 20.0,
+// x 5120 25.3 and 24.0).
+static bool turn_strided(const QuantJob& j) { return j.dtype == SRQ_F32 && j.cols % 4096 == 0 && j.rows > 2048; }
+
 // Requirements (checked by the callers): rows % 16 == 0 and cols % 16 == 0 for every job,
 // store is STORE_BYTE or STORE_BF16.
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
   uint32_t first = 0;
   size_t bytes = jobs.other_bytes;
-  bool duals = true;  // all of them such as launch_quantize_duals takes
+  bool turned = true;  // all of them such as launch_quantize_turned takes
   for (int i = 0; i < jobs.njobs; ++i) {
     QuantJob& j = jobs.job[i];
     bytes += source_bytes((size_t)j.rows * j.cols, j.dtype);
@@ -342,20 +349,21 @@ hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
     if (j.transpose) {
       const size_t tr = tile_rows(j.store == STORE_BF16, j.rows, j.cols);
       nb = (size_t)((j.cols + TC - 1) / TC) * ((j.rows + tr - 1) / tr);
-      duals = duals && tr == DUAL_TILE_ROWS;
+      turned = turned && tr == TURN_TILE_ROWS;
     } else {
       const size_t groups = (size_t)j.rows * j.cols / 8;
       nb = (groups + FLAT_GROUPS_PER_BLOCK - 1) / FLAT_GROUPS_PER_BLOCK;
       if (nb > (1u << 20)) nb = 1u << 20;
     }
-    duals = duals && j.transpose && j.store == STORE_BYTE && (j.kind == SRQ_E4M3 || j.kind == SRQ_E5M2) && j.out2 && j.kind2 &&
-            j.round == SRQ_SR && j.round2 == SRQ_SR;
+    const bool two = j.out2 && j.kind2;
+    turned = turned && j.transpose && j.store == STORE_BYTE && (j.kind == SRQ_E4M3 || j.kind == SRQ_E5M2) && j.round == SRQ_SR &&
+             !(two && j.round2 != SRQ_SR) && (two || !turn_strided(j));
     j.first_block = first;
     j.nblocks = (uint32_t)nb;
     first += (uint32_t)nb;
   }
   if (first == 0) return hipSuccess;
-  if (duals) return launch_quantize_duals(jobs, first, bytes <= JOBS_CACHED_BYTES, stream);
+  if (turned) return launch_quantize_turned(jobs, first, bytes <= JOBS_CACHED_BYTES, stream);
   // decided for the launch (two forms inside one kernel cost more than they gave)
   if (bytes <= JOBS_CACHED_BYTES) quantize_jobs_kernel<true><<<first, QBLOCK, 0, stream>>>(jobs);
   else quantize_jobs_kernel<false><<<first, QBLOCK, 0, stream>>>(jobs);
