@@ -86,9 +86,9 @@ struct QuantJobs {
   QuantJob job[QUANT_JOBS_MAX];
 };
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream);
-// Those of them whose jobs are all of one sort, which has a kernel of its own (srq_quantize_dual.hip): E4M3 or E5M2 codes turned,
-// rounding stochastically, in tiles of TURN_TILE_ROWS rows, alone, with the same codes as the source lies, or with the codes of a
-// second, integer quantizer that rounds stochastically.
+// Those of them whose jobs are all of one sort, which has a kernel of its own (srq_quantize_dual.hip): byte codes turned, rounding
+// stochastically, in tiles of TURN_TILE_ROWS rows, alone, with the same codes as the source lies, or (8-bit floats) with the codes of a
+// second, integer quantizer that rounds stochastically.  Not the E4M3 sub-grids, nor 4-bit values two per byte.
 constexpr uint32_t TURN_TILE_ROWS = 128;
 hipError_t launch_quantize_turned(const QuantJobs& jobs, uint32_t blocks, bool cached, hipStream_t stream);
 

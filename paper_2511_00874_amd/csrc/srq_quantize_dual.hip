@@ -1,6 +1,6 @@
-// The operand quantizers that write E4M3 or E5M2 codes turned: of a forward pass that also saves its operands for the backward pass
-// (every element of A and W goes through two quantizers, its integer code is written as the source lies), and of a backward pass (an
-// output gradient in both layouts; A and W, turned only).  (Such launches of quantize_jobs_kernel, by conversion and by permutes; a
+// The operand quantizers that write byte codes turned, rounding stochastically: of a forward pass that also saves its operands as 8-bit floats for
+// the backward pass (every element of A and W goes through two quantizers, its integer code is written as the source lies), and of a
+// backward pass (an output gradient in both layouts; A and W, turned only).  (Such launches of quantize_jobs_kernel, by conversion and by permutes; a
 // kernel of its own because that one's registers have no room for it.)
 //
 // What bounds it is the vector ALU, one or two Philox blocks for eight elements, beside the loads.  The stochastic conversions
@@ -12,8 +12,11 @@
 //   one quantizer in both layouts, E5M2, binary32 and bfloat16: 4096 x 2048 11.8 -> 10.3, 11.6 -> 9.2; 8192 x 2048 23.0 -> 19.1, 18.5 ->
 //   14.3; 8192 x 3072 28.5 -> 27.1, 26.3 -> 21.4; 65536 x 256 20.8 -> 19.0, 19.9 -> 15.9; the three of a backward call, 1008 x 3072 and
 //   3072 x 3072 16.7 -> 13.5, 8192 x 2048 and 2048 x 2048 38.6 -> 33.2, 16384 x 1024 and 1024 x 1024 35.4 -> 35.5 (bfloat16 16.6 -> 12.4,
-//   35.9 -> 24.9, 31.9 -> 24.3).  E4M3 within 2 % of these.  Not so binary32 rows 16 KiB apart (turn_strided).
-// Not for large tensors (65536 x 2048, rows a power of two apart, int4 108 -> 143) or integers turned, where there is less to save.
+//   35.9 -> 24.9, 31.9 -> 24.3).  E4M3 within 2 % of these.  Integers in both layouts, int8, binary32 and bfloat16: 2048 x 2048 8.9 -> 8.6,
+//   9.0 -> 8.6; 4096 x 2048 10.6 -> 10.0, 10.0 -> 8.7; 8192 x 2048 22.0 -> 19.2, 16.1 -> 13.7; 15360 x 2048 37.2 -> 32.7, 32.1 -> 25.3.
+//   Not so binary32 rows 16 KiB apart (turn_strided).
+// Not for large tensors (65536 x 2048, rows a power of two apart, int4 108 -> 143), nor two integer quantizers: they take 68 registers, and within
+// 64 they spill (8192 x 2048 26.4 -> 26.6, 16384 x 1024 23.9 -> 27.9).
 #include <cstddef>
 #include <type_traits>
 
@@ -205,9 +208,11 @@ __device__ __forceinline__ void turn_tile(job_words job, uint32_t local, uint8_t
 
 template <int KIND, bool CACHED>
 __device__ __forceinline__ void turn_job(const QuantJob& j, job_words job, uint32_t local, uint8_t* tile) {
-  if (j.out2 && j.kind2) {
-    if (j.dtype == SRQ_F32) turn_tile<KIND, true, SECOND_INT, CACHED>(job, local, tile);
-    else turn_tile<KIND, false, SECOND_INT, CACHED>(job, local, tile);
+  if (Grid<KIND>::is_float && j.out2 && j.kind2) {  // (two of integers take 68 registers)
+    if constexpr (Grid<KIND>::is_float) {
+      if (j.dtype == SRQ_F32) turn_tile<KIND, true, SECOND_INT, CACHED>(job, local, tile);
+      else turn_tile<KIND, false, SECOND_INT, CACHED>(job, local, tile);
+    }
   } else if (j.out2) {
     if (j.dtype == SRQ_F32) turn_tile<KIND, true, SECOND_SAME, CACHED>(job, local, tile);
     else turn_tile<KIND, false, SECOND_SAME, CACHED>(job, local, tile);
@@ -230,7 +235,8 @@ __global__ __launch_bounds__(QBLOCK) void quantize_dual_kernel(QuantJobs jobs) {
   const QuantJob j = read_job(job);
   const uint32_t local = blockIdx.x - j.first_block;
   if (j.kind == SRQ_E5M2) turn_job<SRQ_E5M2, CACHED>(j, job, local, tile);
-  else turn_job<SRQ_E4M3_CONV, CACHED>(j, job, local, tile);
+  else if (j.kind == SRQ_E4M3) turn_job<SRQ_E4M3_CONV, CACHED>(j, job, local, tile);
+  else turn_job<SRQ_INTX, CACHED>(j, job, local, tile);
 }
 
 }  // namespace

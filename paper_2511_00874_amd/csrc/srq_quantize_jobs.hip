@@ -333,8 +333,8 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
 // then share a few memory channels, and many tiles of them wait for each other where the four neighbouring rows of
 // quantize_jobs_kernel do not (one quantizer, E5M2 in both layouts, us there and here: rows x 4096 at 2048 rows 11.8 and 11.5, 3072 14.4 and
 // 15.5, 4096 21.5 and 27.5, 6144 28.8 and 36.7; x 8192 at 2048 27.6 and 23.6, 3072 32.4 and 32.8; at 4096 rows x 4160 21.3 and 20.0,
-// x 5120 25.3 and 24.0).
-static bool turn_strided(const QuantJob& j) { return j.dtype == SRQ_F32 && j.cols % 4096 == 0 && j.rows > 2048; }
+// x 5120 25.3 and 24.0; int8 x 4096 at 2048 rows 10.2 and 11.6).
+static bool turn_strided(const QuantJob& j) { return j.dtype == SRQ_F32 && j.cols % 4096 == 0 && j.rows > (kind_is_int(j.kind) ? 1024u : 2048u); }
 
 // Requirements (checked by the callers): rows % 16 == 0 and cols % 16 == 0 for every job,
 // store is STORE_BYTE or STORE_BF16.
@@ -356,8 +356,8 @@ hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
       if (nb > (1u << 20)) nb = 1u << 20;
     }
     const bool two = j.out2 && j.kind2;
-    turned = turned && j.transpose && j.store == STORE_BYTE && (j.kind == SRQ_E4M3 || j.kind == SRQ_E5M2) && j.round == SRQ_SR &&
-             !(two && j.round2 != SRQ_SR) && (two || !turn_strided(j));
+    turned = turned && j.transpose && j.store == STORE_BYTE && !kind_is_e4mx(j.kind) && !j.pack_t && !j.pack_2 && j.round == SRQ_SR &&
+             (two ? !kind_is_int(j.kind) && j.round2 == SRQ_SR : !turn_strided(j));
     j.first_block = first;
     j.nblocks = (uint32_t)nb;
     first += (uint32_t)nb;

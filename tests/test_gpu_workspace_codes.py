@@ -166,19 +166,20 @@ def test_stash_codes_of_two_quantizers(M, N, K, kind, fwd):
         assert np.array_equal(_piece(stash, _up(2 * M * K), N * K), _expect(tW, kind, oq[3], True, 1)), "Q(W)^T"
 
 
-# the quantizers of a backward call that round 8-bit floats stochastically have a kernel of their own (tiles of 128 rows and 64 columns,
+# the quantizers of a backward call that round stochastically to bytes have a kernel of their own (tiles of 128 rows and 64 columns,
 # steps of 64 and 128 rows, pieces of four): both sides of its edges and of the rule on binary32 rows a multiple of 4096 apart (2048
-# rows and more); the scale takes some elements into the subnormals of the formats and some to saturation
+# rows, of integers 1024, and more); the scale takes some elements into the subnormals of the formats and some to saturation
 @pytest.mark.parametrize("M,N,K,kind", [(16, 16, 16, L.E5M2), (80, 1040, 144, L.E5M2), (144, 80, 4240, L.E5M2), (2192, 208, 336, L.E5M2),
                                         (2048, 4096, 16, L.E5M2), (2064, 4096, 16, L.E5M2), (1040, 528, 272, L.E4M3),
-                                        (2064, 144, 464, L.E4M3)])
+                                        (2064, 144, 464, L.E4M3), (16, 16, 16, L.INT8), (144, 80, 4240, L.INT8), (2192, 208, 336, L.INT4),
+                                        (1024, 4096, 16, L.INT8), (1040, 4096, 16, L.INT8), (272, 1040, 528, L.INT4)])
 @pytest.mark.parametrize("bf16", [False, True])
-def test_backward_codes_of_floats(M, N, K, kind, bf16):
+def test_backward_codes(M, N, K, kind, bf16):
     say("backward codes", M, N, K, L.KIND_NAMES[kind], bf16)
     rng = np.random.default_rng(M + N + K)
     A, W, dY = (to_dev((rng.standard_normal(s) * np.exp2(rng.uniform(-24, 3, s))).astype(np.float32), bf16)
                 for s in ((M, K), (N, K), (M, N)))
-    assert kind == L.E5M2 or M * N * K >= 2**27  # one byte an element
+    assert kind != L.E4M3 or M * N * K >= 2**27  # one byte an element
     oq = [oracle.Quant(kind, s, 17, 1000 * i) for i, s in enumerate((0.01, 0.02, 0.015))]
     qdY, qW, qA = (L.Quant(q.kind, q.scale, q.seed, q.counter_offset) for q in oq)
     ws = torch.zeros(L.sr_linear_workspace_bytes(L.OP_BWD_STASHED, M, N, K), dtype=torch.uint8, device=A.device)
