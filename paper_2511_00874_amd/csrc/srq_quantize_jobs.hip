@@ -53,7 +53,8 @@ __device__ __forceinline__ void store_group(uint8_t* out, size_t base, const uin
 // left over group-wise.  A group of a bfloat16 source is one 16-byte load: a thread issues four of
 // them, a block's width apart, before it rounds the first (11.5 M weights -> int8: 14.0 us, one after
 // another 15.6).
-template <int KIND, bool AS_BF16, bool CACHED>
+// WORDS: a group of a bfloat16 source four codes at a time (quantize_flat_f8_kernel).
+template <int KIND, bool AS_BF16, bool CACHED, bool WORDS = false>
 __device__ __forceinline__ void flat_path(const QuantJob& j, uint32_t local, uint32_t nblocks) {
   const InvScale inv = inv_scale(j.scale, j.scale_dev, j.kind);
   const uint64_t ctr = first_block(j.counter_offset, j.counter_dev);
@@ -96,8 +97,12 @@ __device__ __forceinline__ void flat_path(const QuantJob& j, uint32_t local, uin
           v[2 * e] = bf16_to_f32(raw[i][e] & 0xFFFFu);
           v[2 * e + 1] = bf16_to_f32(raw[i][e] >> 16);
         }
-        job_quantize_group<KIND, AS_BF16>(c, v, inv, j, ctr, g, k0, k1);
-        store_group<AS_BF16>(j.out, g * 8, c);
+        if constexpr (WORDS) {
+          *as_global(reinterpret_cast<u32x2*>(j.out + g * 8)) = quantize_group_words<KIND>(v, inv, ctr + g, k0, k1, true);
+        } else {
+          job_quantize_group<KIND, AS_BF16>(c, v, inv, j, ctr, g, k0, k1);
+          store_group<AS_BF16>(j.out, g * 8, c);
+        }
       }
     }
   }
@@ -284,18 +289,14 @@ __device__ __forceinline__ void run_job(const QuantJob& j, uint32_t local, uint8
   else flat_path<KIND, AS_BF16, CACHED>(j, local, j.nblocks);
 }
 
-template <bool CACHED>
-__global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[TC * (128 + 2) * 2];
-  static_assert(TC * (256 + 4) <= (int)sizeof(smem), "the tile of 256 rows of bytes fits as well");
+// The job descriptor of a workgroup, which is uniform.  Indexing the by-value argument would make the compiler copy the whole
+// argument to per-lane scratch memory; instead the one descriptor is read from the kernel-argument segment (constant address space, scalar
+// loads), where the explicit arguments start at offset 0.
+__device__ __forceinline__ QuantJob job_of_block(const QuantJobs& jobs) {
   int ji = 0;
 #pragma unroll
   for (int i = 1; i < QUANT_JOBS_MAX; ++i)
     if (i < jobs.njobs && blockIdx.x >= jobs.job[i].first_block) ji = i;
-  // The job descriptor is workgroup-uniform.  Indexing the by-value argument with ji would make
-  // the compiler copy the whole argument to per-lane scratch memory; instead the one descriptor
-  // is read from the kernel-argument segment (constant address space, scalar loads), where the
-  // explicit arguments start at offset 0.
   struct alignas(8) Raw { uint32_t w[sizeof(QuantJob) / 4]; } raw;
   static_assert(sizeof(QuantJob) % 4 == 0 && offsetof(QuantJobs, job) % 4 == 0, "descriptor is read word-wise");
   typedef __attribute__((address_space(4))) const uint32_t* kernarg_words;
@@ -303,7 +304,14 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
                            (offsetof(QuantJobs, job) + (size_t)ji * sizeof(QuantJob)) / 4;
 #pragma unroll
   for (unsigned k = 0; k < sizeof(QuantJob) / 4; ++k) raw.w[k] = kw[k];
-  const QuantJob j = __builtin_bit_cast(QuantJob, raw);
+  return __builtin_bit_cast(QuantJob, raw);
+}
+
+template <bool CACHED>
+__global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[TC * (128 + 2) * 2];
+  static_assert(TC * (256 + 4) <= (int)sizeof(smem), "the tile of 256 rows of bytes fits as well");
+  const QuantJob j = job_of_block(jobs);
   const uint32_t local = blockIdx.x - j.first_block;
   const bool bf = j.store == STORE_BF16;
   switch (j.kind) {
@@ -327,6 +335,17 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
   }
 }
 
+// Operands of a forward pass in E4M3, all in the source layout, by conversion (BY_CONVERSION; the kernel above has no registers for it, and
+// a small kernel starts sooner).  What bounds it is the vector ALU, then HBM.  us there and here of A (binary32) and W (bfloat16), normal / with 1 %
+// of outliers / over 40 binades: 512 x 512 and 512 x 512 4.1 -> 3.3 / 4.1 -> 3.7 / 4.1 -> 3.7; 4096 x 2048 and 2048 x 2048 12.9 -> 10.4 /
+// 12.4 -> 10.8 / 12.6 -> 10.9 (A bfloat16 12.2 -> 9.3 / 12.1 -> 10.4 / 12.3 -> 10.5); 8192 x 5632 and 2048 x 5632 48.6 -> 46.4 / 48.6 -> 47.5 /
+// 48.5 -> 47.9 (41.3 -> 32.5 / 41.4 -> 35.6 / 41.2 -> 37.7).
+template <bool CACHED>
+__global__ __launch_bounds__(QBLOCK) void quantize_flat_f8_kernel(QuantJobs jobs) {
+  const QuantJob j = job_of_block(jobs);
+  flat_path<SRQ_E4M3_CONV, false, CACHED, true>(j, blockIdx.x - j.first_block, j.nblocks);
+}
+
 }  // namespace
 
 // Binary32 rows a multiple of 16 KiB apart: the sixteen rows that a wave instruction of launch_quantize_turned's kernel reads a piece of
@@ -341,6 +360,7 @@ static bool turn_strided(const QuantJob& j) { return j.dtype == SRQ_F32 && j.col
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
   uint32_t first = 0;
   size_t bytes = jobs.other_bytes;
+  bool flat = true;    // all of them such as quantize_flat_f8_kernel takes
   bool turned = true;  // all of them such as launch_quantize_turned takes
   for (int i = 0; i < jobs.njobs; ++i) {
     QuantJob& j = jobs.job[i];
@@ -355,6 +375,7 @@ hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
       nb = (groups + FLAT_GROUPS_PER_BLOCK - 1) / FLAT_GROUPS_PER_BLOCK;
       if (nb > (1u << 20)) nb = 1u << 20;
     }
+    flat = flat && !j.transpose && j.store == STORE_BYTE && j.kind == SRQ_E4M3 && j.round == SRQ_SR;
     const bool two = j.out2 && j.kind2;
     turned = turned && j.transpose && j.store == STORE_BYTE && !kind_is_e4mx(j.kind) && !j.pack_t && !j.pack_2 && j.round == SRQ_SR &&
              (two ? !kind_is_int(j.kind) && j.round2 == SRQ_SR : !turn_strided(j));
@@ -364,6 +385,11 @@ hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
   }
   if (first == 0) return hipSuccess;
   if (turned) return launch_quantize_turned(jobs, first, bytes <= JOBS_CACHED_BYTES, stream);
+  if (flat) {
+    if (bytes <= JOBS_CACHED_BYTES) quantize_flat_f8_kernel<true><<<first, QBLOCK, 0, stream>>>(jobs);
+    else quantize_flat_f8_kernel<false><<<first, QBLOCK, 0, stream>>>(jobs);
+    return hipGetLastError();
+  }
   // decided for the launch (two forms inside one kernel cost more than they gave)
   if (bytes <= JOBS_CACHED_BYTES) quantize_jobs_kernel<true><<<first, QBLOCK, 0, stream>>>(jobs);
   else quantize_jobs_kernel<false><<<first, QBLOCK, 0, stream>>>(jobs);
