@@ -53,7 +53,7 @@ __device__ __forceinline__ void store_group(uint8_t* out, size_t base, const uin
 // left over group-wise.  A group of a bfloat16 source is one 16-byte load: a thread issues four of
 // them, a block's width apart, before it rounds the first (11.5 M weights -> int8: 14.0 us, one after
 // another 15.6).
-// WORDS: a group of a bfloat16 source four codes at a time (quantize_flat_f8_kernel).
+// WORDS: a group of a bfloat16 source four codes at a time, stochastic rounding (quantize_flat_jobs_kernel).
 template <int KIND, bool AS_BF16, bool CACHED, bool WORDS = false>
 __device__ __forceinline__ void flat_path(const QuantJob& j, uint32_t local, uint32_t nblocks) {
   const InvScale inv = inv_scale(j.scale, j.scale_dev, j.kind);
@@ -335,15 +335,21 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
   }
 }
 
-// Operands of a forward pass in E4M3, all in the source layout, by conversion (BY_CONVERSION; the kernel above has no registers for it, and
-// a small kernel starts sooner).  What bounds it is the vector ALU, then HBM.  us there and here of A (binary32) and W (bfloat16), normal / with 1 %
-// of outliers / over 40 binades: 512 x 512 and 512 x 512 4.1 -> 3.3 / 4.1 -> 3.7 / 4.1 -> 3.7; 4096 x 2048 and 2048 x 2048 12.9 -> 10.4 /
-// 12.4 -> 10.8 / 12.6 -> 10.9 (A bfloat16 12.2 -> 9.3 / 12.1 -> 10.4 / 12.3 -> 10.5); 8192 x 5632 and 2048 x 5632 48.6 -> 46.4 / 48.6 -> 47.5 /
-// 48.5 -> 47.9 (41.3 -> 32.5 / 41.4 -> 35.6 / 41.2 -> 37.7).
+// Operands of a forward pass, all in the source layout as bytes and rounding stochastically: 8-bit floats by conversion (BY_CONVERSION; the
+// kernel above has no registers for it), bfloat16 sources four codes a word, and a small kernel starts sooner.  What bounds it is the vector
+// ALU, then HBM.  us there and here of A (binary32 or bfloat16, within 3 % of each other where one figure stands) and W (bfloat16):
+//   int8: 16 x 512 and 512 x 512 3.4 -> 3.0; 32 x 2048 and 5632 x 2048 10.0 -> 9.2, 9.8 -> 8.8; 4096 x 2048 and 2048 x 2048 10.7 -> 10.3,
+//   9.5 -> 8.8; 8192 x 5632 and 2048 x 5632 45.9 -> 45.9, 32.0 -> 31.6
+//   E5M2: 3.9 -> 3.1; 12.2 -> 9.0; 11.4 -> 10.2, 12.2 -> 9.0; 48.4 -> 46.4, 42.3 -> 32.1
+//   E4M3, normal / with 1 % of outliers / over 40 binades: 512 x 512 twice 4.1 -> 3.3 / 4.1 -> 3.7 / 4.1 -> 3.7; 4096 x 2048 and 2048 x 2048
+//   12.9 -> 10.4 / 12.4 -> 10.8 / 12.6 -> 10.9; 8192 x 5632 and 2048 x 5632 48.6 -> 46.4 / 48.6 -> 47.5 / 48.5 -> 47.9
 template <bool CACHED>
-__global__ __launch_bounds__(QBLOCK) void quantize_flat_f8_kernel(QuantJobs jobs) {
+__global__ __launch_bounds__(QBLOCK) void quantize_flat_jobs_kernel(QuantJobs jobs) {
   const QuantJob j = job_of_block(jobs);
-  flat_path<SRQ_E4M3_CONV, false, CACHED, true>(j, blockIdx.x - j.first_block, j.nblocks);
+  const uint32_t local = blockIdx.x - j.first_block;
+  if (j.kind == SRQ_E4M3) flat_path<SRQ_E4M3_CONV, false, CACHED, true>(j, local, j.nblocks);
+  else if (j.kind == SRQ_E5M2) flat_path<SRQ_E5M2, false, CACHED, true>(j, local, j.nblocks);
+  else flat_path<SRQ_INTX, false, CACHED, true>(j, local, j.nblocks);
 }
 
 }  // namespace
@@ -360,7 +366,7 @@ static bool turn_strided(const QuantJob& j) { return j.dtype == SRQ_F32 && j.col
 hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
   uint32_t first = 0;
   size_t bytes = jobs.other_bytes;
-  bool flat = true;    // all of them such as quantize_flat_f8_kernel takes
+  bool flat = true;    // all of them such as quantize_flat_jobs_kernel takes
   bool turned = true;  // all of them such as launch_quantize_turned takes
   for (int i = 0; i < jobs.njobs; ++i) {
     QuantJob& j = jobs.job[i];
@@ -375,7 +381,7 @@ hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
       nb = (groups + FLAT_GROUPS_PER_BLOCK - 1) / FLAT_GROUPS_PER_BLOCK;
       if (nb > (1u << 20)) nb = 1u << 20;
     }
-    flat = flat && !j.transpose && j.store == STORE_BYTE && j.kind == SRQ_E4M3 && j.round == SRQ_SR;
+    flat = flat && !j.transpose && j.store == STORE_BYTE && !kind_is_e4mx(j.kind) && j.round == SRQ_SR;
     const bool two = j.out2 && j.kind2;
     turned = turned && j.transpose && j.store == STORE_BYTE && !kind_is_e4mx(j.kind) && !j.pack_t && !j.pack_2 && j.round == SRQ_SR &&
              (two ? !kind_is_int(j.kind) && j.round2 == SRQ_SR : !turn_strided(j));
@@ -386,8 +392,8 @@ hipError_t launch_quantize_jobs(QuantJobs& jobs, hipStream_t stream) {
   if (first == 0) return hipSuccess;
   if (turned) return launch_quantize_turned(jobs, first, bytes <= JOBS_CACHED_BYTES, stream);
   if (flat) {
-    if (bytes <= JOBS_CACHED_BYTES) quantize_flat_f8_kernel<true><<<first, QBLOCK, 0, stream>>>(jobs);
-    else quantize_flat_f8_kernel<false><<<first, QBLOCK, 0, stream>>>(jobs);
+    if (bytes <= JOBS_CACHED_BYTES) quantize_flat_jobs_kernel<true><<<first, QBLOCK, 0, stream>>>(jobs);
+    else quantize_flat_jobs_kernel<false><<<first, QBLOCK, 0, stream>>>(jobs);
     return hipGetLastError();
   }
   // decided for the launch (two forms inside one kernel cost more than they gave)

@@ -198,6 +198,23 @@ def test_backward_codes(M, N, K, kind, bf16):
     assert saved.find(want["dY", True].tobytes()) >= 0, "Q(dY)^T of the stash call"
 
 
+# operands of a forward pass: chunks of 512 elements and what is left over, four loads of a bfloat16 source and fewer
+@pytest.mark.parametrize("M,N,K,kind", [(16, 16, 16, L.INT8), (48, 80, 208, L.INT4), (272, 1040, 528, L.INT8), (16, 16, 16, L.E5M2),
+                                        (48, 1040, 272, L.E5M2), (1040, 528, 272, L.E4M3)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_forward_codes(M, N, K, kind, bf16):
+    say("forward codes", M, N, K, L.KIND_NAMES[kind], bf16)
+    rng = np.random.default_rng(M + N + K)
+    A, W = (to_dev((rng.standard_normal(s) * np.exp2(rng.uniform(-24, 3, s))).astype(np.float32), b)
+            for s, b in (((M, K), bf16), ((N, K), not bf16)))
+    oq = [oracle.Quant(kind, s, 17, 1000 * i) for i, s in enumerate((0.01, 0.02))]
+    lq = [L.Quant(q.kind, q.scale, q.seed, q.counter_offset, flags=L.FLAG_QUANTIZE_ONCE) for q in oq]
+    ws = torch.zeros(L.sr_linear_workspace_bytes(L.OP_FWD, M, N, K), dtype=torch.uint8, device=A.device)
+    L.sr_linear_fwd(A, W, *lq, out=torch.empty((M, N), device=A.device), workspace=ws, phase=L.PHASE_QUANTIZE)
+    assert np.array_equal(_piece(ws, 0, M * K), _expect(A, kind, oq[0], False, 1)), "Q(A)"
+    assert np.array_equal(_piece(ws, _up(M * K), N * K), _expect(W, kind, oq[1], False, 1)), "Q(W)"
+
+
 def _nib16(codes):
     """Two 4-bit values per byte: byte j of every 8 holds elements j (low nibble) and j + 8 (high nibble)
     of a run of 16 along the last axis."""
