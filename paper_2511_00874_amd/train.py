@@ -31,6 +31,14 @@ def _matrix(x, cols):
     return x.reshape(-1, cols).contiguous().float()
 
 
+def _quant(scales, i, kind, rounding, seed, position):
+    """The quantizer with the i-th of `scales`, in the form of the C interface: for calls while `scales` lives.  A position held on
+    the device (a 1-element int64 tensor) stays there and is read when the kernels run."""
+    if isinstance(position, torch.Tensor):
+        return L.Quant(kind, scales[i:i + 1], seed, position, rounding)
+    return L.srq_quant(kind, rounding, 0.0, 0, scales.data_ptr() + 4 * i, seed & MASK64, position & MASK64)
+
+
 class SRLinearFn(torch.autograd.Function):
     """Everything the backward pass of ONE forward call needs travels on the autograd context:
     the saved activation -- as the codes of its backward quantizer when the forward pass can write
@@ -115,15 +123,12 @@ class SRLinear(torch.nn.Module):
         return need
 
     def _q(self, name, scales, i, position):
-        """The quantizer of `name` with the i-th of `scales`, in the form of the C interface: for calls while `scales` lives."""
-        return L.srq_quant(self.kinds[name], self.round_mode, 0.0, 0, scales.data_ptr() + 4 * i, self.seed & MASK64,
-                           position & MASK64)
+        return _quant(scales, i, self.kinds[name], self.round_mode, self.seed, position)
 
     @staticmethod
     def _q_saved(saved):
         """The weights' quantizer of a forward pass for its backward pass (everything but the address of its scale is kept)."""
-        i, kind, rounding, seed, position = saved["w"]
-        return L.srq_quant(kind, rounding, 0.0, 0, saved["scales"].data_ptr() + 4 * i, seed, position)
+        return _quant(saved["scales"], *saved["w"])
 
     def _workspace(self, op, M):
         need = self._size(op, M)
@@ -142,11 +147,11 @@ class SRLinear(torch.nn.Module):
             pairs.append((a, self.kinds["A_bwd"]))
         sc = L.absmax_scales(pairs)
         qw = self._q("W_fwd", sc, 0, self.position)   # the same copy serves the backward pass
-        saved = {"scales": sc, "w": (0, qw.kind, qw.round, qw.seed, qw.counter_offset)}
-        self.position += (N * K + 7) // 8
+        saved = {"scales": sc, "w": (0, self.kinds["W_fwd"], self.round_mode, self.seed, self.position)}
+        pos_a = self.position + (N * K + 7) // 8      # (a new position, also where it is a tensor: the old one is kept above)
         if qat:
-            saved["a"] = 1, self.position
-            self.position += (M * K + 7) // 8
+            saved["a"] = 1, pos_a
+        self.position = pos_a + (M * K + 7) // 8 if qat else pos_a
         y = torch.empty((M, N), dtype=torch.float32, device=a.device)
         for r0 in range(0, M, MAX_ROWS):
             r1 = min(M, r0 + MAX_ROWS)
@@ -187,7 +192,7 @@ class SRLinear(torch.nn.Module):
         pos_w_bwd = pos_a_bwd + a_blocks
         self.__dict__["position"] = pos_w_bwd + w_blocks  # (Module.__setattr__ would look for parameters and modules first)
         qw, qw_bwd = self._q("W_fwd", sc, 1, pos_w), self._q("W_bwd", sc, 3, pos_w_bwd)
-        saved = {"scales": sc, "a": (2, pos_a_bwd), "w": (3, qw_bwd.kind, qw_bwd.round, qw_bwd.seed, qw_bwd.counter_offset)}
+        saved = {"scales": sc, "a": (2, pos_a_bwd), "w": (3, self.kinds["W_bwd"], self.round_mode, self.seed, pos_w_bwd)}
         y = torch.empty((M, N), dtype=torch.float32, device=a.device)
         # integer forward formats: the same pass over A and W also writes the codes of their backward
         # quantizers (one stash per chunk of rows), and the activation itself need not be kept

@@ -221,3 +221,46 @@ def test_qat_training_step_reduces_the_loss():
     losses = [float(train.train_step(model, ids, tgt, lr=0.05, micro_batches=2)) for _ in range(12)]
     say("qat losses", [round(v, 3) for v in losses])
     assert all(np.isfinite(losses)) and losses[-1] < losses[0] - 0.05
+
+
+@pytest.mark.parametrize("objective", train.OBJECTIVES)
+def test_a_position_on_the_device_gives_what_the_same_number_gives(objective):
+    say("device position", objective)
+    M, K, N = 96, 64, 48
+    g = torch.Generator(device=DEV).manual_seed(2)
+    x0 = torch.randn((M, K), device=DEV, generator=g)
+    dy = torch.randn((M, N), device=DEV, generator=g) * 1e-2
+
+    def step(position):
+        layer = train.SRLinear(K, N, 9, device=DEV, objective=objective)
+        layer.position = position
+        x = x0.clone().requires_grad_()
+        y = layer(x)
+        y.backward(dy)
+        return y.detach(), x.grad, layer.dW, layer.position
+
+    host = step(1000)
+    device = step(torch.tensor([1000], dtype=torch.int64, device=DEV))
+    assert all(torch.equal(a, b) for a, b in zip(host[:3], device[:3]))
+    assert int(device[3]) == host[3]
+    assert not torch.equal(step(1001)[0], host[0])
+
+    # a captured forward pass draws from where the position is when it is replayed
+    layer = train.SRLinear(K, N, 9, device=DEV, objective=objective)
+    at = torch.tensor([1000], dtype=torch.int64, device=DEV)
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.no_grad(), torch.cuda.stream(stream):
+        layer.position = at
+        layer(x0)  # warm up on the capture stream
+        torch.cuda.synchronize()
+        layer.position = at
+        graph.capture_begin()
+        y = layer(x0)
+        graph.capture_end()
+    torch.cuda.synchronize()
+    for position in (1000, 1001, 7, 1000):
+        at.fill_(position)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, step(position)[0]), position
