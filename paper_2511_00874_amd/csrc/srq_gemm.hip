@@ -708,12 +708,17 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
   acc_t acc[TM][TN];
   // A stage is a row of units: a sub-step of half the wave's X rows.  A unit's fragments of X are read one by one into the
   // registers that the unit before has just left, and the next sub-step's fragments of Z beside them: LDS reads spread
-  // between the MFMAs, and few enough registers (216) that two waves of this kernel leave a SIMD 64, enough for one wave
-  // of the quantizer or absmax kernels: a memory-bound launch on another stream runs BESIDE this kernel on the same CUs
-  // instead of behind it.
+  // between the MFMAs, and few enough registers (int8 216, packed X and fp8 222, bfloat16 217) that two waves of this kernel leave a
+  // SIMD 64, enough for one wave of the quantizer or absmax kernels: a memory-bound launch on another stream runs BESIDE this kernel
+  // on the same CUs instead of behind it.  Widened codes take 230 and leave 48: room for the quantizers in the source layout and the
+  // absmax of a binary32 tensor, not for the kernels of several tensors at once.  (With X read four ahead and all of Z before
+  // the turn 242, beside which nothing fits: E5M2, both products of 8192 x 8192 x 2048 alone 368 us and 367 now, beside an int8
+  // quantizer of 2^26 elements on another stream 431 and 404, beside their absmax 443 and 404.  With X two ahead and only the
+  // first fragment of Z before the turn 222, but 1.02 to 1.04 of the time.)
   auto compute = [&](uint32_t buf) {
     const uint8_t* const stage = lds + buf * STAGE;
     if constexpr (!XP) {
+      constexpr int AHEAD = MMA::WIDENS ? HM - 1 : HM, Z_LATE = MMA::WIDENS ? 2 : 0;  // (below)
       raw_t xf[HM], zf[2][TN];
       auto fetch_x = [&](int u, int i) { xf[i] = load_frag(stage + ((u & 1) * HM + i) * T * BK, xoff ^ ((u >> 1) * KS_XOR)); };
       auto fetch_z = [&](int ks, int j) { zf[ks & 1][j] = load_frag(stage + j * T * BK, zoff ^ (ks * KS_XOR)); };
@@ -722,7 +727,7 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
 #pragma unroll
       for (int j = 1; j < TN; ++j) fetch_z(0, j);
 #pragma unroll
-      for (int i = 1; i < HM; ++i) fetch_x(0, i);
+      for (int i = 1; i < AHEAD; ++i) fetch_x(0, i);
       __builtin_amdgcn_sched_barrier(0);
       frag_t xe[2], ze[TN];  // (plain copies unless the pipeline widens its operands)
       if constexpr (MMA::WIDENS) {
@@ -763,8 +768,15 @@ __global__ __launch_bounds__(512) void gemm_nt_persist_kernel(GemmParams g, Slic
             }
           }
           __builtin_amdgcn_sched_barrier(0);
-          if (u + 1 < 2 * KS) fetch_x(u + 1, i);
-          if ((u & 1) == 0 && u + 2 < 2 * KS) fetch_z((u >> 1) + 1, i);
+          // X: the fragment that takes the place just left, four ahead; three where widened ones take registers too.  Z: beside the
+          // first unit's; where they are widened the last two at the turn, into the registers of the widened ones that it frees.
+          const int n = u * HM + i + AHEAD;
+          if (n < 2 * KS * HM) fetch_x(n / HM, n % HM);
+          if ((u & 1) == 0 && u + 2 < 2 * KS && i < TN - Z_LATE) fetch_z((u >> 1) + 1, i);
+          if (turn) {
+#pragma unroll
+            for (int j = TN - Z_LATE; j < TN; ++j) fetch_z((u >> 1) + 1, j);
+          }
           __builtin_amdgcn_sched_barrier(0);
         }
       }

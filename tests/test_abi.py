@@ -230,3 +230,16 @@ def test_memory_bound_kernels_hold_at_most_64_registers(lib):
         for name, k in of.items():
             assert k[".vgpr_count"] <= 64 and k[".agpr_count"] == 0, name
             assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
+
+
+def test_large_tile_products_leave_registers_for_another_stream(lib):
+    # two waves of them a SIMD and, of its 512 registers, 64 for a wave of a memory-bound kernel; 48 where codes are widened, which
+    # is enough for the quantizers in the source layout and the absmax of a binary32 tensor
+    kernels = {n: k for n, k in _kernels(lib.LIB_PATH).items() if "gemm_nt_persist" in n}
+    assert kernels
+    for name, k in kernels.items():
+        assert k[".vgpr_count"] <= (232 if "F8F16Mma" in name else 224) and k[".agpr_count"] == 0, name
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
+    for part, limit in (("quantize_flat_kernel", 48), ("quantize_flat_f32", 48), ("absmax_kernelILi0", 48)):
+        of = {n: k for n, k in _kernels(lib.LIB_PATH).items() if part in n}
+        assert of and all(k[".vgpr_count"] <= limit for k in of.values()), part
