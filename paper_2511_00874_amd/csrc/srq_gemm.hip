@@ -210,15 +210,8 @@ __device__ __forceinline__ void write_wave_tile(const GemmParams& g, const typen
 // longer ring of stages keeps more loads in flight (with four, 17.4 with the matrix work left out, 23.8 in all; with three 23.1).
 // SETS = 2 (one group): two sets of accumulators, for the first and the second half of the sub-steps of every stage, added at the
 // end: the sums of two groups of waves, in the same order.
-template <class PIPE, int BM, int BN, int WGM, int WGN, int STAGES, int KG, int SETS>
+template <class MMA, int BM, int BN, int WGM, int WGN, int STAGES, int KG, int SETS>
 __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block, uint8_t* lds) {
-  // MFMA tiles of 16 x 16 (srq_mma.hpp) but for two cases: four groups, which have a sub-step of 32 bytes each, and codes to widen
-  // in more than one set of sums, where half a stage is a single sub-step, nothing is left to widen beside, and they are
-  // slower (2048 x 2048 x 4096 E5M2, two groups, 38.5 -> 41.5 us; with the groups taking turns at LDS and the MFMAs 43.5).  Forms
-  // that agree bit for bit have tiles of one size: their sums round differently, though to the same error.  Kernels, us, 32 x 32 and
-  // 16 x 16: int8 4096 x 2048 x 2048 24.4 -> 23.0, both its backward products in a pair 39.6 -> 38.4, 8192 x 768 x 3072 31.5 -> 30.6,
-  // 2432 x 4240 x 1216 24.6 -> 21.7; E5M2 8192 x 768 x 3072 47.3 -> 43.5 and 43.1 -> 43.4 in two runs.
-  using MMA = typename std::conditional<PIPE::WIDENS ? KG * SETS == 1 : KG <= 2, typename Tiles16<PIPE>::type, PIPE>::type;
   constexpr int NG = WGM * WGN, NW = NG * KG;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile (p x q)
   constexpr int T = MMA::TILE, LG = 64 / T, TM = WTM / T, TN = WTN / T;
@@ -543,19 +536,20 @@ __global__ __launch_bounds__(WGM* WGN* KG * 64, SETS) void gemm_nt_kernel(GemmPa
 // one with the longer tiles), the rest the second, in tiles of one size, so that both fill the same slots: the stores of one's tiles go out
 // beside the matrix work of the other's, a product of few tiles leaves no CU idle, and there is one start and one end instead of two.
 // choose_pair says where that is faster.  The results are bit for bit those of the products in launches of their own.
-template <int WGM_, int WGN_, int KG_, int SETS_>
+template <class MMA_, int WGM_, int WGN_, int KG_, int SETS_>
 struct Waves {
+  using MMA = MMA_;
   static constexpr int WGM = WGM_, WGN = WGN_, KG = KG_, SETS = SETS_, THREADS = WGM * WGN * KG * 64;
 };
-template <class MMA, int BM, int BN, int STAGES, class WA, class WB>
+template <int BM, int BN, int STAGES, class WA, class WB>
 __global__ __launch_bounds__(WA::THREADS, (WA::SETS > WB::SETS ? WA::SETS : WB::SETS)) void gemm_pair_kernel(GemmParams a, GemmParams b,
                                                                                                          uint32_t blocks_a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   static_assert(WA::THREADS == WB::THREADS, "one launch");
   if (blockIdx.x < blocks_a)
-    product_tile<MMA, BM, BN, WA::WGM, WA::WGN, STAGES, WA::KG, WA::SETS>(a, blockIdx.x, lds);
+    product_tile<typename WA::MMA, BM, BN, WA::WGM, WA::WGN, STAGES, WA::KG, WA::SETS>(a, blockIdx.x, lds);
   else
-    product_tile<MMA, BM, BN, WB::WGM, WB::WGN, STAGES, WB::KG, WB::SETS>(b, blockIdx.x - blocks_a, lds);
+    product_tile<typename WB::MMA, BM, BN, WB::WGM, WB::WGN, STAGES, WB::KG, WB::SETS>(b, blockIdx.x - blocks_a, lds);
 }
 
 // ---- 256 x 256 tiles, workgroups that stay -------------------------------------------------------
@@ -1227,32 +1221,53 @@ hipError_t launch_persist(GemmParams g, const SliceSumPlan& ss, hipStream_t stre
   return e;
 }
 
+// Which forms multiply in MFMA tiles of 16 x 16 (srq_mma.hpp): those whose workgroups fill the chip, so that its clock counts.  Where
+// a CU has one workgroup, or its waves wait for each other's sums, it is the loads and the chain of a tile that count, and 32 x 32 ones are
+// faster.  Kernels, us, 32 x 32 and 16 x 16:
+//   128 x 128, one set of sums: int8 5552 x 1840 x 1184 with the other product of the call 47.2 -> 46.0, 2176 x 1232 x 8320 35.0 -> 33.1; bfloat16 values
+//   1856 x 3312 x 1088 19.8 -> 18.5; widened codes 4368 x 8656 x 240 42.1 -> 40.0, pairs 0.95 to 1.0 of
+//   the time.  One or two stages on a CU each: 6.2 and 6.3.
+//   128 x 128, two groups: int8 2208 x 208 x 9248 16.2 -> 15.7, 3168 x 800 x 944 8.3 -> 8.4, 18 shapes 0.99 of the time; bfloat16
+//   values 24.5 -> 26.5 at 3344 x 880 x 2944, 18 shapes 1.02; widened codes, half a stage a single sub-step with nothing to widen beside,
+//   2048 x 2048 x 4096 38.5 -> 41.5 (with the groups taking turns at LDS and the MFMAs 43.5).  Two sets have the tiles of two groups, as
+//   64 x 64 do, so that their binary32 sums stay the same bit for bit.
+//   128 x 192: int8 4864 x 4960 x 624 32.5 -> 30.3; bfloat16 values 46.0 -> 42.6; widened codes, which are the most work between the
+//   reads, 37.9 -> 35.5 with more than the 512 tiles that are on the chip at once, with fewer 30.0 -> 31.5 at 1088 x 4576 x 2496 and 53.5 ->
+//   56.4 at 4544 x 528 x 8688 in two slices (16 shapes 1.00 to 1.09 of the time).
+//   64 x 64: int8 320 x 1552 x 4336 8.4 -> 8.8, bfloat16 values 448 x 1792 x 1152 6.0 -> 6.3.
 template <class MMA>
 hipError_t launch_mma(GemmParams g, const Launch& l, const SliceSumPlan& ss, hipStream_t stream) {
+  constexpr bool IS_INT = std::is_same<MMA, I8Mma>::value;
+  using Mma16 = typename Tiles16<MMA>::type;
   g.nsplit = l.nsplit;
   g.k_per_split = l.k_per_split;
   switch (l.form) {
-    case FORM_256x256: return launch_persist<MMA>(g, ss, stream);                        // 8 waves of 128 x 64, persistent
-    case FORM_128x128: return launch_tile<MMA, 128, 128, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 64
+    case FORM_256x256: return launch_persist<MMA>(g, ss, stream);                          // 8 waves of 128 x 64, persistent
+    case FORM_128x128: return launch_tile<Mma16, 128, 128, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 64
     case FORM_128x128_S2:  // binary32 sums only (choose_launch)
-      if constexpr (!std::is_same<MMA, I8Mma>::value) return launch_tile<MMA, 128, 128, 2, 2, 2, 1, 2>(g, ss, stream);
+      if constexpr (!IS_INT) return launch_tile<MMA, 128, 128, 2, 2, 2, 1, 2>(g, ss, stream);
       break;
-    case FORM_128x128_G2: return launch_tile<MMA, 128, 128, 2, 2, 3, 2>(g, ss, stream);  // 8 waves of 64 x 64
-    case FORM_128x192: return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);        // 4 waves of 64 x 96
-    case FORM_64x64_G2:                                                                  // 8 waves of 32 x 32
+    case FORM_128x128_G2:                                                                  // 8 waves of 64 x 64
+      return launch_tile<typename std::conditional<IS_INT, Mma16, MMA>::type, 128, 128, 2, 2, 3, 2>(g, ss, stream);
+    case FORM_128x192:                                                                     // 4 waves of 64 x 96
+      if constexpr (MMA::WIDENS) {
+        if (sums_in_large_mfma(l.form, g.P, g.Q, l.nsplit)) return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);
+      }
+      return launch_tile<Mma16, 128, 192, 2, 2, 2>(g, ss, stream);
+    case FORM_64x64_G2:                                                                    // 8 waves of 32 x 32
       return l.ring == 3 ? launch_tile<MMA, 64, 64, 2, 2, 3, 2>(g, ss, stream) : launch_tile<MMA, 64, 64, 2, 2, 4, 2>(g, ss, stream);
     case FORM_64x64_G4:  // 8 waves of 64 x 32; binary32 sums only (choose_launch)
-      if constexpr (BK / MMA::KSTEP >= 4 && !std::is_same<MMA, I8Mma>::value)
+      if constexpr (BK / MMA::KSTEP >= 4 && !IS_INT)
         return l.ring == 3 ? launch_tile<MMA, 64, 64, 1, 2, 3, 4>(g, ss, stream) : launch_tile<MMA, 64, 64, 1, 2, 5, 4>(g, ss, stream);
       break;
   }
   return hipErrorInvalidValue;
 }
 
-template <class MMA, int BM, int BN, int STAGES, class WA, class WB>
+template <int BM, int BN, int STAGES, class WA, class WB>
 hipError_t launch_pair(GemmParams a, GemmParams b, hipStream_t stream) {
   constexpr int LDS_BYTES = STAGES * (BM + BN) * BK;
-  auto kern = &gemm_pair_kernel<MMA, BM, BN, STAGES, WA, WB>;
+  auto kern = &gemm_pair_kernel<BM, BN, STAGES, WA, WB>;
   static const hipError_t configured = hipFuncSetAttribute(
       reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
   if (configured != hipSuccess) return configured;
@@ -1267,31 +1282,38 @@ hipError_t launch_pair(GemmParams a, GemmParams b, hipStream_t stream) {
   kern<<<dim3(blocks[0] + blocks[1]), WA::THREADS, LDS_BYTES, stream>>>(a, b, blocks[0]);
   hipError_t e = hipGetLastError();
   for (int i = 0; i < 2 && e == hipSuccess; ++i)
-    if (both[i]->nsplit > 1) e = launch_slice_sum(own_slice_sum<MMA>(*both[i]), stream);
+    if (both[i]->nsplit > 1) e = launch_slice_sum(own_slice_sum<typename WA::MMA>(*both[i]), stream);
   return e;
 }
 
-// wa, wb: sets of accumulators (128 x 128 tiles) or groups of waves (64 x 64) of the two products
+// The forms of the two products: sets of accumulators (128 x 128 tiles) or groups of waves (64 x 64), and the MFMA tiles of their launches
+// apart (launch_mma; of integers, any sums of which are the same, 16 x 16 on 64 x 64 as well: 3824 x 32 x 1872 12.5 -> 12.2 us).
 template <class MMA>
-hipError_t launch_pair_mma(const GemmParams& a, const GemmParams& b, PairForm form, int wa, int wb, hipStream_t stream) {
+hipError_t launch_pair_mma(const GemmParams& a, const GemmParams& b, PairForm form, const Paired& pa, const Paired& pb, hipStream_t stream) {
   constexpr bool IS_INT = std::is_same<MMA, I8Mma>::value;
-  using One = Waves<2, 2, 1, 1>;
-  using Two = Waves<2, 2, 1, 2>;
-  using G2 = Waves<2, 2, 2, 1>;
+  using Mma16 = typename Tiles16<MMA>::type;
+  using One = Waves<Mma16, 2, 2, 1, 1>;
+  using G2 = Waves<typename std::conditional<IS_INT, Mma16, MMA>::type, 2, 2, 2, 1>;
   if (form == PAIR_128x128) {
     if constexpr (IS_INT) {
-      return launch_pair<MMA, 128, 128, 2, One, One>(a, b, stream);
+      return launch_pair<128, 128, 2, One, One>(a, b, stream);
     } else {
-      if (wa == 1) return wb == 1 ? launch_pair<MMA, 128, 128, 2, One, One>(a, b, stream) : launch_pair<MMA, 128, 128, 2, One, Two>(a, b, stream);
-      return wb == 1 ? launch_pair<MMA, 128, 128, 2, Two, One>(a, b, stream) : launch_pair<MMA, 128, 128, 2, Two, Two>(a, b, stream);
+      const auto with = [](const Paired& p, const auto& f) {
+        if (p.waves == 2) return f(Waves<MMA, 2, 2, 1, 2>{});
+        if constexpr (MMA::WIDENS) {
+          if (p.large_mfma) return f(Waves<MMA, 2, 2, 1, 1>{});
+        }
+        return f(One{});
+      };
+      return with(pa, [&](auto wa) { return with(pb, [&](auto wb) { return launch_pair<128, 128, 2, decltype(wa), decltype(wb)>(a, b, stream); }); });
     }
   }
   if constexpr (BK / MMA::KSTEP >= 4 && !IS_INT) {
-    using G4 = Waves<1, 2, 4, 1>;
-    if (wa == 4) return wb == 4 ? launch_pair<MMA, 64, 64, 3, G4, G4>(a, b, stream) : launch_pair<MMA, 64, 64, 3, G4, G2>(a, b, stream);
-    if (wb == 4) return launch_pair<MMA, 64, 64, 3, G2, G4>(a, b, stream);
+    using G4 = Waves<MMA, 1, 2, 4, 1>;
+    if (pa.waves == 4) return pb.waves == 4 ? launch_pair<64, 64, 3, G4, G4>(a, b, stream) : launch_pair<64, 64, 3, G4, G2>(a, b, stream);
+    if (pb.waves == 4) return launch_pair<64, 64, 3, G2, G4>(a, b, stream);
   }
-  return launch_pair<MMA, 64, 64, 3, G2, G2>(a, b, stream);
+  return launch_pair<64, 64, 3, G2, G2>(a, b, stream);
 }
 
 // Tiles and contraction slices of gemm_cut3_kernel, by the same model: 128 x 128 tiles of four waves,
@@ -1464,8 +1486,8 @@ hipError_t launch_gemm_pair(const PairedProduct& w, const PairedProduct& d, int 
   return with_pipeline(pipe, kindX, w.kindZ, [&](auto mma) {
     using MMA = decltype(mma);
     if constexpr (std::is_same<MMA, BF16Mma>::value) return hipErrorInvalidValue;
-    else return p.weight_first ? launch_pair_mma<MMA>(gw, gd, p.form, p.w.waves, p.d.waves, stream)
-                               : launch_pair_mma<MMA>(gd, gw, p.form, p.d.waves, p.w.waves, stream);
+    else return p.weight_first ? launch_pair_mma<MMA>(gw, gd, p.form, p.w, p.d, stream)
+                               : launch_pair_mma<MMA>(gd, gw, p.form, p.d, p.w, stream);
   });
 }
 

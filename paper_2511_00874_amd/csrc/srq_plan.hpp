@@ -208,6 +208,13 @@ inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes
   return room ? Launch{FORM_128x128_G2, pl.nsplit, pl.k_per_split, 3} : Launch{four_waves, pl.nsplit, pl.k_per_split, 2};
 }
 
+// One set of binary32 sums of widened codes: in MFMA tiles of 32 x 32 (true) or of 16 x 16, which round differently.  The larger ones
+// where the product is planned on 128 x 192 tiles that are all on the chip at once (launch_mma says why), also where its tiles in a
+// pair are 128 x 128.
+inline bool sums_in_large_mfma(Form form, size_t P, size_t Q, uint32_t nsplit) {
+  return form == FORM_128x192 && ((P + 127) / 128) * ((Q + 191) / 192) * nsplit <= 2 * NUM_CU;
+}
+
 // The two products of a backward call, dW (N x K, contraction M) and dA (M x K, contraction N), in one launch of tiles of
 // one size, each over the slices that it is planned with (sums of slices follow in launches of their own).  Not where one takes
 // the 256 x 256 tiles, and only forms in which an accumulator of a binary32 sum holds the same part of the contraction as in a
@@ -239,6 +246,7 @@ enum PairForm { PAIR_NONE, PAIR_128x128, PAIR_64x64 };
 struct Paired {
   int waves;  // sets of accumulators (128 x 128 tiles of four waves) or groups of waves (64 x 64 of eight)
   uint32_t nsplit, k_per_split;
+  bool large_mfma = false;  // one set, widened codes: sums_in_large_mfma
 };
 struct Pair {
   PairForm form;
@@ -325,6 +333,8 @@ inline Pair choose_pair(size_t M, size_t N, size_t K, int pipe, const Plan& plan
   p.form = small ? PAIR_64x64 : PAIR_128x128;
   p.w.waves = small ? parts[0] : halves[0];
   p.d.waves = small ? parts[1] : halves[1];
+  p.w.large_mfma = sums_in_large_mfma(l[0].form, N, K, l[0].nsplit);
+  p.d.large_mfma = sums_in_large_mfma(l[1].form, M, K, l[1].nsplit);
   return p;
 }
 

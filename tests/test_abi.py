@@ -243,3 +243,19 @@ def test_large_tile_products_leave_registers_for_another_stream(lib):
     for part, limit in (("quantize_flat_kernel", 48), ("quantize_flat_f32", 48), ("absmax_kernelILi0", 48)):
         of = {n: k for n, k in _kernels(lib.LIB_PATH).items() if part in n}
         assert of and all(k[".vgpr_count"] <= limit for k in of.values()), part
+
+
+def test_mfma_tiles_of_the_product_forms(lib):
+    # 16 x 16 where the workgroups fill the chip, 32 x 32 where a tile's loads and its chain count (a form has the tiles that are
+    # measured to be faster with it: widened codes on 128 x 192 tiles by the number of tiles, both); the fp8 pipeline has 32 x 32 only
+    got = {}
+    for name in _kernels(lib.LIB_PATH):
+        m = re.search(r"gemm_nt_kernelINS_3mma\d+(I8|BF16|F8F16)Mma(16)?(?:ILi\dELi\dEE)?E"
+                      r"Li(\d+)ELi(\d+)ELi\d+ELi\d+ELi\d+ELi(\d+)ELi(\d+)E", name)
+        if m:
+            pipe, tile, *form = m.groups()
+            got.setdefault((pipe, *(int(v) for v in form)), set()).add(int(tile or 32))
+    assert got == {("I8", 128, 128, 1, 1): {16}, ("I8", 128, 128, 2, 1): {16}, ("I8", 128, 192, 1, 1): {16}, ("I8", 64, 64, 2, 1): {32},
+                   **{(p, 128, 128, 1, 1): {16} for p in ("BF16", "F8F16")}, **{(p, 128, 128, 1, 2): {32} for p in ("BF16", "F8F16")},
+                   **{(p, 128, 128, 2, 1): {32} for p in ("BF16", "F8F16")}, ("BF16", 128, 192, 1, 1): {16},
+                   ("F8F16", 128, 192, 1, 1): {16, 32}, **{(p, 64, 64, g, 1): {32} for p in ("BF16", "F8F16") for g in (2, 4)}}

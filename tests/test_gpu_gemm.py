@@ -6,7 +6,7 @@ import torch
 import oracle
 from paper_2511_00874_amd import lib as L
 from paper_2511_00874_amd import synth
-from gpu_util import (DEV, GROUP_SHAPES, PAIR_SHAPES, RIDE_SHAPES, check_product, check_product_f8_pipeline, group_max_sum,
+from gpu_util import (DEV, GROUP_SHAPES, LARGE_MFMA_SHAPES, PAIR_SHAPES, RIDE_SHAPES, check_product, check_product_f8_pipeline, group_max_sum,
                       host_src, say, to_dev)
 
 pytestmark = pytest.mark.gpu
@@ -394,6 +394,25 @@ def test_backward_products_in_one_launch_equal_the_separate_calls(M, N, K, kind,
     _, stash = L.sr_linear_fwd_stash(A, W, *qf, q[2], q[1])
     dA3, dW3 = L.sr_linear_bwd_stashed(dY, stash, K, *q)
     assert torch.equal(dA3, want_dA) and torch.equal(dW3, want_dW)
+
+
+# one set of sums of widened codes is in MFMA tiles of either size, by the product's own plan
+@pytest.mark.parametrize("M,N,K", LARGE_MFMA_SHAPES)
+@pytest.mark.parametrize("kind", [L.E5M2, L.E4M3])
+def test_pairs_of_products_planned_on_wide_tiles(M, N, K, kind):
+    say("wide tiles", M, N, K, L.KIND_NAMES[kind])
+    A, W, dY = synth.single_layer(M, N, K, 31, std_dy=1e-3)
+    A, W, dY = to_dev(A), to_dev(W, True), to_dev(dY)
+    q = [L.Quant(kind, oracle.absmax_scale(host_src(t), kind), 4, i << 24) for i, t in enumerate((dY, W, A))]
+    dA, dW = L.sr_linear_bwd(dY, W, A, *q)
+    assert torch.equal(dA, L.sr_linear_bwd_data(dY, W, q[0], q[1]))
+    assert torch.equal(dW, L.sr_linear_bwd_weight(dY, A, q[0], q[2]))
+    oq = [oracle.Quant(kind, qq.scale, 4, i << 24) for i, qq in enumerate(q)]
+    for got, f, (x, qx), (z, qz) in ((dW, oracle.linear_bwd_weight, (dY, oq[0]), (A, oq[2])),
+                                     (dA, oracle.linear_bwd_data, (dY, oq[0]), (W, oq[1]))):
+        idx = np.random.default_rng(5).integers(0, got.numel(), size=2000).astype(np.uint64)
+        ref, ab = f(host_src(x), host_src(z), qx, qz, want_abs=True, at=idx)
+        check_product(got.view(-1).cpu().numpy()[idx.astype(np.int64)], ref, ab)
 
 
 # weight gradients whose bfloat16 form cuts the contraction into more slices than the code form would by its own

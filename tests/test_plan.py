@@ -5,7 +5,7 @@ import subprocess
 
 import pytest
 
-from gpu_util import GROUP_SHAPES, PAIR_SHAPES, RIDE_SHAPES
+from gpu_util import GROUP_SHAPES, LARGE_MFMA_SHAPES, PAIR_SHAPES, RIDE_SHAPES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2511_00874_amd", "csrc")
@@ -24,6 +24,14 @@ extern "C" void plan(size_t P, size_t Q, size_t R, int pipe, int leaves, unsigne
 extern "C" void pair(size_t M, size_t N, size_t K, int pipe, unsigned* o) {
   const Pair p = choose_pair(M, N, K, pipe, plan_for(N, K, M, pipe), plan_for(M, K, N, pipe));
   const unsigned v[] = {(unsigned)p.form, p.weight_first, (unsigned)p.w.waves, p.w.nsplit, p.w.k_per_split, (unsigned)p.d.waves, p.d.nsplit, p.d.k_per_split};
+  for (int i = 0; i < 8; ++i) o[i] = v[i];
+}
+extern "C" void large_mfma(size_t M, size_t N, size_t K, int pipe, unsigned* o) {
+  const Plan w = plan_for(N, K, M, pipe), d = plan_for(M, K, N, pipe);
+  const Pair p = choose_pair(M, N, K, pipe, w, d);
+  const Launch lw = choose_launch(w, N, K, M, pipe, true, 0), ld = choose_launch(d, M, K, N, pipe, false, 0);
+  const unsigned v[] = {(unsigned)p.form, p.weight_first, (unsigned)p.w.waves, p.w.large_mfma, (unsigned)p.d.waves, p.d.large_mfma,
+                        sums_in_large_mfma(lw.form, N, K, lw.nsplit), sums_in_large_mfma(ld.form, M, K, ld.nsplit)};
   for (int i = 0; i < 8; ++i) o[i] = v[i];
 }
 // nanoseconds of the plans of a backward call, and of what chooses between one launch and two beside them
@@ -57,7 +65,7 @@ def plan(tmp_path_factory):
                    check=True)
     lib = C.CDLL(str(d / "plan.so"))
     lib.plan.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_int, C.c_uint, C.c_void_p]
-    lib.pair.argtypes = lib.host_time.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_void_p]
+    lib.pair.argtypes = lib.large_mfma.argtypes = lib.host_time.argtypes = [C.c_size_t] * 3 + [C.c_int, C.c_void_p]
 
     def pair(M, N, K, pipe):
         o = (C.c_uint * 8)()
@@ -68,7 +76,7 @@ def plan(tmp_path_factory):
         o = (C.c_uint * 5)()
         lib.plan(P, Q, R, pipe, leaves, rides, o)
         return dict(planned_slices=o[0], form=o[1], slices=o[2], k_per_split=o[3], ring=o[4])
-    f.pair, f.host_time = pair, lib.host_time
+    f.pair, f.large_mfma, f.host_time = pair, lib.large_mfma, lib.host_time
     return f
 
 
@@ -264,3 +272,15 @@ def test_gpu_tests_reach_every_form(plan):
     assert {(P64_G2, False), (P128_S2, False), (P128_G2, False)} <= carried[F8]
     for pipe in (F16C, F16W):
         assert {(P64_G2, False), (P128_S2, False), (P128_G2, False)} <= carried[pipe]
+
+
+def test_one_set_of_sums_has_the_mfma_tiles_of_its_launch_in_a_pair_as_well(plan):
+    seen = set()
+    for M, N, K in LARGE_MFMA_SHAPES:
+        o = (C.c_uint * 8)()
+        plan.large_mfma(M, N, K, F16C, o)
+        form, first, waves_w, w, waves_d, d, alone_w, alone_d = o
+        assert form == 1 and (w, d) == (alone_w, alone_d), (M, N, K)
+        kinds = tuple("two" if waves == 2 else "large" if large else "small" for waves, large in ((waves_w, w), (waves_d, d)))
+        seen.add(kinds if first else kinds[::-1])
+    assert seen == {(a, b) for a in ("two", "large", "small") for b in ("large", "small")}  # (the longer tiles, of two sets, go first)
