@@ -1003,8 +1003,8 @@ __device__ __forceinline__ void cut3(const v4f (&x)[2], v4i (&plane)[3]) {
 // TWO: the large parts gather in one set of accumulators, the middle and small ones in another, and the two are added
 // at the end.  A binary32 sum rounds at its own size whatever it is given, so one set over all three parts rounds
 // three times for every 16 products instead of once: error over the 2-norm, 736 x 688 x 1744 2.5e-7 with one set,
-// 7.1e-8 with two, 10976 x 1760 x 3312 5.4e-7 and 1.4e-7.  Twice the accumulators are 189 registers instead of 125,
-// two workgroups per CU instead of three: 8192 x 3072 x 768 forward and input gradient 233 us against 253, 16384 x 4096
+// 7.1e-8 with two, 10976 x 1760 x 3312 5.4e-7 and 1.4e-7.  Twice the accumulators are 211 registers instead of 148
+// (with MFMA tiles of 32 x 32 189 and 128), two workgroups per CU instead of three: with those 8192 x 3072 x 768 forward and input gradient 233 us against 253, 16384 x 4096
 // x 1024 737 against 774.  Three stages in that ring (147 KiB of LDS): 251 and 767.  make_cut3_plan says which.
 template <class MMA, int NW, int TN, int STAGES, bool TWO>
 __global__ __launch_bounds__(NW * 64, TWO ? 2 : 1) void gemm_cut3_kernel(GemmParams g) {
@@ -1510,12 +1510,18 @@ hipError_t launch_gemm_f32_bf16(float* out, const float* X, const uint16_t* Z, s
   g.k_per_split = pl.k_per_split;
   g.nsplit = pl.nsplit;
   g.alpha = s.alpha; g.sx = s.sx; g.sz = s.sz; g.sx_dev = s.sx_dev; g.sz_dev = s.sz_dev;
-  // MFMA tiles of 16 x 16 where the chip is full of 128 x 128 tiles and its clock counts; the small ones wait for LDS, the
-  // cut and their stores instead, and take 32 x 32 (forward and input gradient, int8 weights, us with 32 x 32 and 16 x 16:
-  // 8192 x 3072 x 768 220.7 and 208.9, 16384 x 4096 x 1024 696 and 646; 736 x 688 x 1744 46.5 and 48.2, 496 x 496 x 352 29.0 and
-  // 30.2; error against 64 bits 3.68e-7 and 3.65e-7 at the first, 6.012e-7 and 5.989e-7 at the second)
-  if (pl.two) return pl.kind == 0 ? launch_cut3<BF16Mma16, 4, 4, 2, true>(g, stream) : launch_cut3<BF16Mma, 2, 2, 3, true>(g, stream);
-  return pl.kind == 0 ? launch_cut3<BF16Mma16, 4, 4, 2, false>(g, stream) : launch_cut3<BF16Mma, 2, 2, 3, false>(g, stream);
+  // MFMA tiles of 16 x 16 where CUs have more than one 128 x 128 tile and the clock counts.  With one, and the small ones, a tile waits
+  // for LDS, the cut and its stores instead, and 32 x 32 are faster (int8 weights, us with 32 x 32 and 16 x 16; forward and input gradient
+  // 8192 x 3072 x 768 220.7 and 208.9, 16384 x 4096 x 1024 696 and 646, 736 x 688 x 1744 46.5 and 48.2, 496 x 496 x 352 29.0 and
+  // 30.2; forward calls, a tile a CU 192 x 5744 x 752 26.4 and 27.2, 544 x 976 x 4576 in slices 31.8 and 32.9, 16 shapes 0.97 to 1.03 of
+  // the time of 16 x 16; 257 to 512 tiles 2112 x 3824 x 496 33.7 and 31.9, 944 x 2208 x 1664 37.9 and 36.3, 16 shapes 0.99 to 1.09;
+  // error against 64 bits 3.68e-7 and 3.65e-7 at the first, 6.012e-7 and 5.989e-7 at the second)
+  const size_t tiles = ((P + 127) / 128) * ((Q + 127) / 128) * pl.nsplit;
+  const auto large_tiles = [&](auto two) {
+    return tiles > NUM_CU ? launch_cut3<BF16Mma16, 4, 4, 2, two.value>(g, stream) : launch_cut3<BF16Mma, 4, 4, 2, two.value>(g, stream);
+  };
+  if (pl.two) return pl.kind == 0 ? large_tiles(std::true_type{}) : launch_cut3<BF16Mma, 2, 2, 3, true>(g, stream);
+  return pl.kind == 0 ? large_tiles(std::false_type{}) : launch_cut3<BF16Mma, 2, 2, 3, false>(g, stream);
 }
 
 }  // namespace srq

@@ -259,3 +259,6 @@ def test_mfma_tiles_of_the_product_forms(lib):
                    **{(p, 128, 128, 1, 1): {16} for p in ("BF16", "F8F16")}, **{(p, 128, 128, 1, 2): {32} for p in ("BF16", "F8F16")},
                    **{(p, 128, 128, 2, 1): {32} for p in ("BF16", "F8F16")}, ("BF16", 128, 192, 1, 1): {16},
                    ("F8F16", 128, 192, 1, 1): {16, 32}, **{(p, 64, 64, g, 1): {32} for p in ("BF16", "F8F16") for g in (2, 4)}}
+    # weight-only products: both sizes on 128 x 128 tiles (by the number of tiles), 32 x 32 on 64 x 64
+    cut = {(m[1], m[2]) for n in _kernels(lib.LIB_PATH) if (m := re.search(r"gemm_cut3_kernelINS_3mma\d+(BF16Mma(?:16)?)ELi(\d)E", n))}
+    assert cut == {("BF16Mma", "4"), ("BF16Mma16", "4"), ("BF16Mma", "2")}

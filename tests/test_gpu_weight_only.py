@@ -107,6 +107,17 @@ def test_binary32_rows_at_the_edges_of_tiles_stages_and_slices(M, N, K):
     assert torch.equal(Y[keep], clean[keep])
 
 
+# 128 x 128 tiles multiply in MFMA tiles of 32 x 32 up to 256 of them, of 16 x 16 beyond: 256 and 272 tiles with one set of sums, and
+# slices with two sets, few and many; the last rows and columns end inside a tile
+@pytest.mark.parametrize("M,N,K", [(2048, 2048, 144), (2064, 2032, 144), (544, 976, 4576), (944, 2208, 1664)])
+def test_binary32_rows_on_both_sizes_of_mfma_tiles(M, N, K):
+    A, _, W, sW = _case(M, N, K, L.INT8, False, True, seed=95)
+    say("binary32 rows, MFMA tiles", M, N, K)
+    Y = L.sr_linear_fwd(A, W, NOQ, L.Quant(L.INT8, sW, seed=6, counter_offset=3)).cpu().numpy()
+    ref, ab = oracle.linear_fwd_weight_only(host_src(A), host_src(W), oracle.Quant(L.INT8, sW, seed=6, counter_offset=3), want_abs=True)
+    check_product(Y, ref, ab, "Y")
+
+
 # contractions that one bfloat16 product over the three parts side by side would leave whole (the first two) and
 # would cut into 2, 2, 3, 6, 7 and 11 slices
 @pytest.mark.parametrize("M,N,K", [(256, 256, 256), (2064, 1040, 272), (1200, 608, 400), (8192, 768, 3072),
