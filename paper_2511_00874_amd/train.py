@@ -108,6 +108,14 @@ class SRLinear(torch.nn.Module):
         self.seed, self.position, self.round_mode = seed, 0, round_mode
         self.ws = None
 
+    def __setattr__(self, name, value):
+        # Module's own looks for parameters, buffers and modules first, 1.4 us; an attribute that is there is none of these, and a
+        # number does not become one
+        if type(value) in (int, bool) and name in self.__dict__:
+            object.__setattr__(self, name, value)
+        else:
+            super().__setattr__(name, value)
+
     _sizes = None  # bytes that calls of so many rows need
 
     def _size(self, op, M):
@@ -190,7 +198,7 @@ class SRLinear(torch.nn.Module):
         pos_a = pos_w + w_blocks
         pos_a_bwd = pos_a + a_blocks
         pos_w_bwd = pos_a_bwd + a_blocks
-        self.__dict__["position"] = pos_w_bwd + w_blocks  # (Module.__setattr__ would look for parameters and modules first)
+        self.position = pos_w_bwd + w_blocks
         qw, qw_bwd = self._q("W_fwd", sc, 1, pos_w), self._q("W_bwd", sc, 3, pos_w_bwd)
         saved = {"scales": sc, "a": (2, pos_a_bwd), "w": (3, self.kinds["W_bwd"], self.round_mode, self.seed, pos_w_bwd)}
         y = torch.empty((M, N), dtype=torch.float32, device=a.device)
@@ -224,7 +232,7 @@ class SRLinear(torch.nn.Module):
         sdy = L.absmax_scales([(dy, self.kinds["dY_bwd"])])
         da = torch.empty((M, K), dtype=torch.float32, device=dy.device)
         pos_dy = self.position
-        self.__dict__["position"] = pos_dy + (M * N + 7) // 8
+        self.position = pos_dy + (M * N + 7) // 8
         scales, (i_a, pos_a), qw = saved["scales"], saved["a"], self._q_saved(saved)
         for i, r0 in enumerate(range(0, M, MAX_ROWS)):
             r1 = min(M, r0 + MAX_ROWS)
@@ -237,7 +245,7 @@ class SRLinear(torch.nn.Module):
             else:
                 L.sr_linear_bwd(_rows(dy, r0, r1), w, _rows(a, r0, r1), qdy, qw, qa,
                                 out_dA=_rows(da, r0, r1), out_dW=self.dW, beta=beta, workspace=self._workspace(L.OP_BWD, r1 - r0))
-            self.__dict__["have_grad"] = True
+            self.have_grad = True
         return da
 
     def forward(self, x):

@@ -37,3 +37,33 @@ def test_a_position_on_the_device_is_not_read_by_the_host(objective, calls):
     _step(layer)
     assert all(isinstance(q, L.Quant) and isinstance(q.counter_offset, torch.Tensor) for q in calls)  # (marshalled as device counters)
     assert [(q.kind, q.round_mode, q.seed, int(q.counter_offset)) for q in calls] == host
+
+
+@pytest.mark.parametrize("objective", train.OBJECTIVES)
+def test_a_subclass_sees_every_write_of_the_layers_state(objective, calls):
+    seen = []
+
+    class Property(train.SRLinear):
+        position = property(lambda self: self._position, lambda self, v: object.__setattr__(self, "_position", v))
+        have_grad = property(lambda self: self._have, lambda self, v: object.__setattr__(self, "_have", v))
+
+    class Watched(train.SRLinear):
+        def __setattr__(self, name, value):
+            if name in ("position", "have_grad"):
+                seen.append((name, value))
+            super().__setattr__(name, value)
+
+    plain = train.SRLinear(K, N, 7, device="cpu", objective=objective)
+    _step(plain)
+    for cls in (Property, Watched):
+        layer = cls(K, N, 7, device="cpu", objective=objective)
+        seen.clear()
+        _step(layer)
+        assert (layer.position, layer.have_grad) == (plain.position, True) and plain.have_grad
+        assert not {"position", "have_grad"} & set(vars(layer)) or cls is Watched
+    assert ("position", plain.position) in seen and ("have_grad", True) in seen
+    plain.register_buffer("kept", torch.zeros(1))
+    with pytest.raises(TypeError):
+        plain.kept = 3  # as a module refuses it
+    plain.position = torch.nn.Parameter(torch.zeros(1))
+    assert "position" in dict(plain.named_parameters())
