@@ -292,26 +292,27 @@ __device__ __forceinline__ void run_job(const QuantJob& j, uint32_t local, uint8
 // The job descriptor of a workgroup, which is uniform.  Indexing the by-value argument would make the compiler copy the whole
 // argument to per-lane scratch memory; instead the one descriptor is read from the kernel-argument segment (constant address space, scalar
 // loads), where the explicit arguments start at offset 0.
-__device__ __forceinline__ QuantJob job_of_block(const QuantJobs& jobs) {
+typedef __attribute__((address_space(4))) const uint32_t* job_words;
+__device__ __forceinline__ job_words job_of_block(const QuantJobs& jobs) {
   int ji = 0;
 #pragma unroll
   for (int i = 1; i < QUANT_JOBS_MAX; ++i)
     if (i < jobs.njobs && blockIdx.x >= jobs.job[i].first_block) ji = i;
-  struct alignas(8) Raw { uint32_t w[sizeof(QuantJob) / 4]; } raw;
-  static_assert(sizeof(QuantJob) % 4 == 0 && offsetof(QuantJobs, job) % 4 == 0, "descriptor is read word-wise");
-  typedef __attribute__((address_space(4))) const uint32_t* kernarg_words;
-  const kernarg_words kw = (kernarg_words)__builtin_amdgcn_kernarg_segment_ptr() +
-                           (offsetof(QuantJobs, job) + (size_t)ji * sizeof(QuantJob)) / 4;
-#pragma unroll
-  for (unsigned k = 0; k < sizeof(QuantJob) / 4; ++k) raw.w[k] = kw[k];
-  return __builtin_bit_cast(QuantJob, raw);
+  return (job_words)__builtin_amdgcn_kernarg_segment_ptr() + (offsetof(QuantJobs, job) + (size_t)ji * sizeof(QuantJob)) / 4;
 }
-
+struct alignas(8) RawJob {
+  uint32_t w[sizeof(QuantJob) / 4];
+};
+static_assert(sizeof(QuantJob) % 4 == 0 && offsetof(QuantJobs, job) % 4 == 0, "descriptor is read word-wise");
 template <bool CACHED>
 __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[TC * (128 + 2) * 2];
   static_assert(TC * (256 + 4) <= (int)sizeof(smem), "the tile of 256 rows of bytes fits as well");
-  const QuantJob j = job_of_block(jobs);
+  const job_words words = job_of_block(jobs);
+  RawJob raw;  // (returned from a function the descriptor costs 17 scalar registers spilled instead of 11)
+#pragma unroll
+  for (unsigned k = 0; k < sizeof(QuantJob) / 4; ++k) raw.w[k] = words[k];
+  const QuantJob j = __builtin_bit_cast(QuantJob, raw);
   const uint32_t local = blockIdx.x - j.first_block;
   const bool bf = j.store == STORE_BF16;
   switch (j.kind) {
@@ -345,7 +346,11 @@ __global__ __launch_bounds__(QBLOCK) void quantize_jobs_kernel(QuantJobs jobs) {
 //   12.9 -> 10.4 / 12.4 -> 10.8 / 12.6 -> 10.9; 8192 x 5632 and 2048 x 5632 48.6 -> 46.4 / 48.6 -> 47.5 / 48.5 -> 47.9
 template <bool CACHED>
 __global__ __launch_bounds__(QBLOCK) void quantize_flat_jobs_kernel(QuantJobs jobs) {
-  const QuantJob j = job_of_block(jobs);
+  const job_words words = job_of_block(jobs);
+  RawJob raw;
+#pragma unroll
+  for (unsigned k = 0; k < sizeof(QuantJob) / 4; ++k) raw.w[k] = words[k];
+  const QuantJob j = __builtin_bit_cast(QuantJob, raw);
   const uint32_t local = blockIdx.x - j.first_block;
   if (j.kind == SRQ_E4M3) flat_path<SRQ_E4M3_CONV, false, CACHED, true>(j, local, j.nblocks);
   else if (j.kind == SRQ_E5M2) flat_path<SRQ_E5M2, false, CACHED, true>(j, local, j.nblocks);
