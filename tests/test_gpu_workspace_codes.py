@@ -166,21 +166,32 @@ def test_stash_codes_of_two_quantizers(M, N, K, kind, fwd):
         assert np.array_equal(_piece(stash, _up(2 * M * K), N * K), _expect(tW, kind, oq[3], True, 1)), "Q(W)^T"
 
 
+def _spread(shape, rng, bf16):
+    """Elements over 27 binades (some in the subnormals of the formats, some at saturation), one in 40 of them zeros of both signs,
+    infinities, NaN, subnormals of binary32 and numbers near its end."""
+    x = (rng.standard_normal(shape) * np.exp2(rng.uniform(-24, 3, shape))).astype(np.float32)
+    flat = x.reshape(-1)
+    at = rng.permutation(flat.size)[:flat.size // 40 + 8]
+    flat[at] = np.resize(np.float32([0.0, -0.0, np.inf, -np.inf, np.nan, 1e-40, -1e-40, 3e38, -3e38]), at.size)
+    return to_dev(x, bf16)
+
+
 # the quantizers of a backward call that round stochastically to bytes have a kernel of their own (tiles of 128 rows and 64 columns,
 # steps of 64 and 128 rows, pieces of four): both sides of its edges and of the rule on binary32 rows a multiple of 4096 apart (2048
-# rows, of integers 1024, and more); the scale takes some elements into the subnormals of the formats and some to saturation
-@pytest.mark.parametrize("M,N,K,kind", [(16, 16, 16, L.E5M2), (80, 1040, 144, L.E5M2), (144, 80, 4240, L.E5M2), (2192, 208, 336, L.E5M2),
-                                        (2048, 4096, 16, L.E5M2), (2064, 4096, 16, L.E5M2), (1040, 528, 272, L.E4M3),
-                                        (2064, 144, 464, L.E4M3), (16, 16, 16, L.INT8), (144, 80, 4240, L.INT8), (2192, 208, 336, L.INT4),
-                                        (1024, 4096, 16, L.INT8), (1040, 4096, 16, L.INT8), (272, 1040, 528, L.INT4)])
+# rows, of integers 1024, and more); one format for all operands, and one for dY beside another for W and A
+@pytest.mark.parametrize("M,N,K,kind,kind_dy", [
+    (16, 16, 16, L.E5M2, L.E5M2), (80, 1040, 144, L.E5M2, L.E5M2), (144, 80, 4240, L.E5M2, L.E5M2), (2192, 208, 336, L.E5M2, L.E5M2),
+    (2048, 4096, 16, L.E5M2, L.E5M2), (2064, 4096, 16, L.E5M2, L.E5M2), (1040, 528, 272, L.E4M3, L.E4M3), (2064, 144, 464, L.E4M3, L.E4M3),
+    (1040, 528, 272, L.E4M3, L.E5M2), (2064, 144, 464, L.E4M3, L.E5M2),
+    (16, 16, 16, L.INT8, L.INT8), (144, 80, 4240, L.INT8, L.INT8), (2192, 208, 336, L.INT4, L.INT4), (1024, 4096, 16, L.INT8, L.INT8),
+    (1040, 4096, 16, L.INT8, L.INT8), (272, 1040, 528, L.INT4, L.INT4), (272, 1040, 528, L.INT8, L.INT4)])
 @pytest.mark.parametrize("bf16", [False, True])
-def test_backward_codes(M, N, K, kind, bf16):
-    say("backward codes", M, N, K, L.KIND_NAMES[kind], bf16)
+def test_backward_codes(M, N, K, kind, kind_dy, bf16):
+    say("backward codes", M, N, K, L.KIND_NAMES[kind], L.KIND_NAMES[kind_dy], bf16)
     rng = np.random.default_rng(M + N + K)
-    A, W, dY = (to_dev((rng.standard_normal(s) * np.exp2(rng.uniform(-24, 3, s))).astype(np.float32), bf16)
-                for s in ((M, K), (N, K), (M, N)))
-    assert kind != L.E4M3 or M * N * K >= 2**27  # one byte an element
-    oq = [oracle.Quant(kind, s, 17, 1000 * i) for i, s in enumerate((0.01, 0.02, 0.015))]
+    A, W, dY = (_spread(s, rng, bf16) for s in ((M, K), (N, K), (M, N)))
+    assert L.E4M3 not in (kind, kind_dy) or M * N * K >= 2**27  # one byte an element
+    oq = [oracle.Quant(k, s, 17, 1000 * i) for i, (k, s) in enumerate(((kind_dy, 0.01), (kind, 0.02), (kind, 0.015)))]
     qdY, qW, qA = (L.Quant(q.kind, q.scale, q.seed, q.counter_offset) for q in oq)
     ws = torch.zeros(L.sr_linear_workspace_bytes(L.OP_BWD_STASHED, M, N, K), dtype=torch.uint8, device=A.device)
     stash = torch.zeros(L.sr_linear_stash_bytes(M, N, K), dtype=torch.uint8, device=A.device)
@@ -188,25 +199,26 @@ def test_backward_codes(M, N, K, kind, bf16):
     whole = torch.zeros(L.sr_linear_workspace_bytes(L.OP_BWD, M, N, K), dtype=torch.uint8, device=A.device)
     L.sr_linear_bwd(dY, W, A, qdY, qW, qA, out_dA=dA, out_dW=dW, workspace=whole, phase=L.PHASE_QUANTIZE)
     L.sr_linear_bwd_stashed(dY, stash, K, qdY, qW, qA, out_dA=dA, out_dW=dW, workspace=ws, phase=L.PHASE_QUANTIZE)
-    want = {(name, tr): _expect(t, kind, q, tr, 1)
-            for name, t, q, trs in (("dY", dY, oq[0], (False, True)), ("W", W, oq[1], (True,)), ("A", A, oq[2], (True,))) for tr in trs}
-    blob, saved = whole.cpu().numpy().tobytes(), ws.cpu().numpy().tobytes()
-    assert blob.startswith(want["dY", False].tobytes()) and saved.startswith(want["dY", False].tobytes()), "Q(dY)"
-    for name in ("W", "dY", "A"):  # (256-byte aligned pieces of the workspace, partial sums between them)
-        at = blob.find(want[name, True].tobytes())
-        assert at >= 0, name
-    assert saved.find(want["dY", True].tobytes()) >= 0, "Q(dY)^T of the stash call"
+    slices = L.sr_gemm_workspace_bytes if kind in (L.INT8, L.INT4) else L.raw.sr_gemm_e5m2_workspace_bytes
+    partial = _up(slices(M, K, N))
+    assert L.E4M3 not in (kind, kind_dy) or partial == _up(L.raw.sr_gemm_bf16_workspace_bytes(M, K, N))  # (it may take that plan)
+    o_wt = _up(M * N)
+    o_dyt = o_wt + _up(K * N) + partial
+    o_at = o_dyt + _up(N * M)
+    for what, blob, off, t, q, tr in (("Q(dY)", whole, 0, dY, oq[0], False), ("Q(W)^T", whole, o_wt, W, oq[1], True),
+                                      ("Q(dY)^T", whole, o_dyt, dY, oq[0], True), ("Q(A)^T", whole, o_at, A, oq[2], True),
+                                      ("Q(dY), stashed", ws, 0, dY, oq[0], False), ("Q(dY)^T, stashed", ws, o_wt + partial, dY, oq[0], True)):
+        assert np.array_equal(_piece(blob, off, t.numel()), _expect(t, q.kind, q, tr, 1)), what
 
 
 # operands of a forward pass: chunks of 512 elements and what is left over, four loads of a bfloat16 source and fewer
 @pytest.mark.parametrize("M,N,K,kind", [(16, 16, 16, L.INT8), (48, 80, 208, L.INT4), (272, 1040, 528, L.INT8), (16, 16, 16, L.E5M2),
-                                        (48, 1040, 272, L.E5M2), (1040, 528, 272, L.E4M3)])
+                                        (48, 1040, 272, L.E5M2), (1040, 528, 272, L.E4M3), (272, 1040, 528, L.E4M3)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_forward_codes(M, N, K, kind, bf16):
     say("forward codes", M, N, K, L.KIND_NAMES[kind], bf16)
     rng = np.random.default_rng(M + N + K)
-    A, W = (to_dev((rng.standard_normal(s) * np.exp2(rng.uniform(-24, 3, s))).astype(np.float32), b)
-            for s, b in (((M, K), bf16), ((N, K), not bf16)))
+    A, W = (_spread(s, rng, b) for s, b in (((M, K), bf16), ((N, K), not bf16)))
     oq = [oracle.Quant(kind, s, 17, 1000 * i) for i, s in enumerate((0.01, 0.02))]
     lq = [L.Quant(q.kind, q.scale, q.seed, q.counter_offset, flags=L.FLAG_QUANTIZE_ONCE) for q in oq]
     ws = torch.zeros(L.sr_linear_workspace_bytes(L.OP_FWD, M, N, K), dtype=torch.uint8, device=A.device)
