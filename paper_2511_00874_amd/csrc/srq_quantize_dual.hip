@@ -14,7 +14,7 @@
 //   3072 x 3072 16.7 -> 13.5, 8192 x 2048 and 2048 x 2048 38.6 -> 33.2, 16384 x 1024 and 1024 x 1024 35.4 -> 35.5 (bfloat16 16.6 -> 12.4,
 //   35.9 -> 24.9, 31.9 -> 24.3).  E4M3 within 2 % of these.  Integers in both layouts, int8, binary32 and bfloat16: 2048 x 2048 8.9 -> 8.6,
 //   9.0 -> 8.6; 4096 x 2048 10.6 -> 10.0, 10.0 -> 8.7; 8192 x 2048 22.0 -> 19.2, 16.1 -> 13.7; 15360 x 2048 37.2 -> 32.7, 32.1 -> 25.3.
-//   Not so binary32 rows 16 KiB apart (turn_strided).
+//   Not so many binary32 rows 16 or 32 KiB apart (turn_strided).
 // Not for large tensors (65536 x 2048, rows a power of two apart, int4 108 -> 143), nor two integer quantizers: they take 68 registers, and within
 // 64 they spill (8192 x 2048 26.4 -> 26.6, 16384 x 1024 23.9 -> 27.9).
 #include <cstddef>
@@ -222,7 +222,7 @@ __device__ __forceinline__ void turn_job(const QuantJob& j, job_words job, uint3
   }
 }
 
-// At most 64 registers: a wave fits on a SIMD beside two of the persistent product kernel.
+// (Two quantizers was all it took at first, hence the name.)  At most 64 registers: a wave fits on a SIMD beside two of the persistent product kernel.
 template <bool CACHED>
 __global__ __launch_bounds__(QBLOCK) void quantize_dual_kernel(QuantJobs jobs) {
   __shared__ __attribute__((aligned(16))) uint8_t tile[TC * PITCH];

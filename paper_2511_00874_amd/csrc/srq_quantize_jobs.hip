@@ -359,12 +359,17 @@ __global__ __launch_bounds__(QBLOCK) void quantize_flat_jobs_kernel(QuantJobs jo
 
 }  // namespace
 
-// Binary32 rows a multiple of 16 KiB apart: the sixteen rows that a wave instruction of launch_quantize_turned's kernel reads a piece of
-// then share a few memory channels, and many tiles of them wait for each other where the four neighbouring rows of
-// quantize_jobs_kernel do not (one quantizer, E5M2 in both layouts, us there and here: rows x 4096 at 2048 rows 11.8 and 11.5, 3072 14.4 and
-// 15.5, 4096 21.5 and 27.5, 6144 28.8 and 36.7; x 8192 at 2048 27.6 and 23.6, 3072 32.4 and 32.8; at 4096 rows x 4160 21.3 and 20.0,
-// x 5120 25.3 and 24.0; int8 x 4096 at 2048 rows 10.2 and 11.6).
-static bool turn_strided(const QuantJob& j) { return j.dtype == SRQ_F32 && j.cols % 4096 == 0 && j.rows > (kind_is_int(j.kind) ? 1024u : 2048u); }
+// More than 2048 binary32 rows 16 or 32 KiB apart: the sixteen rows that a wave instruction of launch_quantize_turned's kernel reads a
+// piece of then share a few memory channels, and many tiles of them wait for each other where the four neighbouring rows of
+// quantize_jobs_kernel do not.  One quantizer in both layouts, us there and here: int8 rows x 4096 at 2048 rows 6.7 and 7.9, 2304 10.5
+// and 10.4, 2560 12.1 and 11.3, 3072 13.5 to 14.3 and 13.2, 4096 23.4 and 17.8, 6144 35.6 and 26.5; E5M2 7.5 and 9.8, 10.5 and 11.5,
+// 12.0 and 11.9, 14.6 and 13.8, 23.1 and 19.7, 35.6 and 27.0, E4M3 like it.  x 8192 it depends on where the tensor lies: int8 at 2048 20.1
+// and 23.7, 2560 26.5 and 25.0 to 26.5, 3072 27.0 or 33.2 and 28.4 to 29.7, 3584 33.1 or 39.4 and 34.3 to 35.7, E5M2 within 1 of these.
+// Rows further apart cost both kernels alike (int8 and E5M2 1024 x 12288 12.7 and 13.0, 12.8 and 13.6; 2560 x 12288 33.7 and 33.4; 1536 x
+// 16384 27.2 and 27.0 to 28.0, 27.3 and 29.1), and other distances have nothing of it (4096 x 4160 and x 5120 20.0 and 21.3, 24.0 and
+// 25.3).  Two quantizers are faster there at every size (E5M2 beside int8 2048 x 4096 10.7 and 13.4, 4096 x 4096 24.8 and 25.1, 2048 x 8192
+// 22.9 and 27.0).
+static bool turn_strided(const QuantJob& j) { return j.dtype == SRQ_F32 && (j.cols == 4096 || j.cols == 8192) && j.rows > 2048; }
 
 // Requirements (checked by the callers): rows % 16 == 0 and cols % 16 == 0 for every job,
 // store is STORE_BYTE or STORE_BF16.

@@ -177,14 +177,14 @@ def _spread(shape, rng, bf16):
 
 
 # the quantizers of a backward call that round stochastically to bytes have a kernel of their own (tiles of 128 rows and 64 columns,
-# steps of 64 and 128 rows, pieces of four): both sides of its edges and of the rule on binary32 rows a multiple of 4096 apart (2048
-# rows, of integers 1024, and more); one format for all operands, and one for dY beside another for W and A
+# steps of 64 and 128 rows, pieces of four): both sides of its edges and of the rule on binary32 rows 4096 and 8192 apart
+# (2048 rows, and more; other multiples of 4096 have none); one format for all operands, and one for dY beside another for W and A
 @pytest.mark.parametrize("M,N,K,kind,kind_dy", [
     (16, 16, 16, L.E5M2, L.E5M2), (80, 1040, 144, L.E5M2, L.E5M2), (144, 80, 4240, L.E5M2, L.E5M2), (2192, 208, 336, L.E5M2, L.E5M2),
-    (2048, 4096, 16, L.E5M2, L.E5M2), (2064, 4096, 16, L.E5M2, L.E5M2), (1040, 528, 272, L.E4M3, L.E4M3), (2064, 144, 464, L.E4M3, L.E4M3),
+    (2048, 4096, 16, L.E5M2, L.E5M2), (2064, 4096, 16, L.E5M2, L.E5M2), (2064, 8192, 16, L.E5M2, L.E5M2), (1040, 528, 272, L.E4M3, L.E4M3), (2064, 144, 464, L.E4M3, L.E4M3),
     (1040, 528, 272, L.E4M3, L.E5M2), (2064, 144, 464, L.E4M3, L.E5M2),
-    (16, 16, 16, L.INT8, L.INT8), (144, 80, 4240, L.INT8, L.INT8), (2192, 208, 336, L.INT4, L.INT4), (1024, 4096, 16, L.INT8, L.INT8),
-    (1040, 4096, 16, L.INT8, L.INT8), (272, 1040, 528, L.INT4, L.INT4), (272, 1040, 528, L.INT8, L.INT4)])
+    (16, 16, 16, L.INT8, L.INT8), (144, 80, 4240, L.INT8, L.INT8), (2192, 208, 336, L.INT4, L.INT4), (2048, 4096, 16, L.INT8, L.INT8),
+    (2064, 4096, 16, L.INT8, L.INT8), (2048, 8192, 16, L.INT8, L.INT8), (272, 1040, 528, L.INT4, L.INT4), (272, 1040, 528, L.INT8, L.INT4)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_backward_codes(M, N, K, kind, kind_dy, bf16):
     say("backward codes", M, N, K, L.KIND_NAMES[kind], L.KIND_NAMES[kind_dy], bf16)
