@@ -329,6 +329,7 @@ __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block
       // After the MFMAs of an X fragment the next sub-step's fragments are read one by one into the registers that have
       // just come free.  Fragments that have to be widened (VALU) are, one ahead, between the MFMAs of the one before, those of Z
       // between the first ones that do without them.  The scheduling barriers pin that order.
+      static_assert(!MMA::WIDENS || (TM >= 2 && TN >= 2), "the first fragments of a sub-step are read before they are widened at its turn");
       raw_t xf[TM], zf[2][TN];
       auto fetch_x = [&](int ks, int i) { xf[i] = load_frag(stage + i * T * BK, xoff ^ (ks * LG * FC * 16u)); };
       auto fetch_z = [&](int ks, int j) { zf[ks & 1][j] = load_frag(stage + j * T * BK, zoff ^ (ks * LG * FC * 16u)); };
@@ -365,7 +366,7 @@ __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block
             sum = MMA::mma(ze[j], xe[n & 1], sum);
             if constexpr (MMA::WIDENS) {
               if (i == 0 && j + 1 < TN) ze[j + 1] = MMA::expand_z(zf[ks & 1][j + 1]);
-              if (turn && TM > 1 && j == 0) ze[0] = MMA::expand_z(zf[(ks + 1) & 1][0]);
+              if (turn && j == 0) ze[0] = MMA::expand_z(zf[(ks + 1) & 1][0]);
             }
           }
           if constexpr (MMA::WIDENS) {
@@ -374,8 +375,7 @@ __device__ __forceinline__ void product_tile(const GemmParams& g, uint32_t block
 #pragma unroll
             for (int m = 0; m < N_MFMA; ++m) {
               __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-              if (valu > 4 * N_MFMA) __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
-              else if (valu > 3 * N_MFMA) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+              if (valu > 3 * N_MFMA) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
               else if (valu > N_MFMA) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
               else __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
             }
