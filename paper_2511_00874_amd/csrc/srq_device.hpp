@@ -211,10 +211,11 @@ __device__ __forceinline__ uint32_t pack4_bytes(const uint32_t (&c)[4]) {
 // 47 -> 44; E5M2 bfloat16 45 -> 36 / 45 -> 36 / 45 -> 42.
 constexpr uint32_t RTN_WORD = 0x7FFF7FFFu;
 
-// Formats whose codes come out of the conversions a word at a time.  E4M3 not in the shortest launches: its smallest normal number is
-// 2^-15 of the largest, so a few waves of most tensors hold rare cases, and a launch of some microseconds waits for the first of them,
-// whose code is not in the instruction cache.  For E5M2 that is 2^-30 (1024 x 1024 binary32, turned: normal 4.15 -> 3.8 us, 40 binades
-// 4.15 -> 4.25; bfloat16 4.1 -> 3.6 and 4.1).
+// Formats whose codes come out of the conversions a word at a time.  E4M3's smallest normal number is 2^-15 of the largest, so a few
+// waves of most tensors hold rare cases, and a launch of some microseconds waits for the first of them, whose code is not in the
+// instruction cache: the quantizer of one tensor converts it from 2^22 elements on (E4M3_CONV_ELEMENTS), those of several operands at every
+// size, where their small kernels save more than that costs (512 x 512 twice with 1 % of outliers 4.1 -> 3.7 us).  For E5M2 it is
+// 2^-30 (1024 x 1024 binary32, turned: normal 4.15 -> 3.8 us, 40 binades 4.15 -> 4.25; bfloat16 4.1 -> 3.6 and 4.1).
 template <int KIND>
 constexpr bool BY_CONVERSION = KIND == SRQ_E4M3_CONV || KIND == SRQ_E5M2;
 

@@ -5,13 +5,13 @@
 //
 // All three products of Alg. 1 / Alg. 2 have this form once the quantizer has written the
 // operands with the contraction index contiguous.  Four matrix pipelines:
-//   int8 codes          v_mfma_i32_32x32x32_i8        int32 accumulators, exact
-//   E4M3/E5M2 as bf16   v_mfma_f32_32x32x16_bf16      exact products, binary32 sums
-//   E4M3/E5M2 as f16    v_mfma_f32_32x32x16_f16       the same, from one-byte codes: every value is a
-//                                                     binary16 number, the operands are widened in
-//                                                     registers
-//   E4M3/E5M2 codes     v_mfma_f32_32x32x64_f8f6f4    fp8 pipeline (aligns groups of 8 products)
-// Most kernels multiply in MFMA tiles of 16 x 16 and twice that depth, under which the chip clocks higher (srq_mma.hpp).
+//   int8 codes          v_mfma_i32_16x16x64_i8, _32x32x32_i8        int32 accumulators, exact
+//   E4M3/E5M2 as bf16   v_mfma_f32_16x16x32_bf16, _32x32x16_bf16    exact products, binary32 sums
+//   E4M3/E5M2 as f16    v_mfma_f32_16x16x32_f16, _32x32x16_f16      the same, from one-byte codes: every value is a
+//                                                                   binary16 number, the operands are widened in
+//                                                                   registers
+//   E4M3/E5M2 codes     v_mfma_f32_32x32x64_f8f6f4                  fp8 pipeline (aligns groups of 8 products)
+// in MFMA tiles of 16 x 16, under which the chip clocks higher (srq_mma.hpp), or of 32 x 32, by the form of the product (launch_mma).
 //
 // Kernel shape.  A workgroup owns a BM x BN output tile, its waves a WGM x WGN grid of
 // sub-tiles made of MFMA tiles.  The contraction advances BK = 128 bytes per stage.
@@ -578,7 +578,8 @@ __global__ __launch_bounds__(WA::THREADS, (WA::SETS > WB::SETS ? WA::SETS : WB::
 // tiles of 16 x 16, under which the clock is higher (the fp8 pipeline excepted), and LDS reads one at a time between the
 // MFMAs.  int8, us before (32 x 32 tiles, all fragments of a sub-step read at its start) and now, Gaussian codes:
 // 8192 x 2048 x 5632 84.9 -> 77.7 (79.2 -> 76.4 with the reads spread), 8192^3 450 -> 411, 65536 x 2048 x 5632 671 -> 645,
-// 65536 x 2048 x 2048 264 -> 250, 65536 x 5632 x 2048 719 -> 683; with packed 4-bit X 65536 x 5632 x 2048 700 -> 680.  Whole steps:
+// 65536 x 2048 x 2048 264 -> 250, 65536 x 5632 x 2048 719 -> 683; with packed 4-bit X 65536 x 5632 x 2048 700 -> 680 (in the order of a
+// step, beside a slice sum, 759 -> 752; it takes 2 to 3 % more cycles).  Whole steps:
 // 65536 x 5632 x 2048 2834 -> 2768, 8192 x 2048 x 5632 E4M3 641 -> 603.  Errors against 64 bits of the 8-bit float products are what
 // they were (0.9997 to 1.0003 of it over 8 large shapes).  Measured against it, all slower or equal: the two waves of a SIMD
 // taking turns at LDS and at the MFMAs, a barrier between the turns, with half stages of 64 bytes (rows of 64 bytes
@@ -1323,6 +1324,7 @@ struct Cut3Kind {
   int waves, tn, per_cu;
   double rate_chip, fixed;
 };
+// (measured with MFMA tiles of 32 x 32; with those of 16 x 16 more than 256 large tiles take 0.93 to 1.0 of the time)
 constexpr Cut3Kind CUT3_KINDS[2][2] = {{{4, 4, 3, 1.2e15, 8.0}, {2, 2, 4, 0.5e15, 8.0}},   // one set of accumulators
                                        {{4, 4, 2, 1.1e15, 8.0}, {2, 2, 4, 0.5e15, 8.0}}};  // two
 

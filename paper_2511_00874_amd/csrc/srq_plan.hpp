@@ -30,8 +30,8 @@ constexpr int NUM_CU = 256;
 // Tile shape and number of contraction slices by a cost model (seconds, for ranking only):
 //   time = rounds x (stages per item + fixed per-item stages) x operations per stage / rate
 //          + the pass over the partial results that every extra slice adds.
-// `rate` is what a CU sustains with that tile shape once its slots are full (measured, int8: the
-// other pipelines scale alike): 256 x 256 tiles on workgroups that stay run one per CU and hide
+// `rate` is what a CU sustains with that tile shape once its slots are full (measured with MFMA tiles of 32 x 32, int8: the
+// other pipelines scale alike; those of 16 x 16 take 0.95 to 0.97 of the time on 256 x 256, 0.93 to 1.0 on 128-row tiles in full rounds): 256 x 256 tiles on workgroups that stay run one per CU and hide
 // most of a tile's start and end; the 128-row tiles run two workgroups per CU (one alone gets
 // about 0.85 of the CU's rate); 64 x 64 is for problems too small for anything else.
 struct TileKind {
@@ -261,6 +261,9 @@ struct PairLines {  // microseconds: constant, per stage (of a tile, by form, or
   double pair64, load64, partial64, sum64;
   double worth128;
 };
+// (Fitted with MFMA tiles of 32 x 32.  With those of 16 x 16 in one set of sums, pairs of 128 x 128 tiles take 0.97 to 1.03 of the time
+// that they took, int8 0.996 on average of 10 shapes and widened codes 0.997 of 40, and the launches apart that others keep 0.95 to 1.02,
+// 0.989 of 54 and 0.991 of 82: less than what a pair has to be worth.)
 constexpr PairLines PAIR_LINES[2] = {
     {5.7, 0.51, 0.21, 0.42, 0.53, 0.56, 0.70, 0.51, 0.15, 0.55, 1.5, 3.2, 0.57, 0.44, 0.07, 0.43, 1.7, 4.2, 0.27, 0.42, 1.7, 0.93},
     {6.7, 0.77, 0.27, 0.46, 0.78, 0.82, 1.21, 0.39, 0.13, 0.38, 2.3, 3.7, 0.92, 0.24, 0.05, 0.34, 2.6, 4.8, 0.31, 0.36, 1.7, 0.88}};  // widened
