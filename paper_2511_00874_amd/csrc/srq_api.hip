@@ -207,7 +207,7 @@ int launch_backward_products(float* dA, float* dW, const uint8_t* dy_rm, const u
   int st = launch_product(dW, dy_t, qdY, a_t, qA, N, K, M, pw, beta, gws_w, s, ROLE_WEIGHT_GRADIENT, nullptr,
                           &sum_w, packed_t);
   if (st != SRQ_OK) return st;
-  st = launch_product(dA, dy_rm, qdY, w_t, qW, M, K, N, pd, 0.0f, gws_d, s, ROLE_ANY, &sum_w, nullptr, packed_rm);
+  st = launch_product(dA, dy_rm, qdY, w_t, qW, M, K, N, pd, 0.0f, gws_d, s, ROLE_INPUT_GRADIENT, &sum_w, nullptr, packed_rm);
   // the weight gradient is already enqueued: if the launch that was to carry its slice sum
   // failed, finish it in a launch of its own so that dW is whole whatever happens to dA
   if (st != SRQ_OK) (void)launch_slice_sum(sum_w, s);
@@ -599,7 +599,7 @@ int sr_linear_bwd_data(float* dA, const void* dY, int dtypedY, const void* W, in
   if (is_none(qdY_bwd))  // weight-only objective: dY enters as it is
     return run_weight_only(dA, dY, dtypedY, W, dtypeW, N, K, 1, qW_bwd, M, K, N, workspace, workspace_bytes, stream);
   return run_linear(dA, dY, dtypedY, M, N, 0, qdY_bwd, W, dtypeW, N, K, 1, qW_bwd, M, K, N, 0.0f,
-                    workspace, workspace_bytes, stream);
+                    workspace, workspace_bytes, stream, SRQ_PHASE_BOTH, ROLE_INPUT_GRADIENT);
 }
 
 // Alg. 2: dW = dYhat^T Ahat.  Contraction over M: dY written as N x M, A written as K x M.

@@ -1236,8 +1236,9 @@ hipError_t launch_persist(GemmParams g, const SliceSumPlan& ss, hipStream_t stre
 //   reads, 37.9 -> 35.5 with more than the 512 tiles that are on the chip at once, with fewer 30.0 -> 31.5 at 1088 x 4576 x 2496 and 53.5 ->
 //   56.4 at 4544 x 528 x 8688 in two slices (16 shapes 1.00 to 1.09 of the time).
 //   64 x 64: int8 320 x 1552 x 4336 8.4 -> 8.8, bfloat16 values 448 x 1792 x 1152 6.0 -> 6.3.
+// `large`: one set of sums of widened codes in MFMA tiles of 32 x 32 (sums_in_large_mfma).
 template <class MMA>
-hipError_t launch_mma(GemmParams g, const Launch& l, const SliceSumPlan& ss, hipStream_t stream) {
+hipError_t launch_mma(GemmParams g, const Launch& l, bool large, const SliceSumPlan& ss, hipStream_t stream) {
   constexpr bool IS_INT = std::is_same<MMA, I8Mma>::value;
   using Mma16 = typename Tiles16<MMA>::type;
   g.nsplit = l.nsplit;
@@ -1252,7 +1253,7 @@ hipError_t launch_mma(GemmParams g, const Launch& l, const SliceSumPlan& ss, hip
       return launch_tile<typename std::conditional<IS_INT, Mma16, MMA>::type, 128, 128, 2, 2, 3, 2>(g, ss, stream);
     case FORM_128x192:                                                                     // 4 waves of 64 x 96
       if constexpr (MMA::WIDENS) {
-        if (sums_in_large_mfma(l.form, g.P, g.Q, l.nsplit)) return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);
+        if (large) return launch_tile<MMA, 128, 192, 2, 2, 2>(g, ss, stream);
       }
       return launch_tile<Mma16, 128, 192, 2, 2, 2>(g, ss, stream);
     case FORM_64x64_G2:                                                                    // 8 waves of 32 x 32
@@ -1299,14 +1300,15 @@ hipError_t launch_pair_mma(const GemmParams& a, const GemmParams& b, PairForm fo
     if constexpr (IS_INT) {
       return launch_pair<128, 128, 2, One, One>(a, b, stream);
     } else {
-      const auto with = [](const Paired& p, const auto& f) {
-        if (p.waves == 2) return f(Waves<MMA, 2, 2, 1, 2>{});
-        if constexpr (MMA::WIDENS) {
-          if (p.large_mfma) return f(Waves<MMA, 2, 2, 1, 1>{});
-        }
-        return f(One{});
-      };
-      return with(pa, [&](auto wa) { return with(pb, [&](auto wb) { return launch_pair<128, 128, 2, decltype(wa), decltype(wb)>(a, b, stream); }); });
+      using Two = Waves<MMA, 2, 2, 1, 2>;
+      if (pa.waves == 1 && pb.waves == 1) return launch_pair<128, 128, 2, One, One>(a, b, stream);
+      if constexpr (MMA::WIDENS) {
+        using Large = Waves<MMA, 2, 2, 1, 1>;
+        if (pa.large_mfma) return launch_pair<128, 128, 2, Large, Two>(a, b, stream);
+        if (pb.large_mfma) return launch_pair<128, 128, 2, Two, Large>(a, b, stream);
+      }
+      if (pa.waves == 1) return launch_pair<128, 128, 2, One, Two>(a, b, stream);
+      return pb.waves == 1 ? launch_pair<128, 128, 2, Two, One>(a, b, stream) : launch_pair<128, 128, 2, Two, Two>(a, b, stream);
     }
   }
   if constexpr (BK / MMA::KSTEP >= 4 && !IS_INT) {
@@ -1470,7 +1472,13 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
   const bool leaves = pipe == PIPE_I8 ? defer != nullptr : role == ROLE_WEIGHT_GRADIENT;
   const uint32_t rides = carry && carry->total > 0 ? carry->nsplit : 0;
   const Launch l = choose_launch(pl, P, Q, row_bytes, pipe, leaves, rides);
-  return with_pipeline(pipe, kindX, kindZ, [&](auto mma) { return launch_mma<decltype(mma)>(g, l, ss, stream); });
+  bool large = sums_in_large_mfma(l.form, P, Q, l.nsplit);
+  if (large && (pipe == PIPE_F16C || pipe == PIPE_F16W) && role != ROLE_ANY) {
+    const size_t M = role == ROLE_WEIGHT_GRADIENT ? R : P, N = role == ROLE_WEIGHT_GRADIENT ? P : R, K = Q;
+    const Plan other = role == ROLE_WEIGHT_GRADIENT ? plan_for(M, K, N, pipe) : plan_for(N, K, M, pipe);
+    large = !one_set_pair(role == ROLE_WEIGHT_GRADIENT ? choose_pair(M, N, K, pipe, pl, other) : choose_pair(M, N, K, pipe, other, pl));
+  }
+  return with_pipeline(pipe, kindX, kindZ, [&](auto mma) { return launch_mma<decltype(mma)>(g, l, large, ss, stream); });
 }
 
 hipError_t launch_gemm_pair(const PairedProduct& w, const PairedProduct& d, int kindX, int pipe, hipStream_t stream, bool& done) {

@@ -144,11 +144,12 @@ struct SliceSum {
   int accumulate, is_int;
 };
 // Which product of a layer a launch is.  It has a say in the kernel form, and in binary32 the form decides the order of a sum: a
-// product must have the same role in every entry point that promises its result bit for bit (sr_linear_bwd and
-// sr_linear_bwd_weight, the stash and phase calls), whether or not its sum is in fact deferred there.
+// product must have the same role in every entry point that promises its result bit for bit (sr_linear_bwd, sr_linear_bwd_weight
+// and sr_linear_bwd_data, the stash and phase calls), whether or not its sum is in fact deferred there.
 enum ProductRole {
   ROLE_ANY = 0,
-  ROLE_WEIGHT_GRADIENT = 1  // sr_linear_bwd leaves its slice sum to the launch of the input gradient
+  ROLE_WEIGHT_GRADIENT = 1,  // sr_linear_bwd leaves its slice sum to the launch of the input gradient
+  ROLE_INPUT_GRADIENT = 2    // (of either gradient it is known what pair sr_linear_bwd would make of the two)
 };
 hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint8_t* Z, int kindZ,
                              size_t P, size_t Q, size_t R, size_t pitch, int pipe, const GemmScale& s,

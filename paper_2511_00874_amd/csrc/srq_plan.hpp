@@ -209,8 +209,8 @@ inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes
 }
 
 // One set of binary32 sums of widened codes: in MFMA tiles of 32 x 32 (true) or of 16 x 16, which round differently.  The larger ones
-// where the product is planned on 128 x 192 tiles that are all on the chip at once (launch_mma says why), also where its tiles in a
-// pair are 128 x 128.
+// where the product is planned on 128 x 192 tiles that are all on the chip at once (launch_mma says why), also where its tiles
+// in a pair are 128 x 128 beside one of two sets; not in a pair of one set each, whose tiles fill the chip (one_set_pair).
 inline bool sums_in_large_mfma(Form form, size_t P, size_t Q, uint32_t nsplit) {
   return form == FORM_128x192 && ((P + 127) / 128) * ((Q + 191) / 192) * nsplit <= 2 * NUM_CU;
 }
@@ -246,13 +246,19 @@ enum PairForm { PAIR_NONE, PAIR_128x128, PAIR_64x64 };
 struct Paired {
   int waves;  // sets of accumulators (128 x 128 tiles of four waves) or groups of waves (64 x 64 of eight)
   uint32_t nsplit, k_per_split;
-  bool large_mfma = false;  // one set, widened codes: sums_in_large_mfma
+  bool large_mfma = false;  // one set of widened codes: sums_in_large_mfma
 };
 struct Pair {
   PairForm form;
   bool weight_first;  // the product with the longer tiles goes first
   Paired w, d;
 };
+// Both products in one set of sums on 128 x 128 tiles, more than are on the chip at once.  Widened codes then have MFMA tiles of 16 x 16
+// whatever they have alone, and a call that has only one of the two products gives it the same, so that the sums are the same bit for
+// bit.  (us of both with those planned on 128 x 192 in 32 x 32, and in 16 x 16: 1104 x 4448 x 3888 E5M2 75.5 and 72.7, 688 x 1088 x
+// 8112 30.2 and 29.4, 10 random shapes 0.966 to 0.993 of the time; few rows beyond a tile 528 x 528 x 6736 16.3 and 17.1, 544 x 784 x
+// 7424 20.3 and 21.4.)
+inline bool one_set_pair(const Pair& p) { return p.form == PAIR_128x128 && p.w.waves == 1 && p.d.waves == 1; }
 struct PairLines {  // microseconds: constant, per stage (of a tile, by form, or of all tiles a CU), of the last tiles to end beyond an even
                     // share, MB of results, MB of partial sums, a sum; most of the separate launches' time that is worth a pair of
                     // 128 x 128 tiles
@@ -336,8 +342,8 @@ inline Pair choose_pair(size_t M, size_t N, size_t K, int pipe, const Plan& plan
   p.form = small ? PAIR_64x64 : PAIR_128x128;
   p.w.waves = small ? parts[0] : halves[0];
   p.d.waves = small ? parts[1] : halves[1];
-  p.w.large_mfma = sums_in_large_mfma(l[0].form, N, K, l[0].nsplit);
-  p.d.large_mfma = sums_in_large_mfma(l[1].form, M, K, l[1].nsplit);
+  p.w.large_mfma = !one_set_pair(p) && sums_in_large_mfma(l[0].form, N, K, l[0].nsplit);
+  p.d.large_mfma = !one_set_pair(p) && sums_in_large_mfma(l[1].form, M, K, l[1].nsplit);
   return p;
 }
 

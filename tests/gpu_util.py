@@ -26,7 +26,7 @@ PAIR_SHAPES = [(16, 16, 16), (528, 16, 16), (16, 528, 16), (1008, 3072, 768), (5
                (1440, 1040, 3664), (784, 144, 4752), (5408, 144, 672), (4592, 5008, 80), (5104, 784, 288), (144, 3008, 1184),
                (1696, 144, 2016), (3344, 3536, 128), (2000, 4352, 16), (6192, 3888, 16), (3408, 3648, 80)]
 # M, N, K of such calls with a product of 8-bit floats that is planned on 128 x 192 tiles, up to 512 of them and more, first and second, beside
-# one set of sums in either size of MFMA tiles and beside two (test_plan.py says which)
+# one set of sums and beside two (test_plan.py says which)
 LARGE_MFMA_SHAPES = [(528, 528, 6736), (528, 656, 6592), (144, 528, 6608), (544, 144, 6560), (800, 528, 7152), (544, 784, 7424),
                      (1056, 832, 7504), (688, 1088, 8112), (144, 2224, 7200), (2960, 144, 5520), (144, 6384, 5440), (5904, 144, 5600),
                      (144, 7280, 6288)]

@@ -396,7 +396,7 @@ def test_backward_products_in_one_launch_equal_the_separate_calls(M, N, K, kind,
     assert torch.equal(dA3, want_dA) and torch.equal(dW3, want_dW)
 
 
-# one set of sums of widened codes is in MFMA tiles of either size, by the product's own plan
+# one set of sums of widened codes is in MFMA tiles of either size, by the product's plan and the pair that it would be part of
 @pytest.mark.parametrize("M,N,K", LARGE_MFMA_SHAPES)
 @pytest.mark.parametrize("kind", [L.E5M2, L.E4M3])
 def test_pairs_of_products_planned_on_wide_tiles(M, N, K, kind):

@@ -274,13 +274,17 @@ def test_gpu_tests_reach_every_form(plan):
         assert {(P64_G2, False), (P128_S2, False), (P128_G2, False)} <= carried[pipe]
 
 
-def test_one_set_of_sums_has_the_mfma_tiles_of_its_launch_in_a_pair_as_well(plan):
-    seen = set()
+def test_mfma_tiles_of_one_set_of_sums_in_a_pair(plan):
+    seen, planned = set(), set()
     for M, N, K in LARGE_MFMA_SHAPES:
         o = (C.c_uint * 8)()
         plan.large_mfma(M, N, K, F16C, o)
         form, first, waves_w, w, waves_d, d, alone_w, alone_d = o
-        assert form == 1 and (w, d) == (alone_w, alone_d), (M, N, K)
+        one_set = waves_w == waves_d == 1  # (16 x 16 in both)
+        assert form == 1 and (w, d) == ((0, 0) if one_set else (alone_w, alone_d)), (M, N, K)
         kinds = tuple("two" if waves == 2 else "large" if large else "small" for waves, large in ((waves_w, w), (waves_d, d)))
         seen.add(kinds if first else kinds[::-1])
-    assert seen == {(a, b) for a in ("two", "large", "small") for b in ("large", "small")}  # (the longer tiles, of two sets, go first)
+        if one_set:
+            planned.add((alone_w, alone_d) if first else (alone_d, alone_w))
+    assert seen == {("two", "large"), ("two", "small"), ("small", "small")}  # (the longer tiles, of two sets, go first)
+    assert planned >= {(0, 1), (1, 0), (1, 1)}  # planned on up to 512 tiles of 128 x 192: first, second, both
