@@ -1233,10 +1233,10 @@ hipError_t launch_persist(GemmParams g, const SliceSumPlan& ss, hipStream_t stre
 //   2048 x 2048 x 4096 38.5 -> 41.5 (with the groups taking turns at LDS and the MFMAs 43.5).  Two sets have the tiles of two groups, as
 //   64 x 64 do, so that their binary32 sums stay the same bit for bit.
 //   128 x 192: int8 4864 x 4960 x 624 32.5 -> 30.3; bfloat16 values 46.0 -> 42.6; widened codes, which are the most work between the
-//   reads, 37.9 -> 35.5 with more than the 512 tiles that are on the chip at once, with fewer 30.0 -> 31.5 at 1088 x 4576 x 2496 and 53.5 ->
-//   56.4 at 4544 x 528 x 8688 in two slices (16 shapes 1.00 to 1.09 of the time).
+//   reads, 37.9 -> 35.5, with 458 tiles 29264 x 304 x 1648 4 less of 268 for its step, with 333 14160 x 528 x 272 21.7 -> 21.1; with a CU
+//   for each tile 30.0 -> 31.5 at 1088 x 4576 x 2496 and 53.5 -> 56.4 at 4544 x 528 x 8688 in two slices (11 shapes 1.02 to 1.09 of the time).
 //   64 x 64: int8 320 x 1552 x 4336 8.4 -> 8.8, bfloat16 values 448 x 1792 x 1152 6.0 -> 6.3.
-// `large`: one set of sums of widened codes in MFMA tiles of 32 x 32 (sums_in_large_mfma).
+// `large`: one set of sums of widened codes in MFMA tiles of 32 x 32 (sums_in_large_mfma, large_mfma_of_gradient).
 template <class MMA>
 hipError_t launch_mma(GemmParams g, const Launch& l, bool large, const SliceSumPlan& ss, hipStream_t stream) {
   constexpr bool IS_INT = std::is_same<MMA, I8Mma>::value;
@@ -1288,19 +1288,19 @@ hipError_t launch_pair(GemmParams a, GemmParams b, hipStream_t stream) {
   return e;
 }
 
-// The forms of the two products: sets of accumulators (128 x 128 tiles) or groups of waves (64 x 64), and the MFMA tiles of their launches
-// apart (launch_mma; of integers, any sums of which are the same, 16 x 16 on 64 x 64 as well: 3824 x 32 x 1872 12.5 -> 12.2 us).
+// The forms of the two products: sets of accumulators (128 x 128 tiles) or groups of waves (64 x 64), in the MFMA tiles of launch_mma or
+// choose_pair (of integers, any sums of which are the same, 16 x 16 on 64 x 64 as well: 3824 x 32 x 1872 12.5 -> 12.2 us).
 template <class MMA>
 hipError_t launch_pair_mma(const GemmParams& a, const GemmParams& b, PairForm form, const Paired& pa, const Paired& pb, hipStream_t stream) {
   constexpr bool IS_INT = std::is_same<MMA, I8Mma>::value;
   using Mma16 = typename Tiles16<MMA>::type;
   using One = Waves<Mma16, 2, 2, 1, 1>;
+  using Two = Waves<MMA, 2, 2, 1, 2>;
   using G2 = Waves<typename std::conditional<IS_INT, Mma16, MMA>::type, 2, 2, 2, 1>;
   if (form == PAIR_128x128) {
     if constexpr (IS_INT) {
       return launch_pair<128, 128, 2, One, One>(a, b, stream);
     } else {
-      using Two = Waves<MMA, 2, 2, 1, 2>;
       if (pa.waves == 1 && pb.waves == 1) return launch_pair<128, 128, 2, One, One>(a, b, stream);
       if constexpr (MMA::WIDENS) {
         using Large = Waves<MMA, 2, 2, 1, 1>;
@@ -1472,12 +1472,9 @@ hipError_t launch_gemm_codes(float* out, const uint8_t* X, int kindX, const uint
   const bool leaves = pipe == PIPE_I8 ? defer != nullptr : role == ROLE_WEIGHT_GRADIENT;
   const uint32_t rides = carry && carry->total > 0 ? carry->nsplit : 0;
   const Launch l = choose_launch(pl, P, Q, row_bytes, pipe, leaves, rides);
-  bool large = sums_in_large_mfma(l.form, P, Q, l.nsplit);
-  if (large && (pipe == PIPE_F16C || pipe == PIPE_F16W) && role != ROLE_ANY) {
-    const size_t M = role == ROLE_WEIGHT_GRADIENT ? R : P, N = role == ROLE_WEIGHT_GRADIENT ? P : R, K = Q;
-    const Plan other = role == ROLE_WEIGHT_GRADIENT ? plan_for(M, K, N, pipe) : plan_for(N, K, M, pipe);
-    large = !one_set_pair(role == ROLE_WEIGHT_GRADIENT ? choose_pair(M, N, K, pipe, pl, other) : choose_pair(M, N, K, pipe, other, pl));
-  }
+  const bool widens = pipe == PIPE_F16C || pipe == PIPE_F16W;
+  const bool large = widens && (role == ROLE_ANY ? sums_in_large_mfma(l.form, P, Q, l.nsplit)
+                                                 : large_mfma_of_gradient(pl, l, role == ROLE_WEIGHT_GRADIENT, P, Q, R, pipe));
   return with_pipeline(pipe, kindX, kindZ, [&](auto mma) { return launch_mma<decltype(mma)>(g, l, large, ss, stream); });
 }
 

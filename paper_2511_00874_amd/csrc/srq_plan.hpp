@@ -209,10 +209,9 @@ inline Launch choose_launch(const Plan& pl, size_t P, size_t Q, size_t row_bytes
 }
 
 // One set of binary32 sums of widened codes: in MFMA tiles of 32 x 32 (true) or of 16 x 16, which round differently.  The larger ones
-// where the product is planned on 128 x 192 tiles that are all on the chip at once (launch_mma says why), also where its tiles
-// in a pair are 128 x 128 beside one of two sets; not in a pair of one set each, whose tiles fill the chip (one_set_pair).
-inline bool sums_in_large_mfma(Form form, size_t P, size_t Q, uint32_t nsplit) {
-  return form == FORM_128x192 && ((P + 127) / 128) * ((Q + 191) / 192) * nsplit <= 2 * NUM_CU;
+// where a product has at most `slots` tiles of 128 x 192: alone a CU for each (launch_mma says why); in a pair see choose_pair's end.
+inline bool sums_in_large_mfma(Form form, size_t P, size_t Q, uint32_t nsplit, size_t slots = NUM_CU) {
+  return form == FORM_128x192 && ((P + 127) / 128) * ((Q + 191) / 192) * nsplit <= slots;
 }
 
 // The two products of a backward call, dW (N x K, contraction M) and dA (M x K, contraction N), in one launch of tiles of
@@ -253,12 +252,6 @@ struct Pair {
   bool weight_first;  // the product with the longer tiles goes first
   Paired w, d;
 };
-// Both products in one set of sums on 128 x 128 tiles, more than are on the chip at once.  Widened codes then have MFMA tiles of 16 x 16
-// whatever they have alone, and a call that has only one of the two products gives it the same, so that the sums are the same bit for
-// bit.  (us of both with those planned on 128 x 192 in 32 x 32, and in 16 x 16: 1104 x 4448 x 3888 E5M2 75.5 and 72.7, 688 x 1088 x
-// 8112 30.2 and 29.4, 10 random shapes 0.966 to 0.993 of the time; few rows beyond a tile 528 x 528 x 6736 16.3 and 17.1, 544 x 784 x
-// 7424 20.3 and 21.4.)
-inline bool one_set_pair(const Pair& p) { return p.form == PAIR_128x128 && p.w.waves == 1 && p.d.waves == 1; }
 struct PairLines {  // microseconds: constant, per stage (of a tile, by form, or of all tiles a CU), of the last tiles to end beyond an even
                     // share, MB of results, MB of partial sums, a sum; most of the separate launches' time that is worth a pair of
                     // 128 x 128 tiles
@@ -342,9 +335,24 @@ inline Pair choose_pair(size_t M, size_t N, size_t K, int pipe, const Plan& plan
   p.form = small ? PAIR_64x64 : PAIR_128x128;
   p.w.waves = small ? parts[0] : halves[0];
   p.d.waves = small ? parts[1] : halves[1];
-  p.w.large_mfma = !one_set_pair(p) && sums_in_large_mfma(l[0].form, N, K, l[0].nsplit);
-  p.d.large_mfma = !one_set_pair(p) && sums_in_large_mfma(l[1].form, M, K, l[1].nsplit);
+  // MFMA tiles of one set of widened codes.  Both products in one set: 16 x 16, their many tiles fill the chip (1104 x 4448 x 3888 E5M2,
+  // whose input gradient has 189 tiles of 128 x 192 alone, 75.5 us with that in 32 x 32, 72.7 so; 10 random shapes 0.966 to 0.993 of the time).
+  // Beside two sets, in 32 x 32 themselves: as well where the product has up to 512 tiles of 128 x 192 alone (160 x 5808 x 1776 21.4 ->
+  // 20.0, 1152 x 448 x 4256 13.5 -> 12.6; 28 random shapes with others in 16 x 16 0.94 to 1.02, 0.985 on average; all in 32 x 32 0.94 to 1.06).
+  if (p.form == PAIR_128x128 && p.w.waves != p.d.waves) {
+    p.w.large_mfma = sums_in_large_mfma(l[0].form, N, K, l[0].nsplit, SLOTS);
+    p.d.large_mfma = sums_in_large_mfma(l[1].form, M, K, l[1].nsplit, SLOTS);
+  }
   return p;
+}
+// The same of a gradient in a call of its own: as in the pair that the whole backward call would make of both, so that its sums are the
+// same bit for bit.
+inline bool large_mfma_of_gradient(const Plan& pl, const Launch& l, bool weight, size_t P, size_t Q, size_t R, int pipe) {
+  if (l.form != FORM_128x192) return false;
+  const size_t M = weight ? R : P, N = weight ? P : R;
+  const Plan other = weight ? plan_for(M, Q, N, pipe) : plan_for(N, Q, M, pipe);
+  const Pair p = choose_pair(M, N, Q, pipe, weight ? pl : other, weight ? other : pl);
+  return p.form == PAIR_NONE ? sums_in_large_mfma(l.form, P, Q, l.nsplit) : (weight ? p.w : p.d).large_mfma;
 }
 
 }  // namespace srq

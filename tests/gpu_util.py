@@ -25,11 +25,11 @@ RIDE_SHAPES = [(2048, 192, 352), (976, 208, 560), (4240, 1360, 224), (2736, 432,
 PAIR_SHAPES = [(16, 16, 16), (528, 16, 16), (16, 528, 16), (1008, 3072, 768), (592, 5584, 704), (2000, 2272, 1392),
                (1440, 1040, 3664), (784, 144, 4752), (5408, 144, 672), (4592, 5008, 80), (5104, 784, 288), (144, 3008, 1184),
                (1696, 144, 2016), (3344, 3536, 128), (2000, 4352, 16), (6192, 3888, 16), (3408, 3648, 80)]
-# M, N, K of such calls with a product of 8-bit floats that is planned on 128 x 192 tiles, up to 512 of them and more, first and second, beside
-# one set of sums and beside two (test_plan.py says which)
-LARGE_MFMA_SHAPES = [(528, 528, 6736), (528, 656, 6592), (144, 528, 6608), (544, 144, 6560), (800, 528, 7152), (544, 784, 7424),
-                     (1056, 832, 7504), (688, 1088, 8112), (144, 2224, 7200), (2960, 144, 5520), (144, 6384, 5440), (5904, 144, 5600),
-                     (144, 7280, 6288)]
+# M, N, K of backward calls with a product of 8-bit floats on 128 x 192 tiles, up to 256, up to 512 of them and more, alone and in pairs
+# beside one set of sums and two (test_plan.py says which)
+LARGE_MFMA_SHAPES = [(64, 528, 6640), (64, 1040, 7376), (64, 2192, 7232), (144, 2320, 3360), (144, 2352, 6992), (144, 5520, 5920),
+                     (144, 6656, 528), (528, 1200, 6688), (544, 144, 6608), (608, 528, 6640), (1056, 528, 7488), (1296, 144, 5968),
+                     (2720, 144, 6000), (5408, 64, 656), (6160, 64, 2576), (6208, 144, 5440), (7200, 64, 1040)]
 
 
 def say(*a):

@@ -249,7 +249,7 @@ def test_large_tile_products_leave_registers_for_another_stream(lib):
 
 def test_mfma_tiles_of_the_product_forms(lib):
     # 16 x 16 where the workgroups fill the chip, 32 x 32 where a tile's loads and its chain count (a form has the tiles that are
-    # measured to be faster with it: widened codes on 128 x 192 tiles by the number of tiles, both); the fp8 pipeline has 32 x 32 only
+    # measured to be faster with it: widened codes on 128 x 192 tiles both, by the number of tiles and by their pair); the fp8 pipeline has 32 x 32 only
     got = {}
     for name in _kernels(lib.LIB_PATH):
         m = re.search(r"gemm_nt_kernelINS_3mma\d+(I8|BF16|F8F16)Mma(16)?(?:ILi\dELi\dEE)?E"

@@ -396,10 +396,10 @@ def test_backward_products_in_one_launch_equal_the_separate_calls(M, N, K, kind,
     assert torch.equal(dA3, want_dA) and torch.equal(dW3, want_dW)
 
 
-# one set of sums of widened codes is in MFMA tiles of either size, by the product's plan and the pair that it would be part of
+# widened codes on 128 x 192 tiles: in MFMA tiles of either size, by their number and by the pair that the product would be part of
 @pytest.mark.parametrize("M,N,K", LARGE_MFMA_SHAPES)
 @pytest.mark.parametrize("kind", [L.E5M2, L.E4M3])
-def test_pairs_of_products_planned_on_wide_tiles(M, N, K, kind):
+def test_gradients_planned_on_wide_tiles(M, N, K, kind):
     say("wide tiles", M, N, K, L.KIND_NAMES[kind])
     A, W, dY = synth.single_layer(M, N, K, 31, std_dy=1e-3)
     A, W, dY = to_dev(A), to_dev(W, True), to_dev(dY)

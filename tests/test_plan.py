@@ -30,9 +30,10 @@ extern "C" void large_mfma(size_t M, size_t N, size_t K, int pipe, unsigned* o) 
   const Plan w = plan_for(N, K, M, pipe), d = plan_for(M, K, N, pipe);
   const Pair p = choose_pair(M, N, K, pipe, w, d);
   const Launch lw = choose_launch(w, N, K, M, pipe, true, 0), ld = choose_launch(d, M, K, N, pipe, false, 0);
-  const unsigned v[] = {(unsigned)p.form, p.weight_first, (unsigned)p.w.waves, p.w.large_mfma, (unsigned)p.d.waves, p.d.large_mfma,
-                        sums_in_large_mfma(lw.form, N, K, lw.nsplit), sums_in_large_mfma(ld.form, M, K, ld.nsplit)};
-  for (int i = 0; i < 8; ++i) o[i] = v[i];
+  const auto tiles = [](const Launch& l, size_t P, size_t Q) { return l.form == FORM_128x192 ? (P + 127) / 128 * ((Q + 191) / 192) * l.nsplit : 0; };
+  const size_t v[] = {p.form, p.w.waves != p.d.waves, p.w.large_mfma, p.d.large_mfma, large_mfma_of_gradient(w, lw, true, N, K, M, pipe),
+                      large_mfma_of_gradient(d, ld, false, M, K, N, pipe), tiles(lw, N, K), tiles(ld, M, K)};
+  for (int i = 0; i < 8; ++i) o[i] = (unsigned)v[i];
 }
 // nanoseconds of the plans of a backward call, and of what chooses between one launch and two beside them
 extern "C" void host_time(size_t M, size_t N, size_t K, int pipe, double* o) {
@@ -274,17 +275,18 @@ def test_gpu_tests_reach_every_form(plan):
         assert {(P64_G2, False), (P128_S2, False), (P128_G2, False)} <= carried[pipe]
 
 
-def test_mfma_tiles_of_one_set_of_sums_in_a_pair(plan):
-    seen, planned = set(), set()
+def test_mfma_tiles_of_gradients_on_wide_tiles(plan):
+    # 32 x 32 alone with up to 256 tiles of 128 x 192, beside two sets of a pair with up to 512; 16 x 16 in a pair of one set each.  A
+    # gradient in a call of its own has those of the pair
+    seen = set()
     for M, N, K in LARGE_MFMA_SHAPES:
         o = (C.c_uint * 8)()
         plan.large_mfma(M, N, K, F16C, o)
-        form, first, waves_w, w, waves_d, d, alone_w, alone_d = o
-        one_set = waves_w == waves_d == 1  # (16 x 16 in both)
-        assert form == 1 and (w, d) == ((0, 0) if one_set else (alone_w, alone_d)), (M, N, K)
-        kinds = tuple("two" if waves == 2 else "large" if large else "small" for waves, large in ((waves_w, w), (waves_d, d)))
-        seen.add(kinds if first else kinds[::-1])
-        if one_set:
-            planned.add((alone_w, alone_d) if first else (alone_d, alone_w))
-    assert seen == {("two", "large"), ("two", "small"), ("small", "small")}  # (the longer tiles, of two sets, go first)
-    assert planned >= {(0, 1), (1, 0), (1, 1)}  # planned on up to 512 tiles of 128 x 192: first, second, both
+        form, mixed, *values = o
+        for gradient, paired, alone, tiles in zip(("weight", "input"), *(values[i:i + 2] for i in (0, 2, 4))):
+            assert alone == (0 < tiles <= (256 if not form else 512 if mixed else 0)), (M, N, K, gradient)
+            assert not form or paired == alone
+            if tiles:
+                seen.add((gradient, (tiles > 256) + (tiles > 512), "mixed" if form and mixed else "pair" if form else "alone"))
+    want = {(n, beside) for n in range(3) for beside in ("alone", "pair", "mixed")}
+    assert seen == {(gradient,) + s for gradient in ("weight", "input") for s in want}, seen ^ {(g,) + s for g in ("weight", "input") for s in want}
