@@ -216,7 +216,8 @@ int sr_linear_fwd(float* Y, const void* A, int dtypeA, const void* W, int dtypeW
  * memory-bound half of one layer (rounding the operands into the workspace: SRQ_PHASE_QUANTIZE) beside
  * the matrix half of another (the products from the workspace: SRQ_PHASE_PRODUCT) on two streams; the
  * quantizer kernels fit into the registers and LDS the product kernels leave free on a CU (but beside some
- * launches of both backward products, where they start as its workgroups end).  Arguments as
+ * launches of both backward products and beside large products of 8-bit floats from their codes, where they
+ * start as its workgroups end).  Arguments as
  * for the whole call, plus `phase`; the two calls of a pair take the same arguments and workspace, the
  * caller orders them (same stream, or an event) and keeps the workspace untouched in between.
  * SRQ_PHASE_BOTH is the whole call, except that sr_linear_fwd_phase always rounds into the workspace
